@@ -130,6 +130,29 @@ __device__ __forceinline__ void copy16_to_lds(const void* src, uint32_t lds_base
 
 #endif
 
+#ifdef __HIPCC__
+// fp32 matrix products read 16 k of a row per step, lane group g = lane / 16 the four at k0 + 4g (ffn_f32.hip says how
+// the MFMAs use them).
+// 4 consecutive k of a row; VEC: the widest load the row pitch and the base addresses allow
+template <int VEC>
+__device__ __forceinline__ f32x4 load_k4(const float* __restrict__ p) {
+    if constexpr (VEC == 4) return *reinterpret_cast<const f32x4*>(p);
+    if constexpr (VEC == 2) {
+        const float2 a = *reinterpret_cast<const float2*>(p), b = *reinterpret_cast<const float2*>(p + 2);
+        return f32x4{a.x, a.y, b.x, b.y};
+    }
+    return f32x4{p[0], p[1], p[2], p[3]};
+}
+// the same at the end of a row: only `left` of the four exist (none if left <= 0), the others are zero
+__device__ __forceinline__ f32x4 load_k4_tail(const float* __restrict__ p, int left) {
+    f32x4 v = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+        if (i < left) v[i] = p[i];
+    return v;
+}
+#endif
+
 struct TileLists {
     Tile* small_tiles;     // capacity A / small_rows + E
     Tile* big_tiles;       // capacity A / kBigTileRows + E (unused when big_min == 0)
@@ -353,6 +376,9 @@ hipError_t launch_tile_product(bool first, const uint16_t* act, const int32_t* r
                                float* partials, int N, int K, bool act_kmajor, int activation,
                                const float* bias, const FoldOut& fold, hipStream_t st);
 int tile_product_grid();
+hipError_t launch_f32_product(bool first, const float* act, const int32_t* rowmap, const float* w, float* outp,
+                              const Tile* tiles, const int32_t* ntiles, long max_tiles, int N, int K, int activation,
+                              const float* bias, hipStream_t st);
 hipError_t launch_permute(const moe_shape& s, const void* x, const int32_t* idx,
                           const int32_t* offsets, int32_t* perm, int32_t* inv_perm, void* x_perm,
                           int32_t* hist_ws, hipStream_t st);

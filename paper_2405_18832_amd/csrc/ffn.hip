@@ -477,49 +477,6 @@ __global__ __launch_bounds__(256) void ffn_stream_kernel(const uint16_t* __restr
 }
 
 // ---------------------------------------------------------------------------
-// fp32 storage: plain FMA kernel (small layers only).  Tiles of 16 rows; a thread owns one
-// output column of a tile and walks the rows.
-// ---------------------------------------------------------------------------
-template <bool FIRST>
-__global__ __launch_bounds__(256) void ffn_f32_kernel(const float* __restrict__ act,
-                                                      const int32_t* __restrict__ rowmap,
-                                                      const float* __restrict__ w,
-                                                      float* __restrict__ outp,
-                                                      const Tile* __restrict__ tiles,
-                                                      const int32_t* __restrict__ ntiles_p, int N, int K,
-                                                      int activation, const float* __restrict__ bias) {
-    const int nchunks = (N + 255) / 256;
-    const int nbu = ntiles_p[0] * nchunks;
-    for (int bu = blockIdx.x; bu < nbu; bu += gridDim.x) {
-        const Tile tl = tiles[bu / nchunks];
-        const int n = (bu % nchunks) * 256 + threadIdx.x;
-        if (n >= N) continue;
-        const float* wr = w + (static_cast<size_t>(tl.expert) * N + n) * K;
-        for (int i = 0; i < tl.rows; ++i) {
-            const int src = rowmap ? rowmap[tl.row0 + i] : tl.row0 + i;
-            const float* ar = act + static_cast<size_t>(src) * K;
-            // four running sums over c mod 4 (16-byte loads, four independent chains), added pairwise at the end
-            float s0 = 0.f, s1 = 0.f, s2 = 0.f, s3 = 0.f;
-            int c = 0;
-            if ((K & 3) == 0) {                            // rows of x, h and the weights are then 16-byte aligned
-                for (; c < K; c += 4) {
-                    const float4 a = *reinterpret_cast<const float4*>(ar + c);
-                    const float4 b = *reinterpret_cast<const float4*>(wr + c);
-                    s0 = fmaf(a.x, b.x, s0);
-                    s1 = fmaf(a.y, b.y, s1);
-                    s2 = fmaf(a.z, b.z, s2);
-                    s3 = fmaf(a.w, b.w, s3);
-                }
-            }
-            for (; c < K; ++c) s0 = fmaf(ar[c], wr[c], s0);
-            float s = (s0 + s1) + (s2 + s3);
-            if (bias) s += bias[static_cast<size_t>(tl.expert) * N + n];
-            outp[static_cast<size_t>(tl.row0 + i) * N + n] = FIRST ? activate(s, activation) : s;
-        }
-    }
-}
-
-// ---------------------------------------------------------------------------
 // host side
 // ---------------------------------------------------------------------------
 // per device, written once by configure_ffn_kernels (under the set-up lock) before any launch reads them
@@ -706,7 +663,7 @@ static hipError_t mark(int i, hipStream_t st) {
 // token fragments per tile: an expert holds at most T rows (a token picks an expert at most once)
 static int ffn_tfmax(const moe_shape& s) { return s.T <= 16 ? 1 : (s.T <= 32 ? 2 : 4); }
 
-int ffn_tile_rows(const moe_shape& s) { return s.dtype == MOE_BF16 ? 16 * ffn_tfmax(s) : 16; }
+int ffn_tile_rows(const moe_shape& s) { return 16 * ffn_tfmax(s); }
 
 TileLists ffn_tile_lists(const moe_shape& s, Tile* small_ws, Tile* big_ws, int32_t* ntiles_ws, float* partials_ws) {
     TileLists l;
@@ -754,19 +711,13 @@ hipError_t launch_expert_products(const moe_shape& s, const void* act, const int
     if ((err = mark(0, st)) != hipSuccess) return err;
 
     if (s.dtype == MOE_F32) {
-        const long g1 = max_tiles * ((f + 255) / 256), g2 = max_tiles * ((d + 255) / 256);
-        const long cap = static_cast<long>(device_cu_count()) * 8;
         if ((err = mark(1, st)) != hipSuccess) return err;
-        hipLaunchKernelGGL(ffn_f32_kernel<true>, dim3(static_cast<unsigned>(g1 < cap ? g1 : cap)), dim3(256), 0, st,
-                           static_cast<const float*>(act), rowmap, static_cast<const float*>(w1),
-                           static_cast<float*>(h_ws), tiles, ntiles, f, d, s.activation, b1);
-        err = hipGetLastError();
+        err = launch_f32_product(true, static_cast<const float*>(act), rowmap, static_cast<const float*>(w1),
+                                 static_cast<float*>(h_ws), tiles, ntiles, max_tiles, f, d, s.activation, b1, st);
         if (err != hipSuccess) return err;
         if ((err = mark(2, st)) != hipSuccess || (err = mark(3, st)) != hipSuccess) return err;
-        hipLaunchKernelGGL(ffn_f32_kernel<false>, dim3(static_cast<unsigned>(g2 < cap ? g2 : cap)), dim3(256), 0, st,
-                           static_cast<const float*>(h_ws), static_cast<const int32_t*>(nullptr),
-                           static_cast<const float*>(w2), y_perm, tiles, ntiles, d, f, s.activation, b2);
-        err = hipGetLastError();
+        err = launch_f32_product(false, static_cast<const float*>(h_ws), nullptr, static_cast<const float*>(w2), y_perm,
+                                 tiles, ntiles, max_tiles, d, f, s.activation, b2, st);
         if (err != hipSuccess) return err;
         return mark(4, st);
     }

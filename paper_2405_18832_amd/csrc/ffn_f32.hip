@@ -1,0 +1,204 @@
+// Expert FFN products of fp32 layers on the fp32 matrix instruction (v_mfma_f32_16x16x4_f32: fp32 operands, fp32
+// accumulation, nothing rounded in between):
+//
+//   out[row, n] = sum_k act[row, k] * W_e[n, k]          (FIRST: bias and activation, else bias)
+//
+// Weights are plain rows [N][K].  A unit is one row tile (up to 64 rows of one expert) x 16 columns; the four
+// wavefronts of a block split the contraction and add their partial sums in LDS in wave order.  Per 32 k a wavefront
+// loads one 128-byte line of each of its rows, eight consecutive lanes a line, turns the fragments round in its own part
+// of LDS, and reads them back as matrix operands: lane (r, g) holds k0 + 4g ... + 3 of row r and feeds element j to the
+// j-th of four MFMAs (the four k of one MFMA are k0 + j + {0, 4, 8, 12}, the same for both operands).  Loading the
+// operands straight into that form puts 16 different rows under 16 consecutive lanes: 64 cache accesses per load
+// instruction instead of 16, which bounded the kernel (57 + 67 us on the layer below).
+//
+// What bounds it: with about 64 rows per expert the MFMA time (64 flop per clock and SIMD) and reading the weights once
+// are about equal, 17 and 14 us on a layer of 500 tokens, 8 experts, 768 x 3072, one expert per token (2.4 GFLOP and
+// 75 MB of weights per product); the rest is the start of the units (tile, row numbers, first lines: three dependent
+// trips to memory) and the last round.  Measured there: 47 + 46 us for the two products; a thread per column with
+// fused multiply-adds took 1353 + 2432 us.  Units of 32 columns need fewer row loads but leave room for two blocks per
+// CU only: 48 + 63 us.
+#include <algorithm>
+
+#include "common.hpp"
+
+namespace moe {
+
+constexpr int kF32Waves = 4;        // wavefronts of a block: slices of the contraction
+constexpr int kF32Step = 32;        // k per step: one 128-byte line of every row
+constexpr int kF32FragFloats = 16 * kF32Step;
+
+// 16-byte piece p (of 8) of row r of a fragment in LDS.  The pieces of a row are permuted by its row number: the eight
+// rows that a read touches at once then lie in different banks.
+__device__ __forceinline__ int f32_slot(int r, int p) { return r * kF32Step + ((p ^ (r & 7)) << 2); }
+
+template <int TFC, int VEC, bool FIRST>
+__device__ __forceinline__ void f32_unit(const float* __restrict__ act, const int32_t* __restrict__ rowmap,
+                                         const float* __restrict__ w, float* __restrict__ outp, const Tile tl,
+                                         const int n0, const int N, const int K, const int activation,
+                                         const float* __restrict__ bias, float* lds) {
+    constexpr int F = 1 + TFC;                            // fragments per step: the 16 weight rows, the token rows
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63, r = lane & 15, g = lane >> 4;
+    // loads: half a fragment (8 rows x 128 bytes) per instruction, 8 consecutive lanes a row
+    const int lrow = lane >> 3, lpiece = lane & 7;
+    const float* src[F][2];
+#pragma unroll
+    for (int i = 0; i < F; ++i)
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+            const int fr = h * 8 + lrow;
+            if (i == 0) {
+                src[i][h] = w + (static_cast<size_t>(tl.expert) * N + min(n0 + fr, N - 1)) * K + lpiece * 4;
+            } else {
+                int row = tl.row0 + min((i - 1) * 16 + fr, tl.rows - 1);
+                if (rowmap != nullptr) row = rowmap[row];
+                src[i][h] = act + static_cast<size_t>(row) * K + lpiece * 4;
+            }
+        }
+    f32x4 acc[TFC];
+#pragma unroll
+    for (int tf = 0; tf < TFC; ++tf) acc[tf] = f32x4{0.f, 0.f, 0.f, 0.f};
+    float* mine = lds + wave * (F * kF32FragFloats);      // private to the wavefront: its LDS accesses stay in order
+    f32x4 raw[F][2];
+    auto issue = [&]() {                                  // loads a step and moves on to the next
+#pragma unroll
+        for (int i = 0; i < F; ++i)
+#pragma unroll
+            for (int h = 0; h < 2; ++h) {
+                raw[i][h] = load_k4<VEC>(src[i][h]);
+                src[i][h] += kF32Step;
+            }
+    };
+    auto to_lds = [&]() {
+#pragma unroll
+        for (int i = 0; i < F; ++i)
+#pragma unroll
+            for (int h = 0; h < 2; ++h)
+                *reinterpret_cast<f32x4*>(mine + i * kF32FragFloats + f32_slot(h * 8 + lrow, lpiece)) = raw[i][h];
+    };
+    auto fma = [&]() {
+#pragma unroll
+        for (int q = 0; q < 2; ++q) {
+            f32x4 v[F];
+#pragma unroll
+            for (int i = 0; i < F; ++i) v[i] = *reinterpret_cast<const f32x4*>(mine + i * kF32FragFloats + f32_slot(r, q * 4 + g));
+#pragma unroll
+            for (int j = 0; j < 4; ++j)
+#pragma unroll
+                for (int tf = 0; tf < TFC; ++tf)
+                    acc[tf] = __builtin_amdgcn_mfma_f32_16x16x4f32(v[0][j], v[1 + tf][j], acc[tf], 0, 0, 0);
+        }
+    };
+    const int steps = K / kF32Step, per = (steps + kF32Waves - 1) / kF32Waves;      // whole steps; the rest of the row below
+    const int s0 = min(steps, wave * per), s1 = min(steps, s0 + per);
+    auto start_at = [&](int step) {
+#pragma unroll
+        for (int i = 0; i < F; ++i)
+#pragma unroll
+            for (int h = 0; h < 2; ++h) src[i][h] += step * kF32Step;
+    };
+    if (s0 < s1) {
+        start_at(s0);
+        issue();
+        for (int s = s0; s < s1; ++s) {
+            to_lds();
+            // the next step's loads go out before this step's MFMAs (the compiler would move them behind)
+            __builtin_amdgcn_sched_barrier(0);
+            if (s + 1 < s1) issue();
+            __builtin_amdgcn_sched_barrier(0);
+            fma();
+        }
+        start_at(-s1);
+    }
+    if (K % kF32Step != 0 && wave == kF32Waves - 1) {     // wave-uniform
+        const int left = K % kF32Step - lpiece * 4;
+#pragma unroll
+        for (int i = 0; i < F; ++i)
+#pragma unroll
+            for (int h = 0; h < 2; ++h) raw[i][h] = load_k4_tail(src[i][h] + steps * kF32Step, left);
+        to_lds();
+        fma();
+    }
+    f32x4* red = reinterpret_cast<f32x4*>(lds);
+    __syncthreads();                                      // the operands in LDS give way to the partial sums
+
+    // row fragment i of every wavefront at red[(wave * TFC + i) * 64 + lane]; wavefront i adds and stores it
+#pragma unroll
+    for (int tf = 0; tf < TFC; ++tf) red[(wave * TFC + tf) * 64 + lane] = acc[tf];
+    __syncthreads();
+    if (wave < TFC) {
+        const int lr = wave * 16 + r, n = n0 + g * 4;
+        f32x4 v = red[wave * 64 + lane];
+#pragma unroll
+        for (int s = 1; s < kF32Waves; ++s) v += red[(s * TFC + wave) * 64 + lane];
+        if (lr < tl.rows) {
+            float* o = outp + static_cast<size_t>(tl.row0 + lr) * N + n;
+            const float* be = bias ? bias + static_cast<size_t>(tl.expert) * N + n : nullptr;
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                if (n + q < N && be != nullptr) v[q] += be[q];
+                if (FIRST) v[q] = activate(v[q], activation);
+            }
+            if (VEC == 4 && (N & 3) == 0) {               // out rows are then 16-byte aligned (see launch_f32_product)
+                if (n < N) *reinterpret_cast<f32x4*>(o) = v;
+            } else {
+#pragma unroll
+                for (int q = 0; q < 4; ++q)
+                    if (n + q < N) o[q] = v[q];
+            }
+        }
+    }
+    __syncthreads();                                      // LDS may be reused
+}
+
+// at least 4 wavefronts per SIMD: the turn through LDS and the start of a unit are covered by the other blocks' MFMAs
+template <int VEC, bool FIRST>
+__global__ __launch_bounds__(256, 4) void ffn_f32_kernel(const float* __restrict__ act, const int32_t* __restrict__ rowmap,
+                                                      const float* __restrict__ w, float* __restrict__ outp,
+                                                      const Tile* __restrict__ tiles,
+                                                      const int32_t* __restrict__ ntiles_p, int N, int K,
+                                                      int activation, const float* __restrict__ bias) {
+    __shared__ __attribute__((aligned(16))) float lds[kF32Waves * 5 * kF32FragFloats];
+    const int ngroups = (N + 15) / 16;
+    // Blocks go to the 8 XCDs round-robin, and each XCD has its own L2.  XCD x takes the x-th eighth of the column groups
+    // of every tile: each weight enters one L2 only, and the XCDs have equal work whatever the tiles' row counts are.
+    // (With runs of whole tiles per XCD the last, partly filled round of units sat on one or two XCDs.)
+    const bool sliced = gridDim.x % 8 == 0 && ngroups >= 8;
+    const int x = sliced ? static_cast<int>(blockIdx.x & 7) : 0, nx = sliced ? 8 : 1;
+    const int g0 = ngroups * x / nx, ng = ngroups * (x + 1) / nx - g0;
+    const int units = ntiles_p[0] * ng, stride = static_cast<int>(gridDim.x) / nx;
+    for (int u = static_cast<int>(blockIdx.x) / nx; u < units; u += stride) {     // block-uniform
+        const Tile tl = tiles[u / ng];
+        const int n0 = (g0 + u % ng) * 16;
+        switch ((tl.rows + 15) >> 4) {                    // exact number of row fragments: a fixed number of loads per step
+            case 1: f32_unit<1, VEC, FIRST>(act, rowmap, w, outp, tl, n0, N, K, activation, bias, lds); break;
+            case 2: f32_unit<2, VEC, FIRST>(act, rowmap, w, outp, tl, n0, N, K, activation, bias, lds); break;
+            case 3: f32_unit<3, VEC, FIRST>(act, rowmap, w, outp, tl, n0, N, K, activation, bias, lds); break;
+            default: f32_unit<4, VEC, FIRST>(act, rowmap, w, outp, tl, n0, N, K, activation, bias, lds); break;
+        }
+    }
+}
+
+template <int VEC>
+static hipError_t launch_f32(bool first, unsigned grid, const float* act, const int32_t* rowmap, const float* w,
+                             float* outp, const Tile* tiles, const int32_t* ntiles, int N, int K, int activation,
+                             const float* bias, hipStream_t st) {
+    auto kern = first ? ffn_f32_kernel<VEC, true> : ffn_f32_kernel<VEC, false>;
+    hipLaunchKernelGGL(kern, dim3(grid), dim3(256), 0, st, act, rowmap, w, outp, tiles, ntiles, N, K, activation, bias);
+    return hipGetLastError();
+}
+
+hipError_t launch_f32_product(bool first, const float* act, const int32_t* rowmap, const float* w, float* outp,
+                              const Tile* tiles, const int32_t* ntiles, long max_tiles, int N, int K, int activation,
+                              const float* bias, hipStream_t st) {
+    const long units = max_tiles * ((N + 15) / 16), cap = static_cast<long>(device_cu_count()) * 4;
+    const unsigned grid = static_cast<unsigned>(std::max(1L, std::min((units + 7) / 8 * 8, cap)));
+    // the widest load that every row's start allows
+    const uintptr_t bases = reinterpret_cast<uintptr_t>(act) | reinterpret_cast<uintptr_t>(w) | reinterpret_cast<uintptr_t>(outp);
+    if (K % 4 == 0 && bases % 16 == 0)
+        return launch_f32<4>(first, grid, act, rowmap, w, outp, tiles, ntiles, N, K, activation, bias, st);
+    if (K % 2 == 0 && bases % 8 == 0)
+        return launch_f32<2>(first, grid, act, rowmap, w, outp, tiles, ntiles, N, K, activation, bias, st);
+    return launch_f32<1>(first, grid, act, rowmap, w, outp, tiles, ntiles, N, K, activation, bias, st);
+}
+
+}  // namespace moe

@@ -9,6 +9,8 @@
 // into counts, prefix sums (per expert over chunks, and over experts), the hot mask and the
 // expert tile list.  Nothing is ordered through atomics on global memory, so every output
 // is the same on every run.
+#include <type_traits>
+
 #include "common.hpp"
 
 namespace moe {
@@ -152,7 +154,7 @@ __host__ __device__ inline int route_row_stride(int E, int NF) { return (E + 16 
 //  every row, so x and the gate matrix cross L1 once per block) and add their partial logits
 //  into LDS one after the other, in wave order (deterministic).  Every k-step issues exactly
 //  NF + TF loads (rows past the end are clamped, their results dropped), two steps ahead.
-//  fp32: plain FMA dot products, one (token, expert) pair per thread and pass.
+//  fp32: the same with 16x16x4 fp32 MFMAs, one fragment of 16 experts at a time.
 // The chunk's histogram goes to chunk_hist[chunk * E + e].
 // Dynamic LDS: logits [16*TF][route_row_stride(E, NF)] floats, then the histogram [E] ints.
 // ---------------------------------------------------------------------------
@@ -265,15 +267,55 @@ __global__ __launch_bounds__(NW * 64) void route_fused_kernel(const ST* __restri
             }
         }
     } else {
-        for (int i = threadIdx.x; i < TOK * E; i += NT) {
-            const int tl = i / E, e = i % E;
-            const float* xr = reinterpret_cast<const float*>(x) + static_cast<size_t>(min(t0 + tl, T - 1)) * d;
-            const float* wr = reinterpret_cast<const float*>(wg) + static_cast<size_t>(e) * d;
-            float s = 0.f;
-            for (int c = 0; c < d; ++c) s = fmaf(xr[c], wr[c], s);
-            L[tl * Ep + e] = s + (bias ? bias[e] : 0.f);
+        // the same with the fp32 matrix instruction, 16 k per step (operands as in ffn_f32.hip); the wavefronts split
+        // the contraction and meet in LDS in wave order
+        static_assert(sizeof(ST) == 2 || (TF == 1 && NF == 1), "fp32 routing takes one fragment of each operand");
+        const int r = lane & 15, g = lane >> 4;
+        const float* xr = reinterpret_cast<const float*>(x) + static_cast<size_t>(min(t0 + r, T - 1)) * d + g * 4;
+        const int steps = d >> 4, per = (steps + NW - 1) / NW;
+        const int s0 = min(steps, wave * per), s1 = min(steps, s0 + per);
+        const bool aligned = d % 4 == 0 && ((reinterpret_cast<uintptr_t>(x) | reinterpret_cast<uintptr_t>(wg)) & 15) == 0;
+        for (int ec = 0; ec < E; ec += 16) {
+            const float* wr = reinterpret_cast<const float*>(wg) + static_cast<size_t>(min(ec + r, E - 1)) * d + g * 4;
+            f32x4 acc = f32x4{0.f, 0.f, 0.f, 0.f};
+            auto fma = [&](const f32x4 a, const f32x4 b) {
+#pragma unroll
+                for (int j = 0; j < 4; ++j) acc = __builtin_amdgcn_mfma_f32_16x16x4f32(a[j], b[j], acc, 0, 0, 0);
+            };
+            auto walk = [&](auto vec) {
+                constexpr int PF = 8;
+                for (int s = s0; s < s1; s += PF) {
+                    f32x4 a[PF], b[PF];
+#pragma unroll
+                    for (int p = 0; p < PF; ++p) {
+                        const int k0 = min(s + p, s1 - 1) * 16;          // past the end: re-read, not used
+                        a[p] = load_k4<decltype(vec)::value>(wr + k0);
+                        b[p] = load_k4<decltype(vec)::value>(xr + k0);
+                    }
+#pragma unroll
+                    for (int p = 0; p < PF; ++p)
+                        if (s + p < s1) fma(a[p], b[p]);
+                }
+            };
+            if (aligned) walk(std::integral_constant<int, 4>{});
+            else walk(std::integral_constant<int, 1>{});
+            if ((d & 15) != 0 && wave == NW - 1)
+                fma(load_k4_tail(wr + steps * 16, (d & 15) - g * 4), load_k4_tail(xr + steps * 16, (d & 15) - g * 4));
+            for (int w = 0; w < NW; ++w) {
+                if (wave == w) {
+                    f32x4* p = reinterpret_cast<f32x4*>(L + r * Ep + ec + g * 4);
+                    f32x4 sofar = f32x4{0.f, 0.f, 0.f, 0.f};
+                    if (w > 0) {
+                        sofar = *p;
+                    } else if (bias != nullptr) {
+#pragma unroll
+                        for (int i = 0; i < 4; ++i) sofar[i] = bias[min(ec + g * 4 + i, E - 1)];
+                    }
+                    *p = acc + sofar;
+                }
+                __syncthreads();
+            }
         }
-        __syncthreads();
     }
 
     // top-k: 4 tokens per wavefront and pass

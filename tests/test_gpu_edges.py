@@ -1,0 +1,92 @@
+"""Sizes at which the kernels' tiles, remainders and dispatch rules change, against the CPU oracle through the C ABI:
+expert FFNs over chosen numbers of rows per expert, and whole layers at chosen token counts."""
+import sys
+
+import numpy as np
+import pytest
+import torch
+
+import workloads as wl
+from oracle import moe_oracle as orc
+
+pytestmark = pytest.mark.gpu
+
+
+def say(*a):
+    print(*a, file=sys.stderr, flush=True)
+
+
+def ffn_rows(moe, rows, d, f, dtype, activation="relu", biases=False, seed=0, mask=None):
+    """moe_expert_ffn over experts with the given row counts; returns (y, the oracle's y at storage precision)."""
+    from paper_2405_18832_amd.device_layer import to_device
+    E, A = len(rows), int(sum(rows))
+    rng = np.random.default_rng([seed, d, f, E, A])
+    draw = lambda shape, s: wl.round_to_storage(rng.standard_normal(shape, dtype=np.float32) * np.float32(s), dtype)
+    x, w1, w2 = draw((A, d), 1.0), draw((E, f, d), d ** -0.5), draw((E, d, f), f ** -0.5)
+    b1, b2 = (draw((E, f), 0.25), draw((E, d), 0.25)) if biases else (None, None)
+    offsets = np.concatenate([[0], np.cumsum(rows)]).astype(np.int32)
+    shape = moe.make_shape(A, d, f, E, 1, dtype, False, {"relu": 0, "gelu": 1}[activation])
+    dev = lambda a, dt: None if a is None else to_device(a, dt, "cuda")
+    packed = []
+    for which, w in ((1, w1), (2, w2)):
+        src = dev(w, dtype)
+        packed.append(torch.empty_like(src))
+        moe.moe_pack_weights(shape, which, src, packed[-1])
+    y = torch.full((A, d), float("nan"), dtype=torch.float32, device="cuda")
+    ws = torch.full((moe.moe_workspace_bytes(shape),), 0xFF, dtype=torch.uint8, device="cuda")
+    m = None if mask is None else torch.tensor(mask, dtype=torch.uint8, device="cuda")
+    moe.moe_expert_ffn_biased(shape, dev(x, dtype), packed[0], dev(b1, "f32"), packed[1], dev(b2, "f32"),
+                              torch.from_numpy(offsets).cuda(), m, y, ws)
+    torch.cuda.synchronize()
+    ref = np.full((A, d), np.nan)
+    for e in range(E):
+        lo, hi = offsets[e], offsets[e + 1]
+        if hi > lo and (mask is None or mask[e]):
+            ref[lo:hi] = orc.expert_ffn(x[lo:hi], w1[e], w2[e], "bf16" if dtype == "bf16" else None, activation,
+                                        *(() if b1 is None else (b1[e], b2[e])))
+    return y.cpu().numpy().astype(np.float64), ref
+
+
+def check(y, ref, tol):
+    assert np.array_equal(np.isnan(y), np.isnan(ref))
+    on = ~np.isnan(ref[:, 0])
+    err = float(orc.rel_error_rows(y[on], ref[on]).max())
+    say(f"[edges] element-wise max {err:.3e} (bar {tol:g})")
+    assert err <= tol
+
+
+# fp32 kernel: row tiles of 1 ... 64 rows (4 fragments of 16) and more, contractions below, at and past a 32-k step, row
+# pitches that allow 16-, 8- and 4-byte loads, column counts that are no multiple of 16.  Bar: sums of at most 300 products
+# in fp32, each within 300 * 2^-24 = 1.8e-5 of the terms' size in the worst case and about 2^-24 * sqrt(300) = 1e-6 in
+# practice.
+@pytest.mark.parametrize("d,f", [(4, 5), (20, 36), (31, 33), (32, 64), (66, 258), (130, 300)])
+def test_f32_ffn_row_tiles(gpu_lib, d, f):
+    say(f"[case] f32 ffn d={d} f={f}")
+    check(*ffn_rows(gpu_lib, [1, 16, 0, 17, 33, 64, 65, 130], d, f, "f32", "gelu", biases=True), 1e-5)
+
+
+def test_f32_ffn_few_rows_masked(gpu_lib):
+    say("[case] f32 ffn few rows, masked")
+    check(*ffn_rows(gpu_lib, [3, 9, 4], 64, 96, "f32", mask=[1, 0, 1]), 1e-5)
+
+
+# fp32 routing: contraction remainders and expert counts around one fragment of 16
+@pytest.mark.parametrize("T,d,E", [(1, 7, 3), (17, 16, 16), (33, 50, 17), (40, 260, 40)])
+def test_f32_route(gpu_lib, T, d, E):
+    say(f"[case] f32 route T={T} d={d} E={E}")
+    moe, k = gpu_lib, 2
+    rng = np.random.default_rng([T, d, E])
+    x, wg = rng.standard_normal((T, d), dtype=np.float32), rng.standard_normal((E, d), dtype=np.float32)
+    b = rng.standard_normal(E, dtype=np.float32)
+    shape = moe.make_shape(T, d, 4, E, k, "f32", True)
+    idx = torch.empty((T, k), dtype=torch.int32, device="cuda")
+    w, margin = torch.empty((T, k), device="cuda"), torch.empty(T, device="cuda")
+    counts, offsets = (torch.empty(n, dtype=torch.int32, device="cuda") for n in (E, E + 1))
+    ws = torch.empty(moe.moe_workspace_bytes(shape), dtype=torch.uint8, device="cuda")
+    moe.moe_route(shape, *(torch.from_numpy(a).cuda() for a in (x, wg, b)), idx, w, margin, counts, offsets, -1, None, ws)
+    torch.cuda.synchronize()
+    r = orc.route(x, wg, b, k, True)
+    ok = r["margin"] >= 1e-4
+    assert np.array_equal(idx.cpu().numpy()[ok], r["idx"][ok])
+    assert np.allclose(w.cpu().numpy()[ok], r["g"][ok], rtol=2e-4)
+    assert np.array_equal(counts.cpu().numpy(), np.bincount(idx.cpu().numpy().ravel(), minlength=E))
