@@ -106,7 +106,7 @@ size_t moe_packed_weight_bytes(const moe_shape* shape) {
 int32_t moe_tiled_kernel_min_rows(const moe_shape* shape, const int32_t* rows_host) {
     if (check_shape(shape) != MOE_OK || rows_host == nullptr) return 0;
     (void)ensure_ready();                                   // the device's CU count; a default stands in without one
-    const TileLists l = ffn_tile_lists(*shape, nullptr, nullptr, nullptr, nullptr);
+    const TileLists l = ffn_tile_lists(*shape, nullptr, nullptr, nullptr, nullptr, nullptr);
     if (l.big_min <= 0) return 0;
     int big_tiles = 0;
     for (int e = 0; e < shape->E; ++e)
@@ -281,8 +281,8 @@ moe_status moe_expert_ffn_biased(const moe_shape* shape, const void* x_perm, con
     if (ensure_ready() != hipSuccess) return MOE_ERR_HIP;
     const WsLayout L = ws_layout(*shape);
     return from_hip(launch_expert_ffn(*shape, x_perm, w1, w2, b1, b2, offsets, mask, y_perm, at<void>(ws, L.h),
-                                      at<Tile>(ws, L.tiles), at<Tile>(ws, L.tiles_big), at<int32_t>(ws, L.ntiles),
-                                      at<float>(ws, L.partials), at<void>(ws, L.x_kmajor), static_cast<hipStream_t>(stream)));
+                                      at<Tile>(ws, L.tiles), at<Tile>(ws, L.tiles_big), at<Tile>(ws, L.tiles_half),
+                                      at<int32_t>(ws, L.ntiles), at<float>(ws, L.partials), at<void>(ws, L.x_kmajor), static_cast<hipStream_t>(stream)));
 }
 
 moe_status moe_combine(const moe_shape* shape, const float* y_perm, const int32_t* inv_perm,
@@ -333,7 +333,8 @@ moe_status moe_layer_forward_biased(const moe_shape* shape, const void* x, const
     int32_t* hist = at<int32_t>(ws, L.hist);
     int32_t* tokmap = at<int32_t>(ws, L.tokmap);
     const TileLists lists = ffn_tile_lists(*shape, at<Tile>(ws, L.tiles), at<Tile>(ws, L.tiles_big),
-                                           at<int32_t>(ws, L.ntiles), at<float>(ws, L.partials));
+                                           at<Tile>(ws, L.tiles_half), at<int32_t>(ws, L.ntiles),
+                                           at<float>(ws, L.partials));
     hipError_t e;
     const int tok = route_chunk_tokens(*shape);
     // few assignments: the finalize block also places them (one launch less)

@@ -54,6 +54,10 @@ struct Tile {
 // kBigTileRows rows); smaller experts are weight-streaming work.
 constexpr int kBigTileRows = 256;
 constexpr int kBigMinRows = 128;
+// The same experts are listed in tiles of kHalfTileRows rows too, for products whose large tiles are too few to
+// occupy the chip (tiled_product_is_fine in tile_schedule.hpp).
+constexpr int kHalfTileRows = 128;
+constexpr int kHalfCount = 4;           // int of the `ntiles` array that holds their number
 // Experts between one streaming tile and kBigMinRows rows would have their weights streamed once per
 // streaming tile; as one mostly empty tile of the tiled kernel they cost about what a single pass over their
 // weights costs -- as long as the tiled kernel has whole rounds of units to run anyway, which hide the one
@@ -156,7 +160,8 @@ __device__ __forceinline__ f32x4 load_k4_tail(const float* __restrict__ p, int l
 struct TileLists {
     Tile* small_tiles;     // capacity A / small_rows + E
     Tile* big_tiles;       // capacity A / kBigTileRows + E (unused when big_min == 0)
-    int32_t* ntiles;       // [0] small count, [1] big count, [2], [3] part counters of the tiled products
+    Tile* half_tiles;      // the same experts in tiles of kHalfTileRows rows, capacity A / kHalfTileRows + E
+    int32_t* ntiles;       // [0] small count, [1] big count, [2], [3] part counters of the tiled products, [4] half count
     float* partials;       // kSplitSlots partial tiles (nullptr when big_min == 0)
     int small_rows;        // rows per small tile
     int big_min;           // experts with >= big_min rows are "big"; 0 = none
@@ -201,58 +206,86 @@ __device__ __forceinline__ void place_chunk(const int32_t* __restrict__ idx, int
     }
 }
 
-// Inclusive prefix sum over the 1024 threads of a block (thread e contributes v): shuffles inside each
-// wavefront, one LDS round for the 16 wavefront totals.  `tmp` is an LDS array of >= 16 ints; two barriers.
-__device__ __forceinline__ int block_scan_1024(int v, int32_t* tmp) {
+// Inclusive prefix sums of N values at once over the 1024 threads of a block (thread e contributes v[i]) and their
+// totals: shuffles inside each wavefront, one LDS round for the 16 wavefront totals.  `tmp` is an LDS array of
+// >= 16 * N ints; two barriers, whatever N.
+template <int N>
+__device__ __forceinline__ void block_scan_1024(const int (&v)[N], int (&incl)[N], int (&total)[N], int32_t* tmp) {
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    int incl = v;
+#pragma unroll
+    for (int i = 0; i < N; ++i) incl[i] = v[i];
 #pragma unroll
     for (int s = 1; s < 64; s <<= 1) {
-        const int o = __shfl_up(incl, s);
-        if (lane >= s) incl += o;
+#pragma unroll
+        for (int i = 0; i < N; ++i) {
+            const int o = __shfl_up(incl[i], s);
+            if (lane >= s) incl[i] += o;
+        }
     }
     __syncthreads();                       // tmp may still be read from a previous call
-    if (lane == 63) tmp[wave] = incl;
+    if (lane == 63) {
+#pragma unroll
+        for (int i = 0; i < N; ++i) tmp[i * 16 + wave] = incl[i];
+    }
     __syncthreads();
-    int base = 0;
-    for (int w = 0; w < wave; ++w) base += tmp[w];
-    return base + incl;
+#pragma unroll
+    for (int i = 0; i < N; ++i) {
+        int base = 0, sum = 0;
+#pragma unroll
+        for (int w = 0; w < 16; ++w) {
+            const int t = tmp[i * 16 + w];
+            if (w < wave) base += t;
+            sum += t;
+        }
+        incl[i] += base;
+        total[i] = sum;
+    }
+}
+
+// tiles of the large experts' kernel that an expert of m rows contributes to the sum tiled_min_rows is asked with
+__device__ __forceinline__ int big_tiles_at_min(int m, const TileLists& tl) {
+    return tl.big_min > 0 && m >= tl.big_min ? (m + kBigTileRows - 1) / kBigTileRows : 0;
+}
+
+// The tiles of one expert (row0, m rows), `rows` rows each, to out[0 ...].  Called by whole wavefronts, a lane per
+// expert.  An expert with more than two tiles is written by all lanes of its wavefront (thousands of rows make dozens
+// of tiles, which one lane alone would store one after the other).
+__device__ __forceinline__ void write_tiles(Tile* __restrict__ out, int e, int row0, int m, int rows, int nt) {
+    for (int i = 0; i < 2; ++i)
+        if (nt <= 2 && i < nt) out[i] = Tile{e, row0 + i * rows, min(rows, m - i * rows), 0};
+    uint64_t many = __ballot(nt > 2);
+    while (many != 0) {                                    // wave-uniform
+        const int src = __builtin_ctzll(many);
+        many &= many - 1;
+        const int r0 = __builtin_amdgcn_readlane(row0, src), mm = __builtin_amdgcn_readlane(m, src);
+        const int n = __builtin_amdgcn_readlane(nt, src), ee = __builtin_amdgcn_readlane(e, src);
+        const uint64_t at = reinterpret_cast<uint64_t>(out);
+        const uint64_t lo = static_cast<uint32_t>(__builtin_amdgcn_readlane(static_cast<int>(at), src));
+        const uint64_t hi = static_cast<uint32_t>(__builtin_amdgcn_readlane(static_cast<int>(at >> 32), src));
+        Tile* o = reinterpret_cast<Tile*>(lo | hi << 32);
+        for (int i = threadIdx.x & 63; i < n; i += 64) o[i] = Tile{ee, r0 + i * rows, min(rows, mm - i * rows), 0};
+    }
 }
 
 // Called by all 1024 threads of a block, thread e owning expert e (row0, m rows; m = 0 when the
-// expert is empty or masked out).  `scan` is an LDS array of MOE_MAX_E ints.
-__device__ __forceinline__ void emit_tiles(int e, int row0, int m, const TileLists tl, int32_t* scan) {
-    int min_rows = tl.big_min;
-    if (tl.big_min > 0 && tl.join_tiles > 0) {
-        // tiles of the experts that are large in any case, summed over the block
-        const int incl = block_scan_1024(m >= tl.big_min ? (m + kBigTileRows - 1) / kBigTileRows : 0, scan);
-        __syncthreads();
-        if (threadIdx.x == 1023) scan[16] = incl;
-        __syncthreads();
-        min_rows = tiled_min_rows(scan[16], tl.small_rows, tl.join_tiles);
+// expert is empty or masked out).  `big_at_min`: the block's sum of big_tiles_at_min.  `tmp` is an LDS array of
+// >= 48 ints.
+__device__ __forceinline__ void emit_tiles(int e, int row0, int m, int big_at_min, const TileLists tl, int32_t* tmp) {
+    const bool big = tl.big_min > 0 && m >= tiled_min_rows(big_at_min, tl.small_rows, tl.join_tiles);
+    const int nt[3] = {big ? 0 : (m + tl.small_rows - 1) / tl.small_rows, big ? (m + kBigTileRows - 1) / kBigTileRows : 0,
+                       big ? (m + kHalfTileRows - 1) / kHalfTileRows : 0};
+    int incl[3], total[3];
+    block_scan_1024(nt, incl, total, tmp);
+    write_tiles(tl.small_tiles + incl[0] - nt[0], e, row0, m, tl.small_rows, nt[0]);
+    if (tl.big_min > 0) {
+        write_tiles(tl.big_tiles + incl[1] - nt[1], e, row0, m, kBigTileRows, nt[1]);
+        write_tiles(tl.half_tiles + incl[2] - nt[2], e, row0, m, kHalfTileRows, nt[2]);
     }
-    const bool big = tl.big_min > 0 && m >= min_rows;
-    for (int pass = 0; pass < 2; ++pass) {
-        const int rows = pass == 0 ? tl.small_rows : kBigTileRows;
-        const bool mine = (pass == 1) == big;
-        const int nt = mine ? (m + rows - 1) / rows : 0;
-        const int incl = block_scan_1024(nt, scan);
-        Tile* out = pass == 0 ? tl.small_tiles : tl.big_tiles;
-        const int base = incl - nt;
-        for (int i = 0; i < nt; ++i) {
-            Tile t;
-            t.expert = e;
-            t.row0 = row0 + i * rows;
-            t.rows = min(rows, m - i * rows);
-            t.pad = 0;
-            out[base + i] = t;
-        }
-        if (e == MOE_MAX_E - 1) tl.ntiles[pass] = incl;
-        if (pass == 0 && e < 2) tl.ntiles[kSplitCounter + e] = 0;
-        if (tl.big_min <= 0 && pass == 0) {      // no large experts possible
-            if (e == 0) tl.ntiles[1] = 0;
-            break;
-        }
+    if (e == 0) {
+        tl.ntiles[0] = total[0];
+        tl.ntiles[1] = total[1];
+        tl.ntiles[kHalfCount] = total[2];
+        tl.ntiles[kSplitCounter] = tl.ntiles[kSplitCounter + 1] = 0;
     }
 }
 #endif
@@ -263,6 +296,7 @@ struct WsLayout {
     size_t ntiles;     // int32 [64]  ([0] = tiles of small experts, [1] = of large experts, [2], [3] counters)
     size_t tiles;      // Tile [A/16 + E + 1]   row tiles of the weight-streaming kernel
     size_t tiles_big;  // Tile [A/256 + E + 1]  row tiles of the LDS-tiled kernel
+    size_t tiles_half; // Tile [A/128 + E + 1]  the same rows in the half-sized tiles of that kernel (if an expert can have them)
     size_t h;          // dtype [A rounded up to kRowBlock, f]
     size_t idx;        // int32 [A]         -- the rest is used by moe_layer_forward only
     size_t gate;       // float [A]
@@ -305,6 +339,8 @@ inline WsLayout ws_layout(const moe_shape& s) {
     L.ntiles = take(64 * 4);
     L.tiles = take((A / 16 + E + 1) * sizeof(Tile));
     L.tiles_big = take((A / 256 + E + 1) * sizeof(Tile));
+    const bool big = s.dtype == MOE_BF16 && s.T >= kBigMinRows;
+    L.tiles_half = take(big ? (A / kHalfTileRows + E + 1) * sizeof(Tile) : 0);
     const size_t Ab = (A + kRowBlock - 1) / kRowBlock * kRowBlock;     // the blocked layouts hold whole row blocks
     L.h = take(Ab * s.d_ff * es);
     L.idx = take(A * 4);
@@ -316,7 +352,6 @@ inline WsLayout ws_layout(const moe_shape& s) {
     L.mask = take(E);
     L.tokmap = take(A * 4);
     L.y_perm = take(A * s.d_model * 4);
-    const bool big = s.dtype == MOE_BF16 && s.T >= kBigMinRows;
     L.partials = take(big ? static_cast<size_t>(kSplitSlots) * kBigTileRows * 256 * 4 : 0);
     L.x_kmajor = take(big ? Ab * s.d_model * es : 0);
     L.gate_part = take(route_is_split(s) ? static_cast<size_t>(kGateSplit) * ((s.T + 15) / 16 * 16) * E * 4 : 0);
@@ -361,7 +396,7 @@ hipError_t launch_route_finalize(const moe_shape& s, const void* x, const void* 
 hipError_t launch_scan_finalize(int32_t* chunk_hist, int nchunks, int E, int32_t* counts, int32_t* offsets, int H,
                                 uint8_t* hot_mask, const uint8_t* mask_in, const TileLists* lists,
                                 const PlaceArgs* place, hipStream_t st);
-TileLists ffn_tile_lists(const moe_shape& s, Tile* small_ws, Tile* big_ws, int32_t* ntiles_ws, float* partials_ws);
+TileLists ffn_tile_lists(const moe_shape& s, Tile* small_ws, Tile* big_ws, Tile* half_ws, int32_t* ntiles_ws, float* partials_ws);
 hipError_t launch_place(const moe_shape& s, const int32_t* idx, const int32_t* offsets, const int32_t* chunk_base,
                         int32_t* perm, int32_t* inv_perm, int32_t* tokmap, int chunk, hipStream_t st);
 int ffn_tile_rows(const moe_shape& s);
@@ -372,8 +407,7 @@ hipError_t launch_expert_products(const moe_shape& s, const void* act, const int
 bool layer_gathers_kmajor(const moe_shape& s);
 hipError_t launch_gather_kmajor(const moe_shape& s, const void* x, const int32_t* tokmap, void* xk, hipStream_t st);
 hipError_t launch_tile_product(bool first, const uint16_t* act, const int32_t* rowmap, const uint16_t* wpk,
-                               void* outp, const Tile* tiles, const int32_t* ntiles, int32_t* part_counter,
-                               float* partials, int N, int K, bool act_kmajor, int activation,
+                               void* outp, const TileLists& lists, long A, int N, int K, bool act_kmajor, int activation,
                                const float* bias, const FoldOut& fold, hipStream_t st);
 int tile_product_grid();
 hipError_t launch_f32_product(bool first, const float* act, const int32_t* rowmap, const float* w, float* outp,
@@ -385,7 +419,7 @@ hipError_t launch_permute(const moe_shape& s, const void* x, const int32_t* idx,
 hipError_t launch_expert_ffn(const moe_shape& s, const void* x_perm, const void* w1, const void* w2,
                              const float* b1, const float* b2,
                              const int32_t* offsets, const uint8_t* mask, float* y_perm,
-                             void* h_ws, Tile* tiles_ws, Tile* tiles_big_ws, int32_t* ntiles_ws, float* partials_ws,
+                             void* h_ws, Tile* tiles_ws, Tile* tiles_big_ws, Tile* tiles_half_ws, int32_t* ntiles_ws, float* partials_ws,
                              void* x_kmajor_ws, hipStream_t st);
 hipError_t launch_combine(const moe_shape& s, const float* y_perm, const int32_t* inv_perm,
                           const int32_t* idx, const float* gate, const uint8_t* mask, void* out,

@@ -58,7 +58,7 @@ hipError_t launch_pack(const moe_shape& s, int which, const void* src, void* dst
 __global__ __launch_bounds__(1024) void build_tiles_kernel(const int32_t* __restrict__ offsets,
                                                            const uint8_t* __restrict__ mask, int E, int A,
                                                            const TileLists lists) {
-    __shared__ int32_t scan[MOE_MAX_E];
+    __shared__ int32_t scan[48];
     const int e = threadIdx.x;
     int row0 = 0, m = 0;
     bool bad = false;
@@ -72,7 +72,10 @@ __global__ __launch_bounds__(1024) void build_tiles_kernel(const int32_t* __rest
     // With every count >= 0 the segments are disjoint and their sum is at most A, which is what the capacity of
     // the tile lists assumes.
     if (__syncthreads_or(bad ? 1 : 0)) m = 0;
-    emit_tiles(e, row0, m, lists, scan);
+    const int at_min[1] = {big_tiles_at_min(m, lists)};
+    int incl[1], total[1];
+    block_scan_1024(at_min, incl, total, scan);
+    emit_tiles(e, row0, m, total[0], lists, scan);
 }
 
 // ---------------------------------------------------------------------------
@@ -404,7 +407,8 @@ __global__ __launch_bounds__(256) void ffn_stream_kernel(const uint16_t* __restr
                                                          const int32_t* __restrict__ ntiles_p, int N,
                                                          int K, int balance,
                                                          const Tile* __restrict__ big_tiles,
-                                                         const float* __restrict__ partials, int tile_grid,
+                                                         const Tile* __restrict__ half_tiles,
+                                                         const float* __restrict__ partials, int cus,
                                                          int act_kmajor, int rows_in_lds,
                                                          const float* __restrict__ bias, const FoldOut fold) {
     extern __shared__ __attribute__((aligned(16))) unsigned char tok_lds[];
@@ -439,11 +443,11 @@ __global__ __launch_bounds__(256) void ffn_stream_kernel(const uint16_t* __restr
         const int idle = stride - nbu;                    // blocks with pb >= nbu have no unit (balance is off here)
         if (idle * 4 >= stride) {
             if (pb >= nbu)
-                finish_split_units<FIRST, FOLD>(big_tiles, ntiles_p[1], partials, outp, N, K >> 5, tile_grid, bias, fold,
-                                                pb - nbu, idle);
+                finish_tiled_product<FIRST, FOLD>(big_tiles, half_tiles, ntiles_p, partials, outp, N, K >> 5, cus, bias, fold,
+                                                  pb - nbu, idle);
         } else {
-            finish_split_units<FIRST, FOLD>(big_tiles, ntiles_p[1], partials, outp, N, K >> 5, tile_grid, bias, fold,
-                                            static_cast<int>(blockIdx.x), static_cast<int>(gridDim.x));
+            finish_tiled_product<FIRST, FOLD>(big_tiles, half_tiles, ntiles_p, partials, outp, N, K >> 5, cus, bias, fold,
+                                              static_cast<int>(blockIdx.x), static_cast<int>(gridDim.x));
         }
     }
     for (int base = 0; base < nbu; base += stride) {
@@ -530,7 +534,7 @@ __global__ __launch_bounds__(256) void ffn_stream_narrow_kernel(const uint16_t* 
 template <int TFMAX, int KSPLIT, int FIRST, bool FOLD>
 static hipError_t launch_stream(const uint16_t* act, const int32_t* rowmap, const uint16_t* wpk, void* outp,
                                 const Tile* tiles, const int32_t* ntiles, int N, int K, long max_units,
-                                const Tile* big_tiles, const float* partials, bool act_kmajor,
+                                const TileLists& big, bool act_kmajor,
                                 const float* bias, const FoldOut& fold, hipStream_t st) {
     auto kern = ffn_stream_kernel<TFMAX, KSPLIT, FIRST, FOLD>;
     const int per_cu = std::max(1, StreamKernelInfo<TFMAX, KSPLIT, FIRST, FOLD>::per_cu[current_device_index()]);
@@ -543,11 +547,11 @@ static hipError_t launch_stream(const uint16_t* act, const int32_t* rowmap, cons
     int blocks_per_cu = per_cu;
     if (lds > 0) blocks_per_cu = std::max(1, std::min(per_cu, static_cast<int>(kLdsPerCu / lds)));
     long grid = static_cast<long>(device_cu_count()) * blocks_per_cu;
-    if (grid > max_units && partials == nullptr) grid = max_units;   // with partial tiles to add: all blocks
+    if (grid > max_units && big.partials == nullptr) grid = max_units;   // with partial tiles to add: all blocks
     if (grid < 1) grid = 1;
     // decode-sized tiles (many units per block): balanced grid; larger tiles: every block stays busy
     hipLaunchKernelGGL(kern, dim3(static_cast<unsigned>(grid)), dim3(256), lds, st, act, rowmap, wpk, outp, tiles,
-                       ntiles, N, K, TFMAX <= 2 ? 1 : 0, big_tiles, partials, tile_product_grid(),
+                       ntiles, N, K, TFMAX <= 2 ? 1 : 0, big.big_tiles, big.half_tiles, big.partials, device_cu_count(),
                        act_kmajor ? 1 : 0, rows_in_lds ? 1 : 0, bias, fold);
     return hipGetLastError();
 }
@@ -555,18 +559,18 @@ static hipError_t launch_stream(const uint16_t* act, const int32_t* rowmap, cons
 template <int TFMAX, int FIRST, bool FOLD>
 static hipError_t launch_stream_kf(int ksplit, const uint16_t* act, const int32_t* rowmap, const uint16_t* wpk,
                                    void* outp, const Tile* tiles, const int32_t* ntiles, int N, int K,
-                                   long max_tiles, const Tile* big_tiles, const float* partials,
+                                   long max_tiles, const TileLists& big,
                                    bool act_kmajor, const float* bias, const FoldOut& fold, hipStream_t st) {
     const long ngroups = (N / 16 + 3) / 4;
     if (ksplit == 4)
         return launch_stream<TFMAX, 4, FIRST, FOLD>(act, rowmap, wpk, outp, tiles, ntiles, N, K, max_tiles * ngroups,
-                                                    big_tiles, partials, act_kmajor, bias, fold, st);
+                                                    big, act_kmajor, bias, fold, st);
     if (ksplit == 2)
         return launch_stream<TFMAX, 2, FIRST, FOLD>(act, rowmap, wpk, outp, tiles, ntiles, N, K,
-                                                    max_tiles * ((ngroups + 1) / 2), big_tiles, partials,
+                                                    max_tiles * ((ngroups + 1) / 2), big,
                                                     act_kmajor, bias, fold, st);
     return launch_stream<TFMAX, 1, FIRST, FOLD>(act, rowmap, wpk, outp, tiles, ntiles, N, K,
-                                                max_tiles * ((ngroups + 3) / 4), big_tiles, partials,
+                                                max_tiles * ((ngroups + 3) / 4), big,
                                                 act_kmajor, bias, fold, st);
 }
 
@@ -574,15 +578,15 @@ static hipError_t launch_stream_kf(int ksplit, const uint16_t* act, const int32_
 template <int TFMAX, int FIRST>
 static hipError_t launch_stream_k(int ksplit, const uint16_t* act, const int32_t* rowmap, const uint16_t* wpk,
                                   void* outp, const Tile* tiles, const int32_t* ntiles, int N, int K,
-                                  long max_tiles, const Tile* big_tiles, const float* partials,
+                                  long max_tiles, const TileLists& big,
                                   bool act_kmajor, const float* bias, const FoldOut& fold, hipStream_t st) {
     if constexpr (FIRST == 0) {
         if (fold.out != nullptr)
             return launch_stream_kf<TFMAX, 0, true>(ksplit, act, rowmap, wpk, outp, tiles, ntiles, N, K, max_tiles,
-                                                    big_tiles, partials, act_kmajor, bias, fold, st);
+                                                    big, act_kmajor, bias, fold, st);
     }
     return launch_stream_kf<TFMAX, FIRST, false>(ksplit, act, rowmap, wpk, outp, tiles, ntiles, N, K, max_tiles,
-                                                 big_tiles, partials, act_kmajor, bias, fold, st);
+                                                 big, act_kmajor, bias, fold, st);
 }
 
 template <int TFMAX, int KSPLIT, int FIRST, bool FOLD>
@@ -665,10 +669,12 @@ static int ffn_tfmax(const moe_shape& s) { return s.T <= 16 ? 1 : (s.T <= 32 ? 2
 
 int ffn_tile_rows(const moe_shape& s) { return 16 * ffn_tfmax(s); }
 
-TileLists ffn_tile_lists(const moe_shape& s, Tile* small_ws, Tile* big_ws, int32_t* ntiles_ws, float* partials_ws) {
+TileLists ffn_tile_lists(const moe_shape& s, Tile* small_ws, Tile* big_ws, Tile* half_ws, int32_t* ntiles_ws,
+                         float* partials_ws) {
     TileLists l;
     l.small_tiles = small_ws;
     l.big_tiles = big_ws;
+    l.half_tiles = half_ws;
     l.ntiles = ntiles_ws;
     l.small_rows = ffn_tile_rows(s);
     // a large expert needs kBigMinRows rows, and an expert holds at most T rows
@@ -705,8 +711,6 @@ hipError_t launch_expert_products(const moe_shape& s, const void* act, const int
     const int32_t* ntiles = lists.ntiles;
     const long max_tiles = A / tile_rows + (E < A ? E : A);
     const bool big = lists.big_min > 0;
-    int32_t* part1 = lists.ntiles + kSplitCounter;
-    int32_t* part2 = part1 + 1;
     hipError_t err;
     if ((err = mark(0, st)) != hipSuccess) return err;
 
@@ -728,34 +732,32 @@ hipError_t launch_expert_products(const moe_shape& s, const void* act, const int
     uint16_t* h = static_cast<uint16_t*>(h_ws);
     const long tiles_expected = A < E ? A : E;      // every assignment on its own expert, at most E of them
     const int ks1 = pick_ksplit(d, f, ffn_tfmax(s), tiles_expected), ks2 = pick_ksplit(f, d, ffn_tfmax(s), tiles_expected);
-    const Tile* bt = lists.big_tiles;
-    const float* pt = big ? lists.partials : nullptr;
     // Per product: the tiled kernel (large experts) first, then the streaming kernel (small experts), which
     // also adds up the partial tiles that the tiled kernel left for the units it cut along K.
     if (big) {
-        err = launch_tile_product(true, xp, rowmap, p1, h, bt, ntiles + 1, part1, lists.partials, f, d, act_kmajor, s.activation, b1,
+        err = launch_tile_product(true, xp, rowmap, p1, h, lists, A, f, d, act_kmajor, s.activation, b1,
                                   FoldOut{nullptr, nullptr, nullptr}, st);
         if (err != hipSuccess) return err;
     }
     if ((err = mark(1, st)) != hipSuccess) return err;
     const bool gelu = s.activation == MOE_ACT_GELU;
     switch (ffn_tfmax(s) * 2 + (gelu ? 1 : 0)) {
-        case 2: err = launch_stream_k<1, kFirstRelu>(ks1, xp, rowmap, p1, h, tiles, ntiles, f, d, max_tiles, bt, pt, act_kmajor, b1, FoldOut{nullptr, nullptr, nullptr}, st); break;
-        case 3: err = launch_stream_k<1, kFirstGelu>(ks1, xp, rowmap, p1, h, tiles, ntiles, f, d, max_tiles, bt, pt, act_kmajor, b1, FoldOut{nullptr, nullptr, nullptr}, st); break;
-        case 4: err = launch_stream_k<2, kFirstRelu>(ks1, xp, rowmap, p1, h, tiles, ntiles, f, d, max_tiles, bt, pt, act_kmajor, b1, FoldOut{nullptr, nullptr, nullptr}, st); break;
-        case 5: err = launch_stream_k<2, kFirstGelu>(ks1, xp, rowmap, p1, h, tiles, ntiles, f, d, max_tiles, bt, pt, act_kmajor, b1, FoldOut{nullptr, nullptr, nullptr}, st); break;
-        case 8: err = launch_stream_k<4, kFirstRelu>(ks1, xp, rowmap, p1, h, tiles, ntiles, f, d, max_tiles, bt, pt, act_kmajor, b1, FoldOut{nullptr, nullptr, nullptr}, st); break;
-        default: err = launch_stream_k<4, kFirstGelu>(ks1, xp, rowmap, p1, h, tiles, ntiles, f, d, max_tiles, bt, pt, act_kmajor, b1, FoldOut{nullptr, nullptr, nullptr}, st); break;
+        case 2: err = launch_stream_k<1, kFirstRelu>(ks1, xp, rowmap, p1, h, tiles, ntiles, f, d, max_tiles, lists, act_kmajor, b1, FoldOut{nullptr, nullptr, nullptr}, st); break;
+        case 3: err = launch_stream_k<1, kFirstGelu>(ks1, xp, rowmap, p1, h, tiles, ntiles, f, d, max_tiles, lists, act_kmajor, b1, FoldOut{nullptr, nullptr, nullptr}, st); break;
+        case 4: err = launch_stream_k<2, kFirstRelu>(ks1, xp, rowmap, p1, h, tiles, ntiles, f, d, max_tiles, lists, act_kmajor, b1, FoldOut{nullptr, nullptr, nullptr}, st); break;
+        case 5: err = launch_stream_k<2, kFirstGelu>(ks1, xp, rowmap, p1, h, tiles, ntiles, f, d, max_tiles, lists, act_kmajor, b1, FoldOut{nullptr, nullptr, nullptr}, st); break;
+        case 8: err = launch_stream_k<4, kFirstRelu>(ks1, xp, rowmap, p1, h, tiles, ntiles, f, d, max_tiles, lists, act_kmajor, b1, FoldOut{nullptr, nullptr, nullptr}, st); break;
+        default: err = launch_stream_k<4, kFirstGelu>(ks1, xp, rowmap, p1, h, tiles, ntiles, f, d, max_tiles, lists, act_kmajor, b1, FoldOut{nullptr, nullptr, nullptr}, st); break;
     }
     if (err != hipSuccess) return err;
     if ((err = mark(2, st)) != hipSuccess) return err;
     if (big) {
-        err = launch_tile_product(false, h, nullptr, p2, y_perm, bt, ntiles + 1, part2, lists.partials, d, f, true, s.activation, b2, fold, st);
+        err = launch_tile_product(false, h, nullptr, p2, y_perm, lists, A, d, f, true, s.activation, b2, fold, st);
         if (err != hipSuccess) return err;
     }
     if ((err = mark(3, st)) != hipSuccess) return err;
     // few tokens and few experts: units of one column block, so that every CU has one
-    const bool narrow = ffn_tfmax(s) == 1 && ks2 == 4 && fold.out == nullptr && pt == nullptr &&
+    const bool narrow = ffn_tfmax(s) == 1 && ks2 == 4 && fold.out == nullptr && !big &&
                         tiles_expected * ((d / 16 + 3) / 4) < device_cu_count();
     if (narrow) {
         long grid = max_tiles * (d / 16);
@@ -766,9 +768,9 @@ hipError_t launch_expert_products(const moe_shape& s, const void* act, const int
         return mark(4, st);
     }
     switch (ffn_tfmax(s)) {
-        case 1: err = launch_stream_k<1, 0>(ks2, h, nullptr, p2, y_perm, tiles, ntiles, d, f, max_tiles, bt, pt, true, b2, fold, st); break;
-        case 2: err = launch_stream_k<2, 0>(ks2, h, nullptr, p2, y_perm, tiles, ntiles, d, f, max_tiles, bt, pt, true, b2, fold, st); break;
-        default: err = launch_stream_k<4, 0>(ks2, h, nullptr, p2, y_perm, tiles, ntiles, d, f, max_tiles, bt, pt, true, b2, fold, st); break;
+        case 1: err = launch_stream_k<1, 0>(ks2, h, nullptr, p2, y_perm, tiles, ntiles, d, f, max_tiles, lists, true, b2, fold, st); break;
+        case 2: err = launch_stream_k<2, 0>(ks2, h, nullptr, p2, y_perm, tiles, ntiles, d, f, max_tiles, lists, true, b2, fold, st); break;
+        default: err = launch_stream_k<4, 0>(ks2, h, nullptr, p2, y_perm, tiles, ntiles, d, f, max_tiles, lists, true, b2, fold, st); break;
     }
     if (err != hipSuccess) return err;
     return mark(4, st);
@@ -777,9 +779,9 @@ hipError_t launch_expert_products(const moe_shape& s, const void* act, const int
 hipError_t launch_expert_ffn(const moe_shape& s, const void* x_perm, const void* w1, const void* w2,
                              const float* b1, const float* b2,
                              const int32_t* offsets, const uint8_t* mask, float* y_perm, void* h_ws,
-                             Tile* tiles_ws, Tile* tiles_big_ws, int32_t* ntiles_ws, float* partials_ws,
+                             Tile* tiles_ws, Tile* tiles_big_ws, Tile* tiles_half_ws, int32_t* ntiles_ws, float* partials_ws,
                              void* x_kmajor_ws, hipStream_t st) {
-    const TileLists lists = ffn_tile_lists(s, tiles_ws, tiles_big_ws, ntiles_ws, partials_ws);
+    const TileLists lists = ffn_tile_lists(s, tiles_ws, tiles_big_ws, tiles_half_ws, ntiles_ws, partials_ws);
     hipLaunchKernelGGL(build_tiles_kernel, dim3(1), dim3(1024), 0, st, offsets, mask, s.E, s.T * s.k, lists);
     hipError_t err = hipGetLastError();
     if (err != hipSuccess) return err;

@@ -4,7 +4,7 @@
 //
 //   out[row, n] = sum_k act[row, k] * W_e[n, k]          (FIRST: relu, rounded to bf16)
 //
-// Block = 8 wavefronts on a 256 (rows) x 256 (columns) output tile, K in steps of 32 through a
+// Big units: block = 8 wavefronts on a 256 (rows) x 256 (columns) output tile, K in steps of 32 through a
 // ring of four LDS stages of 32 KiB: the copies of two stages are in flight while two are being
 // read (the current one, and the next one into registers ahead of its MFMAs).  Both operands sit in LDS in MFMA-fragment order (16 x 32 fragments of
 // 1 KiB, one 16-byte piece per lane), so every LDS read of the inner loop is a conflict-free
@@ -13,7 +13,17 @@
 // activation rows (optionally gathered through `rowmap`) each lane fetches the piece that
 // belongs at its own slot.  Wavefront (wm, wn) of the 2 x 4 grid owns 128 rows x 64 columns:
 // 4 weight fragments (MFMA A operand) x 8 row fragments (B operand) of 16x16x32 per 32-k step,
-// 128 accumulator registers.  Blocks are persistent over (row tile, column tile) pairs taken
+// 128 accumulator registers.
+//
+// Fine units, for products whose big units would leave much of the chip idle (tiled_product_is_fine): 4 wavefronts
+// on 128 x 128, each 64 x 64, the same ring of stages half the size, two blocks per CU.  A CU can pull about 35 GB/s
+// from beyond its L2 however much it has in flight, so a handful of big units is bound by the CUs they run on, not by
+// memory or matrix units.  Per output they copy twice the bytes of big units, and they cut less along K.  Measured, 8
+// experts of 137 ... 228 rows, 768 x 3072: 39.7 -> 30.6 us (96 big units of 24 steps) and 33.2 + 8.9 -> 19.3 + 11.1 us
+// (24 units of 96 steps; the second figure adds up the parts); one expert of 327 rows, 1024 x 4096: 28 -> 15 and 32 -> 13 us.
+// Three blocks per CU with a ring of three stages, or five stages, are no faster.
+//
+// Blocks are persistent over (row tile, column tile) pairs taken
 // from the device-built list of large-expert row tiles.
 #include <type_traits>
 
@@ -21,14 +31,10 @@
 
 namespace moe {
 
-constexpr int kTM = kBigTileRows;   // 256 rows
-constexpr int kTN = kTileCols;      // 256 columns
 constexpr int kTK = 32;             // k per LDS stage
 constexpr int kStages = 4;          // ring of LDS stages: two being read, two in flight (a fifth, which
                                     // fits, bought nothing: the copies are not limited by ring depth)
 constexpr int kAhead = kStages - 1; // the iteration for stage j issues the copies of stage j + kAhead
-constexpr int kOperandBytes = kTM * kTK * 2;        // 16 KiB per operand per stage
-constexpr int kStageBytes = 2 * kOperandBytes;      // 32 KiB per stage
 
 // Wait until at most `stages` stages' worth of this wavefront's copies (4 each) are still in flight.
 __device__ __forceinline__ void wait_copies(int stages) {
@@ -39,7 +45,7 @@ __device__ __forceinline__ void wait_copies(int stages) {
 }
 
 // Register fragments of one wavefront: the 4 weight fragments of a stage, double-buffered over stages,
-// and the 8 row fragments as 4 pairs.
+// and the 8 row fragments as 4 pairs (big units) or the 4 row fragments as 2 pairs, double-buffered like the weights.
 struct StageFrags {
     bf16x8 w[2][4];
     bf16x8 x[4][2];
@@ -56,8 +62,8 @@ __device__ __forceinline__ void lds_read_x(bf16x8 (&x)[2], const unsigned char* 
 }
 
 // 4 weight fragments x row-fragment pair P: 8 MFMAs
-template <int P>
-__device__ __forceinline__ void mfma_pair(const bf16x8 (&w)[4], const bf16x8 (&x)[2], f32x4 (&acc)[4][8]) {
+template <int P, int RF>
+__device__ __forceinline__ void mfma_pair(const bf16x8 (&w)[4], const bf16x8 (&x)[2], f32x4 (&acc)[4][RF]) {
 #pragma unroll
     for (int nf = 0; nf < 4; ++nf) {
         acc[nf][2 * P] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w[nf], x[0], acc[nf][2 * P], 0, 0, 0);
@@ -65,8 +71,8 @@ __device__ __forceinline__ void mfma_pair(const bf16x8 (&w)[4], const bf16x8 (&x
     }
 }
 
-template <int FIRST>
-__global__ __launch_bounds__(512) void ffn_tile_kernel(const uint16_t* __restrict__ act,
+template <int FIRST, typename Units>
+__global__ __launch_bounds__(Units::kWaves * 64, 2) void ffn_tile_kernel(const uint16_t* __restrict__ act,
                                                        const int32_t* __restrict__ rowmap,
                                                        const uint16_t* __restrict__ wpk,
                                                        void* __restrict__ outp, const Tile* __restrict__ tiles,
@@ -75,26 +81,33 @@ __global__ __launch_bounds__(512) void ffn_tile_kernel(const uint16_t* __restric
                                                        float* __restrict__ partials, int N, int K,
                                                        int act_kmajor,
                                                        const float* __restrict__ bias, const FoldOut fold) {
+    constexpr bool FINE = Units::kWaves == 4;
+    constexpr int kTM = Units::kRows, kTN = Units::kCols;
+    constexpr int WN = kTN / 64;                        // wavefronts side by side; two in the row direction
+    constexpr int RF = kTM / 32;                        // row fragments of a wavefront
+    constexpr int kOperandBytes = kTM * kTK * 2;        // per operand and stage (kTM == kTN)
+    constexpr int kStageBytes = 2 * kOperandBytes;
+    static_assert(kTM == kTN && Units::kWaves == 2 * WN && kTM / 16 == 2 * Units::kWaves, "two fragments per wavefront and copy");
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
     // between units, when no stage is in use, the first word of the ring passes the next part's number on
     int* next_part = reinterpret_cast<int*>(smem);
-    // stage st: 16 row fragments at smem + st * kStageBytes, 16 weight fragments behind them
+    // stage st: kTM / 16 row fragments at smem + st * kStageBytes, as many weight fragments behind them
 
     const int t = threadIdx.x, wave = t >> 6, lane = t & 63;
-    const int wm = wave >> 2, wn = wave & 3;
+    const int wm = wave / WN, wn = wave % WN;
     const int r = lane & 15, g = lane >> 4;
     const int nblk = N >> 4, kblk = K >> 5;
-    const int ntn = (N + kTN - 1) / kTN;
-    const int ntiles = ntiles_p[0];
-    if (ntiles <= 0) return;                            // no large expert in this call (block-uniform)
+    const int ntiles = ntiles_p[FINE ? kHalfCount : 1];
+    const int G = gridDim.x;
+    // no large expert in this call, or the product runs in the other units (block-uniform)
+    if (ntiles <= 0 || tiled_product_is_fine(ntiles_p[1], N, G / Units::kPerCu) != FINE) return;
     // LDS byte address of the first of the two fragments that this wavefront copies in, stage 0
     const uint32_t copy_base = lds_address(smem) + 2 * wave * 1024;
 
     // Blocks are handed to the 8 XCDs round-robin, and each XCD has its own L2: block b takes position pb
     // of a round, so that the blocks of one XCD hold G / 8 consecutive units, a GM x GN patch whose
     // activation panels that L2 serves GN times and whose weight panels GM times.
-    const int G = gridDim.x;
-    const TileSchedule sch = tile_schedule(ntiles, N, kblk, G, partials != nullptr);
+    const TileSchedule sch = tile_schedule<Units>(ntiles, N, kblk, G, partials != nullptr);
     const int pb = (G % 8 == 0) ? static_cast<int>(blockIdx.x & 7) * (G >> 3) + static_cast<int>(blockIdx.x >> 3)
                                 : static_cast<int>(blockIdx.x);
     const int nleft = sch.R * sch.split;                // parts of the left-over units
@@ -181,7 +194,7 @@ __global__ __launch_bounds__(512) void ffn_tile_kernel(const uint16_t* __restric
             // operand rows are row-major (the caller's x or x_perm) or k-step-major (h, gathered x)
             arow[i] = act_kmajor ? act + h_index(row, w.kb0 * 32 + g * 8, kblk)
                                  : act + static_cast<size_t>(row) * K + static_cast<size_t>(w.kb0) * 32 + g * 8;
-            const int nb = min(w.nt * 16 + 2 * wave + i, nblk - 1);
+            const int nb = min(w.nt * (kTN / 16) + 2 * wave + i, nblk - 1);
             brow[i] = wpk + ((static_cast<size_t>(w.tl.expert) * nblk + nb) * kblk + w.kb0) * 512 + lane * 8;
         }
     };
@@ -199,7 +212,7 @@ __global__ __launch_bounds__(512) void ffn_tile_kernel(const uint16_t* __restric
             if (sidx < w.nk) stage_in((slot + sidx) % kStages);
     };
 
-    const int wave_w = kOperandBytes + (wn * 4 * 64 + lane) * 16, wave_x = (wm * 8 * 64 + lane) * 16;
+    const int wave_w = kOperandBytes + (wn * 4 * 64 + lane) * 16, wave_x = (wm * RF * 64 + lane) * 16;
     Unit cur = unit_at(0);
     if (cur.valid) start_unit(cur);
     for (int it = 0; cur.valid; ++it) {
@@ -213,11 +226,11 @@ __global__ __launch_bounds__(512) void ffn_tile_kernel(const uint16_t* __restric
         // there, when the unit is known by then, needs no row lookups (a vector load here would make the
         // compiler wait for every copy in flight) and both units are at least as long as the ring is deep.
         const bool ahead = next_known && nxt.valid && rowmap == nullptr && nk >= kAhead && nxt.nk >= kAhead;
-        f32x4 acc[4][8];
+        f32x4 acc[4][RF];
 #pragma unroll
         for (int nf = 0; nf < 4; ++nf)
 #pragma unroll
-            for (int tf = 0; tf < 8; ++tf) acc[nf][tf] = f32x4{0.f, 0.f, 0.f, 0.f};
+            for (int tf = 0; tf < RF; ++tf) acc[nf][tf] = f32x4{0.f, 0.f, 0.f, 0.f};
         StageFrags fr;
         // One stage of 32 k, software-pipelined across stages so that the MFMA pipe never waits for LDS.
         // The iteration for stage j starts by making sure that stage j + 1 has landed for every wavefront
@@ -250,31 +263,45 @@ __global__ __launch_bounds__(512) void ffn_tile_kernel(const uint16_t* __restric
             // the four copies of stage j + kAhead are issued between the first MFMAs, whose execution
             // covers the scalar and address arithmetic of the copies
             const bool refill = (more && (STEADY || j + kAhead < nk)) || (!STEADY && ahead && j + kAhead >= nk);
+            // Fine units: both row pairs of stage j are in registers, and the second group of MFMAs covers the reads of
+            // stage j + 1 into the other buffers.
+            const bf16x8 (&x0)[2] = fr.x[FINE ? 2 * C : 0];
 #pragma unroll
             for (int nf = 0; nf < 4; ++nf) {
                 __builtin_amdgcn_sched_barrier(0);
-                acc[nf][0] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fr.w[C][nf], fr.x[0][0], acc[nf][0], 0, 0, 0);
-                acc[nf][1] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fr.w[C][nf], fr.x[0][1], acc[nf][1], 0, 0, 0);
+                acc[nf][0] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fr.w[C][nf], x0[0], acc[nf][0], 0, 0, 0);
+                acc[nf][1] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fr.w[C][nf], x0[1], acc[nf][1], 0, 0, 0);
                 __builtin_amdgcn_sched_barrier(0);
                 if (refill) copy_piece(slot_free, nf);
             }
             __builtin_amdgcn_sched_barrier(0);
-            lds_read_x(fr.x[3], st_cur + wave_x, 3);
-            if (more) {
-                lds_read_w(fr.w[C ^ 1], st_nxt + wave_w);
-                lds_read_x(fr.x[0], st_nxt + wave_x, 0);
+            if constexpr (FINE) {
+                if (more) {
+                    lds_read_w(fr.w[C ^ 1], st_nxt + wave_w);
+                    lds_read_x(fr.x[2 * (C ^ 1)], st_nxt + wave_x, 0);
+                    lds_read_x(fr.x[2 * (C ^ 1) + 1], st_nxt + wave_x, 1);
+                }
+                __builtin_amdgcn_sched_barrier(0);
+                mfma_pair<1>(fr.w[C], fr.x[2 * C + 1], acc);
+                __builtin_amdgcn_sched_barrier(0);
+            } else {
+                lds_read_x(fr.x[3], st_cur + wave_x, 3);
+                if (more) {
+                    lds_read_w(fr.w[C ^ 1], st_nxt + wave_w);
+                    lds_read_x(fr.x[0], st_nxt + wave_x, 0);
+                }
+                __builtin_amdgcn_sched_barrier(0);
+                mfma_pair<1>(fr.w[C], fr.x[1], acc);
+                __builtin_amdgcn_sched_barrier(0);
+                if (more) lds_read_x(fr.x[1], st_nxt + wave_x, 1);
+                __builtin_amdgcn_sched_barrier(0);
+                mfma_pair<2>(fr.w[C], fr.x[2], acc);
+                __builtin_amdgcn_sched_barrier(0);
+                if (more) lds_read_x(fr.x[2], st_nxt + wave_x, 2);
+                __builtin_amdgcn_sched_barrier(0);
+                mfma_pair<3>(fr.w[C], fr.x[3], acc);
+                __builtin_amdgcn_sched_barrier(0);
             }
-            __builtin_amdgcn_sched_barrier(0);
-            mfma_pair<1>(fr.w[C], fr.x[1], acc);
-            __builtin_amdgcn_sched_barrier(0);
-            if (more) lds_read_x(fr.x[1], st_nxt + wave_x, 1);
-            __builtin_amdgcn_sched_barrier(0);
-            mfma_pair<2>(fr.w[C], fr.x[2], acc);
-            __builtin_amdgcn_sched_barrier(0);
-            if (more) lds_read_x(fr.x[2], st_nxt + wave_x, 2);
-            __builtin_amdgcn_sched_barrier(0);
-            mfma_pair<3>(fr.w[C], fr.x[3], acc);
-            __builtin_amdgcn_sched_barrier(0);
             slot = slot_next;
         };
 
@@ -286,7 +313,7 @@ __global__ __launch_bounds__(512) void ffn_tile_kernel(const uint16_t* __restric
         lds_read_w(fr.w[0], smem + slot * kStageBytes + wave_w);
         lds_read_x(fr.x[0], smem + slot * kStageBytes + wave_x, 0);
         lds_read_x(fr.x[1], smem + slot * kStageBytes + wave_x, 1);
-        lds_read_x(fr.x[2], smem + slot * kStageBytes + wave_x, 2);
+        if constexpr (!FINE) lds_read_x(fr.x[2], smem + slot * kStageBytes + wave_x, 2);
         int j = 0;
         for (; j + 1 + kAhead < nk; j += 2) {
             iterate(std::integral_constant<int, 0>{}, std::true_type{}, j);
@@ -309,21 +336,22 @@ __global__ __launch_bounds__(512) void ffn_tile_kernel(const uint16_t* __restric
             // part of a unit: the partial tile goes to the workspace; the next kernel adds the parts up
             float* mine = partials + (static_cast<size_t>(cur.u - sch.rounds * G) * cur.nparts + cur.part) * (kTM * kTN);
 #pragma unroll
-            for (int tf = 0; tf < 8; ++tf)
+            for (int tf = 0; tf < RF; ++tf)
 #pragma unroll
                 for (int nf = 0; nf < 4; ++nf)
-                    *reinterpret_cast<f32x4*>(mine + (wm * 128 + tf * 16 + r) * kTN + (wn * 4 + nf) * 16 + g * 4) =
+                    *reinterpret_cast<f32x4*>(mine + (wm * (kTM / 2) + tf * 16 + r) * kTN + (wn * 4 + nf) * 16 + g * 4) =
                         acc[nf][tf];
         } else {
             const float* be = bias ? bias + static_cast<size_t>(cur.tl.expert) * N : nullptr;
 #pragma unroll
-            for (int tf = 0; tf < 8; ++tf) {
-                const int lr = wm * 128 + tf * 16 + r;
+            for (int tf = 0; tf < RF; ++tf) {
+                if (wm * (kTM / 2) + tf * 16 >= cur.tl.rows) break;     // wave-uniform: no row from here on
+                const int lr = wm * (kTM / 2) + tf * 16 + r;
                 const bool ok = lr < cur.tl.rows;
                 if constexpr (FIRST != 0) {
 #pragma unroll
                     for (int m = 0; m < 2; ++m) {
-                        const int nb = cur.nt * 16 + wn * 4 + 2 * m;   // N / 16 is even: a pair exists as a whole
+                        const int nb = cur.nt * (kTN / 16) + wn * 4 + 2 * m;   // N / 16 is even: a pair exists as a whole
                         if (nb >= nblk) continue;                       // wave-uniform
                         store_h_pair<FIRST, false>(outp, cur.tl.row0 + lr, ok, nb * 16, N, be, acc[2 * m][tf],
                                                    acc[2 * m + 1][tf]);
@@ -338,14 +366,14 @@ __global__ __launch_bounds__(512) void ffn_tile_kernel(const uint16_t* __restric
                     if (fold.out != nullptr) {                          // block-uniform
 #pragma unroll
                         for (int m = 0; m < 2; ++m) {
-                            const int nb = cur.nt * 16 + wn * 4 + 2 * m;
+                            const int nb = cur.nt * (kTN / 16) + wn * 4 + 2 * m;
                             if (nb >= nblk) continue;                   // wave-uniform
                             store_folded_pair(fold.out, ftok, fw, ok, nb * 16, N, be, acc[2 * m][tf], acc[2 * m + 1][tf]);
                         }
                     } else {
 #pragma unroll
                         for (int nf = 0; nf < 4; ++nf) {
-                            const int nb = cur.nt * 16 + wn * 4 + nf;
+                            const int nb = cur.nt * (kTN / 16) + wn * 4 + nf;
                             if (ok && nb < nblk)
                                 store_out<0>(outp, cur.tl.row0 + lr, nb * 16 + g * 4, N, be, acc[nf][tf]);
                         }
@@ -357,47 +385,62 @@ __global__ __launch_bounds__(512) void ffn_tile_kernel(const uint16_t* __restric
     }
 }
 
-template <int FIRST>
+template <int FIRST, typename Units>
 static hipError_t launch_tile(const uint16_t* act, const int32_t* rowmap, const uint16_t* wpk, void* outp,
-                              const Tile* tiles, const int32_t* ntiles, int32_t* part_counter, float* partials, int N,
-                              int K, bool act_kmajor, const float* bias, const FoldOut& fold, hipStream_t st) {
-    auto kern = ffn_tile_kernel<FIRST>;
-    constexpr int lds = kStages * kStageBytes;  // 128 KiB: above the default per-block limit (raised by configure_tile_kernels)
-    // Always the whole chip, one block per CU (the LDS ring allows no more): how many units there are is
+                              const TileLists& lists, int N, int K, bool act_kmajor, const float* bias, const FoldOut& fold,
+                              hipStream_t st) {
+    auto kern = ffn_tile_kernel<FIRST, Units>;
+    constexpr int lds = kStages * 2 * Units::kRows * kTK * 2;   // 128 KiB or 64 KiB (limit raised by configure_tile_kernels)
+    // Always the whole chip, as many blocks per CU as the LDS rings allow: how many units there are is
     // only known on the device, and few units are cut along K over blocks that would otherwise idle.
-    const int grid = tile_product_grid();
-    hipLaunchKernelGGL(kern, dim3(static_cast<unsigned>(grid)), dim3(512), lds, st, act, rowmap, wpk, outp, tiles,
-                       ntiles, part_counter, partials, N, K, act_kmajor ? 1 : 0, bias, fold);
+    const int grid = device_cu_count() * Units::kPerCu;
+    hipLaunchKernelGGL(kern, dim3(static_cast<unsigned>(grid)), dim3(Units::kWaves * 64), lds, st, act, rowmap, wpk, outp,
+                       Units::kPerCu == 1 ? lists.big_tiles : lists.half_tiles, lists.ntiles,
+                       lists.ntiles + kSplitCounter + (FIRST != 0 ? 0 : 1), lists.partials, N, K, act_kmajor ? 1 : 0, bias, fold);
     return hipGetLastError();
+}
+
+template <int FIRST>
+static hipError_t launch_tiles(const uint16_t* act, const int32_t* rowmap, const uint16_t* wpk, void* outp,
+                               const TileLists& lists, long A, int N, int K, bool act_kmajor, const float* bias,
+                               const FoldOut& fold, hipStream_t st) {
+    // An expert of m >= kBigMinRows rows has at most m / 128 big tiles, so A / 128 of them are the most there can be
+    // (smaller experts join only when there are at least a round's).
+    if (!tiled_product_is_fine(A / kBigMinRows, N, device_cu_count())) {
+        const hipError_t e = launch_tile<FIRST, BigUnits>(act, rowmap, wpk, outp, lists, N, K, act_kmajor, bias, fold, st);
+        if (e != hipSuccess) return e;
+    }
+    return launch_tile<FIRST, FineUnits>(act, rowmap, wpk, outp, lists, N, K, act_kmajor, bias, fold, st);
 }
 
 int tile_product_grid() { return device_cu_count(); }
 
-template <int FIRST>
+template <int FIRST, typename Units>
 static hipError_t configure_tile() {
-    return hipFuncSetAttribute(reinterpret_cast<const void*>(ffn_tile_kernel<FIRST>),
-                               hipFuncAttributeMaxDynamicSharedMemorySize, kStages * kStageBytes);
+    return hipFuncSetAttribute(reinterpret_cast<const void*>(ffn_tile_kernel<FIRST, Units>),
+                               hipFuncAttributeMaxDynamicSharedMemorySize, kStages * 2 * Units::kRows * kTK * 2);
+}
+
+template <typename Units>
+static hipError_t configure_tiles() {
+    hipError_t e;
+    if ((e = configure_tile<0, Units>()) != hipSuccess) return e;
+    if ((e = configure_tile<kFirstRelu, Units>()) != hipSuccess) return e;
+    return configure_tile<kFirstGelu, Units>();
 }
 
 hipError_t configure_tile_kernels(int) {
-    hipError_t e;
-    if ((e = configure_tile<0>()) != hipSuccess) return e;
-    if ((e = configure_tile<kFirstRelu>()) != hipSuccess) return e;
-    return configure_tile<kFirstGelu>();
+    const hipError_t e = configure_tiles<BigUnits>();
+    return e != hipSuccess ? e : configure_tiles<FineUnits>();
 }
 
 hipError_t launch_tile_product(bool first, const uint16_t* act, const int32_t* rowmap, const uint16_t* wpk,
-                               void* outp, const Tile* tiles, const int32_t* ntiles, int32_t* part_counter,
-                               float* partials, int N, int K, bool act_kmajor, int activation,
+                               void* outp, const TileLists& lists, long A, int N, int K, bool act_kmajor, int activation,
                                const float* bias, const FoldOut& fold, hipStream_t st) {
-    if (!first)
-        return launch_tile<0>(act, rowmap, wpk, outp, tiles, ntiles, part_counter, partials, N, K,
-                              act_kmajor, bias, fold, st);
+    if (!first) return launch_tiles<0>(act, rowmap, wpk, outp, lists, A, N, K, act_kmajor, bias, fold, st);
     if (activation == MOE_ACT_GELU)
-        return launch_tile<kFirstGelu>(act, rowmap, wpk, outp, tiles, ntiles, part_counter, partials, N, K,
-                                       act_kmajor, bias, fold, st);
-    return launch_tile<kFirstRelu>(act, rowmap, wpk, outp, tiles, ntiles, part_counter, partials, N, K,
-                                   act_kmajor, bias, fold, st);
+        return launch_tiles<kFirstGelu>(act, rowmap, wpk, outp, lists, A, N, K, act_kmajor, bias, fold, st);
+    return launch_tiles<kFirstRelu>(act, rowmap, wpk, outp, lists, A, N, K, act_kmajor, bias, fold, st);
 }
 
 }  // namespace moe

@@ -351,7 +351,7 @@ __device__ __forceinline__ void scan_finalize_body(int32_t* __restrict__ chunk_h
                                                    const uint8_t* __restrict__ mask_in, const TileLists lists,
                                                    const int want_tiles, const PlaceArgs place) {
     __shared__ int32_t cnt[MOE_MAX_E];
-    __shared__ int32_t scan[MOE_MAX_E];
+    __shared__ int32_t scan[48];
     __shared__ int32_t place_next[16][kScanPlaceMaxE];   // per wavefront: next free slot of every expert
     __shared__ int32_t group_total[1024];                // phase 1: [group][expert] sums over a group's chunks
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
@@ -410,13 +410,6 @@ __device__ __forceinline__ void scan_finalize_body(int32_t* __restrict__ chunk_h
     __syncthreads();
     const int e = threadIdx.x;
     const int mine = (e < E) ? cnt[e] : 0;
-    const int incl = block_scan_1024(mine, scan);
-    const int row0 = incl - mine;
-    if (e < E) {
-        if (counts) counts[e] = mine;
-        if (offsets) offsets[e] = row0;
-    }
-    if (e == E - 1 && offsets) offsets[E] = incl;
     bool on = e < E;
     if (H >= 0 && e < E) {
         int rank = 0;
@@ -426,7 +419,16 @@ __device__ __forceinline__ void scan_finalize_body(int32_t* __restrict__ chunk_h
     } else if (mask_in != nullptr && e < E) {
         on = mask_in[e] != 0;
     }
-    if (want_tiles) emit_tiles(e, row0, on ? mine : 0, lists, scan);     // uniform: a kernel argument
+    const int v[2] = {mine, on ? big_tiles_at_min(mine, lists) : 0};
+    int incl[2], total[2];
+    block_scan_1024(v, incl, total, scan);
+    const int row0 = incl[0] - mine;
+    if (e < E) {
+        if (counts) counts[e] = mine;
+        if (offsets) offsets[e] = row0;
+    }
+    if (e == 0 && offsets) offsets[E] = total[0];
+    if (want_tiles) emit_tiles(e, row0, on ? mine : 0, total[1], lists, scan);     // uniform: a kernel argument
     if (place.idx == nullptr) return;                                    // uniform
     // Small layers: this block also places the assignments (the last step of the counting sort), wavefront
     // w taking chunks w, w + 16, ...: one launch less on a path that is a chain of short kernels.  The slot
@@ -785,7 +787,7 @@ bool scan_can_place(const moe_shape& s) {
 hipError_t launch_scan_finalize(int32_t* chunk_hist, int nchunks, int E, int32_t* counts, int32_t* offsets, int H,
                                 uint8_t* hot_mask, const uint8_t* mask_in, const TileLists* lists,
                                 const PlaceArgs* place, hipStream_t st) {
-    const TileLists none{nullptr, nullptr, nullptr, nullptr, 16, 0};
+    const TileLists none{nullptr, nullptr, nullptr, nullptr, nullptr, 16, 0, 0};
     const PlaceArgs no_place{nullptr, nullptr, nullptr, nullptr, 0, 1, 1};
     hipLaunchKernelGGL(scan_finalize_kernel, dim3(1), dim3(1024), 0, st, chunk_hist, nchunks, E, counts, offsets, H,
                        hot_mask, mask_in, lists ? *lists : none, lists ? 1 : 0, place ? *place : no_place);
@@ -810,7 +812,7 @@ hipError_t launch_route_finalize(const moe_shape& s, const void* x, const void* 
             if (err != hipSuccess) return err;
             // at most kTopkFinalizeLdsMax: the limit configure_route_kernels has raised this kernel to
             const size_t lds = static_cast<size_t>(64) * (s.E + 1) * 4 + static_cast<size_t>(4) * s.E * 4;
-            const TileLists none{nullptr, nullptr, nullptr, nullptr, 16, 0};
+            const TileLists none{nullptr, nullptr, nullptr, nullptr, nullptr, 16, 0, 0};
             const PlaceArgs no_place{nullptr, nullptr, nullptr, nullptr, 0, 1, 1};
             hipLaunchKernelGGL(route_topk_finalize_kernel, dim3(1), dim3(1024), lds, st, gate_part_ws, bias, idx, gate,
                                margin, hist_ws, s.T, s.E, s.k, s.renormalize, Tpad, counts, offsets, H, hot_mask, mask_in,

@@ -12,12 +12,32 @@
 
 namespace moe {
 
-constexpr int kTileCols = 256;      // columns per unit (rows: kBigTileRows)
 constexpr int kMaxSplit = 8;        // parts per left-over unit, at most ...
 #ifndef MOE_MIN_SPLIT_STEPS
 #define MOE_MIN_SPLIT_STEPS 32
 #endif
-constexpr int kMinSplitSteps = MOE_MIN_SPLIT_STEPS;  // ... and 32-k steps per part, at least
+#ifndef MOE_MIN_SPLIT_STEPS_FINE
+#define MOE_MIN_SPLIT_STEPS_FINE 16
+#endif
+
+// The two shapes of a unit: rows x columns of its output, wavefronts and blocks per CU of the kernel that runs it, and
+// the fewest 32-k steps of a part.
+struct BigUnits {
+    static constexpr int kRows = kBigTileRows, kCols = 256, kWaves = 8, kPerCu = 1, kMinSplitSteps = MOE_MIN_SPLIT_STEPS;
+};
+struct FineUnits {
+    static constexpr int kRows = kHalfTileRows, kCols = 128, kWaves = 4, kPerCu = 2, kMinSplitSteps = MOE_MIN_SPLIT_STEPS_FINE;
+};
+
+// Which of them a product runs in: big units from 5/8 of a round of them on.  (96 units: fine 30.6 us, big 39.7 us;
+// 256 units of 32 steps: 35 us as big units, 55 us as fine ones.  Between them both take about as long where four fine
+// units per big one need a second round of blocks, from 128 big units on.)
+#ifndef MOE_FINE_BELOW_PCT
+#define MOE_FINE_BELOW_PCT 62
+#endif
+inline __host__ __device__ bool tiled_product_is_fine(long big_tiles, int N, int cus) {
+    return big_tiles * ((N + BigUnits::kCols - 1) / BigUnits::kCols) * 100 < static_cast<long>(cus) * MOE_FINE_BELOW_PCT;
+}
 
 struct TileSchedule {
     int ntiles, ntn;    // row tiles, column tiles
@@ -27,16 +47,18 @@ struct TileSchedule {
 };
 
 #ifdef __HIPCC__
+template <typename Units>
 __device__ __forceinline__ TileSchedule tile_schedule(int ntiles, int N, int kblk, int G, bool have_partials) {
     TileSchedule s;
     s.ntiles = ntiles;
-    s.ntn = (N + kTileCols - 1) / kTileCols;
+    s.ntn = (N + Units::kCols - 1) / Units::kCols;
     const int U = ntiles * s.ntn;
     s.rounds = U / G;
     s.R = U - s.rounds * G;
     s.split = 1;
     if (s.R > 0 && have_partials) {
-        const int by_blocks = G / s.R, by_steps = kblk / kMinSplitSteps, by_slots = kSplitSlots / s.R;
+        constexpr int slots = kSplitSlots * (kBigTileRows * 256 / (Units::kRows * Units::kCols));
+        const int by_blocks = G / s.R, by_steps = kblk / Units::kMinSplitSteps, by_slots = slots / s.R;
         s.split = min(min(by_blocks, kMaxSplit), min(by_steps, by_slots));
         if (s.split < 2) s.split = 1;
     }
@@ -221,54 +243,72 @@ __device__ __forceinline__ void store_folded_block32(uint16_t* out, int t, float
 // its row tile, for a folded output the row's token and gate weight -- is looked up once per wavefront, and the
 // 4 x split loads of partial sums go out together (one row at a time, with a lookup per element, the pass was a
 // chain of dependent trips to memory: 35 of the 50 us of the kernel that did it on the Switch-large preset).
-template <int FIRST, bool FOLD>
+template <typename Units, int FIRST, bool FOLD>
 __device__ __forceinline__ void finish_split_units(const Tile* __restrict__ big_tiles, int ntiles_big,
                                                    const float* __restrict__ partials, void* __restrict__ outp,
                                                    int N, int kblk, int G,
                                                    const float* __restrict__ bias, const FoldOut fold, int block,
                                                    int nblocks) {
     if (ntiles_big <= 0 || partials == nullptr) return;
-    const TileSchedule s = tile_schedule(ntiles_big, N, kblk, G, true);
+    const TileSchedule s = tile_schedule<Units>(ntiles_big, N, kblk, G, true);
     if (s.split < 2) return;
-    constexpr int kRowsAtOnce = 4;
-    constexpr int kGroups = kBigTileRows / kRowsAtOnce;         // row groups per unit
-    constexpr size_t kTileFloats = static_cast<size_t>(kBigTileRows) * kTileCols;
-    const int lane = threadIdx.x & 63;
+    constexpr int kLoads = 4;                                    // 16-byte loads per lane and part
+    constexpr int kRowLanes = Units::kCols / 4;                  // lanes of a row: 64 (big units) or 32
+    constexpr int kRowsPerLoad = kWave / kRowLanes;
+    constexpr int kGroups = Units::kRows / (kLoads * kRowsPerLoad);     // row groups per unit
+    constexpr size_t kTileFloats = static_cast<size_t>(Units::kRows) * Units::kCols;
+    const int lane = (threadIdx.x & 63) % kRowLanes, sub = (threadIdx.x & 63) / kRowLanes;
     const int waves_per_block = blockDim.x >> 6;
     const int first = __builtin_amdgcn_readfirstlane(block * waves_per_block + static_cast<int>(threadIdx.x >> 6));
     const int nwaves = nblocks * waves_per_block;
     const int total = s.R * kGroups;
     for (int i = first; i < total; i += nwaves) {              // wave-uniform
-        const int ru = i / kGroups, lr0 = (i % kGroups) * kRowsAtOnce;
+        const int ru = i / kGroups, lr0 = (i % kGroups) * (kLoads * kRowsPerLoad) + sub;
         int mt, nt;
         unit_of(s, s.rounds * G + ru, mt, nt);
         const Tile tl = big_tiles[mt];
-        if (lr0 >= tl.rows) continue;
-        const int c = nt * kTileCols + lane * 4;
-        const float* base = partials + static_cast<size_t>(ru) * s.split * kTileFloats + static_cast<size_t>(lr0) * kTileCols + lane * 4;
-        f32x4 sum[kRowsAtOnce];
-        int tok[kRowsAtOnce];
+        if (lr0 - sub >= tl.rows) continue;
+        const int c = nt * Units::kCols + lane * 4;
+        const float* base = partials + static_cast<size_t>(ru) * s.split * kTileFloats + static_cast<size_t>(lr0) * Units::kCols + lane * 4;
+        f32x4 sum[kLoads];
+        int tok[kLoads];
 #pragma unroll
-        for (int q = 0; q < kRowsAtOnce; ++q) {
-            sum[q] = *reinterpret_cast<const f32x4*>(base + q * kTileCols);
-            tok[q] = (FOLD && lr0 + q < tl.rows) ? fold.tokmap[tl.row0 + lr0 + q] : 0;
+        for (int q = 0; q < kLoads; ++q) {
+            const int lr = lr0 + q * kRowsPerLoad;
+            sum[q] = *reinterpret_cast<const f32x4*>(base + q * kRowsPerLoad * Units::kCols);
+            tok[q] = (FOLD && lr < tl.rows) ? fold.tokmap[tl.row0 + lr] : 0;
         }
         for (int p = 1; p < s.split; ++p) {                    // in part order, whichever block computed the parts
 #pragma unroll
-            for (int q = 0; q < kRowsAtOnce; ++q)
-                sum[q] += *reinterpret_cast<const f32x4*>(base + static_cast<size_t>(p) * kTileFloats + q * kTileCols);
+            for (int q = 0; q < kLoads; ++q)
+                sum[q] += *reinterpret_cast<const f32x4*>(base + static_cast<size_t>(p) * kTileFloats + q * kRowsPerLoad * Units::kCols);
         }
         const float* be = bias ? bias + static_cast<size_t>(tl.expert) * N : nullptr;
 #pragma unroll
-        for (int q = 0; q < kRowsAtOnce; ++q) {
-            if (lr0 + q >= tl.rows || c >= N) continue;
+        for (int q = 0; q < kLoads; ++q) {
+            const int lr = lr0 + q * kRowsPerLoad;
+            if (lr >= tl.rows || c >= N) continue;
             if constexpr (FOLD) {
                 store_folded(fold.out, tok[q], fold.gate[tok[q]], c, N, be, sum[q]);
             } else {
-                store_out<FIRST>(outp, tl.row0 + lr0 + q, c, N, be, sum[q]);
+                store_out<FIRST>(outp, tl.row0 + lr, c, N, be, sum[q]);
             }
         }
     }
+}
+
+// after a tiled product: whichever units it ran in
+template <int FIRST, bool FOLD>
+__device__ __forceinline__ void finish_tiled_product(const Tile* __restrict__ big_tiles, const Tile* __restrict__ half_tiles,
+                                                     const int32_t* __restrict__ ntiles, const float* __restrict__ partials,
+                                                     void* __restrict__ outp, int N, int kblk, int cus,
+                                                     const float* __restrict__ bias, const FoldOut& fold, int block, int nblocks) {
+    if (tiled_product_is_fine(ntiles[1], N, cus))
+        finish_split_units<FineUnits, FIRST, FOLD>(half_tiles, ntiles[kHalfCount], partials, outp, N, kblk, cus * FineUnits::kPerCu,
+                                                   bias, fold, block, nblocks);
+    else
+        finish_split_units<BigUnits, FIRST, FOLD>(big_tiles, ntiles[1], partials, outp, N, kblk, cus * BigUnits::kPerCu, bias,
+                                                  fold, block, nblocks);
 }
 #endif
 

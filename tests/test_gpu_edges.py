@@ -90,3 +90,13 @@ def test_f32_route(gpu_lib, T, d, E):
     assert np.array_equal(idx.cpu().numpy()[ok], r["idx"][ok])
     assert np.allclose(w.cpu().numpy()[ok], r["g"][ok], rtol=2e-4)
     assert np.array_equal(counts.cpu().numpy(), np.bincount(idx.cpu().numpy().ravel(), minlength=E))
+
+
+# tiled kernels: experts around their 128- and 256-row tiles, columns that are no multiple of a tile's, contractions of one
+# step, of fewer steps than the LDS ring holds, and long enough to be cut; the last shape has few large units in one product
+# and many in the other.  Bar: y against the oracle that rounds the hidden activation once, as the kernels do; what is left
+# is fp32 sums (2^-24 * sqrt(K) of the terms) and a rare hidden value at a rounding boundary (2^-8 of one of f terms).
+@pytest.mark.parametrize("d,f", [(32, 96), (96, 160), (160, 1056), (64, 5120)])
+def test_tiled_ffn_row_tiles(gpu_lib, d, f):
+    say(f"[case] tiled ffn d={d} f={f}")
+    check(*ffn_rows(gpu_lib, [128, 129, 64, 255, 0, 257, 300, 1], d, f, "bf16", "gelu", biases=True), 4e-3)
