@@ -328,8 +328,8 @@ moe_status moe_layer_forward_biased(const moe_shape* shape, const void* x, const
     const bool derive = (mask == nullptr && H >= 0);
     const uint8_t* used = mask ? mask : (derive ? own_mask : nullptr);
 
-    // route -> chunk histograms; one block turns them into counts, offsets, slot bases, the hot mask and the
-    // tile list; the chunks place their assignments; the first product gathers token rows through tokmap.
+    // route -> chunk histograms; these become counts, offsets, the hot mask and the tile lists, and every chunk places
+    // its assignments; the first product gathers token rows through tokmap.
     int32_t* hist = at<int32_t>(ws, L.hist);
     int32_t* tokmap = at<int32_t>(ws, L.tokmap);
     const TileLists lists = ffn_tile_lists(*shape, at<Tile>(ws, L.tiles), at<Tile>(ws, L.tiles_big),
@@ -337,22 +337,16 @@ moe_status moe_layer_forward_biased(const moe_shape* shape, const void* x, const
                                            at<float>(ws, L.partials));
     hipError_t e;
     const int tok = route_chunk_tokens(*shape);
-    // few assignments: the finalize block also places them (one launch less)
-    const bool fused_place = shape->T > 0 && scan_can_place(*shape);
     const PlaceArgs place{idx, perm, inv, tokmap, shape->T * shape->k, shape->k, tok * shape->k};
     e = launch_route_finalize(*shape, x, w_gate, gate_bias, idx, gate, nullptr, hist, at<float>(ws, L.gate_part), cnt,
                               offsets, derive ? H : -1, derive ? own_mask : nullptr, mask, &lists,
-                              fused_place ? &place : nullptr, hs);
+                              shape->T > 0 ? &place : nullptr, hs);
     if (e != hipSuccess) return MOE_ERR_HIP;
     if (hot_mask_out != nullptr) {
         e = launch_mask_out(used, hot_mask_out, shape->E, hs);
         if (e != hipSuccess) return MOE_ERR_HIP;
     }
     if (shape->T == 0) return MOE_OK;
-    if (!fused_place) {
-        e = launch_place(*shape, idx, offsets, hist, perm, inv, tokmap, tok * shape->k, hs);
-        if (e != hipSuccess) return MOE_ERR_HIP;
-    }
     // One expert per token and every expert running: each row of the permuted order is the whole output of
     // its token, so the second product scales it by the gate weight and writes `out` directly (Section 2.1's
     // combine step without the fp32 round trip through memory); otherwise a combine pass follows.

@@ -175,7 +175,20 @@ struct TileLists {
 // expert find each other with one ballot per bit of the expert id, take consecutive slots in lane order,
 // and the last of them advances the expert's slot.  Writes (each may be NULL) perm[pos] = a,
 // inv_perm[a] = pos, tokmap[pos] = a / k.
-__device__ __forceinline__ void place_chunk(const int32_t* __restrict__ idx, int32_t* next,
+// `first`: the chunk's first 256 experts, fetched by the caller (chunk_experts) ahead of what it does before.
+constexpr int kChunkAhead = 4;
+struct ChunkExperts { int e[kChunkAhead]; };
+__device__ __forceinline__ ChunkExperts chunk_experts(const int32_t* __restrict__ idx, int A, int chunk, int c) {
+    const int lane = threadIdx.x & 63;
+    ChunkExperts r;
+#pragma unroll
+    for (int i = 0; i < kChunkAhead; ++i) {
+        const int o = i * 64 + lane;
+        r.e[i] = (o < chunk && c * chunk + o < A) ? idx[c * chunk + o] : 0;
+    }
+    return r;
+}
+__device__ __forceinline__ void place_chunk(const int32_t* __restrict__ idx, const ChunkExperts& first, int32_t* next,
                                             int32_t* __restrict__ perm, int32_t* __restrict__ inv_perm,
                                             int32_t* __restrict__ tokmap, int A, int E, int k, int ebits, int chunk,
                                             int c) {
@@ -184,7 +197,12 @@ __device__ __forceinline__ void place_chunk(const int32_t* __restrict__ idx, int
     for (int i0 = 0; i0 < chunk; i0 += 64) {
         const int a = base + i0 + lane;
         const bool live = (i0 + lane < chunk) && a < A;
-        const int e = live ? min(max(idx[a], 0), E - 1) : 0;   // clamped: a bad index must not fault
+        int ex = 0;
+#pragma unroll
+        for (int i = 0; i < kChunkAhead; ++i)
+            if (i0 == i * 64) ex = first.e[i];
+        if (i0 >= kChunkAhead * 64 && live) ex = idx[a];
+        const int e = live ? min(max(ex, 0), E - 1) : 0;       // clamped: a bad index must not fault
         uint64_t same = __ballot(live);
         for (int b = 0; b < ebits; ++b) {
             const uint64_t has = __ballot(live && ((e >> b) & 1));
@@ -380,7 +398,7 @@ struct FoldOut {
     const float* gate;       // [T] (k = 1)
 };
 
-// what the finalize kernel needs to place the assignments itself (small layers: one launch less)
+// what placing the assignments needs (the counting sort's last step)
 struct PlaceArgs {
     const int32_t* idx;    // nullptr: do not place
     int32_t* perm;
@@ -388,17 +406,13 @@ struct PlaceArgs {
     int32_t* tokmap;
     int A, k, chunk;
 };
-bool scan_can_place(const moe_shape& s);
 hipError_t launch_route_finalize(const moe_shape& s, const void* x, const void* w_gate, const float* bias,
                                  int32_t* idx, float* gate, float* margin, int32_t* hist_ws, float* gate_part_ws,
                                  int32_t* counts, int32_t* offsets, int H, uint8_t* hot_mask, const uint8_t* mask_in,
                                  const TileLists* lists, const PlaceArgs* place, hipStream_t st);
-hipError_t launch_scan_finalize(int32_t* chunk_hist, int nchunks, int E, int32_t* counts, int32_t* offsets, int H,
-                                uint8_t* hot_mask, const uint8_t* mask_in, const TileLists* lists,
-                                const PlaceArgs* place, hipStream_t st);
+hipError_t launch_place(int32_t* chunk_hist, int nchunks, int E, const int32_t* offsets, const PlaceArgs& place,
+                        hipStream_t st);
 TileLists ffn_tile_lists(const moe_shape& s, Tile* small_ws, Tile* big_ws, Tile* half_ws, int32_t* ntiles_ws, float* partials_ws);
-hipError_t launch_place(const moe_shape& s, const int32_t* idx, const int32_t* offsets, const int32_t* chunk_base,
-                        int32_t* perm, int32_t* inv_perm, int32_t* tokmap, int chunk, hipStream_t st);
 int ffn_tile_rows(const moe_shape& s);
 int tiled_join_tiles(const moe_shape& s);
 hipError_t launch_expert_products(const moe_shape& s, const void* act, const int32_t* rowmap, bool act_kmajor,

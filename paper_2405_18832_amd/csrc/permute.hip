@@ -4,15 +4,15 @@
 // one slot and segments have no padding).
 //
 // The sort never orders anything through atomics on global memory: assignments are cut into
-// chunks of consecutive flat ids, each chunk is counted (kernel 1, or the routing kernel when
-// the whole layer runs), the per-expert counts are prefix-summed over the chunks (kernel 2),
-// and each chunk then places its assignments in flat-id order (kernel 3).  The result is the
+// chunks of consecutive flat ids, each chunk is counted (perm_hist_kernel, or the routing kernel when
+// the whole layer runs), the per-expert counts are prefix-summed over the chunks, and each chunk then
+// places its assignments in flat-id order (dispatch_kernel in route.hip).  The result is the
 // same on every run.
 #include "common.hpp"
 
 namespace moe {
 
-// kernel 1: hist[chunk][e] = number of assignments of expert e inside the chunk.
+// hist[chunk][e] = number of assignments of expert e inside the chunk.
 // One wavefront per chunk, 4 chunks per block.
 __global__ __launch_bounds__(256) void perm_hist_kernel(const int32_t* __restrict__ idx,
                                                         int32_t* __restrict__ hist, int A, int E,
@@ -34,26 +34,36 @@ __global__ __launch_bounds__(256) void perm_hist_kernel(const int32_t* __restric
         for (int e = lane; e < E; e += 64) hist[static_cast<size_t>(c) * E + e] = h[wave][e];
 }
 
-// kernel 3: place the chunk's assignments (kernel 2, the prefix sum over chunks, is
-// scan_finalize_kernel).  The wavefront walks its chunk 64 flat ids at a time; lanes that hold
-// the same expert find each other with one ballot per bit of the expert id, take consecutive
-// slots in lane order, and the last of them advances the expert's running slot.
-// Writes (each may be NULL) perm[pos] = a, inv_perm[a] = pos, tokmap[pos] = a / k.
-__global__ __launch_bounds__(256) void perm_place_kernel(const int32_t* __restrict__ idx,
-                                                         const int32_t* __restrict__ offsets,
-                                                         const int32_t* __restrict__ chunk_base,
-                                                         int32_t* __restrict__ perm,
-                                                         int32_t* __restrict__ inv_perm,
-                                                         int32_t* __restrict__ tokmap, int A, int E, int k,
-                                                         int ebits, int chunk, int nchunks) {
-    __shared__ int32_t next_all[4][MOE_MAX_E];
-    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-    const int c = blockIdx.x * 4 + wave;
-    if (c >= nchunks) return;                   // no block-wide barrier below: waves are independent
-    int32_t* next = next_all[wave];
-    for (int e = lane; e < E; e += 64) next[e] = offsets[e] + chunk_base[static_cast<size_t>(c) * E + e];
-    __builtin_amdgcn_wave_barrier();
-    place_chunk(idx, next, perm, inv_perm, tokmap, A, E, k, ebits, chunk, c);
+// Few assignments: one block counts, sums and places in one go.  Wavefront w owns chunk w; a chunk is at most
+// 64 * kChunkAhead assignments, so its experts stay in registers.  Dynamic LDS: [16][E] ints, histograms, then slots.
+constexpr int kSmallPermWaves = 16;
+constexpr int kSmallPermMax = kSmallPermWaves * 64 * kChunkAhead;
+__global__ __launch_bounds__(1024) void perm_small_kernel(const int32_t* __restrict__ offsets, int E, const PlaceArgs place) {
+    extern __shared__ int32_t hist[];
+    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, e = threadIdx.x;
+    const ChunkExperts first = chunk_experts(place.idx, place.A, place.chunk, wave);
+    int at = e < E ? offsets[e] : 0;
+    for (int i = threadIdx.x; i < kSmallPermWaves * E; i += 1024) hist[i] = 0;
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < kChunkAhead; ++i) {
+        const int o = i * 64 + lane;
+        if (o < place.chunk && wave * place.chunk + o < place.A) atomicAdd(&hist[wave * E + min(max(first.e[i], 0), E - 1)], 1);
+    }
+    __syncthreads();
+    if (e < E) {
+#pragma unroll
+        for (int w = 0; w < kSmallPermWaves; ++w) {
+            const int n = hist[w * E + e];
+            hist[w * E + e] = at;
+            at += n;
+        }
+    }
+    __syncthreads();
+    int ebits = 0;
+    while ((1 << ebits) < E) ++ebits;
+    place_chunk(place.idx, first, hist + wave * E, place.perm, place.inv_perm, place.tokmap, place.A, E, place.k, ebits,
+                place.chunk, wave);
 }
 
 // gather: x_perm[p] = x[perm[p] / k]; one wavefront per row, 16 bytes (or 4) per lane and step
@@ -106,17 +116,6 @@ hipError_t launch_gather_kmajor(const moe_shape& s, const void* x, const int32_t
     return hipGetLastError();
 }
 
-hipError_t launch_place(const moe_shape& s, const int32_t* idx, const int32_t* offsets, const int32_t* chunk_base,
-                        int32_t* perm, int32_t* inv_perm, int32_t* tokmap, int chunk, hipStream_t st) {
-    const int A = s.T * s.k, E = s.E;
-    const int nchunks = (A + chunk - 1) / chunk;
-    int ebits = 0;
-    while ((1 << ebits) < E) ++ebits;
-    hipLaunchKernelGGL(perm_place_kernel, dim3((nchunks + 3) / 4), dim3(256), 0, st, idx, offsets, chunk_base, perm,
-                       inv_perm, tokmap, A, E, s.k, ebits, chunk, nchunks);
-    return hipGetLastError();
-}
-
 hipError_t launch_gather(const moe_shape& s, const void* x, const int32_t* perm, void* x_perm, hipStream_t st) {
     const int A = s.T * s.k;
     const size_t row_bytes = static_cast<size_t>(s.d_model) * elem_size(s.dtype);
@@ -136,14 +135,21 @@ hipError_t launch_permute(const moe_shape& s, const void* x, const int32_t* idx,
                           const int32_t* offsets, int32_t* perm, int32_t* inv_perm, void* x_perm,
                           int32_t* hist_ws, hipStream_t st) {
     const int A = s.T * s.k, E = s.E;
-    const int nchunks = (A + kPermChunk - 1) / kPermChunk;
-    hipLaunchKernelGGL(perm_hist_kernel, dim3((nchunks + 3) / 4), dim3(256), 0, st, idx, hist_ws, A, E, kPermChunk,
-                       nchunks);
-    hipError_t err = hipGetLastError();
-    if (err != hipSuccess) return err;
-    err = launch_scan_finalize(hist_ws, nchunks, E, nullptr, nullptr, -1, nullptr, nullptr, nullptr, nullptr, st);
-    if (err != hipSuccess) return err;
-    err = launch_place(s, idx, offsets, hist_ws, perm, inv_perm, nullptr, kPermChunk, st);
+    hipError_t err;
+    if (A <= kSmallPermMax) {
+        const int chunk = ((A + kSmallPermWaves - 1) / kSmallPermWaves + 63) / 64 * 64;
+        const PlaceArgs place{idx, perm, inv_perm, nullptr, A, s.k, chunk};
+        hipLaunchKernelGGL(perm_small_kernel, dim3(1), dim3(1024), static_cast<size_t>(kSmallPermWaves) * E * 4, st, offsets, E,
+                           place);
+        err = hipGetLastError();
+    } else {
+        const int nchunks = (A + kPermChunk - 1) / kPermChunk;
+        hipLaunchKernelGGL(perm_hist_kernel, dim3((nchunks + 3) / 4), dim3(256), 0, st, idx, hist_ws, A, E, kPermChunk,
+                           nchunks);
+        err = hipGetLastError();
+        if (err != hipSuccess) return err;
+        err = launch_place(hist_ws, nchunks, E, offsets, PlaceArgs{idx, perm, inv_perm, nullptr, A, s.k, kPermChunk}, st);
+    }
     if (err != hipSuccess) return err;
     if (x_perm != nullptr) err = launch_gather(s, x, perm, x_perm, st);
     return err;

@@ -5,10 +5,11 @@
 //
 // Two kernels.  route_fused_kernel: one block per chunk of 16*TF tokens computes the chunk's
 // logits into LDS, picks each token's experts there and leaves the chunk's per-expert
-// histogram in the workspace.  scan_finalize_kernel: one block turns the chunk histograms
-// into counts, prefix sums (per expert over chunks, and over experts), the hot mask and the
-// expert tile list.  Nothing is ordered through atomics on global memory, so every output
+// histogram in the workspace.  dispatch_kernel: one block turns the chunk histograms
+// into counts, prefix sums, the hot mask and the expert tile lists, while the others place the
+// chunks' assignments.  Nothing is ordered through atomics on global memory, so every output
 // is the same on every run.
+#include <algorithm>
 #include <type_traits>
 
 #include "common.hpp"
@@ -42,7 +43,8 @@ __device__ __forceinline__ int row_rot(int v) {
 template <int V>
 __device__ __forceinline__ void topk_row(float* __restrict__ row, int E, int k, int renorm, int sub, bool live,
                                          int32_t* __restrict__ idx_out, float* __restrict__ w_out,
-                                         float* __restrict__ margin_out, int32_t* __restrict__ hist) {
+                                         float* __restrict__ margin_out, int32_t* __restrict__ hist,
+                                         int32_t* __restrict__ idx_lds) {
     const float NEG = -__builtin_huge_valf();
     float sel_v[kMaxRounds];
     int sel_i[kMaxRounds];
@@ -118,6 +120,7 @@ __device__ __forceinline__ void topk_row(float* __restrict__ row, int E, int k, 
         for (int j = 0; j < MOE_MAX_K; ++j)
             if (j < k) {
                 idx_out[j] = sel_i[j];
+                if (idx_lds != nullptr) idx_lds[j] = sel_i[j];
                 w_out[j] = renorm ? p[j] / psum : p[j];
                 atomicAdd(&hist[sel_i[j]], 1);      // LDS, integer: order does not matter
             }
@@ -135,11 +138,11 @@ __device__ __forceinline__ void topk_row(float* __restrict__ row, int E, int k, 
 __device__ __forceinline__ void topk_from_lds(float* __restrict__ row, int E, int k, int renorm, int sub,
                                               bool live, int32_t* __restrict__ idx_out,
                                               float* __restrict__ w_out, float* __restrict__ margin_out,
-                                              int32_t* __restrict__ hist) {
-    if (E <= 64) topk_row<4>(row, E, k, renorm, sub, live, idx_out, w_out, margin_out, hist);
-    else if (E <= 128) topk_row<8>(row, E, k, renorm, sub, live, idx_out, w_out, margin_out, hist);
-    else if (E <= 256) topk_row<16>(row, E, k, renorm, sub, live, idx_out, w_out, margin_out, hist);
-    else topk_row<0>(row, E, k, renorm, sub, live, idx_out, w_out, margin_out, hist);
+                                              int32_t* __restrict__ hist, int32_t* __restrict__ idx_lds = nullptr) {
+    if (E <= 64) topk_row<4>(row, E, k, renorm, sub, live, idx_out, w_out, margin_out, hist, idx_lds);
+    else if (E <= 128) topk_row<8>(row, E, k, renorm, sub, live, idx_out, w_out, margin_out, hist, idx_lds);
+    else if (E <= 256) topk_row<16>(row, E, k, renorm, sub, live, idx_out, w_out, margin_out, hist, idx_lds);
+    else topk_row<0>(row, E, k, renorm, sub, live, idx_out, w_out, margin_out, hist, idx_lds);
 }
 
 // Floats per token row of the logits in LDS: whole groups of 16 * NF experts (the accumulate step writes
@@ -333,89 +336,66 @@ __global__ __launch_bounds__(NW * 64) void route_fused_kernel(const ST* __restri
 }
 
 // ---------------------------------------------------------------------------
-// scan_finalize_kernel: one block of 1024 threads (16 wavefronts).
-//  phase 1: for every expert, exclusive prefix sum of its chunk histogram over the chunks, in
-//           place (the slot bases of the counting sort); the total is the expert's token count.
-//  phase 2: prefix sums over experts -> offsets; top-H hot mask (rank by count, ties by lowest
-//           index); the tile list of the expert FFN (every active, masked-in expert's segment
-//           cut into row tiles: one list for small experts, one for large ones).
-// Any output pointer may be NULL.
+// From the chunk histograms [nchunks][E] of the assignments to counts, offsets, hot mask, tile lists and places.
 // ---------------------------------------------------------------------------
-constexpr int kScanPlaceMaxE = 256;     // largest E and ...
-constexpr long kScanPlaceMaxA = 512;    // ... most assignments for which the finalize block also places
+constexpr int kMaxWaves = 16;           // wavefronts of a block of 1024 threads
 
-// the work of scan_finalize_kernel, by a block of 1024 threads
-__device__ __forceinline__ void scan_finalize_body(int32_t* __restrict__ chunk_hist, int nchunks, int E,
-                                                   int32_t* __restrict__ counts, int32_t* __restrict__ offsets,
-                                                   int H, uint8_t* __restrict__ hot_mask,
-                                                   const uint8_t* __restrict__ mask_in, const TileLists lists,
-                                                   const int want_tiles, const PlaceArgs place) {
-    __shared__ int32_t cnt[MOE_MAX_E];
-    __shared__ int32_t scan[48];
-    __shared__ int32_t place_next[16][kScanPlaceMaxE];   // per wavefront: next free slot of every expert
-    __shared__ int32_t group_total[1024];                // phase 1: [group][expert] sums over a group's chunks
-    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-    // phase 1: chunk_hist is [nchunks][E], so threads that take consecutive experts of one chunk read and
-    // write contiguously.  The block is cut into ngrp = 1024 / Ew groups of Ew threads (Ew = E rounded up to
-    // whole wavefronts); group q owns the chunks [q * seg, (q + 1) * seg), adds them up per expert 8 loads at
-    // a time, the group totals meet in LDS, and the segment is rewritten with its exclusive prefix sums (kept
-    // in registers between the two sweeps when it has at most 8 chunks, else read again from L2).  (One
-    // shuffle scan of 6 steps per 64 chunks and expert, as before, cost 5.5 us on 64 experts x 128 chunks:
-    // the shuffles are LDS round trips that wait for one another.)
-    {
-        const int Ew = min(1024, (E + 63) & ~63), ngrp = 1024 / Ew;
-        const int q = threadIdx.x / Ew, ex = threadIdx.x - q * Ew;
-        const bool have = q < ngrp && ex < E;              // threads past ngrp * Ew (none when Ew divides 1024)
-        const int seg = (nchunks + ngrp - 1) / ngrp;
-        const int c_begin = min(q * seg, nchunks), c_end = min(c_begin + seg, nchunks);
-        int32_t* col = chunk_hist + (have ? ex : 0);
-        int first[8] = {0, 0, 0, 0, 0, 0, 0, 0};
-        int total = 0;
-        for (int c0 = c_begin; c0 < c_end; c0 += 8) {
-            int v[8];
+// Per expert, the sum of its histogram over all chunks (total) and over the chunks before cfirst (before), by a block
+// of 1024 threads; thread e < E returns with expert e's.  Threads that take consecutive experts of one chunk read
+// contiguously: the block is cut into ngrp = 1024 / Ew groups of Ew threads (Ew = E rounded up to whole wavefronts),
+// group q adds up the chunks [q * seg, (q + 1) * seg) 16 loads at a time, and the group sums meet in LDS (`groups`,
+// 2048 ints).
+__device__ __forceinline__ void sum_chunks(const int32_t* __restrict__ chunk_hist, int nchunks, int E, int cfirst,
+                                           int32_t* groups, int& total, int& before) {
+    const int Ew = min(1024, (E + 63) & ~63), ngrp = 1024 / Ew;
+    const int q = threadIdx.x / Ew, ex = threadIdx.x - q * Ew;
+    const bool have = q < ngrp && ex < E;                  // threads past ngrp * Ew (none when Ew divides 1024)
+    const int seg = (nchunks + ngrp - 1) / ngrp;
+    const int c_begin = min(q * seg, nchunks), c_end = min(c_begin + seg, nchunks);
+    const int32_t* col = chunk_hist + (have ? ex : 0);
+    int sum = 0, low = 0;
+    for (int c0 = c_begin; c0 < c_end; c0 += 16) {
+        int v[16];
 #pragma unroll
-            for (int i = 0; i < 8; ++i) v[i] = (have && c0 + i < c_end) ? col[static_cast<size_t>(c0 + i) * E] : 0;
+        for (int i = 0; i < 16; ++i) v[i] = (have && c0 + i < c_end) ? col[static_cast<size_t>(c0 + i) * E] : 0;
 #pragma unroll
-            for (int i = 0; i < 8; ++i) {
-                if (c0 == c_begin) first[i] = v[i];
-                total += v[i];
-            }
-        }
-        if (have) group_total[q * Ew + ex] = total;
-        __syncthreads();
-        int carry = 0;                                     // chunks of the groups before this one
-        if (have) {
-            for (int o = 0; o < q; ++o) carry += group_total[o * Ew + ex];
-            if (q == ngrp - 1) cnt[ex] = carry + total;
-        }
-        if (seg <= 8) {                                    // block-uniform
-#pragma unroll
-            for (int i = 0; i < 8; ++i) {
-                if (have && c_begin + i < c_end) col[static_cast<size_t>(c_begin + i) * E] = carry;
-                carry += first[i];
-            }
-        } else {
-            for (int c0 = c_begin; c0 < c_end; c0 += 8) {
-                int v[8];
-#pragma unroll
-                for (int i = 0; i < 8; ++i) v[i] = (have && c0 + i < c_end) ? col[static_cast<size_t>(c0 + i) * E] : 0;
-#pragma unroll
-                for (int i = 0; i < 8; ++i) {
-                    if (have && c0 + i < c_end) col[static_cast<size_t>(c0 + i) * E] = carry;
-                    carry += v[i];
-                }
-            }
+        for (int i = 0; i < 16; ++i) {
+            sum += v[i];
+            low += c0 + i < cfirst ? v[i] : 0;
         }
     }
+    if (have) {
+        groups[q * Ew + ex] = sum;
+        groups[1024 + q * Ew + ex] = low;
+    }
     __syncthreads();
+    total = before = 0;
     const int e = threadIdx.x;
-    const int mine = (e < E) ? cnt[e] : 0;
+    if (e < E) {
+        for (int o = 0; o < ngrp; ++o) {
+            total += groups[o * Ew + e];
+            before += groups[1024 + o * Ew + e];
+        }
+    }
+}
+
+// counts, offsets, hot mask and tile lists from the token counts, by a block of 1024 threads, thread e owning expert e
+// with `mine` tokens.  `cnt` (MOE_MAX_E ints) and `scan` (48 ints) are LDS scratch.  Any output pointer may be NULL.
+// Returns the expert's first row.
+__device__ __forceinline__ int finalize_outputs(int mine, int E, int32_t* __restrict__ counts, int32_t* __restrict__ offsets,
+                                                int H, uint8_t* __restrict__ hot_mask, const uint8_t* __restrict__ mask_in,
+                                                const TileLists lists, int want_tiles, int32_t* cnt, int32_t* scan) {
+    const int e = threadIdx.x;
     bool on = e < E;
-    if (H >= 0 && e < E) {
-        int rank = 0;
-        for (int o = 0; o < E; ++o) rank += (cnt[o] > mine || (cnt[o] == mine && o < e)) ? 1 : 0;
-        on = rank < H;
-        if (hot_mask) hot_mask[e] = on ? 1 : 0;
+    if (H >= 0) {                                          // uniform: rank by count, ties by lowest index
+        if (e < E) cnt[e] = mine;
+        __syncthreads();
+        if (e < E) {
+            int rank = 0;
+            for (int o = 0; o < E; ++o) rank += (cnt[o] > mine || (cnt[o] == mine && o < e)) ? 1 : 0;
+            on = rank < H;
+            if (hot_mask) hot_mask[e] = on ? 1 : 0;
+        }
     } else if (mask_in != nullptr && e < E) {
         on = mask_in[e] != 0;
     }
@@ -429,34 +409,123 @@ __device__ __forceinline__ void scan_finalize_body(int32_t* __restrict__ chunk_h
     }
     if (e == 0 && offsets) offsets[E] = total[0];
     if (want_tiles) emit_tiles(e, row0, on ? mine : 0, total[1], lists, scan);     // uniform: a kernel argument
-    if (place.idx == nullptr) return;                                    // uniform
-    // Small layers: this block also places the assignments (the last step of the counting sort), wavefront
-    // w taking chunks w, w + 16, ...: one launch less on a path that is a chain of short kernels.  The slot
-    // bases written to chunk_hist in phase 1 are read back by the same block after a barrier.
-    __syncthreads();
-    if (e < E) cnt[e] = row0;                                            // cnt now holds the offsets
-    __threadfence_block();
-    __syncthreads();
-    int ebits = 0;
-    while ((1 << ebits) < E) ++ebits;
-    int32_t* next = place_next[wave];
-    for (int c = wave; c < nchunks; c += 16) {
-        for (int x = lane; x < E; x += 64) next[x] = cnt[x] + chunk_hist[static_cast<size_t>(c) * E + x];
-        __builtin_amdgcn_wave_barrier();
-        place_chunk(place.idx, next, place.perm, place.inv_perm, place.tokmap, place.A, E, place.k, ebits,
-                    place.chunk, c);
-        __builtin_amdgcn_wave_barrier();
+    return row0;
+}
+
+__device__ __forceinline__ int expert_bits(int E) {
+    int b = 0;
+    while ((1 << b) < E) ++b;
+    return b;
+}
+
+// One launch for the whole step: with `finalize`, block 0 writes the outputs of finalize_outputs, and every other block
+// places the assignments of PW chunks, one wavefront each (PW = 0: nothing is placed).  Every block adds the histograms
+// up by itself: at most kDispatchMaxHist ints from L2, less than a second launch and the trip of the sums through
+// memory (4096 tokens, 128 experts: finalize + place 12.4 + 4.8 us -> see launch_route_finalize).
+// `offsets_in` != NULL: the caller's offsets instead of the counts' prefix sums.
+// Dynamic LDS: PW * E ints, the next free slot of every expert per wavefront.
+template <int PW>
+__global__ __launch_bounds__(1024) void dispatch_kernel(const int32_t* __restrict__ chunk_hist, int nchunks, int E,
+                                                        const int32_t* __restrict__ offsets_in, int finalize,
+                                                        int32_t* __restrict__ counts, int32_t* __restrict__ offsets, int H,
+                                                        uint8_t* __restrict__ hot_mask, const uint8_t* __restrict__ mask_in,
+                                                        const TileLists lists, const int want_tiles, const PlaceArgs place) {
+    extern __shared__ int32_t next_all[];
+    __shared__ int32_t groups[2048];
+    __shared__ int32_t scan[48];
+    const int e = threadIdx.x;
+    int total, before;
+    if (finalize && blockIdx.x == 0) {
+        sum_chunks(chunk_hist, nchunks, E, 0, groups, total, before);
+        __syncthreads();                                   // `groups` becomes `cnt`
+        finalize_outputs(total, E, counts, offsets, H, hot_mask, mask_in, lists, want_tiles, groups, scan);
+        return;
+    }
+    if constexpr (PW > 0) {
+        const int wave = threadIdx.x >> 6;
+        const int cfirst = (static_cast<int>(blockIdx.x) - (finalize ? 1 : 0)) * PW;
+        const int c = cfirst + wave;
+        const bool mine = wave < PW && c < nchunks;        // wave-uniform
+        ChunkExperts first{};
+        if (mine) first = chunk_experts(place.idx, place.A, place.chunk, c);
+        int own[PW];                                       // the block's chunks, expert e
+#pragma unroll
+        for (int w = 0; w < PW; ++w)
+            own[w] = (e < E && cfirst + w < nchunks) ? chunk_hist[static_cast<size_t>(cfirst + w) * E + e] : 0;
+        sum_chunks(chunk_hist, nchunks, E, cfirst, groups, total, before);
+        int at = 0;
+        if (offsets_in != nullptr) {
+            if (e < E) at = offsets_in[e];
+        } else {
+            const int v[1] = {total};
+            int incl[1], all[1];
+            block_scan_1024(v, incl, all, scan);
+            at = incl[0] - total;
+        }
+        at += before;
+#pragma unroll
+        for (int w = 0; w < PW; ++w) {
+            if (e < E) next_all[w * E + e] = at;
+            at += own[w];
+        }
+        __syncthreads();
+        if (mine)
+            place_chunk(place.idx, first, next_all + wave * E, place.perm, place.inv_perm, place.tokmap, place.A, E, place.k,
+                        expert_bits(E), place.chunk, c);
     }
 }
 
-__global__ __launch_bounds__(1024) void scan_finalize_kernel(int32_t* __restrict__ chunk_hist, int nchunks,
-                                                             int E, int32_t* __restrict__ counts,
+// The same for histograms too large to be read by every block: one block writes the outputs and turns the histograms
+// into slot bases in place (per expert, exclusive prefix sums over the chunks), then perm_place_kernel places.
+__global__ __launch_bounds__(1024) void scan_finalize_kernel(int32_t* __restrict__ chunk_hist, int nchunks, int E,
+                                                             int finalize, int32_t* __restrict__ counts,
                                                              int32_t* __restrict__ offsets, int H,
-                                                             uint8_t* __restrict__ hot_mask,
-                                                             const uint8_t* __restrict__ mask_in,
-                                                             const TileLists lists, const int want_tiles,
-                                                             const PlaceArgs place) {
-    scan_finalize_body(chunk_hist, nchunks, E, counts, offsets, H, hot_mask, mask_in, lists, want_tiles, place);
+                                                             uint8_t* __restrict__ hot_mask, const uint8_t* __restrict__ mask_in,
+                                                             const TileLists lists, const int want_tiles) {
+    __shared__ int32_t groups[2048];
+    __shared__ int32_t scan[48];
+    int total, before;
+    sum_chunks(chunk_hist, nchunks, E, 0, groups, total, before);
+    __syncthreads();
+    {
+        const int Ew = min(1024, (E + 63) & ~63), ngrp = 1024 / Ew;      // the groups of sum_chunks
+        const int q = threadIdx.x / Ew, ex = threadIdx.x - q * Ew;
+        const int seg = (nchunks + ngrp - 1) / ngrp;
+        const int c_begin = min(q * seg, nchunks), c_end = min(c_begin + seg, nchunks);
+        if (q < ngrp && ex < E) {
+            int carry = 0;
+            for (int o = 0; o < q; ++o) carry += groups[o * Ew + ex];
+            int32_t* col = chunk_hist + ex;
+            for (int c0 = c_begin; c0 < c_end; c0 += 16) {
+                int v[16];
+#pragma unroll
+                for (int i = 0; i < 16; ++i) v[i] = c0 + i < c_end ? col[static_cast<size_t>(c0 + i) * E] : 0;
+#pragma unroll
+                for (int i = 0; i < 16; ++i) {
+                    if (c0 + i < c_end) col[static_cast<size_t>(c0 + i) * E] = carry;
+                    carry += v[i];
+                }
+            }
+        }
+    }
+    __syncthreads();
+    if (finalize) finalize_outputs(total, E, counts, offsets, H, hot_mask, mask_in, lists, want_tiles, groups, scan);
+}
+
+// places one chunk per wavefront from the slot bases that scan_finalize_kernel left
+__global__ __launch_bounds__(256) void perm_place_kernel(const int32_t* __restrict__ offsets,
+                                                         const int32_t* __restrict__ chunk_base, int E, int nchunks,
+                                                         const PlaceArgs place) {
+    __shared__ int32_t next_all[4][MOE_MAX_E];
+    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+    const int c = blockIdx.x * 4 + wave;
+    if (c >= nchunks) return;                   // no block-wide barrier below: waves are independent
+    int32_t* next = next_all[wave];
+    const ChunkExperts first = chunk_experts(place.idx, place.A, place.chunk, c);
+    for (int e = lane; e < E; e += 64) next[e] = offsets[e] + chunk_base[static_cast<size_t>(c) * E + e];
+    __builtin_amdgcn_wave_barrier();
+    place_chunk(place.idx, first, next, place.perm, place.inv_perm, place.tokmap, place.A, E, place.k, expert_bits(E),
+                place.chunk, c);
 }
 
 // Hot-set size from the counts (Section 3.3, Eq. 6) and the top-H mask.  One block, thread e owns
@@ -658,18 +727,18 @@ __global__ __launch_bounds__(256) void route_topk_kernel(const float* __restrict
     for (int e = threadIdx.x; e < E; e += 256) chunk_hist[static_cast<size_t>(blockIdx.x) * E + e] = hist[e];
 }
 
-// route_topk_kernel and scan_finalize_kernel in one block of 1024 threads, for layers of at most 64 tokens and
+// route_topk_kernel and dispatch_kernel in one block of 1024 threads, for layers of at most 64 tokens and
 // 256 experts (decoder steps): the 16 wavefronts take 4 tokens each, the four 16-token chunks keep their
-// histograms in LDS, and the block goes straight on to the prefix sums, tile lists and (small layers) the
-// placement.  One launch and one trip through memory less on a path that is a chain of short kernels.
-// Dynamic LDS: logits [64][E + 1] floats, then histograms [4][E] ints.
+// histograms and their experts in LDS, and the block goes straight on to the prefix sums, tile lists and the
+// placement.  One launch less on a path that is a chain of short kernels, and no trip through memory between its steps
+// (with histograms and experts read back from memory the kernel took 10.2 us at one token).
+// Dynamic LDS: logits [64][E + 1] floats, then histograms [4][E] ints, then experts [64 * k] ints.
 constexpr int kTopkFinalizeMaxE = 256;
 __global__ __launch_bounds__(1024) void route_topk_finalize_kernel(const float* __restrict__ part,
                                                                    const float* __restrict__ bias,
                                                                    int32_t* __restrict__ topk_idx,
                                                                    float* __restrict__ topk_w,
-                                                                   float* __restrict__ margin,
-                                                                   int32_t* __restrict__ chunk_hist, int T, int E, int k,
+                                                                   float* __restrict__ margin, int T, int E, int k,
                                                                    int renorm, int Tpad, int32_t* __restrict__ counts,
                                                                    int32_t* __restrict__ offsets, int H,
                                                                    uint8_t* __restrict__ hot_mask,
@@ -680,6 +749,9 @@ __global__ __launch_bounds__(1024) void route_topk_finalize_kernel(const float* 
     const int Ep = E + 1;
     float* L = lds;
     int32_t* hist = reinterpret_cast<int32_t*>(lds + 64 * Ep);
+    int32_t* experts = hist + 4 * E;
+    __shared__ int32_t cnt[MOE_MAX_E];
+    __shared__ int32_t scan[48];
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
     const int nchunks = Tpad >> 4;                         // <= 4
     for (int i = threadIdx.x; i < 4 * E; i += 1024) hist[i] = 0;
@@ -713,16 +785,29 @@ __global__ __launch_bounds__(1024) void route_topk_finalize_kernel(const float* 
         const bool live = tl < T;
         const size_t o = static_cast<size_t>(live ? tl : 0) * k;
         topk_from_lds(L + tl * Ep, E, k, renorm, sub, live, topk_idx + o, topk_w + o,
-                      margin ? margin + (live ? tl : 0) : nullptr, hist + (tl >> 4) * E);
+                      margin ? margin + (live ? tl : 0) : nullptr, hist + (tl >> 4) * E, experts + o);
     }
     __syncthreads();
-    for (int i = threadIdx.x; i < nchunks * E; i += 1024) chunk_hist[i] = hist[i];     // [chunk][E], as the other kernels
-    __threadfence_block();
+    const int e = threadIdx.x;
+    int mine = 0;
+    if (e < E)
+        for (int c = 0; c < nchunks; ++c) mine += hist[c * E + e];
+    int at = finalize_outputs(mine, E, counts, offsets, H, hot_mask, mask_in, lists, want_tiles, cnt, scan);
+    if (place.idx == nullptr) return;                      // uniform
+    if (e < E) {                                           // histograms -> the chunks' first free slots
+        for (int c = 0; c < nchunks; ++c) {
+            const int n = hist[c * E + e];
+            hist[c * E + e] = at;
+            at += n;
+        }
+    }
     __syncthreads();
-    scan_finalize_body(chunk_hist, nchunks, E, counts, offsets, H, hot_mask, mask_in, lists, want_tiles, place);
+    if (wave < nchunks)
+        place_chunk(experts, chunk_experts(experts, place.A, place.chunk, wave), hist + wave * E, place.perm, place.inv_perm,
+                    place.tokmap, place.A, E, place.k, expert_bits(E), place.chunk, wave);
 }
 
-constexpr size_t kTopkFinalizeLdsMax = static_cast<size_t>(64) * (kTopkFinalizeMaxE + 1) * 4 + 4 * kTopkFinalizeMaxE * 4;
+constexpr size_t kTopkFinalizeLdsMax = static_cast<size_t>(64) * (kTopkFinalizeMaxE + 1) * 4 + 4 * kTopkFinalizeMaxE * 4 + 64 * MOE_MAX_K * 4;
 
 template <int TF, int NW>
 static hipError_t configure_route_nf() {
@@ -778,20 +863,52 @@ hipError_t launch_route_fused(const moe_shape& s, const void* x, const void* w_g
     return launch_route_nf<1, ROUTE_MID_NW>(c.nf, s, x, w_gate, bias, idx, gate, margin, chunk_hist, st);
 }
 
-// the finalize block places the assignments itself when there are few of them and the per-wavefront slot
-// tables fit into LDS
-bool scan_can_place(const moe_shape& s) {
-    return s.E <= kScanPlaceMaxE && static_cast<long>(s.T) * s.k <= kScanPlaceMaxA;
+// Histograms of up to this many ints are added up by every block of dispatch_kernel; larger ones would cost the blocks
+// more than the second launch does.
+constexpr long kDispatchMaxHist = 64 * 1024;
+constexpr int kDispatchMaxChunks = 1024;      // few experts: a chunk's row is short, and its loads wait for one another
+
+template <int PW>
+static hipError_t launch_dispatch_pw(const int32_t* chunk_hist, int nchunks, int E, const int32_t* offsets_in, bool finalize,
+                                     int32_t* counts, int32_t* offsets, int H, uint8_t* hot_mask, const uint8_t* mask_in,
+                                     const TileLists& lists, bool want_tiles, const PlaceArgs& place, hipStream_t st) {
+    const unsigned blocks = (PW > 0 ? static_cast<unsigned>((nchunks + PW - 1) / std::max(PW, 1)) : 0u) + (finalize ? 1 : 0);
+    hipLaunchKernelGGL(dispatch_kernel<PW>, dim3(blocks), dim3(1024), static_cast<size_t>(PW) * E * 4, st, chunk_hist, nchunks,
+                       E, offsets_in, finalize ? 1 : 0, counts, offsets, H, hot_mask, mask_in, lists, want_tiles ? 1 : 0, place);
+    return hipGetLastError();
 }
 
-hipError_t launch_scan_finalize(int32_t* chunk_hist, int nchunks, int E, int32_t* counts, int32_t* offsets, int H,
-                                uint8_t* hot_mask, const uint8_t* mask_in, const TileLists* lists,
-                                const PlaceArgs* place, hipStream_t st) {
+// chunk histograms -> counts, offsets, hot mask, tile lists (`finalize`) and places (place.idx != NULL); with offsets_in
+// the places start from the caller's offsets.  Overwrites chunk_hist where it is large.
+static hipError_t launch_dispatch(int32_t* chunk_hist, int nchunks, int E, const int32_t* offsets_in, bool finalize,
+                                  int32_t* counts, int32_t* offsets, int H, uint8_t* hot_mask, const uint8_t* mask_in,
+                                  const TileLists* lists, const PlaceArgs* place, hipStream_t st) {
     const TileLists none{nullptr, nullptr, nullptr, nullptr, nullptr, 16, 0, 0};
     const PlaceArgs no_place{nullptr, nullptr, nullptr, nullptr, 0, 1, 1};
-    hipLaunchKernelGGL(scan_finalize_kernel, dim3(1), dim3(1024), 0, st, chunk_hist, nchunks, E, counts, offsets, H,
-                       hot_mask, mask_in, lists ? *lists : none, lists ? 1 : 0, place ? *place : no_place);
+    const TileLists& tl = lists ? *lists : none;
+    const bool tiles = lists != nullptr;
+    if (place == nullptr || nchunks == 0)
+        return launch_dispatch_pw<0>(chunk_hist, nchunks, E, nullptr, true, counts, offsets, H, hot_mask, mask_in, tl, tiles,
+                                     no_place, st);
+    if (static_cast<long>(nchunks) * E <= kDispatchMaxHist && nchunks <= kDispatchMaxChunks) {
+        if (E <= 256)
+            return launch_dispatch_pw<16>(chunk_hist, nchunks, E, offsets_in, finalize, counts, offsets, H, hot_mask, mask_in,
+                                          tl, tiles, *place, st);
+        return launch_dispatch_pw<4>(chunk_hist, nchunks, E, offsets_in, finalize, counts, offsets, H, hot_mask, mask_in, tl,
+                                     tiles, *place, st);
+    }
+    hipLaunchKernelGGL(scan_finalize_kernel, dim3(1), dim3(1024), 0, st, chunk_hist, nchunks, E, finalize ? 1 : 0, counts,
+                       offsets, H, hot_mask, mask_in, tl, tiles ? 1 : 0);
+    const hipError_t err = hipGetLastError();
+    if (err != hipSuccess) return err;
+    hipLaunchKernelGGL(perm_place_kernel, dim3((nchunks + 3) / 4), dim3(256), 0, st, finalize ? offsets : offsets_in, chunk_hist,
+                       E, nchunks, *place);
     return hipGetLastError();
+}
+
+hipError_t launch_place(int32_t* chunk_hist, int nchunks, int E, const int32_t* offsets, const PlaceArgs& place,
+                        hipStream_t st) {
+    return launch_dispatch(chunk_hist, nchunks, E, offsets, false, nullptr, nullptr, -1, nullptr, nullptr, nullptr, &place, st);
 }
 
 // routing followed by the finalize step; one kernel does both for decoder-sized layers
@@ -811,18 +928,18 @@ hipError_t launch_route_finalize(const moe_shape& s, const void* x, const void* 
             hipError_t err = hipGetLastError();
             if (err != hipSuccess) return err;
             // at most kTopkFinalizeLdsMax: the limit configure_route_kernels has raised this kernel to
-            const size_t lds = static_cast<size_t>(64) * (s.E + 1) * 4 + static_cast<size_t>(4) * s.E * 4;
+            const size_t lds = static_cast<size_t>(64) * (s.E + 1) * 4 + static_cast<size_t>(4) * s.E * 4 + static_cast<size_t>(64) * s.k * 4;
             const TileLists none{nullptr, nullptr, nullptr, nullptr, nullptr, 16, 0, 0};
             const PlaceArgs no_place{nullptr, nullptr, nullptr, nullptr, 0, 1, 1};
             hipLaunchKernelGGL(route_topk_finalize_kernel, dim3(1), dim3(1024), lds, st, gate_part_ws, bias, idx, gate,
-                               margin, hist_ws, s.T, s.E, s.k, s.renormalize, Tpad, counts, offsets, H, hot_mask, mask_in,
+                               margin, s.T, s.E, s.k, s.renormalize, Tpad, counts, offsets, H, hot_mask, mask_in,
                                lists ? *lists : none, lists ? 1 : 0, place ? *place : no_place);
             return hipGetLastError();
         }
         hipError_t err = launch_route_fused(s, x, w_gate, bias, idx, gate, margin, hist_ws, gate_part_ws, st);
         if (err != hipSuccess) return err;
     }
-    return launch_scan_finalize(hist_ws, nchunks, s.E, counts, offsets, H, hot_mask, mask_in, lists, place, st);
+    return launch_dispatch(hist_ws, nchunks, s.E, nullptr, true, counts, offsets, H, hot_mask, mask_in, lists, place, st);
 }
 
 hipError_t launch_route(const moe_shape& s, const void* x, const void* w_gate, const float* bias,

@@ -100,3 +100,39 @@ def test_f32_route(gpu_lib, T, d, E):
 def test_tiled_ffn_row_tiles(gpu_lib, d, f):
     say(f"[case] tiled ffn d={d} f={f}")
     check(*ffn_rows(gpu_lib, [128, 129, 64, 255, 0, 257, 300, 1], d, f, "bf16", "gelu", biases=True), 4e-3)
+
+
+# counting sort: one block, a block per 16 or 4 chunks, and slot bases through memory, at the sizes where one form gives way to
+# the next (4096 assignments for moe_permute; 256 experts; 64 k histogram entries or 1024 chunks), by itself and in the layer
+@pytest.mark.parametrize("T,E,k", [(1, 1, 1), (64, 256, 8), (64, 257, 2), (65, 256, 8), (2048, 40, 2), (2049, 40, 2),
+                                   (4000, 257, 3), (4096, 256, 1), (4112, 256, 1), (5000, 1024, 2), (70000, 3, 1)])
+def test_places(gpu_lib, T, E, k):
+    say(f"[case] places T={T} E={E} k={k}")
+    moe, d = gpu_lib, 32
+    gen = torch.Generator(device="cuda").manual_seed(T + E)
+    bf = lambda *s: torch.randn(s, device="cuda", generator=gen).to(torch.bfloat16)
+    i32 = lambda *s: torch.full(s, -1, dtype=torch.int32, device="cuda")
+    x, wg, w = bf(T, d), bf(E, d), bf(E, d * d)
+    shape = moe.make_shape(T, d, d, E, k, "bf16", True)
+    ws = torch.full((moe.moe_workspace_bytes(shape),), 0xFF, dtype=torch.uint8, device="cuda")
+    out, gate = torch.empty((T, d), dtype=torch.bfloat16, device="cuda"), torch.empty((T, k), device="cuda")
+    got = []
+    idx, counts, perm = i32(T, k), i32(E), i32(T * k)
+    mask = torch.empty(E, dtype=torch.uint8, device="cuda")
+    moe.moe_layer_forward(shape, x, wg, None, w, w, None, E // 2, out, idx, gate, counts, perm, mask, ws=ws)
+    got.append((idx, counts, perm))
+    idx, counts, perm, inv, offsets, xp = i32(T, k), i32(E), i32(T * k), i32(T * k), i32(E + 1), torch.empty_like(bf(T * k, d))
+    moe.moe_route(shape, x, wg, None, idx, gate, None, counts, offsets, -1, None, ws)
+    moe.moe_permute(shape, x, idx, offsets, perm, inv, xp, ws)
+    got.append((idx, counts, perm))
+    torch.cuda.synchronize()
+    for i, c, p in got:
+        flat = i.cpu().numpy().ravel()
+        want = np.argsort(flat, kind="stable")
+        assert np.array_equal(c.cpu().numpy(), np.bincount(flat, minlength=E))
+        assert np.array_equal(p.cpu().numpy(), want)
+    n = np.bincount(flat, minlength=E)
+    assert np.array_equal(offsets.cpu().numpy(), np.concatenate([[0], np.cumsum(n)]))
+    assert np.array_equal(inv.cpu().numpy()[want], np.arange(T * k))
+    assert torch.equal(xp.view(torch.int16), x[torch.from_numpy(want // k).cuda()].view(torch.int16))
+    assert np.array_equal(mask.cpu().numpy(), orc.hot_mask_top_h(n, E // 2))
