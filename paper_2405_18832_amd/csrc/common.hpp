@@ -421,7 +421,7 @@ hipError_t launch_expert_products(const moe_shape& s, const void* act, const int
 bool layer_gathers_kmajor(const moe_shape& s);
 hipError_t launch_gather_kmajor(const moe_shape& s, const void* x, const int32_t* tokmap, void* xk, hipStream_t st);
 hipError_t launch_tile_product(bool first, const uint16_t* act, const int32_t* rowmap, const uint16_t* wpk,
-                               void* outp, const TileLists& lists, long A, int N, int K, bool act_kmajor, int activation,
+                               void* outp, const TileLists& lists, int N, int K, bool act_kmajor, int activation,
                                const float* bias, const FoldOut& fold, hipStream_t st);
 int tile_product_grid();
 hipError_t launch_f32_product(bool first, const float* act, const int32_t* rowmap, const float* w, float* outp,

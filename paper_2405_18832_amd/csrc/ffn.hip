@@ -735,7 +735,7 @@ hipError_t launch_expert_products(const moe_shape& s, const void* act, const int
     // Per product: the tiled kernel (large experts) first, then the streaming kernel (small experts), which
     // also adds up the partial tiles that the tiled kernel left for the units it cut along K.
     if (big) {
-        err = launch_tile_product(true, xp, rowmap, p1, h, lists, A, f, d, act_kmajor, s.activation, b1,
+        err = launch_tile_product(true, xp, rowmap, p1, h, lists, f, d, act_kmajor, s.activation, b1,
                                   FoldOut{nullptr, nullptr, nullptr}, st);
         if (err != hipSuccess) return err;
     }
@@ -752,7 +752,7 @@ hipError_t launch_expert_products(const moe_shape& s, const void* act, const int
     if (err != hipSuccess) return err;
     if ((err = mark(2, st)) != hipSuccess) return err;
     if (big) {
-        err = launch_tile_product(false, h, nullptr, p2, y_perm, lists, A, d, f, true, s.activation, b2, fold, st);
+        err = launch_tile_product(false, h, nullptr, p2, y_perm, lists, d, f, true, s.activation, b2, fold, st);
         if (err != hipSuccess) return err;
     }
     if ((err = mark(3, st)) != hipSuccess) return err;

@@ -15,13 +15,15 @@
 // 4 weight fragments (MFMA A operand) x 8 row fragments (B operand) of 16x16x32 per 32-k step,
 // 128 accumulator registers.
 //
-// Fine units, for products whose big units would leave much of the chip idle (tiled_product_is_fine): 4 wavefronts
-// on 128 x 128, each 64 x 64, the same ring of stages half the size, two blocks per CU.  A CU can pull about 35 GB/s
-// from beyond its L2 however much it has in flight, so a handful of big units is bound by the CUs they run on, not by
-// memory or matrix units.  Per output they copy twice the bytes of big units, and they cut less along K.  Measured, 8
-// experts of 137 ... 228 rows, 768 x 3072: 39.7 -> 30.6 us (96 big units of 24 steps) and 33.2 + 8.9 -> 19.3 + 11.1 us
-// (24 units of 96 steps; the second figure adds up the parts); one expert of 327 rows, 1024 x 4096: 28 -> 15 and 32 -> 13 us.
-// Three blocks per CU with a ring of three stages, or five stages, are no faster.
+// Fine units, for products whose big units would leave much of the chip idle (tiled_product_is_fine): 128 x 128, the
+// 8 wavefronts as two groups of four (64 x 64 each) that take half of the contraction each, through a ring of their own
+// with stages half the size, and add up in LDS.  A CU can pull about 35 GB/s from beyond its L2 however much it has in
+// flight, so a handful of big units is bound by the CUs they run on, not by memory or matrix units.  Per output they copy
+// twice the bytes of big units, and they are cut less along K into parts that go through memory.  Measured, big ->
+// fine, the second figure of a sum being the kernel that adds up the parts: 8 experts of 137 ... 228 rows, 768 x 3072:
+// 39.7 -> 35.7 us (96 big units of 24 steps, GeLU) and 33.2 + 8.9 -> 19.4 + 8.9 us (24 units of 96 steps); one expert
+// of 327 rows, 1024 x 4096: 28 -> 14 and 32 -> 14 us; 16 big row tiles, K = 4096, N = 1024: 40.6 + 43.4 -> 37.6 + 23.9 us.
+// As blocks of one group, two per CU, the last was 50.1 + 36.7 us: twice the parts.
 //
 // Blocks are persistent over (row tile, column tile) pairs taken
 // from the device-built list of large-expert row tiles.
@@ -35,6 +37,9 @@ constexpr int kTK = 32;             // k per LDS stage
 constexpr int kStages = 4;          // ring of LDS stages: two being read, two in flight (a fifth, which
                                     // fits, bought nothing: the copies are not limited by ring depth)
 constexpr int kAhead = kStages - 1; // the iteration for stage j issues the copies of stage j + kAhead
+constexpr int kWaves = 8;           // wavefronts of a block
+constexpr int kRingBytes = kStages * 2 * kBigTileRows * kTK * 2;   // 128 KiB of stages
+constexpr int kTileLds = kRingBytes + 32 * 1024;                   // and where the groups of a fine unit exchange sums
 
 // Wait until at most `stages` stages' worth of this wavefront's copies (4 each) are still in flight.
 __device__ __forceinline__ void wait_copies(int stages) {
@@ -72,37 +77,36 @@ __device__ __forceinline__ void mfma_pair(const bf16x8 (&w)[4], const bf16x8 (&x
 }
 
 template <int FIRST, typename Units>
-__global__ __launch_bounds__(Units::kWaves * 64, 2) void ffn_tile_kernel(const uint16_t* __restrict__ act,
-                                                       const int32_t* __restrict__ rowmap,
-                                                       const uint16_t* __restrict__ wpk,
-                                                       void* __restrict__ outp, const Tile* __restrict__ tiles,
-                                                       const int32_t* __restrict__ ntiles_p,
-                                                       int32_t* __restrict__ part_counter,
-                                                       float* __restrict__ partials, int N, int K,
-                                                       int act_kmajor,
-                                                       const float* __restrict__ bias, const FoldOut fold) {
-    constexpr bool FINE = Units::kWaves == 4;
+__device__ __forceinline__ void run_units(const uint16_t* __restrict__ act, const int32_t* __restrict__ rowmap,
+                                          const uint16_t* __restrict__ wpk, void* __restrict__ outp,
+                                          const Tile* __restrict__ tiles, const int ntiles,
+                                          int32_t* __restrict__ part_counter, float* __restrict__ partials, int N, int K,
+                                          int act_kmajor, const float* __restrict__ bias, const FoldOut& fold,
+                                          unsigned char* smem) {
+    constexpr bool FINE = Units::kGroups == 2;
     constexpr int kTM = Units::kRows, kTN = Units::kCols;
-    constexpr int WN = kTN / 64;                        // wavefronts side by side; two in the row direction
+    constexpr int kGroupWaves = kWaves / Units::kGroups;
+    constexpr int WN = kTN / 64;                        // wavefronts of a group side by side; two in the row direction
     constexpr int RF = kTM / 32;                        // row fragments of a wavefront
     constexpr int kOperandBytes = kTM * kTK * 2;        // per operand and stage (kTM == kTN)
     constexpr int kStageBytes = 2 * kOperandBytes;
-    static_assert(kTM == kTN && Units::kWaves == 2 * WN && kTM / 16 == 2 * Units::kWaves, "two fragments per wavefront and copy");
-    extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
+    static_assert(kTM == kTN && kGroupWaves == 2 * WN && kTM / 16 == 2 * kGroupWaves, "two fragments per wavefront and copy");
+    static_assert(Units::kGroups * kStages * kStageBytes == kRingBytes, "the groups' rings fill the LDS");
     // between units, when no stage is in use, the first word of the ring passes the next part's number on
     int* next_part = reinterpret_cast<int*>(smem);
-    // stage st: kTM / 16 row fragments at smem + st * kStageBytes, as many weight fragments behind them
+    f32x4* exchange = reinterpret_cast<f32x4*>(smem + kRingBytes);
+    const int block_wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int group = FINE ? block_wave / kGroupWaves : 0;
+    // stage st of a group: kTM / 16 row fragments at ring + st * kStageBytes, as many weight fragments behind them
+    unsigned char* ring = smem + group * (kStages * kStageBytes);
 
-    const int t = threadIdx.x, wave = t >> 6, lane = t & 63;
+    const int t = threadIdx.x, wave = block_wave % kGroupWaves, lane = t & 63;
     const int wm = wave / WN, wn = wave % WN;
     const int r = lane & 15, g = lane >> 4;
     const int nblk = N >> 4, kblk = K >> 5;
-    const int ntiles = ntiles_p[FINE ? kHalfCount : 1];
     const int G = gridDim.x;
-    // no large expert in this call, or the product runs in the other units (block-uniform)
-    if (ntiles <= 0 || tiled_product_is_fine(ntiles_p[1], N, G / Units::kPerCu) != FINE) return;
     // LDS byte address of the first of the two fragments that this wavefront copies in, stage 0
-    const uint32_t copy_base = lds_address(smem) + 2 * wave * 1024;
+    const uint32_t copy_base = lds_address(ring) + 2 * wave * 1024;
 
     // Blocks are handed to the 8 XCDs round-robin, and each XCD has its own L2: block b takes position pb
     // of a round, so that the blocks of one XCD hold G / 8 consecutive units, a GM x GN patch whose
@@ -115,7 +119,8 @@ __global__ __launch_bounds__(Units::kWaves * 64, 2) void ffn_tile_kernel(const u
     // A unit of work: (row tile mt, column tile nt) over k-steps [kb0, kb0 + nk), whole (nparts == 1) or
     // one of nparts parts of a left-over unit.
     struct Unit {
-        int u, part, nparts, nt, kb0, nk;
+        int u, part, nparts, nt;
+        int kb0, nk, longest;       // the group's run of k-steps; the number of steps of the first group
         Tile tl;
         bool valid;
     };
@@ -160,7 +165,12 @@ __global__ __launch_bounds__(Units::kWaves * 64, 2) void ffn_tile_kernel(const u
         w.nt = 0;
         if (w.valid) unit_of(sch, w.u, mt, w.nt);
         w.kb0 = kblk * w.part / w.nparts;                  // kblk * kMaxSplit fits easily
-        w.nk = kblk * (w.part + 1) / w.nparts - w.kb0;
+        w.nk = w.longest = kblk * (w.part + 1) / w.nparts - w.kb0;
+        if constexpr (FINE) {
+            w.longest = (w.nk + 1) >> 1;
+            if (group == 1) w.kb0 += w.longest;
+            w.nk = group == 0 ? w.longest : w.nk - w.longest;
+        }
         w.tl = tiles[w.valid ? mt : 0];
         return w;
     };
@@ -225,7 +235,7 @@ __global__ __launch_bounds__(Units::kWaves * 64, 2) void ffn_tile_kernel(const u
         // The next unit's first stages go out during this unit's last iterations, in the slots that fall free
         // there, when the unit is known by then, needs no row lookups (a vector load here would make the
         // compiler wait for every copy in flight) and both units are at least as long as the ring is deep.
-        const bool ahead = next_known && nxt.valid && rowmap == nullptr && nk >= kAhead && nxt.nk >= kAhead;
+        const bool ahead = !FINE && next_known && nxt.valid && rowmap == nullptr && nk >= kAhead && nxt.nk >= kAhead;
         f32x4 acc[4][RF];
 #pragma unroll
         for (int nf = 0; nf < 4; ++nf)
@@ -247,8 +257,8 @@ __global__ __launch_bounds__(Units::kWaves * 64, 2) void ffn_tile_kernel(const u
             constexpr bool STEADY = decltype(steady)::value;
             const int slot_next = slot + 1 == kStages ? 0 : slot + 1;
             const int slot_free = slot == 0 ? kStages - 1 : slot - 1;          // held stage j - 1
-            const unsigned char* st_cur = smem + slot * kStageBytes;
-            const unsigned char* st_nxt = smem + slot_next * kStageBytes;
+            const unsigned char* st_cur = ring + slot * kStageBytes;
+            const unsigned char* st_nxt = ring + slot_next * kStageBytes;
             const bool more = STEADY || j + 1 < nk;        // block-uniform
             if (more) {
                 // stages j + 2 ... j + kAhead - 1 (as far as they exist) may stay in flight; with the next unit's
@@ -310,10 +320,10 @@ __global__ __launch_bounds__(Units::kWaves * 64, 2) void ffn_tile_kernel(const u
         // number of operations stays outstanding and the copies complete in order.
         wait_copies(min(kAhead, nk) - 1);                  // stage 0 has landed ...
         asm volatile("s_barrier" ::: "memory");           // ... for every wavefront
-        lds_read_w(fr.w[0], smem + slot * kStageBytes + wave_w);
-        lds_read_x(fr.x[0], smem + slot * kStageBytes + wave_x, 0);
-        lds_read_x(fr.x[1], smem + slot * kStageBytes + wave_x, 1);
-        if constexpr (!FINE) lds_read_x(fr.x[2], smem + slot * kStageBytes + wave_x, 2);
+        lds_read_w(fr.w[0], ring + slot * kStageBytes + wave_w);
+        lds_read_x(fr.x[0], ring + slot * kStageBytes + wave_x, 0);
+        lds_read_x(fr.x[1], ring + slot * kStageBytes + wave_x, 1);
+        if constexpr (!FINE) lds_read_x(fr.x[2], ring + slot * kStageBytes + wave_x, 2);
         int j = 0;
         for (; j + 1 + kAhead < nk; j += 2) {
             iterate(std::integral_constant<int, 0>{}, std::true_type{}, j);
@@ -326,6 +336,26 @@ __global__ __launch_bounds__(Units::kWaves * 64, 2) void ffn_tile_kernel(const u
         if (j + 3 < nk) iterate(std::integral_constant<int, 1>{}, std::false_type{}, j + 3);
         if (j + 4 < nk) iterate(std::integral_constant<int, 0>{}, std::false_type{}, j + 4);
 
+        if constexpr (FINE) {
+            // the second group may have one step and so one barrier less
+            for (int i = cur.longest - max(nk, 1); i > 0; --i) asm volatile("s_barrier" ::: "memory");
+            // The groups' sums meet in LDS: the first keeps row fragments 0 and 1 of every wavefront, the second 2 and 3, and
+            // each takes the other's share of its own, a fragment row at a time (first group's sum + second group's).
+            f32x4* to = exchange + (group * kGroupWaves + wave) * 4 * 64 + lane;
+            const f32x4* from = exchange + ((1 - group) * kGroupWaves + wave) * 4 * 64 + lane;
+#pragma unroll
+            for (int i = 0; i < 2; ++i) {
+#pragma unroll
+                for (int nf = 0; nf < 4; ++nf) to[nf * 64] = group == 0 ? acc[nf][2 + i] : acc[nf][i];
+                asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+#pragma unroll
+                for (int nf = 0; nf < 4; ++nf) acc[nf][i] = (group == 0 ? acc[nf][i] : acc[nf][2 + i]) + from[nf * 64];
+                asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+            }
+        }
+        constexpr int OF = RF / Units::kGroups;            // row fragments of output per wavefront, from the first on:
+        const int lr0 = wm * (kTM / 2) + group * OF * 16;
+
         // The next unit's first copies go out before this unit's output is stored: the copies' latency and
         // the stores overlap, and the load of the next tile's descriptor does not wait behind the stores.
         if (!next_known) nxt = unit_at(it + 1);
@@ -336,17 +366,17 @@ __global__ __launch_bounds__(Units::kWaves * 64, 2) void ffn_tile_kernel(const u
             // part of a unit: the partial tile goes to the workspace; the next kernel adds the parts up
             float* mine = partials + (static_cast<size_t>(cur.u - sch.rounds * G) * cur.nparts + cur.part) * (kTM * kTN);
 #pragma unroll
-            for (int tf = 0; tf < RF; ++tf)
+            for (int tf = 0; tf < OF; ++tf)
 #pragma unroll
                 for (int nf = 0; nf < 4; ++nf)
-                    *reinterpret_cast<f32x4*>(mine + (wm * (kTM / 2) + tf * 16 + r) * kTN + (wn * 4 + nf) * 16 + g * 4) =
+                    *reinterpret_cast<f32x4*>(mine + (lr0 + tf * 16 + r) * kTN + (wn * 4 + nf) * 16 + g * 4) =
                         acc[nf][tf];
         } else {
             const float* be = bias ? bias + static_cast<size_t>(cur.tl.expert) * N : nullptr;
 #pragma unroll
-            for (int tf = 0; tf < RF; ++tf) {
-                if (wm * (kTM / 2) + tf * 16 >= cur.tl.rows) break;     // wave-uniform: no row from here on
-                const int lr = wm * (kTM / 2) + tf * 16 + r;
+            for (int tf = 0; tf < OF; ++tf) {
+                if (lr0 + tf * 16 >= cur.tl.rows) break;     // wave-uniform: no row from here on
+                const int lr = lr0 + tf * 16 + r;
                 const bool ok = lr < cur.tl.rows;
                 if constexpr (FIRST != 0) {
 #pragma unroll
@@ -385,62 +415,60 @@ __global__ __launch_bounds__(Units::kWaves * 64, 2) void ffn_tile_kernel(const u
     }
 }
 
-template <int FIRST, typename Units>
+template <int FIRST>
+__global__ __launch_bounds__(kWaves * 64, 2) void ffn_tile_kernel(const uint16_t* __restrict__ act, const int32_t* __restrict__ rowmap,
+                                                                  const uint16_t* __restrict__ wpk, void* __restrict__ outp,
+                                                                  const Tile* __restrict__ big_tiles,
+                                                                  const Tile* __restrict__ half_tiles,
+                                                                  const int32_t* __restrict__ ntiles_p,
+                                                                  int32_t* __restrict__ part_counter,
+                                                                  float* __restrict__ partials, int N, int K, int act_kmajor,
+                                                                  const float* __restrict__ bias, const FoldOut fold) {
+    extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
+    const int ntiles = ntiles_p[1];
+    if (ntiles <= 0) return;                            // no large expert in this call (block-uniform)
+    if (tiled_product_is_fine(ntiles, N, gridDim.x))
+        run_units<FIRST, FineUnits>(act, rowmap, wpk, outp, half_tiles, ntiles_p[kHalfCount], part_counter, partials, N, K,
+                                    act_kmajor, bias, fold, smem);
+    else
+        run_units<FIRST, BigUnits>(act, rowmap, wpk, outp, big_tiles, ntiles, part_counter, partials, N, K, act_kmajor, bias,
+                                   fold, smem);
+}
+
+template <int FIRST>
 static hipError_t launch_tile(const uint16_t* act, const int32_t* rowmap, const uint16_t* wpk, void* outp,
                               const TileLists& lists, int N, int K, bool act_kmajor, const float* bias, const FoldOut& fold,
                               hipStream_t st) {
-    auto kern = ffn_tile_kernel<FIRST, Units>;
-    constexpr int lds = kStages * 2 * Units::kRows * kTK * 2;   // 128 KiB or 64 KiB (limit raised by configure_tile_kernels)
-    // Always the whole chip, as many blocks per CU as the LDS rings allow: how many units there are is
+    // Always the whole chip, one block per CU (the LDS allows no more): how many units there are is
     // only known on the device, and few units are cut along K over blocks that would otherwise idle.
-    const int grid = device_cu_count() * Units::kPerCu;
-    hipLaunchKernelGGL(kern, dim3(static_cast<unsigned>(grid)), dim3(Units::kWaves * 64), lds, st, act, rowmap, wpk, outp,
-                       Units::kPerCu == 1 ? lists.big_tiles : lists.half_tiles, lists.ntiles,
+    hipLaunchKernelGGL(ffn_tile_kernel<FIRST>, dim3(static_cast<unsigned>(tile_product_grid())), dim3(kWaves * 64), kTileLds, st,
+                       act, rowmap, wpk, outp, lists.big_tiles, lists.half_tiles, lists.ntiles,
                        lists.ntiles + kSplitCounter + (FIRST != 0 ? 0 : 1), lists.partials, N, K, act_kmajor ? 1 : 0, bias, fold);
     return hipGetLastError();
 }
 
-template <int FIRST>
-static hipError_t launch_tiles(const uint16_t* act, const int32_t* rowmap, const uint16_t* wpk, void* outp,
-                               const TileLists& lists, long A, int N, int K, bool act_kmajor, const float* bias,
-                               const FoldOut& fold, hipStream_t st) {
-    // An expert of m >= kBigMinRows rows has at most m / 128 big tiles, so A / 128 of them are the most there can be
-    // (smaller experts join only when there are at least a round's).
-    if (!tiled_product_is_fine(A / kBigMinRows, N, device_cu_count())) {
-        const hipError_t e = launch_tile<FIRST, BigUnits>(act, rowmap, wpk, outp, lists, N, K, act_kmajor, bias, fold, st);
-        if (e != hipSuccess) return e;
-    }
-    return launch_tile<FIRST, FineUnits>(act, rowmap, wpk, outp, lists, N, K, act_kmajor, bias, fold, st);
-}
-
 int tile_product_grid() { return device_cu_count(); }
 
-template <int FIRST, typename Units>
+template <int FIRST>
 static hipError_t configure_tile() {
-    return hipFuncSetAttribute(reinterpret_cast<const void*>(ffn_tile_kernel<FIRST, Units>),
-                               hipFuncAttributeMaxDynamicSharedMemorySize, kStages * 2 * Units::kRows * kTK * 2);
-}
-
-template <typename Units>
-static hipError_t configure_tiles() {
-    hipError_t e;
-    if ((e = configure_tile<0, Units>()) != hipSuccess) return e;
-    if ((e = configure_tile<kFirstRelu, Units>()) != hipSuccess) return e;
-    return configure_tile<kFirstGelu, Units>();
+    return hipFuncSetAttribute(reinterpret_cast<const void*>(ffn_tile_kernel<FIRST>),
+                               hipFuncAttributeMaxDynamicSharedMemorySize, kTileLds);
 }
 
 hipError_t configure_tile_kernels(int) {
-    const hipError_t e = configure_tiles<BigUnits>();
-    return e != hipSuccess ? e : configure_tiles<FineUnits>();
+    hipError_t e;
+    if ((e = configure_tile<0>()) != hipSuccess) return e;
+    if ((e = configure_tile<kFirstRelu>()) != hipSuccess) return e;
+    return configure_tile<kFirstGelu>();
 }
 
 hipError_t launch_tile_product(bool first, const uint16_t* act, const int32_t* rowmap, const uint16_t* wpk,
-                               void* outp, const TileLists& lists, long A, int N, int K, bool act_kmajor, int activation,
+                               void* outp, const TileLists& lists, int N, int K, bool act_kmajor, int activation,
                                const float* bias, const FoldOut& fold, hipStream_t st) {
-    if (!first) return launch_tiles<0>(act, rowmap, wpk, outp, lists, A, N, K, act_kmajor, bias, fold, st);
+    if (!first) return launch_tile<0>(act, rowmap, wpk, outp, lists, N, K, act_kmajor, bias, fold, st);
     if (activation == MOE_ACT_GELU)
-        return launch_tiles<kFirstGelu>(act, rowmap, wpk, outp, lists, A, N, K, act_kmajor, bias, fold, st);
-    return launch_tiles<kFirstRelu>(act, rowmap, wpk, outp, lists, A, N, K, act_kmajor, bias, fold, st);
+        return launch_tile<kFirstGelu>(act, rowmap, wpk, outp, lists, N, K, act_kmajor, bias, fold, st);
+    return launch_tile<kFirstRelu>(act, rowmap, wpk, outp, lists, N, K, act_kmajor, bias, fold, st);
 }
 
 }  // namespace moe

@@ -20,18 +20,18 @@ constexpr int kMaxSplit = 8;        // parts per left-over unit, at most ...
 #define MOE_MIN_SPLIT_STEPS_FINE 16
 #endif
 
-// The two shapes of a unit: rows x columns of its output, wavefronts and blocks per CU of the kernel that runs it, and
-// the fewest 32-k steps of a part.
+// The two shapes of a unit: rows x columns of its output, the groups of wavefronts that share its contraction inside the
+// block (each adds up an equal run of its 32-k steps), and the fewest steps of a part.
 struct BigUnits {
-    static constexpr int kRows = kBigTileRows, kCols = 256, kWaves = 8, kPerCu = 1, kMinSplitSteps = MOE_MIN_SPLIT_STEPS;
+    static constexpr int kRows = kBigTileRows, kCols = 256, kGroups = 1, kMinSplitSteps = MOE_MIN_SPLIT_STEPS;
 };
 struct FineUnits {
-    static constexpr int kRows = kHalfTileRows, kCols = 128, kWaves = 4, kPerCu = 2, kMinSplitSteps = MOE_MIN_SPLIT_STEPS_FINE;
+    static constexpr int kRows = kHalfTileRows, kCols = 128, kGroups = 2, kMinSplitSteps = MOE_MIN_SPLIT_STEPS_FINE;
 };
 
-// Which of them a product runs in: big units from 5/8 of a round of them on.  (96 units: fine 30.6 us, big 39.7 us;
-// 256 units of 32 steps: 35 us as big units, 55 us as fine ones.  Between them both take about as long where four fine
-// units per big one need a second round of blocks, from 128 big units on.)
+// Which of them a product runs in: big units from 5/8 of a round of them on.  Four fine units per big one are then 2.5
+// rounds, with the same steps per round as half a big unit's and a start and an end each.  (96 units of 24 steps: fine
+// 35.7 us, big 39.7 us; 256 units of 32 steps: big 33.7 us.)
 #ifndef MOE_FINE_BELOW_PCT
 #define MOE_FINE_BELOW_PCT 62
 #endif
@@ -304,11 +304,10 @@ __device__ __forceinline__ void finish_tiled_product(const Tile* __restrict__ bi
                                                      void* __restrict__ outp, int N, int kblk, int cus,
                                                      const float* __restrict__ bias, const FoldOut& fold, int block, int nblocks) {
     if (tiled_product_is_fine(ntiles[1], N, cus))
-        finish_split_units<FineUnits, FIRST, FOLD>(half_tiles, ntiles[kHalfCount], partials, outp, N, kblk, cus * FineUnits::kPerCu,
-                                                   bias, fold, block, nblocks);
+        finish_split_units<FineUnits, FIRST, FOLD>(half_tiles, ntiles[kHalfCount], partials, outp, N, kblk, cus, bias, fold,
+                                                   block, nblocks);
     else
-        finish_split_units<BigUnits, FIRST, FOLD>(big_tiles, ntiles[1], partials, outp, N, kblk, cus * BigUnits::kPerCu, bias,
-                                                  fold, block, nblocks);
+        finish_split_units<BigUnits, FIRST, FOLD>(big_tiles, ntiles[1], partials, outp, N, kblk, cus, bias, fold, block, nblocks);
 }
 #endif
 
