@@ -80,11 +80,31 @@ __device__ __forceinline__ float gelu_erf(float z) { return 0.5f * z * (1.f + er
 
 __device__ __forceinline__ float activate(float z, int act) { return act == MOE_ACT_GELU ? gelu_erf(z) : fmaxf(z, 0.f); }
 
+// GeLU where the result is rounded to bf16, without branches and in half the instructions of erff:
+//   Phi(-|z|) = erfc(a) / 2 = exp(-a^2) t Q(t),  a = |z| / sqrt 2,  t = 1 / (1 + a / 2)
+// (the form of Numerical Recipes' erfcc; Q is a Chebyshev fit of degree 8 over 0 <= a <= 10, relative error 4e-8), and
+// Phi(z) = 1 - Phi(-z).  Against 64 bits over |z| <= 8, in fp32: largest error 3.8e-7, relative error for |z| < 4 at most
+// 8.4e-7 (gelu_erf: 4.5e-7 and, because 1 + erf cancels for negative z, 4.6e-4).
+__device__ __forceinline__ float gelu_exp(float z) {
+    const float t = __builtin_amdgcn_rcpf(fmaf(fabsf(z), 0.35355339059327378f, 1.f));
+    float q = -2.953637950e-02f;
+    q = fmaf(q, t, 1.422964782e-01f);
+    q = fmaf(q, t, -2.436179519e-01f);
+    q = fmaf(q, t, 1.390533745e-01f);
+    q = fmaf(q, t, -1.332583465e-02f);
+    q = fmaf(q, t, 1.013486385e-01f);
+    q = fmaf(q, t, 1.215506494e-01f);
+    q = fmaf(q, t, 1.411878169e-01f);
+    q = fmaf(q, t, 1.410432011e-01f);
+    const float tail = q * t * __builtin_amdgcn_exp2f(z * z * -0.72134752044448170f);
+    return z * (z < 0.f ? tail : 1.f - tail);
+}
+
 // Four values at once, the activation a compile-time constant: the MFMA kernels are instantiated per
 // activation (as a run-time choice in their epilogues it cost the ReLU layers 5-10 % of the kernel).
 template <int ACT>
 __device__ __forceinline__ f32x4 activate4(f32x4 v) {
-    if (ACT == MOE_ACT_GELU) return f32x4{gelu_erf(v[0]), gelu_erf(v[1]), gelu_erf(v[2]), gelu_erf(v[3])};
+    if (ACT == MOE_ACT_GELU) return f32x4{gelu_exp(v[0]), gelu_exp(v[1]), gelu_exp(v[2]), gelu_exp(v[3])};
     return f32x4{fmaxf(v[0], 0.f), fmaxf(v[1], 0.f), fmaxf(v[2], 0.f), fmaxf(v[3], 0.f)};
 }
 
