@@ -3,7 +3,7 @@
 // top-H hot mask (paper Section 2.1 for the gating network, Section 3.3 for the token
 // counts and the hot set).
 //
-// Two kernels.  route_fused_kernel: one block per chunk of 16*TF tokens computes the chunk's
+// Two kernels.  route_bf16_kernel / route_f32_kernel: one block per chunk of tokens computes the chunk's
 // logits into LDS, picks each token's experts there and leaves the chunk's per-expert
 // histogram in the workspace.  dispatch_kernel: one block turns the chunk histograms
 // into counts, prefix sums, the hot mask and the expert tile lists, while the others place the
@@ -150,174 +150,210 @@ __device__ __forceinline__ void topk_from_lds(float* __restrict__ row, int E, in
 __host__ __device__ inline int route_row_stride(int E, int NF) { return (E + 16 * NF - 1) / (16 * NF) * (16 * NF) + 4; }
 
 // ---------------------------------------------------------------------------
-// route_fused_kernel<ST, TF, NW, NF>: block = NW wavefronts, chunk = 16*TF tokens.
-//  bf16: MFMA 16x16x32 with gate rows as the A operand and token rows as the B operand (a lane
-//  ends up with 4 consecutive experts of one token).  Experts are taken NF fragments (16*NF
-//  experts) at a time; the NW wavefronts split the contraction (each reads its own slice of
-//  every row, so x and the gate matrix cross L1 once per block) and add their partial logits
-//  into LDS one after the other, in wave order (deterministic).  Every k-step issues exactly
-//  NF + TF loads (rows past the end are clamped, their results dropped), two steps ahead.
-//  fp32: the same with 16x16x4 fp32 MFMAs, one fragment of 16 experts at a time.
-// The chunk's histogram goes to chunk_hist[chunk * E + e].
-// Dynamic LDS: logits [16*TF][route_row_stride(E, NF)] floats, then the histogram [E] ints.
+// Routing of a chunk of tokens by one block: logits into LDS, softmax and top-k there, and the chunk's histogram to
+// chunk_hist[chunk * E + e].
+//
+// route_bf16_kernel<TF, NF>: chunk = 16 * TF tokens, 4 wavefronts, experts 16 * NF at a time.  MFMA 16x16x32 with gate rows
+// as the A operand and token rows as the B operand (a lane ends up with 4 consecutive experts of one token); a wavefront
+// owns NF / 4 fragments of experts for all the chunk's tokens.  Rows of both operands go through a ring of LDS stages, 64 k
+// = one 128-byte line of every row per stage, copied by eight consecutive lanes each.  (Loaded straight into operand form,
+// 16 consecutive lanes touch 16 different rows: 64 cache accesses per load instruction instead of 16, which bounded the
+// kernel; neither more loads in flight nor more wavefronts changed it.)  The 16-byte pieces of a row are permuted by its row
+// number, so that the rows a read touches at once lie in different banks.  The contraction runs in four chains per
+// accumulator, which are added at the end.
+// Dynamic LDS: the ring, then logits [16 * TF][route_row_stride(E, NF)] floats, then the histogram [E] ints.
 // ---------------------------------------------------------------------------
-template <typename ST, int TF, int NW, int NF>
-__global__ __launch_bounds__(NW * 64) void route_fused_kernel(const ST* __restrict__ x, const ST* __restrict__ wg,
-                                                              const float* __restrict__ bias,
-                                                              int32_t* __restrict__ topk_idx,
-                                                              float* __restrict__ topk_w,
-                                                              float* __restrict__ margin,
-                                                              int32_t* __restrict__ chunk_hist, int T, int d,
-                                                              int E, int k, int renorm) {
-    constexpr int TOK = 16 * TF;
-    constexpr int NT = NW * 64;
-    extern __shared__ __attribute__((aligned(16))) float lds[];
+constexpr int kRouteWaves = 4;
+template <int TF, int NF>
+struct RouteRing {
+    static constexpr int kRows = (16 * (TF + NF) + 31) / 32 * 32;      // whole copies for every wavefront
+    static constexpr int kStageBytes = kRows * 128;
+    static constexpr int kCopies = kRows / 32;                         // per wavefront and stage, 8 rows each
+    static constexpr int kStages = 4;
+    static constexpr int kBytes = kStages * kStageBytes;
+};
+
+template <int TF, int NF>
+__global__ __launch_bounds__(kRouteWaves * 64) void route_bf16_kernel(const uint16_t* __restrict__ x,
+                                                                      const uint16_t* __restrict__ wg,
+                                                                      const float* __restrict__ bias,
+                                                                      int32_t* __restrict__ topk_idx,
+                                                                      float* __restrict__ topk_w, float* __restrict__ margin,
+                                                                      int32_t* __restrict__ chunk_hist, int T, int d, int E,
+                                                                      int k, int renorm) {
+    using Ring = RouteRing<TF, NF>;
+    constexpr int TOK = 16 * TF, NW = kRouteWaves, NT = NW * 64, FPW = NF / NW, S = Ring::kStages, P = Ring::kCopies;
+    static_assert(NF % NW == 0, "whole fragments of experts per wavefront");
+    extern __shared__ __attribute__((aligned(16))) unsigned char route_lds[];
     const int Ep = route_row_stride(E, NF);
+    float* L = reinterpret_cast<float*>(route_lds + Ring::kBytes);
+    int32_t* hist = reinterpret_cast<int32_t*>(L + TOK * Ep);
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
+    const int r = lane & 15, g = lane >> 4;
+    const int t0 = blockIdx.x * TOK;
+    for (int e = threadIdx.x; e < E; e += NT) hist[e] = 0;
+
+    const int ksteps = d >> 5, nstages = (ksteps + 1) >> 1;
+    const uint32_t ring0 = lds_address(route_lds);
+    // copies: this wavefront's p-th takes the rows 8 * (wave + NW * p) ... + 7 of a stage, tokens first
+    const int piece = (lane & 7) ^ (lane >> 3);
+    for (int ec = 0; ec < E; ec += 16 * NF) {
+        const uint16_t* src[P];
+#pragma unroll
+        for (int p = 0; p < P; ++p) {
+            const int row = 8 * (wave + NW * p) + (lane >> 3);
+            src[p] = row < TOK ? x + static_cast<size_t>(min(t0 + row, T - 1)) * d
+                               : wg + static_cast<size_t>(min(ec + row - TOK, E - 1)) * d;
+        }
+        auto stage_in = [&](int j) {
+            // a last stage of one 32-k step: its second half is read again from the first, and not used
+            const int q = (2 * j + 1 < ksteps) ? piece : (piece & 3);
+            const uint32_t base = ring0 + (j % S) * Ring::kStageBytes;
+#pragma unroll
+            for (int p = 0; p < P; ++p) copy16_to_lds(src[p] + j * 64 + q * 8, base + (wave + NW * p) * 1024);
+        };
+        f32x4 acc[4][FPW][TF];                             // [chain]
+#pragma unroll
+        for (int c = 0; c < 4; ++c)
+#pragma unroll
+            for (int nf = 0; nf < FPW; ++nf)
+#pragma unroll
+                for (int tf = 0; tf < TF; ++tf) acc[c][nf][tf] = f32x4{0.f, 0.f, 0.f, 0.f};
+        // the last stages of a previous group of experts have been read
+        if (ec > 0) asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory");
+#pragma unroll
+        for (int j = 0; j < S - 1; ++j)
+            if (j < nstages) stage_in(j);
+        f32x4 first[FPW];                                  // what the sums start from: the bias
+#pragma unroll
+        for (int nf = 0; nf < FPW; ++nf) {
+            first[nf] = f32x4{0.f, 0.f, 0.f, 0.f};
+            if (bias != nullptr) {
+#pragma unroll
+                for (int i = 0; i < 4; ++i) first[nf][i] = bias[min(ec + (wave * FPW + nf) * 16 + g * 4 + i, E - 1)];
+            }
+        }
+        auto step = [&](int j, auto parity) {
+            constexpr int C = 2 * decltype(parity)::value;
+            // stage j has landed for every wavefront, and nobody reads stage j - 1 any more
+            if (j + S - 2 < nstages) __builtin_amdgcn_s_waitcnt(0x0F70 | ((S - 2) * P));
+            else __builtin_amdgcn_s_waitcnt(0x0F70);
+            asm volatile("s_barrier" ::: "memory");
+            if (j + S - 1 < nstages) stage_in(j + S - 1);
+            const unsigned char* st = route_lds + (j % S) * Ring::kStageBytes;
+            const int halves = 2 * j + 1 < ksteps ? 2 : 1;
+#pragma unroll
+            for (int h = 0; h < 2; ++h) {
+                if (h == 1 && halves == 1) break;          // uniform
+                const int at = r * 128 + (((h * 4 + g) ^ (r & 7)) << 4);
+                bf16x8 a[FPW], b[TF];
+#pragma unroll
+                for (int nf = 0; nf < FPW; ++nf)
+                    a[nf] = *reinterpret_cast<const bf16x8*>(st + (TOK + (wave * FPW + nf) * 16) * 128 + at);
+#pragma unroll
+                for (int tf = 0; tf < TF; ++tf) b[tf] = *reinterpret_cast<const bf16x8*>(st + tf * 16 * 128 + at);
+#pragma unroll
+                for (int nf = 0; nf < FPW; ++nf)
+#pragma unroll
+                    for (int tf = 0; tf < TF; ++tf)
+                        acc[C + h][nf][tf] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[nf], b[tf], acc[C + h][nf][tf], 0, 0, 0);
+            }
+        };
+        int j = 0;
+        for (; j + 1 < nstages; j += 2) {
+            step(j, std::integral_constant<int, 0>{});
+            step(j + 1, std::integral_constant<int, 1>{});
+        }
+        if (j < nstages) step(j, std::integral_constant<int, 0>{});
+        // The compiler does not see that the branch around the second half of a last stage leads from a matrix instruction
+        // straight to the reads of its result, and leaves out the wait states these need (d = 32 gave wrong logits).
+        __builtin_amdgcn_sched_barrier(0);
+        asm volatile("s_nop 7\n\ts_nop 7");
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int nf = 0; nf < FPW; ++nf)
+#pragma unroll
+            for (int tf = 0; tf < TF; ++tf)
+                *reinterpret_cast<f32x4*>(L + (tf * 16 + r) * Ep + ec + (wave * FPW + nf) * 16 + g * 4) =
+                    (first[nf] + acc[0][nf][tf]) + acc[1][nf][tf] + (acc[2][nf][tf] + acc[3][nf][tf]);
+    }
+    __syncthreads();
+
+    // top-k: 4 tokens per wavefront and pass
+    const int grp = lane >> 4, sub = lane & 15;
+#pragma unroll 1
+    for (int tl = wave * 4 + grp; tl < TOK; tl += NW * 4) {
+        const int t = t0 + tl;
+        const bool live = t < T;
+        const size_t o = static_cast<size_t>(live ? t : 0) * k;
+        topk_from_lds(L + tl * Ep, E, k, renorm, sub, live, topk_idx + o, topk_w + o,
+                      margin ? margin + (live ? t : 0) : nullptr, hist);
+    }
+    __syncthreads();
+    for (int e = threadIdx.x; e < E; e += NT) chunk_hist[static_cast<size_t>(blockIdx.x) * E + e] = hist[e];
+}
+
+// fp32: 16 tokens, 16 experts at a time with the fp32 matrix instruction, 16 k per step (operands as in ffn_f32.hip); the
+// wavefronts split the contraction and meet in LDS in wave order.  Dynamic LDS: logits, then the histogram, as above.
+__global__ __launch_bounds__(kRouteWaves * 64) void route_f32_kernel(const float* __restrict__ x, const float* __restrict__ wg,
+                                                                     const float* __restrict__ bias,
+                                                                     int32_t* __restrict__ topk_idx,
+                                                                     float* __restrict__ topk_w, float* __restrict__ margin,
+                                                                     int32_t* __restrict__ chunk_hist, int T, int d, int E,
+                                                                     int k, int renorm) {
+    constexpr int TOK = 16, NW = kRouteWaves, NT = NW * 64;
+    extern __shared__ __attribute__((aligned(16))) float lds[];
+    const int Ep = route_row_stride(E, 1);
     float* L = lds;
     int32_t* hist = reinterpret_cast<int32_t*>(lds + TOK * Ep);
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
     const int t0 = blockIdx.x * TOK;
     for (int e = threadIdx.x; e < E; e += NT) hist[e] = 0;
 
-    if constexpr (sizeof(ST) == 2) {
-        const int r = lane & 15, g = lane >> 4;
-        const int ksteps = d >> 5;
-        const int per = (ksteps + NW - 1) / NW;
-        const int kb0 = min(ksteps, wave * per), kb1 = min(ksteps, kb0 + per);
-        const uint16_t* xrow[TF];
+    const int r = lane & 15, g = lane >> 4;
+    const float* xr = x + static_cast<size_t>(min(t0 + r, T - 1)) * d + g * 4;
+    const int steps = d >> 4, per = (steps + NW - 1) / NW;
+    const int s0 = min(steps, wave * per), s1 = min(steps, s0 + per);
+    const bool aligned = d % 4 == 0 && ((reinterpret_cast<uintptr_t>(x) | reinterpret_cast<uintptr_t>(wg)) & 15) == 0;
+    for (int ec = 0; ec < E; ec += 16) {
+        const float* wr = wg + static_cast<size_t>(min(ec + r, E - 1)) * d + g * 4;
+        f32x4 acc = f32x4{0.f, 0.f, 0.f, 0.f};
+        auto fma = [&](const f32x4 a, const f32x4 b) {
 #pragma unroll
-        for (int tf = 0; tf < TF; ++tf)
-            xrow[tf] = reinterpret_cast<const uint16_t*>(x) + static_cast<size_t>(min(t0 + tf * 16 + r, T - 1)) * d + g * 8;
-        for (int ec = 0; ec < E; ec += 16 * NF) {
-            const uint16_t* wrow[NF];
+            for (int j = 0; j < 4; ++j) acc = __builtin_amdgcn_mfma_f32_16x16x4f32(a[j], b[j], acc, 0, 0, 0);
+        };
+        auto walk = [&](auto vec) {
+            constexpr int PF = 8;
+            for (int s = s0; s < s1; s += PF) {
+                f32x4 a[PF], b[PF];
 #pragma unroll
-            for (int nf = 0; nf < NF; ++nf)
-                wrow[nf] = reinterpret_cast<const uint16_t*>(wg) + static_cast<size_t>(min(ec + nf * 16 + r, E - 1)) * d + g * 8;
-            f32x4 acc[NF][TF];
-#pragma unroll
-            for (int nf = 0; nf < NF; ++nf)
-#pragma unroll
-                for (int tf = 0; tf < TF; ++tf) acc[nf][tf] = f32x4{0.f, 0.f, 0.f, 0.f};
-            if (kb0 < kb1) {
-                constexpr int PF = 2;
-                bf16x8 a[PF][NF], b[PF][TF];
-                auto issue = [&](int slot, int kb) {
-#pragma unroll
-                    for (int tf = 0; tf < TF; ++tf) b[slot][tf] = *reinterpret_cast<const bf16x8*>(xrow[tf] + kb * 32);
-#pragma unroll
-                    for (int nf = 0; nf < NF; ++nf) a[slot][nf] = *reinterpret_cast<const bf16x8*>(wrow[nf] + kb * 32);
-                };
-                auto fma = [&](int slot) {
-#pragma unroll
-                    for (int nf = 0; nf < NF; ++nf)
-#pragma unroll
-                        for (int tf = 0; tf < TF; ++tf)
-                            acc[nf][tf] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[slot][nf], b[slot][tf], acc[nf][tf], 0, 0, 0);
-                };
-#pragma unroll
-                for (int p = 0; p < PF; ++p) issue(p, min(kb0 + p, kb1 - 1));
-                int kb = kb0;
-                for (; kb + 2 * PF <= kb1; kb += PF) {
-#pragma unroll
-                    for (int p = 0; p < PF; ++p) {
-                        fma(p);
-                        issue(p, kb + p + PF);
-                    }
-                }
-                if (kb + PF < kb1) {
-#pragma unroll
-                    for (int p = 0; p < PF; ++p) {
-                        fma(p);
-                        issue(p, min(kb + p + PF, kb1 - 1));
-                    }
-                    kb += PF;
+                for (int p = 0; p < PF; ++p) {
+                    const int k0 = min(s + p, s1 - 1) * 16;          // past the end: re-read, not used
+                    a[p] = load_k4<decltype(vec)::value>(wr + k0);
+                    b[p] = load_k4<decltype(vec)::value>(xr + k0);
                 }
 #pragma unroll
                 for (int p = 0; p < PF; ++p)
-                    if (kb + p < kb1) fma(p);
+                    if (s + p < s1) fma(a[p], b[p]);
             }
-            // Partial sums are added in wave order (deterministic).  The wavefront whose turn it is reads all
-            // the sums so far as 16-byte pieces (a lane's 4 experts of a token are adjacent), then writes them
-            // back: one LDS latency per turn.  Rows are padded to whole fragments, so nothing here depends on E.
-            f32x4 first[NF];                               // what the first wavefront starts from: the bias
+        };
+        if (aligned) walk(std::integral_constant<int, 4>{});
+        else walk(std::integral_constant<int, 1>{});
+        if ((d & 15) != 0 && wave == NW - 1)
+            fma(load_k4_tail(wr + steps * 16, (d & 15) - g * 4), load_k4_tail(xr + steps * 16, (d & 15) - g * 4));
+        for (int w = 0; w < NW; ++w) {
+            if (wave == w) {
+                f32x4* p = reinterpret_cast<f32x4*>(L + r * Ep + ec + g * 4);
+                f32x4 sofar = f32x4{0.f, 0.f, 0.f, 0.f};
+                if (w > 0) {
+                    sofar = *p;
+                } else if (bias != nullptr) {
 #pragma unroll
-            for (int nf = 0; nf < NF; ++nf) {
-                first[nf] = f32x4{0.f, 0.f, 0.f, 0.f};
-                if (bias != nullptr && wave == 0) {
-#pragma unroll
-                    for (int i = 0; i < 4; ++i) first[nf][i] = bias[min(ec + nf * 16 + g * 4 + i, E - 1)];
+                    for (int i = 0; i < 4; ++i) sofar[i] = bias[min(ec + g * 4 + i, E - 1)];
                 }
+                *p = acc + sofar;
             }
-            for (int w = 0; w < NW; ++w) {
-                if (wave == w) {
-                    f32x4 sofar[NF][TF];
-#pragma unroll
-                    for (int nf = 0; nf < NF; ++nf)
-#pragma unroll
-                        for (int tf = 0; tf < TF; ++tf) {
-                            const f32x4* p = reinterpret_cast<const f32x4*>(L + (tf * 16 + r) * Ep + ec + nf * 16 + g * 4);
-                            sofar[nf][tf] = (w == 0) ? first[nf] : *p;
-                        }
-#pragma unroll
-                    for (int nf = 0; nf < NF; ++nf)
-#pragma unroll
-                        for (int tf = 0; tf < TF; ++tf) {
-                            f32x4* p = reinterpret_cast<f32x4*>(L + (tf * 16 + r) * Ep + ec + nf * 16 + g * 4);
-                            *p = acc[nf][tf] + sofar[nf][tf];
-                        }
-                }
-                __syncthreads();
-            }
-        }
-    } else {
-        // the same with the fp32 matrix instruction, 16 k per step (operands as in ffn_f32.hip); the wavefronts split
-        // the contraction and meet in LDS in wave order
-        static_assert(sizeof(ST) == 2 || (TF == 1 && NF == 1), "fp32 routing takes one fragment of each operand");
-        const int r = lane & 15, g = lane >> 4;
-        const float* xr = reinterpret_cast<const float*>(x) + static_cast<size_t>(min(t0 + r, T - 1)) * d + g * 4;
-        const int steps = d >> 4, per = (steps + NW - 1) / NW;
-        const int s0 = min(steps, wave * per), s1 = min(steps, s0 + per);
-        const bool aligned = d % 4 == 0 && ((reinterpret_cast<uintptr_t>(x) | reinterpret_cast<uintptr_t>(wg)) & 15) == 0;
-        for (int ec = 0; ec < E; ec += 16) {
-            const float* wr = reinterpret_cast<const float*>(wg) + static_cast<size_t>(min(ec + r, E - 1)) * d + g * 4;
-            f32x4 acc = f32x4{0.f, 0.f, 0.f, 0.f};
-            auto fma = [&](const f32x4 a, const f32x4 b) {
-#pragma unroll
-                for (int j = 0; j < 4; ++j) acc = __builtin_amdgcn_mfma_f32_16x16x4f32(a[j], b[j], acc, 0, 0, 0);
-            };
-            auto walk = [&](auto vec) {
-                constexpr int PF = 8;
-                for (int s = s0; s < s1; s += PF) {
-                    f32x4 a[PF], b[PF];
-#pragma unroll
-                    for (int p = 0; p < PF; ++p) {
-                        const int k0 = min(s + p, s1 - 1) * 16;          // past the end: re-read, not used
-                        a[p] = load_k4<decltype(vec)::value>(wr + k0);
-                        b[p] = load_k4<decltype(vec)::value>(xr + k0);
-                    }
-#pragma unroll
-                    for (int p = 0; p < PF; ++p)
-                        if (s + p < s1) fma(a[p], b[p]);
-                }
-            };
-            if (aligned) walk(std::integral_constant<int, 4>{});
-            else walk(std::integral_constant<int, 1>{});
-            if ((d & 15) != 0 && wave == NW - 1)
-                fma(load_k4_tail(wr + steps * 16, (d & 15) - g * 4), load_k4_tail(xr + steps * 16, (d & 15) - g * 4));
-            for (int w = 0; w < NW; ++w) {
-                if (wave == w) {
-                    f32x4* p = reinterpret_cast<f32x4*>(L + r * Ep + ec + g * 4);
-                    f32x4 sofar = f32x4{0.f, 0.f, 0.f, 0.f};
-                    if (w > 0) {
-                        sofar = *p;
-                    } else if (bias != nullptr) {
-#pragma unroll
-                        for (int i = 0; i < 4; ++i) sofar[i] = bias[min(ec + g * 4 + i, E - 1)];
-                    }
-                    *p = acc + sofar;
-                }
-                __syncthreads();
-            }
+            __syncthreads();
         }
     }
 
@@ -380,7 +416,7 @@ __device__ __forceinline__ void sum_chunks(const int32_t* __restrict__ chunk_his
 }
 
 // counts, offsets, hot mask and tile lists from the token counts, by a block of 1024 threads, thread e owning expert e
-// with `mine` tokens.  `cnt` (MOE_MAX_E ints) and `scan` (48 ints) are LDS scratch.  Any output pointer may be NULL.
+// with `mine` tokens.  `cnt` (2 * MOE_MAX_E ints) and `scan` (48 ints) are LDS scratch.  Any output pointer may be NULL.
 // Returns the expert's first row.
 __device__ __forceinline__ int finalize_outputs(int mine, int E, int32_t* __restrict__ counts, int32_t* __restrict__ offsets,
                                                 int H, uint8_t* __restrict__ hot_mask, const uint8_t* __restrict__ mask_in,
@@ -388,11 +424,22 @@ __device__ __forceinline__ int finalize_outputs(int mine, int E, int32_t* __rest
     const int e = threadIdx.x;
     bool on = e < E;
     if (H >= 0) {                                          // uniform: rank by count, ties by lowest index
+        // The ranks are counted by the whole block, group q of Ew threads comparing with its share of the experts (one
+        // thread per expert reads E counts one after the other: 3 us of a step at 128 experts).
+        const int Ew = min(1024, (E + 63) & ~63), ngrp = 1024 / Ew;
+        const int q = threadIdx.x / Ew, ex = threadIdx.x - q * Ew;
         if (e < E) cnt[e] = mine;
+        __syncthreads();
+        if (q < ngrp && ex < E) {
+            const int my = cnt[ex], per = (E + ngrp - 1) / ngrp;
+            int rank = 0;
+            for (int o = q * per; o < min(E, (q + 1) * per); ++o) rank += (cnt[o] > my || (cnt[o] == my && o < ex)) ? 1 : 0;
+            cnt[MOE_MAX_E + q * Ew + ex] = rank;
+        }
         __syncthreads();
         if (e < E) {
             int rank = 0;
-            for (int o = 0; o < E; ++o) rank += (cnt[o] > mine || (cnt[o] == mine && o < e)) ? 1 : 0;
+            for (int o = 0; o < ngrp; ++o) rank += cnt[MOE_MAX_E + o * Ew + e];
             on = rank < H;
             if (hot_mask) hot_mask[e] = on ? 1 : 0;
         }
@@ -570,79 +617,60 @@ hipError_t launch_mask_out(const uint8_t* mask_or_null, uint8_t* dst, int E, hip
     return hipGetLastError();
 }
 
-// chunk size (tokens per routing block) and wavefronts per block, from the shape alone
-#ifndef ROUTE_MID_NW
-#define ROUTE_MID_NW 4     // wavefronts per block of the 16-token variant (measured: 4 < 2 < 8 < 1 < 16 in time)
-#endif
-#ifndef ROUTE_T4K_NW
-#define ROUTE_T4K_NW 4      // wavefronts per block of the 32-token variant
-#endif
-#ifndef ROUTE_BIG_NW
-#define ROUTE_BIG_NW 4     // wavefronts per block (contraction slices) of the 64-token variant
-#endif
-struct RouteCfg { int tok, nw, nf; };
+// Tokens per routing block and fragments of experts taken at a time, from the shape alone.  More tokens per block read the
+// gate matrix fewer times, as long as the chip is one round of blocks: with 313 blocks of 16 tokens on 256 CUs, 5003 tokens
+// took 42 us, with 157 of 32 tokens 31 us (128 experts, d = 2048, an earlier form of the kernel).
+struct RouteCfg { int tok, nf; };
 static RouteCfg route_cfg(const moe_shape& s) {
-    RouteCfg c{16, 4, 1};
+    RouteCfg c{16, 1};
     if (s.dtype != MOE_BF16) return c;
-    c.nf = s.E >= 113 ? 8 : (s.E >= 49 ? 4 : (s.E >= 17 ? 2 : 1));
-    if (route_is_split(s)) { c.tok = 16; c.nw = 8; return c; }   // the split path works in chunks of 16 tokens
-    if (s.T <= 64) { c.tok = 16; c.nw = 16; c.nf = c.nf > 4 ? 4 : c.nf; }   // few blocks: split the contraction 16 ways
-                                                                            // (128 registers per lane: 4 fragments at a time)
-    // More tokens per block reuse every gate-weight fragment for more token fragments, but only as long as
-    // there is still a block for every CU (measured, 128 experts: 4096 tokens take 13.9 us in 256 blocks of 16
-    // and 17.4 us in 128 blocks of 32; 16384 tokens 39 us in 256 blocks of 64 and 47 us in 512 blocks of 32).
-    else if (s.T >= 64 * device_cu_count() && s.E <= 256) { c.tok = 64; c.nw = ROUTE_BIG_NW; }
-    else if (s.T >= 32 * device_cu_count() && s.E <= 256) { c.tok = 32; c.nw = ROUTE_T4K_NW; }
-    else { c.tok = 16; c.nw = ROUTE_MID_NW; }
+    c.nf = s.E > 64 ? 8 : 4;
+    if (route_is_split(s)) return c;                       // the split path works in chunks of 16 tokens
+    if (s.T > 32 * device_cu_count() && s.E <= 128) c.tok = 64;
+    else if (s.T > 16 * device_cu_count() && s.E <= 256) c.tok = 32;
     return c;
 }
 
 int route_chunk_tokens(const moe_shape& s) { return route_cfg(s).tok; }
 
-// Most dynamic LDS a routing kernel asks for: 16 tokens x (1024 experts padded to whole groups of fragments)
-// logits plus the histogram is 78 KiB; 64 tokens x 256 experts is 67 KiB.  configure_route_kernels raises every
-// routing kernel's limit to this once.
-constexpr size_t kRouteLdsMax = 96 * 1024;
+// Most dynamic LDS a routing kernel asks for: a ring of 4 stages of 160 rows (80 KiB) next to the logits of 16 tokens x
+// 1024 experts and the histogram.
+constexpr size_t kRouteLdsMax = kLdsPerCu;
 
-template <typename ST, int TF, int NW, int NF>
-static hipError_t configure_route() {
-    return hipFuncSetAttribute(reinterpret_cast<const void*>(route_fused_kernel<ST, TF, NW, NF>),
-                               hipFuncAttributeMaxDynamicSharedMemorySize, static_cast<int>(kRouteLdsMax));
-}
+template <typename ST>
+using RouteKernel = void (*)(const ST*, const ST*, const float*, int32_t*, float*, float*, int32_t*, int, int, int, int, int);
 
-template <typename ST, int TF, int NW, int NF>
-static hipError_t launch_route_inst(const moe_shape& s, const void* x, const void* w_gate, const float* bias,
-                                    int32_t* idx, float* gate, float* margin, int32_t* chunk_hist, hipStream_t st) {
-    constexpr int tok = 16 * TF;
+template <typename ST>
+static hipError_t launch_route_kernel(RouteKernel<ST> kern, int tok, int nf, size_t ring, const moe_shape& s, const void* x,
+                                      const void* w_gate, const float* bias, int32_t* idx, float* gate, float* margin,
+                                      int32_t* chunk_hist, hipStream_t st) {
     const unsigned grid = static_cast<unsigned>((s.T + tok - 1) / tok);
-    const size_t lds = static_cast<size_t>(tok) * route_row_stride(s.E, NF) * 4 + static_cast<size_t>(s.E) * 4;
-    auto kern = route_fused_kernel<ST, TF, NW, NF>;
+    const size_t lds = ring + static_cast<size_t>(tok) * route_row_stride(s.E, nf) * 4 + static_cast<size_t>(s.E) * 4;
     if (lds > kRouteLdsMax) return hipErrorInvalidValue;     // cannot happen for E <= MOE_MAX_E (see kRouteLdsMax)
-    hipLaunchKernelGGL(kern, dim3(grid), dim3(NW * 64), lds, st, static_cast<const ST*>(x),
+    hipLaunchKernelGGL(kern, dim3(grid), dim3(kRouteWaves * 64), lds, st, static_cast<const ST*>(x),
                        static_cast<const ST*>(w_gate), bias, idx, gate, margin, chunk_hist, s.T, s.d_model, s.E, s.k,
                        s.renormalize);
     return hipGetLastError();
 }
 
-template <int TF, int NW>
-static hipError_t launch_route_nf(int nf, const moe_shape& s, const void* x, const void* w_gate, const float* bias,
-                                  int32_t* idx, float* gate, float* margin, int32_t* chunk_hist, hipStream_t st) {
-    switch (nf) {
-        case 8:
-            if constexpr (NW <= 8)
-                return launch_route_inst<uint16_t, TF, NW, 8>(s, x, w_gate, bias, idx, gate, margin, chunk_hist, st);
-            [[fallthrough]];
-        case 4: return launch_route_inst<uint16_t, TF, NW, 4>(s, x, w_gate, bias, idx, gate, margin, chunk_hist, st);
-        case 2: return launch_route_inst<uint16_t, TF, NW, 2>(s, x, w_gate, bias, idx, gate, margin, chunk_hist, st);
-        default: return launch_route_inst<uint16_t, TF, NW, 1>(s, x, w_gate, bias, idx, gate, margin, chunk_hist, st);
-    }
+template <int TF, int NF>
+static hipError_t launch_route_bf16(const moe_shape& s, const void* x, const void* w_gate, const float* bias, int32_t* idx,
+                                    float* gate, float* margin, int32_t* chunk_hist, hipStream_t st) {
+    return launch_route_kernel<uint16_t>(route_bf16_kernel<TF, NF>, 16 * TF, NF, RouteRing<TF, NF>::kBytes, s, x, w_gate, bias,
+                                         idx, gate, margin, chunk_hist, st);
+}
+
+template <typename Kernel>
+static hipError_t configure_route(Kernel kern) {
+    return hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize,
+                               static_cast<int>(kRouteLdsMax));
 }
 
 // Few tokens (a decode step): the gate product is one skinny GEMM whose cost is reading the gate weights, and
 // one block per 16 tokens would leave that to one or two CUs.  gate_partial_kernel cuts it into
 // (16 experts) x (1 / kGateSplit of the contraction) x (16 tokens) pieces, one wavefront each, which leave fp32
 // partial logits in the workspace; route_topk_kernel adds the slices in order (plus the bias) and does the
-// softmax / top-k / chunk histogram per 16 tokens as route_fused_kernel does.
+// softmax / top-k / chunk histogram per 16 tokens as route_bf16_kernel does.
 __global__ __launch_bounds__(64) void gate_partial_kernel(const uint16_t* __restrict__ x,
                                                           const uint16_t* __restrict__ wg,
                                                           float* __restrict__ part, int T, int d, int E, int Tpad) {
@@ -750,7 +778,7 @@ __global__ __launch_bounds__(1024) void route_topk_finalize_kernel(const float* 
     float* L = lds;
     int32_t* hist = reinterpret_cast<int32_t*>(lds + 64 * Ep);
     int32_t* experts = hist + 4 * E;
-    __shared__ int32_t cnt[MOE_MAX_E];
+    __shared__ int32_t cnt[2 * MOE_MAX_E];
     __shared__ int32_t scan[48];
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
     const int nchunks = Tpad >> 4;                         // <= 4
@@ -809,27 +837,16 @@ __global__ __launch_bounds__(1024) void route_topk_finalize_kernel(const float* 
 
 constexpr size_t kTopkFinalizeLdsMax = static_cast<size_t>(64) * (kTopkFinalizeMaxE + 1) * 4 + 4 * kTopkFinalizeMaxE * 4 + 64 * MOE_MAX_K * 4;
 
-template <int TF, int NW>
-static hipError_t configure_route_nf() {
-    hipError_t e;
-    if constexpr (NW <= 8) {
-        if ((e = configure_route<uint16_t, TF, NW, 8>()) != hipSuccess) return e;
-    }
-    if ((e = configure_route<uint16_t, TF, NW, 4>()) != hipSuccess) return e;
-    if ((e = configure_route<uint16_t, TF, NW, 2>()) != hipSuccess) return e;
-    return configure_route<uint16_t, TF, NW, 1>();
-}
-
 hipError_t configure_route_kernels(int) {
     hipError_t e;
-    if ((e = configure_route<float, 1, 4, 1>()) != hipSuccess) return e;
-    if ((e = configure_route_nf<1, 16>()) != hipSuccess) return e;
-    if ((e = configure_route_nf<4, ROUTE_BIG_NW>()) != hipSuccess) return e;
-    if ((e = configure_route_nf<2, ROUTE_T4K_NW>()) != hipSuccess) return e;
-    if ((e = configure_route_nf<1, ROUTE_MID_NW>()) != hipSuccess) return e;
-    if ((e = hipFuncSetAttribute(reinterpret_cast<const void*>(route_topk_kernel),
-                                 hipFuncAttributeMaxDynamicSharedMemorySize, static_cast<int>(kRouteLdsMax))) != hipSuccess)
-        return e;
+    if ((e = configure_route(route_f32_kernel)) != hipSuccess) return e;
+    if ((e = configure_route(route_bf16_kernel<1, 4>)) != hipSuccess) return e;
+    if ((e = configure_route(route_bf16_kernel<2, 4>)) != hipSuccess) return e;
+    if ((e = configure_route(route_bf16_kernel<4, 4>)) != hipSuccess) return e;
+    if ((e = configure_route(route_bf16_kernel<1, 8>)) != hipSuccess) return e;
+    if ((e = configure_route(route_bf16_kernel<2, 8>)) != hipSuccess) return e;
+    if ((e = configure_route(route_bf16_kernel<4, 8>)) != hipSuccess) return e;
+    if ((e = configure_route(route_topk_kernel)) != hipSuccess) return e;
     return hipFuncSetAttribute(reinterpret_cast<const void*>(route_topk_finalize_kernel),
                                hipFuncAttributeMaxDynamicSharedMemorySize, static_cast<int>(kTopkFinalizeLdsMax));
 }
@@ -853,14 +870,18 @@ hipError_t launch_route_fused(const moe_shape& s, const void* x, const void* w_g
                               int32_t* idx, float* gate, float* margin, int32_t* chunk_hist, float* gate_part_ws,
                               hipStream_t st) {
     if (s.dtype != MOE_BF16)
-        return launch_route_inst<float, 1, 4, 1>(s, x, w_gate, bias, idx, gate, margin, chunk_hist, st);
+        return launch_route_kernel<float>(route_f32_kernel, 16, 1, 0, s, x, w_gate, bias, idx, gate, margin, chunk_hist, st);
     if (route_is_split(s) && gate_part_ws != nullptr)
         return launch_route_small(s, x, w_gate, bias, idx, gate, margin, chunk_hist, gate_part_ws, st);
     const RouteCfg c = route_cfg(s);
-    if (c.nw == 16) return launch_route_nf<1, 16>(c.nf, s, x, w_gate, bias, idx, gate, margin, chunk_hist, st);
-    if (c.tok == 64) return launch_route_nf<4, ROUTE_BIG_NW>(c.nf, s, x, w_gate, bias, idx, gate, margin, chunk_hist, st);
-    if (c.tok == 32) return launch_route_nf<2, ROUTE_T4K_NW>(c.nf, s, x, w_gate, bias, idx, gate, margin, chunk_hist, st);
-    return launch_route_nf<1, ROUTE_MID_NW>(c.nf, s, x, w_gate, bias, idx, gate, margin, chunk_hist, st);
+    switch (c.tok + c.nf) {
+        case 64 + 8: return launch_route_bf16<4, 8>(s, x, w_gate, bias, idx, gate, margin, chunk_hist, st);
+        case 32 + 8: return launch_route_bf16<2, 8>(s, x, w_gate, bias, idx, gate, margin, chunk_hist, st);
+        case 16 + 8: return launch_route_bf16<1, 8>(s, x, w_gate, bias, idx, gate, margin, chunk_hist, st);
+        case 64 + 4: return launch_route_bf16<4, 4>(s, x, w_gate, bias, idx, gate, margin, chunk_hist, st);
+        case 32 + 4: return launch_route_bf16<2, 4>(s, x, w_gate, bias, idx, gate, margin, chunk_hist, st);
+        default: return launch_route_bf16<1, 4>(s, x, w_gate, bias, idx, gate, margin, chunk_hist, st);
+    }
 }
 
 // Histograms of up to this many ints are added up by every block of dispatch_kernel; larger ones would cost the blocks
