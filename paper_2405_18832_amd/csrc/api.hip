@@ -108,10 +108,12 @@ int32_t moe_tiled_kernel_min_rows(const moe_shape* shape, const int32_t* rows_ho
     (void)ensure_ready();                                   // the device's CU count; a default stands in without one
     const TileLists l = ffn_tile_lists(*shape, nullptr, nullptr, nullptr, nullptr, nullptr);
     if (l.big_min <= 0) return 0;
-    int big_tiles = 0;
-    for (int e = 0; e < shape->E; ++e)
-        if (rows_host[e] >= l.big_min) big_tiles += (rows_host[e] + kBigTileRows - 1) / kBigTileRows;
-    return tiled_min_rows(big_tiles, l.small_rows, l.join_tiles);
+    int at_min = 0, joined = 0;
+    for (int e = 0; e < shape->E; ++e) {
+        at_min += big_tiles_at_min(rows_host[e], l);
+        joined += half_tiles_joined(rows_host[e], l);
+    }
+    return tiled_min_rows(at_min, l.join_tiles, joined, l.join_half_tiles);
 }
 
 void moe_set_profile_events(void* const* events) {

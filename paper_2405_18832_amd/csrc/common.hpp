@@ -60,12 +60,19 @@ constexpr int kHalfTileRows = 128;
 constexpr int kHalfCount = 4;           // int of the `ntiles` array that holds their number
 // Experts between one streaming tile and kBigMinRows rows would have their weights streamed once per
 // streaming tile; as one mostly empty tile of the tiled kernel they cost about what a single pass over their
-// weights costs -- as long as the tiled kernel has whole rounds of units to run anyway, which hide the one
-// more unit per column tile.  They join the large experts when the tiles of the experts with kBigMinRows rows
-// already number `join_tiles` (the host's figure: one full round of units in the narrower product); with
-// fewer, an under-filled tiled kernel would only get longer.
-inline __host__ __device__ int tiled_min_rows(int big_tiles_at_min, int small_rows, int join_tiles) {
-    return (join_tiles > 0 && big_tiles_at_min >= join_tiles) ? small_rows + 1 : kBigMinRows;
+// weights costs -- where the tiled kernel runs anyway and hides the additional units:
+//  - with whole rounds of units, i.e. when the tiles of the experts with kBigMinRows rows already number `join_tiles`
+//    (the host's figure: one full round of units in the narrower product);
+//  - in half-sized units, as long as all of them, `half_tiles_joined` tiles of them and the experts that are large in any
+//    case, are at most one round in the wider product (`join_half_tiles`): then they occupy CUs that would be idle.
+//    (Experts of 327, 112, 85, 71 and 12 times at most 45 rows, 1024 x 4096: streaming 41.8 + 39.8 -> 23.8 + 25.5 us, tiled
+//    15.2 + 14.2 -> 19.6 + 18.6 us.)
+// Else an under-filled tiled kernel would only get longer.
+constexpr int kJoinMinRows = 65;
+inline __host__ __device__ int tiled_min_rows(int big_tiles_at_min, int join_tiles, int half_tiles_joined, int join_half_tiles) {
+    if (join_tiles > 0 && big_tiles_at_min >= join_tiles) return kJoinMinRows;
+    if (big_tiles_at_min > 0 && half_tiles_joined <= join_half_tiles) return kJoinMinRows;
+    return kBigMinRows;
 }
 // The LDS-tiled kernel cuts the units of its last, partly filled round along K; the parts leave fp32
 // partial tiles (kBigTileRows x 256) in the workspace and are handed out through a counter.
@@ -186,6 +193,7 @@ struct TileLists {
     int small_rows;        // rows per small tile
     int big_min;           // experts with >= big_min rows are "big"; 0 = none
     int join_tiles;        // tiles of big experts from which the mid-sized experts join them (tiled_min_rows); 0 = never
+    int join_half_tiles;   // half-sized tiles, with the mid-sized experts', up to which they do
 };
 
 #ifdef __HIPCC__
@@ -280,9 +288,12 @@ __device__ __forceinline__ void block_scan_1024(const int (&v)[N], int (&incl)[N
     }
 }
 
-// tiles of the large experts' kernel that an expert of m rows contributes to the sum tiled_min_rows is asked with
-__device__ __forceinline__ int big_tiles_at_min(int m, const TileLists& tl) {
+// what an expert of m rows contributes to the two sums that tiled_min_rows is asked with
+inline __host__ __device__ int big_tiles_at_min(int m, const TileLists& tl) {
     return tl.big_min > 0 && m >= tl.big_min ? (m + kBigTileRows - 1) / kBigTileRows : 0;
+}
+inline __host__ __device__ int half_tiles_joined(int m, const TileLists& tl) {
+    return tl.big_min > 0 && m >= kJoinMinRows ? (m + kHalfTileRows - 1) / kHalfTileRows : 0;
 }
 
 // The tiles of one expert (row0, m rows), `rows` rows each, to out[0 ...].  Called by whole wavefronts, a lane per
@@ -306,10 +317,11 @@ __device__ __forceinline__ void write_tiles(Tile* __restrict__ out, int e, int r
 }
 
 // Called by all 1024 threads of a block, thread e owning expert e (row0, m rows; m = 0 when the
-// expert is empty or masked out).  `big_at_min`: the block's sum of big_tiles_at_min.  `tmp` is an LDS array of
-// >= 48 ints.
-__device__ __forceinline__ void emit_tiles(int e, int row0, int m, int big_at_min, const TileLists tl, int32_t* tmp) {
-    const bool big = tl.big_min > 0 && m >= tiled_min_rows(big_at_min, tl.small_rows, tl.join_tiles);
+// expert is empty or masked out).  `big_at_min`, `half_joined`: the block's sums of big_tiles_at_min and half_tiles_joined.
+// `tmp` is an LDS array of >= 48 ints.
+__device__ __forceinline__ void emit_tiles(int e, int row0, int m, int big_at_min, int half_joined, const TileLists tl,
+                                           int32_t* tmp) {
+    const bool big = tl.big_min > 0 && m >= tiled_min_rows(big_at_min, tl.join_tiles, half_joined, tl.join_half_tiles);
     const int nt[3] = {big ? 0 : (m + tl.small_rows - 1) / tl.small_rows, big ? (m + kBigTileRows - 1) / kBigTileRows : 0,
                        big ? (m + kHalfTileRows - 1) / kHalfTileRows : 0};
     int incl[3], total[3];

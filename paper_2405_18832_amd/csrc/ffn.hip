@@ -72,10 +72,10 @@ __global__ __launch_bounds__(1024) void build_tiles_kernel(const int32_t* __rest
     // With every count >= 0 the segments are disjoint and their sum is at most A, which is what the capacity of
     // the tile lists assumes.
     if (__syncthreads_or(bad ? 1 : 0)) m = 0;
-    const int at_min[1] = {big_tiles_at_min(m, lists)};
-    int incl[1], total[1];
-    block_scan_1024(at_min, incl, total, scan);
-    emit_tiles(e, row0, m, total[0], lists, scan);
+    const int v[2] = {big_tiles_at_min(m, lists), half_tiles_joined(m, lists)};
+    int incl[2], total[2];
+    block_scan_1024(v, incl, total, scan);
+    emit_tiles(e, row0, m, total[0], total[1], lists, scan);
 }
 
 // ---------------------------------------------------------------------------
@@ -681,6 +681,7 @@ TileLists ffn_tile_lists(const moe_shape& s, Tile* small_ws, Tile* big_ws, Tile*
     l.big_min = (s.dtype == MOE_BF16 && s.T >= kBigMinRows) ? kBigMinRows : 0;
     l.partials = l.big_min > 0 ? partials_ws : nullptr;
     l.join_tiles = l.big_min > 0 ? tiled_join_tiles(s) : 0;
+    l.join_half_tiles = tile_product_grid() / ((std::max(s.d_model, s.d_ff) + FineUnits::kCols - 1) / FineUnits::kCols);
     return l;
 }
 

@@ -446,8 +446,8 @@ __device__ __forceinline__ int finalize_outputs(int mine, int E, int32_t* __rest
     } else if (mask_in != nullptr && e < E) {
         on = mask_in[e] != 0;
     }
-    const int v[2] = {mine, on ? big_tiles_at_min(mine, lists) : 0};
-    int incl[2], total[2];
+    const int v[3] = {mine, on ? big_tiles_at_min(mine, lists) : 0, on ? half_tiles_joined(mine, lists) : 0};
+    int incl[3], total[3];
     block_scan_1024(v, incl, total, scan);
     const int row0 = incl[0] - mine;
     if (e < E) {
@@ -455,7 +455,7 @@ __device__ __forceinline__ int finalize_outputs(int mine, int E, int32_t* __rest
         if (offsets) offsets[e] = row0;
     }
     if (e == 0 && offsets) offsets[E] = total[0];
-    if (want_tiles) emit_tiles(e, row0, on ? mine : 0, total[1], lists, scan);     // uniform: a kernel argument
+    if (want_tiles) emit_tiles(e, row0, on ? mine : 0, total[1], total[2], lists, scan);     // uniform: a kernel argument
     return row0;
 }
 
@@ -904,7 +904,7 @@ static hipError_t launch_dispatch_pw(const int32_t* chunk_hist, int nchunks, int
 static hipError_t launch_dispatch(int32_t* chunk_hist, int nchunks, int E, const int32_t* offsets_in, bool finalize,
                                   int32_t* counts, int32_t* offsets, int H, uint8_t* hot_mask, const uint8_t* mask_in,
                                   const TileLists* lists, const PlaceArgs* place, hipStream_t st) {
-    const TileLists none{nullptr, nullptr, nullptr, nullptr, nullptr, 16, 0, 0};
+    const TileLists none{nullptr, nullptr, nullptr, nullptr, nullptr, 16, 0, 0, 0};
     const PlaceArgs no_place{nullptr, nullptr, nullptr, nullptr, 0, 1, 1};
     const TileLists& tl = lists ? *lists : none;
     const bool tiles = lists != nullptr;
@@ -950,7 +950,7 @@ hipError_t launch_route_finalize(const moe_shape& s, const void* x, const void* 
             if (err != hipSuccess) return err;
             // at most kTopkFinalizeLdsMax: the limit configure_route_kernels has raised this kernel to
             const size_t lds = static_cast<size_t>(64) * (s.E + 1) * 4 + static_cast<size_t>(4) * s.E * 4 + static_cast<size_t>(64) * s.k * 4;
-            const TileLists none{nullptr, nullptr, nullptr, nullptr, nullptr, 16, 0, 0};
+            const TileLists none{nullptr, nullptr, nullptr, nullptr, nullptr, 16, 0, 0, 0};
             const PlaceArgs no_place{nullptr, nullptr, nullptr, nullptr, 0, 1, 1};
             hipLaunchKernelGGL(route_topk_finalize_kernel, dim3(1), dim3(1024), lds, st, gate_part_ws, bias, idx, gate,
                                margin, s.T, s.E, s.k, s.renormalize, Tpad, counts, offsets, H, hot_mask, mask_in,
