@@ -321,16 +321,25 @@ __device__ __forceinline__ void write_tiles(Tile* __restrict__ out, int e, int r
 // `tmp` is an LDS array of >= 48 ints.
 __device__ __forceinline__ void emit_tiles(int e, int row0, int m, int big_at_min, int half_joined, const TileLists tl,
                                            int32_t* tmp) {
-    const bool big = tl.big_min > 0 && m >= tiled_min_rows(big_at_min, tl.join_tiles, half_joined, tl.join_half_tiles);
+    if (tl.big_min <= 0) {                                 // no large experts possible: one list (uniform)
+        const int nt[1] = {(m + tl.small_rows - 1) / tl.small_rows};
+        int incl[1], total[1];
+        block_scan_1024(nt, incl, total, tmp);
+        write_tiles(tl.small_tiles + incl[0] - nt[0], e, row0, m, tl.small_rows, nt[0]);
+        if (e == 0) {
+            tl.ntiles[0] = total[0];
+            tl.ntiles[1] = tl.ntiles[kHalfCount] = 0;
+        }
+        return;
+    }
+    const bool big = m >= tiled_min_rows(big_at_min, tl.join_tiles, half_joined, tl.join_half_tiles);
     const int nt[3] = {big ? 0 : (m + tl.small_rows - 1) / tl.small_rows, big ? (m + kBigTileRows - 1) / kBigTileRows : 0,
                        big ? (m + kHalfTileRows - 1) / kHalfTileRows : 0};
     int incl[3], total[3];
     block_scan_1024(nt, incl, total, tmp);
     write_tiles(tl.small_tiles + incl[0] - nt[0], e, row0, m, tl.small_rows, nt[0]);
-    if (tl.big_min > 0) {
-        write_tiles(tl.big_tiles + incl[1] - nt[1], e, row0, m, kBigTileRows, nt[1]);
-        write_tiles(tl.half_tiles + incl[2] - nt[2], e, row0, m, kHalfTileRows, nt[2]);
-    }
+    write_tiles(tl.big_tiles + incl[1] - nt[1], e, row0, m, kBigTileRows, nt[1]);
+    write_tiles(tl.half_tiles + incl[2] - nt[2], e, row0, m, kHalfTileRows, nt[2]);
     if (e == 0) {
         tl.ntiles[0] = total[0];
         tl.ntiles[1] = total[1];

@@ -446,16 +446,28 @@ __device__ __forceinline__ int finalize_outputs(int mine, int E, int32_t* __rest
     } else if (mask_in != nullptr && e < E) {
         on = mask_in[e] != 0;
     }
-    const int v[3] = {mine, on ? big_tiles_at_min(mine, lists) : 0, on ? half_tiles_joined(mine, lists) : 0};
-    int incl[3], total[3];
-    block_scan_1024(v, incl, total, scan);
-    const int row0 = incl[0] - mine;
+    int row0, rows, at_min = 0, joined = 0;
+    if (want_tiles && lists.big_min > 0) {                 // uniform
+        const int v[3] = {mine, on ? big_tiles_at_min(mine, lists) : 0, on ? half_tiles_joined(mine, lists) : 0};
+        int incl[3], total[3];
+        block_scan_1024(v, incl, total, scan);
+        row0 = incl[0] - mine;
+        rows = total[0];
+        at_min = total[1];
+        joined = total[2];
+    } else {
+        const int v[1] = {mine};
+        int incl[1], total[1];
+        block_scan_1024(v, incl, total, scan);
+        row0 = incl[0] - mine;
+        rows = total[0];
+    }
     if (e < E) {
         if (counts) counts[e] = mine;
         if (offsets) offsets[e] = row0;
     }
-    if (e == 0 && offsets) offsets[E] = total[0];
-    if (want_tiles) emit_tiles(e, row0, on ? mine : 0, total[1], total[2], lists, scan);     // uniform: a kernel argument
+    if (e == 0 && offsets) offsets[E] = rows;
+    if (want_tiles) emit_tiles(e, row0, on ? mine : 0, at_min, joined, lists, scan);     // uniform: a kernel argument
     return row0;
 }
 
@@ -701,7 +713,7 @@ __global__ __launch_bounds__(64) void gate_partial_kernel(const uint16_t* __rest
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
         const int e = nb * 16 + g * 4 + i;
-        if (t < Tpad && e < E) dst[e] = acc[i];
+        if (t < T && e < E) dst[e] = acc[i];               // rows of padding are not read again
     }
 }
 
@@ -783,13 +795,14 @@ __global__ __launch_bounds__(1024) void route_topk_finalize_kernel(const float* 
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
     const int nchunks = Tpad >> 4;                         // <= 4
     for (int i = threadIdx.x; i < 4 * E; i += 1024) hist[i] = 0;
-    // 4 logits per thread and pass, their 4 * kGateSplit partial sums loaded before any is added
-    for (int i0 = threadIdx.x; i0 < Tpad * E; i0 += 4 * 1024) {
+    // 4 logits per thread and pass, their 4 * kGateSplit partial sums loaded before any is added (of the T tokens only:
+    // at one token the 16 padded rows were 64 KB for a single CU)
+    for (int i0 = threadIdx.x; i0 < T * E; i0 += 4 * 1024) {
         float p[4][kGateSplit];
         float b[4];
 #pragma unroll
         for (int u = 0; u < 4; ++u) {
-            const int i = min(i0 + u * 1024, Tpad * E - 1);   // past the end: re-read, not stored
+            const int i = min(i0 + u * 1024, T * E - 1);      // past the end: re-read, not stored
             const int tl = i / E, e = i - tl * E;
             b[u] = bias ? bias[e] : 0.f;
 #pragma unroll
@@ -798,7 +811,7 @@ __global__ __launch_bounds__(1024) void route_topk_finalize_kernel(const float* 
 #pragma unroll
         for (int u = 0; u < 4; ++u) {
             const int i = i0 + u * 1024;
-            if (i >= Tpad * E) break;
+            if (i >= T * E) break;
             const int tl = i / E, e = i - tl * E;
             float sum = b[u];
 #pragma unroll
