@@ -16,7 +16,7 @@
 
 namespace moe {
 
-constexpr int kMaxRounds = MOE_MAX_K + 1;
+static_assert(MOE_MAX_K + 1 <= 16, "a token's winners sit in the 16 lanes of its group");
 
 // Value of the lane n places away inside the lane's row of 16 (a DPP row rotation, no LDS traffic).  Four
 // steps with n = 8, 4, 2, 1 leave every lane of the row with the reduction over the row; for sums the
@@ -46,8 +46,8 @@ __device__ __forceinline__ void topk_row(float* __restrict__ row, int E, int k, 
                                          float* __restrict__ margin_out, int32_t* __restrict__ hist,
                                          int32_t* __restrict__ idx_lds) {
     const float NEG = -__builtin_huge_valf();
-    float sel_v[kMaxRounds];
-    int sel_i[kMaxRounds];
+    float sel_v = NEG;                    // lane j of the group keeps the winner of round j
+    int sel_i = 0;
     const int rounds = min(k + (margin_out != nullptr ? 1 : 0), E);   // the margin needs one more winner
     float vmax = 0.f, denom = 1.f;
     float v[V > 0 ? V : 1];
@@ -95,9 +95,7 @@ __device__ __forceinline__ void topk_row(float* __restrict__ row, int E, int k, 
             part += row_rot<1>(part);
             denom = part;
         }
-#pragma unroll
-        for (int q = 0; q < kMaxRounds; ++q)
-            if (q == j) { sel_v[q] = bv; sel_i[q] = bi; }
+        if (sub == j) { sel_v = bv; sel_i = bi; }
         if constexpr (V > 0) {
 #pragma unroll
             for (int q = 0; q < V; ++q)
@@ -107,30 +105,28 @@ __device__ __forceinline__ void topk_row(float* __restrict__ row, int E, int k, 
             __builtin_amdgcn_wave_barrier();
         }
     }
-    if (live && sub == 0) {
-        float p[MOE_MAX_K];
-        float psum = 0.f;
-#pragma unroll
-        for (int j = 0; j < MOE_MAX_K; ++j)
-            if (j < k) {
-                p[j] = expf(sel_v[j] - vmax) / denom;
-                psum += p[j];
-            }
-#pragma unroll
-        for (int j = 0; j < MOE_MAX_K; ++j)
-            if (j < k) {
-                idx_out[j] = sel_i[j];
-                if (idx_lds != nullptr) idx_lds[j] = sel_i[j];
-                w_out[j] = renorm ? p[j] / psum : p[j];
-                atomicAdd(&hist[sel_i[j]], 1);      // LDS, integer: order does not matter
-            }
-        if (margin_out) {
-            float m = __builtin_huge_valf();
-#pragma unroll
-            for (int j = 0; j + 1 < kMaxRounds; ++j)
-                if (j + 1 < rounds) m = fminf(m, sel_v[j] - sel_v[j + 1]);
-            *margin_out = m;
-        }
+    // Lane j finishes winner j: one exponential and one division each, side by side (one lane doing all k of them, unrolled
+    // to MOE_MAX_K, was most of the kernel's code, which a short kernel fetches cold).
+    const float p = expf(sel_v - vmax) / denom;
+    float psum = 0.f;
+    if (renorm) {
+#pragma unroll 1
+        for (int j = 0; j < k; ++j) psum += __shfl(p, j, 16);          // in slot order
+    }
+    if (live && sub < k) {
+        idx_out[sub] = sel_i;
+        if (idx_lds != nullptr) idx_lds[sub] = sel_i;
+        w_out[sub] = renorm ? p / psum : p;
+        atomicAdd(&hist[sel_i], 1);                                    // LDS, integer: order does not matter
+    }
+    if (margin_out != nullptr) {                                       // uniform
+        const float next = __shfl_down(sel_v, 1, 16);
+        float m = sub + 1 < rounds ? sel_v - next : __builtin_huge_valf();
+        m = fminf(m, row_rot<8>(m));
+        m = fminf(m, row_rot<4>(m));
+        m = fminf(m, row_rot<2>(m));
+        m = fminf(m, row_rot<1>(m));
+        if (live && sub == 0) *margin_out = m;
     }
 }
 
