@@ -326,8 +326,9 @@ moe_status moe_layer_forward_biased(const moe_shape* shape, const void* x, const
     int32_t* cnt = counts ? counts : at<int32_t>(ws, L.counts);
     int32_t* offsets = at<int32_t>(ws, L.offsets);
     int32_t* inv = at<int32_t>(ws, L.inv_perm);
-    uint8_t* own_mask = at<uint8_t>(ws, L.mask);
     const bool derive = (mask == nullptr && H >= 0);
+    // a derived mask goes straight where the caller wants it, if anywhere
+    uint8_t* own_mask = derive && hot_mask_out != nullptr ? hot_mask_out : at<uint8_t>(ws, L.mask);
     const uint8_t* used = mask ? mask : (derive ? own_mask : nullptr);
 
     // route -> chunk histograms; these become counts, offsets, the hot mask and the tile lists, and every chunk places
@@ -344,7 +345,7 @@ moe_status moe_layer_forward_biased(const moe_shape* shape, const void* x, const
                               offsets, derive ? H : -1, derive ? own_mask : nullptr, mask, &lists,
                               shape->T > 0 ? &place : nullptr, hs);
     if (e != hipSuccess) return MOE_ERR_HIP;
-    if (hot_mask_out != nullptr) {
+    if (hot_mask_out != nullptr && !derive) {
         e = launch_mask_out(used, hot_mask_out, shape->E, hs);
         if (e != hipSuccess) return MOE_ERR_HIP;
     }
