@@ -17,7 +17,7 @@ constexpr int kMaxSplit = 8;        // parts per left-over unit, at most ...
 #define MOE_MIN_SPLIT_STEPS 32
 #endif
 #ifndef MOE_MIN_SPLIT_STEPS_FINE
-#define MOE_MIN_SPLIT_STEPS_FINE 16
+#define MOE_MIN_SPLIT_STEPS_FINE 24
 #endif
 
 // The two shapes of a unit: rows x columns of its output, the groups of wavefronts that share its contraction inside the
@@ -29,11 +29,12 @@ struct FineUnits {
     static constexpr int kRows = kHalfTileRows, kCols = 128, kGroups = 2, kMinSplitSteps = MOE_MIN_SPLIT_STEPS_FINE;
 };
 
-// Which of them a product runs in: big units from 5/8 of a round of them on.  Four fine units per big one are then 2.5
-// rounds, with the same steps per round as half a big unit's and a start and an end each.  (96 units of 24 steps: fine
-// 35.7 us, big 39.7 us; 256 units of 32 steps: big 33.7 us.)
+// Which of them a product runs in: big units from half a round of them on.  Two rounds of fine units, four per big one, then
+// take as long as a round of big ones, and longer past that.  Measured, big / fine with the pass that adds up parts:
+// 96 units of 24 steps 33.7 / 29.8 us, of 32 steps 35.3 / 36.4; 128 of 32 steps 36.6 / 36.8; 128 of 64 steps 64 / 73; 160 of 32 steps 38.0 / 51.1;
+// 32 units of 96, 128, 160, 192 and 224 steps 40 / 28, 43 / 31, 45 / 35, 49 / 38 and 57 / 53; 64 of 128 steps 66 / 55.
 #ifndef MOE_FINE_BELOW_PCT
-#define MOE_FINE_BELOW_PCT 62
+#define MOE_FINE_BELOW_PCT 50
 #endif
 inline __host__ __device__ bool tiled_product_is_fine(long big_tiles, int N, int cus) {
     return big_tiles * ((N + BigUnits::kCols - 1) / BigUnits::kCols) * 100 < static_cast<long>(cus) * MOE_FINE_BELOW_PCT;
