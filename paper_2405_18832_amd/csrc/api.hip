@@ -327,8 +327,7 @@ moe_status moe_layer_forward_biased(const moe_shape* shape, const void* x, const
     int32_t* offsets = at<int32_t>(ws, L.offsets);
     int32_t* inv = at<int32_t>(ws, L.inv_perm);
     const bool derive = (mask == nullptr && H >= 0);
-    // a derived mask goes straight where the caller wants it, if anywhere
-    uint8_t* own_mask = derive && hot_mask_out != nullptr ? hot_mask_out : at<uint8_t>(ws, L.mask);
+    uint8_t* own_mask = at<uint8_t>(ws, L.mask);           // what the call's kernels read; hot_mask_out is only written
     const uint8_t* used = mask ? mask : (derive ? own_mask : nullptr);
 
     // route -> chunk histograms; these become counts, offsets, the hot mask and the tile lists, and every chunk places
@@ -342,8 +341,8 @@ moe_status moe_layer_forward_biased(const moe_shape* shape, const void* x, const
     const int tok = route_chunk_tokens(*shape);
     const PlaceArgs place{idx, perm, inv, tokmap, shape->T * shape->k, shape->k, tok * shape->k};
     e = launch_route_finalize(*shape, x, w_gate, gate_bias, idx, gate, nullptr, hist, at<float>(ws, L.gate_part), cnt,
-                              offsets, derive ? H : -1, derive ? own_mask : nullptr, mask, &lists,
-                              shape->T > 0 ? &place : nullptr, hs);
+                              offsets, derive ? H : -1, derive ? own_mask : nullptr, derive ? hot_mask_out : nullptr, mask,
+                              &lists, shape->T > 0 ? &place : nullptr, hs);
     if (e != hipSuccess) return MOE_ERR_HIP;
     if (hot_mask_out != nullptr && !derive) {
         e = launch_mask_out(used, hot_mask_out, shape->E, hs);

@@ -449,8 +449,8 @@ struct PlaceArgs {
 };
 hipError_t launch_route_finalize(const moe_shape& s, const void* x, const void* w_gate, const float* bias,
                                  int32_t* idx, float* gate, float* margin, int32_t* hist_ws, float* gate_part_ws,
-                                 int32_t* counts, int32_t* offsets, int H, uint8_t* hot_mask, const uint8_t* mask_in,
-                                 const TileLists* lists, const PlaceArgs* place, hipStream_t st);
+                                 int32_t* counts, int32_t* offsets, int H, uint8_t* hot_mask, uint8_t* mask_copy,
+                                 const uint8_t* mask_in, const TileLists* lists, const PlaceArgs* place, hipStream_t st);
 hipError_t launch_place(int32_t* chunk_hist, int nchunks, int E, const int32_t* offsets, const PlaceArgs& place,
                         hipStream_t st);
 TileLists ffn_tile_lists(const moe_shape& s, Tile* small_ws, Tile* big_ws, Tile* half_ws, int32_t* ntiles_ws, float* partials_ws);

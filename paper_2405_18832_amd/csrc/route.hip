@@ -413,10 +413,12 @@ __device__ __forceinline__ void sum_chunks(const int32_t* __restrict__ chunk_his
 
 // counts, offsets, hot mask and tile lists from the token counts, by a block of 1024 threads, thread e owning expert e
 // with `mine` tokens.  `cnt` (2 * MOE_MAX_E ints) and `scan` (48 ints) are LDS scratch.  Any output pointer may be NULL.
-// Returns the expert's first row.
+// `mask_copy`: a second place for the hot mask (the caller's output buffer, which later kernels of the call must not depend
+// on: the caller may write to it as soon as the call has returned).  Returns the expert's first row.
 __device__ __forceinline__ int finalize_outputs(int mine, int E, int32_t* __restrict__ counts, int32_t* __restrict__ offsets,
-                                                int H, uint8_t* __restrict__ hot_mask, const uint8_t* __restrict__ mask_in,
-                                                const TileLists lists, int want_tiles, int32_t* cnt, int32_t* scan) {
+                                                int H, uint8_t* __restrict__ hot_mask, uint8_t* __restrict__ mask_copy,
+                                                const uint8_t* __restrict__ mask_in, const TileLists lists, int want_tiles,
+                                                int32_t* cnt, int32_t* scan) {
     const int e = threadIdx.x;
     bool on = e < E;
     if (H >= 0) {                                          // uniform: rank by count, ties by lowest index
@@ -438,6 +440,7 @@ __device__ __forceinline__ int finalize_outputs(int mine, int E, int32_t* __rest
             for (int o = 0; o < ngrp; ++o) rank += cnt[MOE_MAX_E + o * Ew + e];
             on = rank < H;
             if (hot_mask) hot_mask[e] = on ? 1 : 0;
+            if (mask_copy) mask_copy[e] = on ? 1 : 0;
         }
     } else if (mask_in != nullptr && e < E) {
         on = mask_in[e] != 0;
@@ -483,8 +486,9 @@ template <int PW>
 __global__ __launch_bounds__(1024) void dispatch_kernel(const int32_t* __restrict__ chunk_hist, int nchunks, int E,
                                                         const int32_t* __restrict__ offsets_in, int finalize,
                                                         int32_t* __restrict__ counts, int32_t* __restrict__ offsets, int H,
-                                                        uint8_t* __restrict__ hot_mask, const uint8_t* __restrict__ mask_in,
-                                                        const TileLists lists, const int want_tiles, const PlaceArgs place) {
+                                                        uint8_t* __restrict__ hot_mask, uint8_t* __restrict__ mask_copy,
+                                                        const uint8_t* __restrict__ mask_in, const TileLists lists,
+                                                        const int want_tiles, const PlaceArgs place) {
     extern __shared__ int32_t next_all[];
     __shared__ int32_t groups[2048];
     __shared__ int32_t scan[48];
@@ -493,7 +497,7 @@ __global__ __launch_bounds__(1024) void dispatch_kernel(const int32_t* __restric
     if (finalize && blockIdx.x == 0) {
         sum_chunks(chunk_hist, nchunks, E, 0, groups, total, before);
         __syncthreads();                                   // `groups` becomes `cnt`
-        finalize_outputs(total, E, counts, offsets, H, hot_mask, mask_in, lists, want_tiles, groups, scan);
+        finalize_outputs(total, E, counts, offsets, H, hot_mask, mask_copy, mask_in, lists, want_tiles, groups, scan);
         return;
     }
     if constexpr (PW > 0) {
@@ -535,8 +539,9 @@ __global__ __launch_bounds__(1024) void dispatch_kernel(const int32_t* __restric
 __global__ __launch_bounds__(1024) void scan_finalize_kernel(int32_t* __restrict__ chunk_hist, int nchunks, int E,
                                                              int finalize, int32_t* __restrict__ counts,
                                                              int32_t* __restrict__ offsets, int H,
-                                                             uint8_t* __restrict__ hot_mask, const uint8_t* __restrict__ mask_in,
-                                                             const TileLists lists, const int want_tiles) {
+                                                             uint8_t* __restrict__ hot_mask, uint8_t* __restrict__ mask_copy,
+                                                             const uint8_t* __restrict__ mask_in, const TileLists lists,
+                                                             const int want_tiles) {
     __shared__ int32_t groups[2048];
     __shared__ int32_t scan[48];
     int total, before;
@@ -564,7 +569,7 @@ __global__ __launch_bounds__(1024) void scan_finalize_kernel(int32_t* __restrict
         }
     }
     __syncthreads();
-    if (finalize) finalize_outputs(total, E, counts, offsets, H, hot_mask, mask_in, lists, want_tiles, groups, scan);
+    if (finalize) finalize_outputs(total, E, counts, offsets, H, hot_mask, mask_copy, mask_in, lists, want_tiles, groups, scan);
 }
 
 // places one chunk per wavefront from the slot bases that scan_finalize_kernel left
@@ -778,6 +783,7 @@ __global__ __launch_bounds__(1024) void route_topk_finalize_kernel(const float* 
                                                                    int renorm, int Tpad, int32_t* __restrict__ counts,
                                                                    int32_t* __restrict__ offsets, int H,
                                                                    uint8_t* __restrict__ hot_mask,
+                                                                   uint8_t* __restrict__ mask_copy,
                                                                    const uint8_t* __restrict__ mask_in,
                                                                    const TileLists lists, const int want_tiles,
                                                                    const PlaceArgs place) {
@@ -829,7 +835,7 @@ __global__ __launch_bounds__(1024) void route_topk_finalize_kernel(const float* 
     int mine = 0;
     if (e < E)
         for (int c = 0; c < nchunks; ++c) mine += hist[c * E + e];
-    int at = finalize_outputs(mine, E, counts, offsets, H, hot_mask, mask_in, lists, want_tiles, cnt, scan);
+    int at = finalize_outputs(mine, E, counts, offsets, H, hot_mask, mask_copy, mask_in, lists, want_tiles, cnt, scan);
     if (place.idx == nullptr) return;                      // uniform
     if (e < E) {                                           // histograms -> the chunks' first free slots
         for (int c = 0; c < nchunks; ++c) {
@@ -900,35 +906,37 @@ constexpr int kDispatchMaxChunks = 1024;      // few experts: a chunk's row is s
 
 template <int PW>
 static hipError_t launch_dispatch_pw(const int32_t* chunk_hist, int nchunks, int E, const int32_t* offsets_in, bool finalize,
-                                     int32_t* counts, int32_t* offsets, int H, uint8_t* hot_mask, const uint8_t* mask_in,
-                                     const TileLists& lists, bool want_tiles, const PlaceArgs& place, hipStream_t st) {
+                                     int32_t* counts, int32_t* offsets, int H, uint8_t* hot_mask, uint8_t* mask_copy,
+                                     const uint8_t* mask_in, const TileLists& lists, bool want_tiles, const PlaceArgs& place,
+                                     hipStream_t st) {
     const unsigned blocks = (PW > 0 ? static_cast<unsigned>((nchunks + PW - 1) / std::max(PW, 1)) : 0u) + (finalize ? 1 : 0);
     hipLaunchKernelGGL(dispatch_kernel<PW>, dim3(blocks), dim3(1024), static_cast<size_t>(PW) * E * 4, st, chunk_hist, nchunks,
-                       E, offsets_in, finalize ? 1 : 0, counts, offsets, H, hot_mask, mask_in, lists, want_tiles ? 1 : 0, place);
+                       E, offsets_in, finalize ? 1 : 0, counts, offsets, H, hot_mask, mask_copy, mask_in, lists, want_tiles ? 1 : 0,
+                       place);
     return hipGetLastError();
 }
 
 // chunk histograms -> counts, offsets, hot mask, tile lists (`finalize`) and places (place.idx != NULL); with offsets_in
 // the places start from the caller's offsets.  Overwrites chunk_hist where it is large.
 static hipError_t launch_dispatch(int32_t* chunk_hist, int nchunks, int E, const int32_t* offsets_in, bool finalize,
-                                  int32_t* counts, int32_t* offsets, int H, uint8_t* hot_mask, const uint8_t* mask_in,
-                                  const TileLists* lists, const PlaceArgs* place, hipStream_t st) {
+                                  int32_t* counts, int32_t* offsets, int H, uint8_t* hot_mask, uint8_t* mask_copy,
+                                  const uint8_t* mask_in, const TileLists* lists, const PlaceArgs* place, hipStream_t st) {
     const TileLists none{nullptr, nullptr, nullptr, nullptr, nullptr, 16, 0, 0, 0};
     const PlaceArgs no_place{nullptr, nullptr, nullptr, nullptr, 0, 1, 1};
     const TileLists& tl = lists ? *lists : none;
     const bool tiles = lists != nullptr;
     if (place == nullptr || nchunks == 0)
-        return launch_dispatch_pw<0>(chunk_hist, nchunks, E, nullptr, true, counts, offsets, H, hot_mask, mask_in, tl, tiles,
-                                     no_place, st);
+        return launch_dispatch_pw<0>(chunk_hist, nchunks, E, nullptr, true, counts, offsets, H, hot_mask, mask_copy, mask_in, tl,
+                                     tiles, no_place, st);
     if (static_cast<long>(nchunks) * E <= kDispatchMaxHist && nchunks <= kDispatchMaxChunks) {
         if (E <= 256)
-            return launch_dispatch_pw<16>(chunk_hist, nchunks, E, offsets_in, finalize, counts, offsets, H, hot_mask, mask_in,
-                                          tl, tiles, *place, st);
-        return launch_dispatch_pw<4>(chunk_hist, nchunks, E, offsets_in, finalize, counts, offsets, H, hot_mask, mask_in, tl,
-                                     tiles, *place, st);
+            return launch_dispatch_pw<16>(chunk_hist, nchunks, E, offsets_in, finalize, counts, offsets, H, hot_mask, mask_copy,
+                                          mask_in, tl, tiles, *place, st);
+        return launch_dispatch_pw<4>(chunk_hist, nchunks, E, offsets_in, finalize, counts, offsets, H, hot_mask, mask_copy, mask_in,
+                                     tl, tiles, *place, st);
     }
     hipLaunchKernelGGL(scan_finalize_kernel, dim3(1), dim3(1024), 0, st, chunk_hist, nchunks, E, finalize ? 1 : 0, counts,
-                       offsets, H, hot_mask, mask_in, tl, tiles ? 1 : 0);
+                       offsets, H, hot_mask, mask_copy, mask_in, tl, tiles ? 1 : 0);
     const hipError_t err = hipGetLastError();
     if (err != hipSuccess) return err;
     hipLaunchKernelGGL(perm_place_kernel, dim3((nchunks + 3) / 4), dim3(256), 0, st, finalize ? offsets : offsets_in, chunk_hist,
@@ -938,14 +946,15 @@ static hipError_t launch_dispatch(int32_t* chunk_hist, int nchunks, int E, const
 
 hipError_t launch_place(int32_t* chunk_hist, int nchunks, int E, const int32_t* offsets, const PlaceArgs& place,
                         hipStream_t st) {
-    return launch_dispatch(chunk_hist, nchunks, E, offsets, false, nullptr, nullptr, -1, nullptr, nullptr, nullptr, &place, st);
+    return launch_dispatch(chunk_hist, nchunks, E, offsets, false, nullptr, nullptr, -1, nullptr, nullptr, nullptr, nullptr, &place,
+                           st);
 }
 
 // routing followed by the finalize step; one kernel does both for decoder-sized layers
 hipError_t launch_route_finalize(const moe_shape& s, const void* x, const void* w_gate, const float* bias,
                                  int32_t* idx, float* gate, float* margin, int32_t* hist_ws, float* gate_part_ws,
-                                 int32_t* counts, int32_t* offsets, int H, uint8_t* hot_mask, const uint8_t* mask_in,
-                                 const TileLists* lists, const PlaceArgs* place, hipStream_t st) {
+                                 int32_t* counts, int32_t* offsets, int H, uint8_t* hot_mask, uint8_t* mask_copy,
+                                 const uint8_t* mask_in, const TileLists* lists, const PlaceArgs* place, hipStream_t st) {
     int nchunks = 0;
     if (s.T > 0) {
         const int tok = route_chunk_tokens(s);
@@ -962,14 +971,14 @@ hipError_t launch_route_finalize(const moe_shape& s, const void* x, const void* 
             const TileLists none{nullptr, nullptr, nullptr, nullptr, nullptr, 16, 0, 0, 0};
             const PlaceArgs no_place{nullptr, nullptr, nullptr, nullptr, 0, 1, 1};
             hipLaunchKernelGGL(route_topk_finalize_kernel, dim3(1), dim3(1024), lds, st, gate_part_ws, bias, idx, gate,
-                               margin, s.T, s.E, s.k, s.renormalize, Tpad, counts, offsets, H, hot_mask, mask_in,
-                               lists ? *lists : none, lists ? 1 : 0, place ? *place : no_place);
+                               margin, s.T, s.E, s.k, s.renormalize, Tpad, counts, offsets, H, hot_mask, mask_copy,
+                               mask_in, lists ? *lists : none, lists ? 1 : 0, place ? *place : no_place);
             return hipGetLastError();
         }
         hipError_t err = launch_route_fused(s, x, w_gate, bias, idx, gate, margin, hist_ws, gate_part_ws, st);
         if (err != hipSuccess) return err;
     }
-    return launch_dispatch(hist_ws, nchunks, s.E, nullptr, true, counts, offsets, H, hot_mask, mask_in, lists, place, st);
+    return launch_dispatch(hist_ws, nchunks, s.E, nullptr, true, counts, offsets, H, hot_mask, mask_copy, mask_in, lists, place, st);
 }
 
 hipError_t launch_route(const moe_shape& s, const void* x, const void* w_gate, const float* bias,
@@ -977,7 +986,7 @@ hipError_t launch_route(const moe_shape& s, const void* x, const void* w_gate, c
                         int32_t* offsets, int32_t H, uint8_t* hot_mask, int32_t* hist_ws, float* gate_part_ws,
                         hipStream_t st) {
     return launch_route_finalize(s, x, w_gate, bias, idx, gate, margin, hist_ws, gate_part_ws, counts, offsets, H, hot_mask,
-                                 nullptr, nullptr, nullptr, st);
+                                 nullptr, nullptr, nullptr, nullptr, st);
 }
 
 }  // namespace moe

@@ -136,3 +136,34 @@ def test_places(gpu_lib, T, E, k):
     assert np.array_equal(inv.cpu().numpy()[want], np.arange(T * k))
     assert torch.equal(xp.view(torch.int16), x[torch.from_numpy(want // k).cuda()].view(torch.int16))
     assert np.array_equal(mask.cpu().numpy(), orc.hot_mask_top_h(n, E // 2))
+
+
+# hot_mask_out is an output only: once the dispatch step has written it (the profile event before the first product stands
+# behind that step), the caller may overwrite it on another stream while the products still run
+@pytest.mark.parametrize("T,E,k", [(48, 40, 2), (1500, 24, 2)])
+def test_derived_mask_output_is_not_read_back(gpu_lib, T, E, k):
+    say(f"[case] derived mask overwritten during the call T={T} E={E}")
+    moe, d, f = gpu_lib, 1024, 4096
+    gen = torch.Generator(device="cuda").manual_seed(T)
+    bf = lambda s, *shape: (torch.randn(shape, device="cuda", generator=gen) * s).to(torch.bfloat16)
+    x, wg, w1, w2 = bf(1.0, T, d), bf(0.05, E, d), bf(d ** -0.5, E, d * f), bf(f ** -0.5, E, d * f)
+    shape = moe.make_shape(T, d, f, E, k, "bf16", True)
+    ws = torch.empty(moe.moe_workspace_bytes(shape), dtype=torch.uint8, device="cuda")
+    want = torch.empty((T, d), dtype=torch.bfloat16, device="cuda")
+    out, mask = torch.empty_like(want), torch.empty(E, dtype=torch.uint8, device="cuda")
+    moe.moe_layer_forward(shape, x, wg, None, w1, w2, None, E // 3, want, ws=ws)
+    before_products, other = torch.cuda.Event(), torch.cuda.Stream()
+    before_products.record()                               # creates the handle
+    torch.cuda.synchronize()
+    moe.moe_set_profile_events([before_products.cuda_event, None, None, None, None])
+    try:
+        moe.moe_layer_forward(shape, x, wg, None, w1, w2, None, E // 3, out, hot_mask_out=mask, ws=ws)
+    finally:
+        moe.moe_set_profile_events(None)
+    other.wait_event(before_products)
+    with torch.cuda.stream(other):
+        written = mask.clone()
+        mask.zero_()
+    torch.cuda.synchronize()
+    assert int(written.sum()) == E // 3 and int(mask.sum()) == 0
+    assert torch.equal(out.view(torch.int16), want.view(torch.int16))
