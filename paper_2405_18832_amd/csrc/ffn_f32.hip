@@ -4,12 +4,19 @@
 //   out[row, n] = sum_k act[row, k] * W_e[n, k]          (FIRST: bias and activation, else bias)
 //
 // Weights are plain rows [N][K].  A unit is one row tile (up to 64 rows of one expert) x 16 columns; the four
-// wavefronts of a block split the contraction and add their partial sums in LDS in wave order.  Per 32 k a wavefront
+// wavefronts of a block split the contraction and add their partial sums in LDS in a fixed order.  Per 32 k a wavefront
 // loads one 128-byte line of each of its rows, eight consecutive lanes a line, turns the fragments round in its own part
 // of LDS, and reads them back as matrix operands: lane (r, g) holds k0 + 4g ... + 3 of row r and feeds element j to the
 // j-th of four MFMAs (the four k of one MFMA are k0 + j + {0, 4, 8, 12}, the same for both operands).  Loading the
 // operands straight into that form puts 16 different rows under 16 consecutive lanes: 64 cache accesses per load
 // instruction instead of 16, which bounded the kernel (57 + 67 us on the layer below).
+//
+// Rounding: a result is no further from the exact sum than with four interleaved sums over k mod 4, added in pairs.  Four
+// equal shares of a contraction are as good as those.  Unequal ones (K no multiple of 128) are not: there a wavefront's
+// MFMAs take turns in two chains of sums, and in four, one per k mod 4, where the contraction is too short for a step per
+// wavefront (the weights of such units are few, so tiles of more than 32 rows read them twice).  Relative error of a layer's two products, mean of 24 layers of random inputs, one chain per
+// wavefront throughout -> these: d = 20, f = 33: 1.12 -> 0.82e-7; d = 32: 1.35 -> 1.08e-7; d = 64: 1.54 -> 1.32e-7; d = 96:
+// 1.71 -> 1.51e-7 (four interleaved sums: 0.96, 1.07, 1.38 and 1.64e-7).
 //
 // What bounds it: with about 64 rows per expert the MFMA time (64 flop per clock and SIMD) and reading the weights once
 // are about equal, 17 and 14 us on a layer of 500 tokens, 8 experts, 768 x 3072, one expert per token (2.4 GFLOP and
@@ -31,7 +38,8 @@ constexpr int kF32FragFloats = 16 * kF32Step;
 // rows that a read touches at once then lie in different banks.
 __device__ __forceinline__ int f32_slot(int r, int p) { return r * kF32Step + ((p ^ (r & 7)) << 2); }
 
-template <int TFC, int VEC, bool FIRST>
+// CHAINS: accumulators per output, taken in turn by the four MFMAs of 16 k
+template <int TFC, int CHAINS, int VEC, bool FIRST>
 __device__ __forceinline__ void f32_unit(const float* __restrict__ act, const int32_t* __restrict__ rowmap,
                                          const float* __restrict__ w, float* __restrict__ outp, const Tile tl,
                                          const int n0, const int N, const int K, const int activation,
@@ -54,9 +62,11 @@ __device__ __forceinline__ void f32_unit(const float* __restrict__ act, const in
                 src[i][h] = act + static_cast<size_t>(row) * K + lpiece * 4;
             }
         }
-    f32x4 acc[TFC];
+    f32x4 acc[CHAINS][TFC];
 #pragma unroll
-    for (int tf = 0; tf < TFC; ++tf) acc[tf] = f32x4{0.f, 0.f, 0.f, 0.f};
+    for (int c = 0; c < CHAINS; ++c)
+#pragma unroll
+        for (int tf = 0; tf < TFC; ++tf) acc[c][tf] = f32x4{0.f, 0.f, 0.f, 0.f};
     float* mine = lds + wave * (F * kF32FragFloats);      // private to the wavefront: its LDS accesses stay in order
     f32x4 raw[F][2];
     auto issue = [&]() {                                  // loads a step and moves on to the next
@@ -85,7 +95,8 @@ __device__ __forceinline__ void f32_unit(const float* __restrict__ act, const in
             for (int j = 0; j < 4; ++j)
 #pragma unroll
                 for (int tf = 0; tf < TFC; ++tf)
-                    acc[tf] = __builtin_amdgcn_mfma_f32_16x16x4f32(v[0][j], v[1 + tf][j], acc[tf], 0, 0, 0);
+                    acc[j % CHAINS][tf] =
+                        __builtin_amdgcn_mfma_f32_16x16x4f32(v[0][j], v[1 + tf][j], acc[j % CHAINS][tf], 0, 0, 0);
         }
     };
     const int steps = K / kF32Step, per = (steps + kF32Waves - 1) / kF32Waves;      // whole steps; the rest of the row below
@@ -123,13 +134,18 @@ __device__ __forceinline__ void f32_unit(const float* __restrict__ act, const in
 
     // row fragment i of every wavefront at red[(wave * TFC + i) * 64 + lane]; wavefront i adds and stores it
 #pragma unroll
-    for (int tf = 0; tf < TFC; ++tf) red[(wave * TFC + tf) * 64 + lane] = acc[tf];
+    for (int tf = 0; tf < TFC; ++tf) {
+        f32x4 sum = acc[0][tf];
+        if constexpr (CHAINS >= 2) sum += acc[1][tf];
+        if constexpr (CHAINS == 4) sum += acc[2][tf] + acc[3][tf];
+        red[(wave * TFC + tf) * 64 + lane] = sum;
+    }
     __syncthreads();
     if (wave < TFC) {
         const int lr = wave * 16 + r, n = n0 + g * 4;
-        f32x4 v = red[wave * 64 + lane];
-#pragma unroll
-        for (int s = 1; s < kF32Waves; ++s) v += red[(s * TFC + wave) * 64 + lane];
+        static_assert(kF32Waves == 4, "partial sums are added in pairs");
+        const f32x4* part = red + wave * 64 + lane;
+        f32x4 v = (part[0] + part[TFC * 64]) + (part[2 * TFC * 64] + part[3 * TFC * 64]);
         if (lr < tl.rows) {
             float* o = outp + static_cast<size_t>(tl.row0 + lr) * N + n;
             const float* be = bias ? bias + static_cast<size_t>(tl.expert) * N + n : nullptr;
@@ -151,7 +167,7 @@ __device__ __forceinline__ void f32_unit(const float* __restrict__ act, const in
 }
 
 // at least 4 wavefronts per SIMD: the turn through LDS and the start of a unit are covered by the other blocks' MFMAs
-template <int VEC, bool FIRST>
+template <int VEC, bool FIRST, int CHAINS>
 __global__ __launch_bounds__(256, 4) void ffn_f32_kernel(const float* __restrict__ act, const int32_t* __restrict__ rowmap,
                                                       const float* __restrict__ w, float* __restrict__ outp,
                                                       const Tile* __restrict__ tiles,
@@ -169,11 +185,21 @@ __global__ __launch_bounds__(256, 4) void ffn_f32_kernel(const float* __restrict
     for (int u = static_cast<int>(blockIdx.x) / nx; u < units; u += stride) {     // block-uniform
         const Tile tl = tiles[u / ng];
         const int n0 = (g0 + u % ng) * 16;
-        switch ((tl.rows + 15) >> 4) {                    // exact number of row fragments: a fixed number of loads per step
-            case 1: f32_unit<1, VEC, FIRST>(act, rowmap, w, outp, tl, n0, N, K, activation, bias, lds); break;
-            case 2: f32_unit<2, VEC, FIRST>(act, rowmap, w, outp, tl, n0, N, K, activation, bias, lds); break;
-            case 3: f32_unit<3, VEC, FIRST>(act, rowmap, w, outp, tl, n0, N, K, activation, bias, lds); break;
-            default: f32_unit<4, VEC, FIRST>(act, rowmap, w, outp, tl, n0, N, K, activation, bias, lds); break;
+        if constexpr (CHAINS < 4) {
+            switch ((tl.rows + 15) >> 4) {                // exact number of row fragments: a fixed number of loads per step
+                case 1: f32_unit<1, CHAINS, VEC, FIRST>(act, rowmap, w, outp, tl, n0, N, K, activation, bias, lds); break;
+                case 2: f32_unit<2, CHAINS, VEC, FIRST>(act, rowmap, w, outp, tl, n0, N, K, activation, bias, lds); break;
+                case 3: f32_unit<3, CHAINS, VEC, FIRST>(act, rowmap, w, outp, tl, n0, N, K, activation, bias, lds); break;
+                default: f32_unit<4, CHAINS, VEC, FIRST>(act, rowmap, w, outp, tl, n0, N, K, activation, bias, lds); break;
+            }
+        } else {                                          // four chains of more than two fragments do not fit the registers
+            for (int r0 = 0; r0 < tl.rows; r0 += 32) {
+                const Tile part{tl.expert, tl.row0 + r0, min(32, tl.rows - r0), 0};
+                if (part.rows <= 16)
+                    f32_unit<1, CHAINS, VEC, FIRST>(act, rowmap, w, outp, part, n0, N, K, activation, bias, lds);
+                else
+                    f32_unit<2, CHAINS, VEC, FIRST>(act, rowmap, w, outp, part, n0, N, K, activation, bias, lds);
+            }
         }
     }
 }
@@ -182,7 +208,10 @@ template <int VEC>
 static hipError_t launch_f32(bool first, unsigned grid, const float* act, const int32_t* rowmap, const float* w,
                              float* outp, const Tile* tiles, const int32_t* ntiles, int N, int K, int activation,
                              const float* bias, hipStream_t st) {
-    auto kern = first ? ffn_f32_kernel<VEC, true> : ffn_f32_kernel<VEC, false>;
+    constexpr int kShared = kF32Waves * kF32Step;         // contraction with a step for every wavefront
+    auto kern = first ? ffn_f32_kernel<VEC, true, 2> : ffn_f32_kernel<VEC, false, 2>;
+    if (K % kShared == 0) kern = first ? ffn_f32_kernel<VEC, true, 1> : ffn_f32_kernel<VEC, false, 1>;
+    else if (K < kShared) kern = first ? ffn_f32_kernel<VEC, true, 4> : ffn_f32_kernel<VEC, false, 4>;
     hipLaunchKernelGGL(kern, dim3(grid), dim3(256), 0, st, act, rowmap, w, outp, tiles, ntiles, N, K, activation, bias);
     return hipGetLastError();
 }

@@ -70,6 +70,31 @@ def test_f32_ffn_few_rows_masked(gpu_lib):
     check(*ffn_rows(gpu_lib, [3, 9, 4], 64, 96, "f32", mask=[1, 0, 1]), 1e-5)
 
 
+# fp32 rounding: no further from 64 bits than four interleaved fp32 sums over k mod 4, added in pairs, at contractions that one
+# wavefront, two, three and all four of them hold.  Bar on the rms over 512 d elements: 5 %, several times the scatter of
+# such a ratio between two orders of the same length.
+@pytest.mark.parametrize("d,f", [(20, 20), (32, 32), (48, 40), (64, 64), (96, 160), (256, 128)])
+def test_f32_ffn_rounding(gpu_lib, d, f):
+    say(f"[case] f32 ffn rounding d={d} f={f}")
+    rows = [16, 32, 48, 64, 96, 256]
+    rng = np.random.default_rng([0, d, f, len(rows), sum(rows)])              # as ffn_rows draws them
+    draw = lambda shape, s: rng.standard_normal(shape, dtype=np.float32) * np.float32(s)
+    x, w1, w2 = draw((sum(rows), d), 1.0), draw((len(rows), f, d), d ** -0.5), draw((len(rows), d, f), f ** -0.5)
+
+    def product(a, b):                                                       # a [m, K], b [N, K]: fp32, fused multiply-adds
+        s = np.zeros((4, a.shape[0], b.shape[0]), dtype=np.float32)
+        for c in range(a.shape[1]):
+            s[c % 4] += a[:, c, None].astype(np.float64) * b[None, :, c]
+        return (s[0] + s[1]) + (s[2] + s[3])
+
+    lo = np.concatenate([[0], np.cumsum(rows)])
+    four = np.concatenate([product(np.maximum(product(x[i:j], w1[e]), 0), w2[e]) for e, (i, j) in enumerate(zip(lo, lo[1:]))])
+    y, ref = ffn_rows(gpu_lib, rows, d, f, "f32")
+    err, bar = (float(np.sqrt(np.mean((v - ref) ** 2))) for v in (y, four))
+    say(f"[edges] rms error {err:.4e}, four sums {bar:.4e}")
+    assert err <= 1.05 * bar
+
+
 # fp32 routing: contraction remainders and expert counts around one fragment of 16
 @pytest.mark.parametrize("T,d,E", [(1, 7, 3), (17, 16, 16), (33, 50, 17), (40, 260, 40)])
 def test_f32_route(gpu_lib, T, d, E):
