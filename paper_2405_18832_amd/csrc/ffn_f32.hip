@@ -14,9 +14,10 @@
 // Rounding: a result is no further from the exact sum than with four interleaved sums over k mod 4, added in pairs.  Four
 // equal shares of a contraction are as good as those.  Unequal ones (K no multiple of 128) are not: there a wavefront's
 // MFMAs take turns in two chains of sums, and in four, one per k mod 4, where the contraction is too short for a step per
-// wavefront (the weights of such units are few, so tiles of more than 32 rows read them twice).  Relative error of a layer's two products, mean of 24 layers of random inputs, one chain per
-// wavefront throughout -> these: d = 20, f = 33: 1.12 -> 0.82e-7; d = 32: 1.35 -> 1.08e-7; d = 64: 1.54 -> 1.32e-7; d = 96:
-// 1.71 -> 1.51e-7 (four interleaved sums: 0.96, 1.07, 1.38 and 1.64e-7).
+// wavefront (the weights of such units are few, so tiles of more than 32 rows read them twice).  Relative error of a
+// layer's two products, mean of 24 layers of random inputs, one chain per wavefront throughout -> these: d = 20, f = 33:
+// 1.12 -> 0.82e-7; d = 32: 1.35 -> 1.08e-7; d = 64: 1.54 -> 1.32e-7; d = 96: 1.71 -> 1.51e-7 (four interleaved sums: 0.96,
+// 1.07, 1.38 and 1.64e-7).
 //
 // What bounds it: with about 64 rows per expert the MFMA time (64 flop per clock and SIMD) and reading the weights once
 // are about equal, 17 and 14 us on a layer of 500 tokens, 8 experts, 768 x 3072, one expert per token (2.4 GFLOP and
