@@ -231,10 +231,11 @@ __global__ __launch_bounds__(kRouteWaves * 64) void route_bf16_kernel(const uint
         }
         auto step = [&](int j, auto parity) {
             constexpr int C = 2 * decltype(parity)::value;
-            // stage j has landed for every wavefront, and nobody reads stage j - 1 any more
+            // Stage j has landed for every wavefront, and nobody reads stage j - 1 any more: the reads are waited for here,
+            // because nothing else keeps the matrix instructions that consume them in front of the barrier.
             if (j + S - 2 < nstages) __builtin_amdgcn_s_waitcnt(0x0F70 | ((S - 2) * P));
             else __builtin_amdgcn_s_waitcnt(0x0F70);
-            asm volatile("s_barrier" ::: "memory");
+            asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
             if (j + S - 1 < nstages) stage_in(j + S - 1);
             const unsigned char* st = route_lds + (j % S) * Ring::kStageBytes;
             const int halves = 2 * j + 1 < ksteps ? 2 : 1;

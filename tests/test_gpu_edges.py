@@ -117,6 +117,44 @@ def test_f32_route(gpu_lib, T, d, E):
     assert np.array_equal(counts.cpu().numpy(), np.bincount(idx.cpu().numpy().ravel(), minlength=E))
 
 
+def route_against_oracle(moe, T, d, E, k, x_at=0, wg_at=0, seed=0):
+    """moe_route in bf16 against the oracle; x and w_gate start `x_at` / `wg_at` elements into their allocations."""
+    rng = np.random.default_rng([seed, T, d, E])
+    x = wl.round_to_storage(rng.standard_normal((T, d), dtype=np.float32), "bf16")
+    wg = wl.round_to_storage(rng.standard_normal((E, d), dtype=np.float32) * np.float32(d ** -0.5), "bf16")
+    b = rng.standard_normal(E, dtype=np.float32)
+
+    def dev(a, at):
+        flat = torch.empty(a.size + 64, dtype=torch.bfloat16, device="cuda")
+        flat[at:at + a.size] = torch.from_numpy(a).cuda().flatten().to(torch.bfloat16)
+        return flat[at:at + a.size].view(a.shape)
+
+    shape = moe.make_shape(T, d, 32, E, k, "bf16", True)
+    idx, w, margin = torch.empty((T, k), dtype=torch.int32, device="cuda"), torch.empty((T, k), device="cuda"), torch.empty(T, device="cuda")
+    counts, offsets = (torch.empty(n, dtype=torch.int32, device="cuda") for n in (E, E + 1))
+    ws = torch.full((moe.moe_workspace_bytes(shape),), 0xFF, dtype=torch.uint8, device="cuda")
+    moe.moe_route(shape, dev(x, x_at), dev(wg, wg_at), torch.from_numpy(b).cuda(), idx, w, margin, counts, offsets, -1, None, ws)
+    torch.cuda.synchronize()
+    r = orc.route(x, wg, b, k, True)
+    ok = r["margin"] >= 1e-4
+    assert ok.mean() > 0.95
+    assert np.array_equal(idx.cpu().numpy()[ok], r["idx"][ok])
+    assert np.allclose(w.cpu().numpy()[ok], r["g"][ok], rtol=2e-4)
+    assert np.allclose(margin.cpu().numpy(), r["margin"], rtol=0, atol=2e-4)
+    assert np.array_equal(counts.cpu().numpy(), np.bincount(idx.cpu().numpy().ravel(), minlength=E))
+
+
+# bf16 routing: every form of the kernel (16, 32 or 64 tokens by 64 or 128 experts at a time; on 256 CUs 32 tokens from 4097
+# tokens on and 64 from 8193), ragged token counts, contractions that go round the ring of four stages of 64 k more than once
+# and end in half a stage, one that is half a stage, expert counts that take a second pass, and the few-token path
+@pytest.mark.parametrize("T,d,E,k", [(65, 352, 60, 2), (700, 320, 129, 4), (300, 608, 1024, 8), (4100, 352, 60, 2), (5003, 352, 128, 2),
+                                     (4500, 352, 200, 3), (8192, 96, 64, 1), (8300, 352, 40, 2), (8300, 544, 128, 2),
+                                     (8300, 352, 200, 1), (9000, 32, 20, 2), (33, 352, 60, 2), (64, 96, 300, 2)])
+def test_bf16_route(gpu_lib, T, d, E, k):
+    say(f"[case] bf16 route T={T} d={d} E={E}")
+    route_against_oracle(gpu_lib, T, d, E, k)
+
+
 # tiled kernels: experts around their 128- and 256-row tiles, columns that are no multiple of a tile's, contractions of one
 # step, of fewer steps than the LDS ring holds, and long enough to be cut; the last shape has few large units in one product
 # and many in the other.  Bar: y against the oracle that rounds the hidden activation once, as the kernels do; what is left
