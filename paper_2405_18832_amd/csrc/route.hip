@@ -157,8 +157,11 @@ __host__ __device__ inline int route_row_stride(int E, int NF) { return (E + 16 
 // kernel; neither more loads in flight nor more wavefronts changed it.)  The 16-byte pieces of a row are permuted by its row
 // number, so that the rows a read touches at once lie in different banks.  The contraction runs in four chains per
 // accumulator, which are added at the end.
+// DIRECT: x and w_gate are 16-byte aligned and the copies go straight into LDS.  Otherwise (a view into a larger buffer) they
+// go through registers: ordinary loads take any alignment, the copy instruction is only documented for whole dwords.
 // Dynamic LDS: the ring, then logits [16 * TF][route_row_stride(E, NF)] floats, then the histogram [E] ints.
 // ---------------------------------------------------------------------------
+typedef uint32_t u32x4_any __attribute__((ext_vector_type(4), aligned(2)));
 constexpr int kRouteWaves = 4;
 template <int TF, int NF>
 struct RouteRing {
@@ -169,7 +172,7 @@ struct RouteRing {
     static constexpr int kBytes = kStages * kStageBytes;
 };
 
-template <int TF, int NF>
+template <int TF, int NF, bool DIRECT>
 __global__ __launch_bounds__(kRouteWaves * 64) void route_bf16_kernel(const uint16_t* __restrict__ x,
                                                                       const uint16_t* __restrict__ wg,
                                                                       const float* __restrict__ bias,
@@ -206,7 +209,15 @@ __global__ __launch_bounds__(kRouteWaves * 64) void route_bf16_kernel(const uint
             const int q = (2 * j + 1 < ksteps) ? piece : (piece & 3);
             const uint32_t base = ring0 + (j % S) * Ring::kStageBytes;
 #pragma unroll
-            for (int p = 0; p < P; ++p) copy16_to_lds(src[p] + j * 64 + q * 8, base + (wave + NW * p) * 1024);
+            for (int p = 0; p < P; ++p) {
+                if constexpr (DIRECT) {
+                    copy16_to_lds(src[p] + j * 64 + q * 8, base + (wave + NW * p) * 1024);
+                } else {
+                    const u32x4_any v = *reinterpret_cast<const u32x4_any*>(src[p] + j * 64 + q * 8);
+                    *reinterpret_cast<uint4*>(route_lds + (j % S) * Ring::kStageBytes + (wave + NW * p) * 1024 + lane * 16) =
+                        uint4{v[0], v[1], v[2], v[3]};
+                }
+            }
         };
         f32x4 acc[4][FPW][TF];                             // [chain]
 #pragma unroll
@@ -670,14 +681,21 @@ static hipError_t launch_route_kernel(RouteKernel<ST> kern, int tok, int nf, siz
 template <int TF, int NF>
 static hipError_t launch_route_bf16(const moe_shape& s, const void* x, const void* w_gate, const float* bias, int32_t* idx,
                                     float* gate, float* margin, int32_t* chunk_hist, hipStream_t st) {
-    return launch_route_kernel<uint16_t>(route_bf16_kernel<TF, NF>, 16 * TF, NF, RouteRing<TF, NF>::kBytes, s, x, w_gate, bias,
-                                         idx, gate, margin, chunk_hist, st);
+    const bool aligned = ((reinterpret_cast<uintptr_t>(x) | reinterpret_cast<uintptr_t>(w_gate)) & 15) == 0;     // rows are 64 k bytes
+    return launch_route_kernel<uint16_t>(aligned ? route_bf16_kernel<TF, NF, true> : route_bf16_kernel<TF, NF, false>, 16 * TF, NF,
+                                         RouteRing<TF, NF>::kBytes, s, x, w_gate, bias, idx, gate, margin, chunk_hist, st);
 }
 
 template <typename Kernel>
 static hipError_t configure_route(Kernel kern) {
     return hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize,
                                static_cast<int>(kRouteLdsMax));
+}
+
+template <int TF, int NF>
+static hipError_t configure_route_bf16() {
+    const hipError_t e = configure_route(route_bf16_kernel<TF, NF, true>);
+    return e != hipSuccess ? e : configure_route(route_bf16_kernel<TF, NF, false>);
 }
 
 // Few tokens (a decode step): the gate product is one skinny GEMM whose cost is reading the gate weights, and
@@ -856,12 +874,12 @@ constexpr size_t kTopkFinalizeLdsMax = static_cast<size_t>(64) * (kTopkFinalizeM
 hipError_t configure_route_kernels(int) {
     hipError_t e;
     if ((e = configure_route(route_f32_kernel)) != hipSuccess) return e;
-    if ((e = configure_route(route_bf16_kernel<1, 4>)) != hipSuccess) return e;
-    if ((e = configure_route(route_bf16_kernel<2, 4>)) != hipSuccess) return e;
-    if ((e = configure_route(route_bf16_kernel<4, 4>)) != hipSuccess) return e;
-    if ((e = configure_route(route_bf16_kernel<1, 8>)) != hipSuccess) return e;
-    if ((e = configure_route(route_bf16_kernel<2, 8>)) != hipSuccess) return e;
-    if ((e = configure_route(route_bf16_kernel<4, 8>)) != hipSuccess) return e;
+    if ((e = configure_route_bf16<1, 4>()) != hipSuccess) return e;
+    if ((e = configure_route_bf16<2, 4>()) != hipSuccess) return e;
+    if ((e = configure_route_bf16<4, 4>()) != hipSuccess) return e;
+    if ((e = configure_route_bf16<1, 8>()) != hipSuccess) return e;
+    if ((e = configure_route_bf16<2, 8>()) != hipSuccess) return e;
+    if ((e = configure_route_bf16<4, 8>()) != hipSuccess) return e;
     if ((e = configure_route(route_topk_kernel)) != hipSuccess) return e;
     return hipFuncSetAttribute(reinterpret_cast<const void*>(route_topk_finalize_kernel),
                                hipFuncAttributeMaxDynamicSharedMemorySize, static_cast<int>(kTopkFinalizeLdsMax));

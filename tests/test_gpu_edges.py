@@ -155,6 +155,15 @@ def test_bf16_route(gpu_lib, T, d, E, k):
     route_against_oracle(gpu_lib, T, d, E, k)
 
 
+# the same from operands that are views into larger buffers, 2, 4 and 8 bytes off a 16-byte line
+@pytest.mark.parametrize("x_at,wg_at", [(0, 1), (4, 0), (1, 2)])
+@pytest.mark.parametrize("T,d,E,k", [(70, 352, 60, 2), (700, 320, 129, 4), (4100, 352, 60, 2), (5003, 96, 128, 2), (8300, 352, 40, 2),
+                                     (8300, 32, 100, 1), (33, 96, 60, 2)])
+def test_bf16_route_unaligned(gpu_lib, T, d, E, k, x_at, wg_at):
+    say(f"[case] bf16 route T={T} d={d} E={E}, operands {x_at} and {wg_at} elements off")
+    route_against_oracle(gpu_lib, T, d, E, k, x_at, wg_at)
+
+
 # tiled kernels: experts around their 128- and 256-row tiles, columns that are no multiple of a tile's, contractions of one
 # step, of fewer steps than the LDS ring holds, and long enough to be cut; the last shape has few large units in one product
 # and many in the other.  Bar: y against the oracle that rounds the hidden activation once, as the kernels do; what is left
