@@ -245,7 +245,7 @@ moe_status moe_combine(const moe_shape* shape, const float* y_perm, const int32_
  * LDS-tiled kernels rather than the weight-streaming one in a call where the experts have `rows_host[e]` rows
  * (HOST array [E]; 0 for experts that are empty or masked out).  It is 128, or one more than a streaming tile
  * holds when the experts of 128 rows and more already fill the tiled kernel for a round, or when they and the
- * smaller ones together take less than a round of its smaller units; 0 when the shape
+ * smaller ones together are at most a round of its smaller units; 0 when the shape
  * never uses the tiled kernel (fp32, or fewer than 128 tokens) or on invalid arguments.  The current device's
  * size enters (as in the calls themselves).
  */

@@ -427,8 +427,9 @@ __global__ __launch_bounds__(kWaves * 64, 2) void ffn_tile_kernel(const uint16_t
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
     const int ntiles = ntiles_p[1];
     if (ntiles <= 0) return;                            // no large expert in this call (block-uniform)
-    if (tiled_product_is_fine(ntiles, N, gridDim.x))
-        run_units<FIRST, FineUnits>(act, rowmap, wpk, outp, half_tiles, ntiles_p[kHalfCount], part_counter, partials, N, K,
+    const int nhalf = ntiles_p[kHalfCount];
+    if (tiled_product_is_fine(ntiles, nhalf, N, gridDim.x, FIRST == kFirstGelu))
+        run_units<FIRST, FineUnits>(act, rowmap, wpk, outp, half_tiles, nhalf, part_counter, partials, N, K,
                                     act_kmajor, bias, fold, smem);
     else
         run_units<FIRST, BigUnits>(act, rowmap, wpk, outp, big_tiles, ntiles, part_counter, partials, N, K, act_kmajor, bias,

@@ -29,15 +29,17 @@ struct FineUnits {
     static constexpr int kRows = kHalfTileRows, kCols = 128, kGroups = 2, kMinSplitSteps = MOE_MIN_SPLIT_STEPS_FINE;
 };
 
-// Which of them a product runs in: big units from half a round of them on.  Two rounds of fine units, four per big one, then
-// take as long as a round of big ones, and longer past that.  Measured, big / fine with the pass that adds up parts:
-// 96 units of 24 steps 33.7 / 29.8 us, of 32 steps 35.3 / 36.4; 128 of 32 steps 36.6 / 36.8; 128 of 64 steps 64 / 73; 160 of 32 steps 38.0 / 51.1;
-// 32 units of 96, 128, 160, 192 and 224 steps 40 / 28, 43 / 31, 45 / 35, 49 / 38 and 57 / 53; 64 of 128 steps 66 / 55.
-#ifndef MOE_FINE_BELOW_PCT
-#define MOE_FINE_BELOW_PCT 50
-#endif
-inline __host__ __device__ bool tiled_product_is_fine(long big_tiles, int N, int cus) {
-    return big_tiles * ((N + BigUnits::kCols - 1) / BigUnits::kCols) * 100 < static_cast<long>(cus) * MOE_FINE_BELOW_PCT;
+// Which of them a product runs in.  Fine ones where they are at most one round: the big units would leave most of the chip
+// idle, or be half empty (experts of up to 128 rows).  Between one round of fine units and half a round of big ones neither
+// is better as such: it depends on how the left-over units of either happen to be cut, and big units copy half as much.
+// There fine units are taken for the first product of GeLU layers only, whose epilogue all CUs work on then instead of
+// those that have a big unit.  Measured in us, fine / big, with the pass that adds up parts, tiles of 256 rows: 64 units of 24,
+// 32, 64 and 128 steps 24 / 34, 26 / 37, 31 / 46 and 57 / 67; 96 units of 24, 32, 64 and 128 steps 35 / 34, 40 / 38, 56 / 56 and
+// 92 / 89; 120 units of 32 and 128 steps 42 / 39 and 106 / 101; tiles of 137 rows, 72 units of 48 steps 38 / 45, 96 of 128 94 / 81,
+// 120 of 32 42 / 37.  GeLU: 72, 96 and 120 units of 24 steps 36 / 41, 38 / 42 and 41 / 42; 96 of 32 43 / 45; 144 of 24 48 / 43.
+inline __host__ __device__ bool tiled_product_is_fine(long big_tiles, long half_tiles, int N, int cus, bool gelu) {
+    if (half_tiles * ((N + FineUnits::kCols - 1) / FineUnits::kCols) <= cus) return true;
+    return gelu && big_tiles * ((N + BigUnits::kCols - 1) / BigUnits::kCols) * 2 < cus;
 }
 
 struct TileSchedule {
@@ -304,7 +306,7 @@ __device__ __forceinline__ void finish_tiled_product(const Tile* __restrict__ bi
                                                      const int32_t* __restrict__ ntiles, const float* __restrict__ partials,
                                                      void* __restrict__ outp, int N, int kblk, int cus,
                                                      const float* __restrict__ bias, const FoldOut& fold, int block, int nblocks) {
-    if (tiled_product_is_fine(ntiles[1], N, cus))
+    if (tiled_product_is_fine(ntiles[1], ntiles[kHalfCount], N, cus, FIRST == kFirstGelu))
         finish_split_units<FineUnits, FIRST, FOLD>(half_tiles, ntiles[kHalfCount], partials, outp, N, kblk, cus, bias, fold,
                                                    block, nblocks);
     else

@@ -223,3 +223,23 @@ def test_tiled_kernel_min_rows():
     # shapes that never use the tiled kernel
     assert moe.moe_tiled_kernel_min_rows(shape(T=64), [10] * 8) == 0
     assert moe.moe_tiled_kernel_min_rows(shape(T=4096, dtype="f32"), [512] * 8) == 0
+
+
+def test_tiled_kernel_min_rows_half_tiles():
+    """Experts of 65 ... 127 rows next to a large one join the tiled kernel while the half-sized (128-row) tiles of both are at
+    most one round of 256 blocks in the wider product (d_ff / 128 column tiles), however few large tiles there are."""
+    def line(s, rows):
+        return moe.moe_tiled_kernel_min_rows(s, rows + [0] * (s.E - len(rows)))
+    s = shape(T=4096, d_model=1024, d_ff=4096, E=32, k=1)            # 32 column tiles: 8 half-sized tiles
+    assert line(s, [128] + [100] * 7) == 65
+    assert line(s, [128] + [100] * 8) == 128
+    assert line(s, [128] + [100] * 7 + [64] * 20) == 65              # up to 64 rows they are no tiles of that kernel
+    assert line(s, [129] + [100] * 6) == 65                          # a large expert's second half-sized tile counts
+    assert line(s, [129] + [100] * 7) == 128
+    assert line(s, [100] * 8) == 128                                 # no large expert: the tiled kernel would run for them alone
+    s = shape(T=4096, d_model=8192, d_ff=1024, E=32, k=1)            # the wider product is the second: 4 tiles
+    assert line(s, [200, 65, 65]) == 65
+    assert line(s, [200, 65, 65, 65]) == 128
+    s = shape(T=4096, d_model=96, d_ff=384, E=128, k=1)              # 3 column tiles: 85
+    assert line(s, [128] + [70] * 84) == 65
+    assert line(s, [128] + [70] * 85) == 128
