@@ -149,30 +149,36 @@ __host__ __device__ inline int route_row_stride(int E, int NF) { return (E + 16 
 // Routing of a chunk of tokens by one block: logits into LDS, softmax and top-k there, and the chunk's histogram to
 // chunk_hist[chunk * E + e].
 //
-// route_bf16_kernel<TF, NF>: chunk = 16 * TF tokens, 4 wavefronts, experts 16 * NF at a time.  MFMA 16x16x32 with gate rows
-// as the A operand and token rows as the B operand (a lane ends up with 4 consecutive experts of one token); a wavefront
-// owns NF / 4 fragments of experts for all the chunk's tokens.  Rows of both operands go through a ring of LDS stages, 64 k
+// route_bf16_kernel<TF, NF, STAGES, KSPLIT>: chunk = 16 * TF tokens, 4 wavefronts, experts 16 * NF at a time.  MFMA 16x16x32
+// with gate rows as the A operand and token rows as the B operand (a lane ends up with 4 consecutive experts of one token);
+// a wavefront owns NF / 4 fragments of experts for all the chunk's tokens.  Rows of both operands go through a ring of LDS stages, 64 k
 // = one 128-byte line of every row per stage, copied by eight consecutive lanes each.  (Loaded straight into operand form,
 // 16 consecutive lanes touch 16 different rows: 64 cache accesses per load instruction instead of 16, which bounded the
-// kernel; neither more loads in flight nor more wavefronts changed it.)  The 16-byte pieces of a row are permuted by its row
-// number, so that the rows a read touches at once lie in different banks.  The contraction runs in four chains per
-// accumulator, which are added at the end.
+// kernel; neither more loads in flight nor more wavefronts changed it, nor do more stages than four.)  The 16-byte pieces of
+// a row are permuted by its row number, so that the rows a read touches at once lie in different banks.  The contraction runs
+// in four chains per accumulator, which are added at the end.
+// KSPLIT = 4: every wavefront takes all the experts for a quarter of the contraction, through a ring of its own (no barriers),
+// and the quarters are added in LDS in order.
 // DIRECT: x and w_gate are 16-byte aligned and the copies go straight into LDS.  Otherwise (a view into a larger buffer) they
 // go through registers: ordinary loads take any alignment, the copy instruction is only documented for whole dwords.
-// Dynamic LDS: the ring, then logits [16 * TF][route_row_stride(E, NF)] floats, then the histogram [E] ints.
+// Dynamic LDS: the ring or rings, then logits [16 * TF][route_row_stride(E, NF)] floats, then the histogram [E] ints.
 // ---------------------------------------------------------------------------
 typedef uint32_t u32x4_any __attribute__((ext_vector_type(4), aligned(2)));
 constexpr int kRouteWaves = 4;
-template <int TF, int NF>
+template <int TF, int NF, int STAGES, int KSPLIT>
 struct RouteRing {
-    static constexpr int kRows = (16 * (TF + NF) + 31) / 32 * 32;      // whole copies for every wavefront
+    static constexpr int kWaves = kRouteWaves / KSPLIT;                // wavefronts that share a ring
+    static constexpr int kRows = (16 * (TF + NF) + 8 * kWaves - 1) / (8 * kWaves) * (8 * kWaves);     // whole copies for each
     static constexpr int kStageBytes = kRows * 128;
-    static constexpr int kCopies = kRows / 32;                         // per wavefront and stage, 8 rows each
-    static constexpr int kStages = 4;
-    static constexpr int kBytes = kStages * kStageBytes;
+    static constexpr int kCopies = kRows / (8 * kWaves);               // per wavefront and stage, 8 rows each
+    static constexpr int kRingBytes = STAGES * kStageBytes;
+    static constexpr int kBytes = KSPLIT * kRingBytes;
+    // s_waitcnt operand that lets all but two stages' worth of a wavefront's copies be in flight (vmcnt: bits 3:0 and 15:14)
+    static constexpr int kInFlight = (STAGES - 2) * kCopies;
+    static constexpr int kWait = 0x0F70 | (kInFlight & 15) | (kInFlight >> 4) << 14;
 };
 
-template <int TF, int NF, bool DIRECT>
+template <int TF, int NF, int STAGES, int KSPLIT, bool DIRECT>
 __global__ __launch_bounds__(kRouteWaves * 64) void route_bf16_kernel(const uint16_t* __restrict__ x,
                                                                       const uint16_t* __restrict__ wg,
                                                                       const float* __restrict__ bias,
@@ -180,9 +186,9 @@ __global__ __launch_bounds__(kRouteWaves * 64) void route_bf16_kernel(const uint
                                                                       float* __restrict__ topk_w, float* __restrict__ margin,
                                                                       int32_t* __restrict__ chunk_hist, int T, int d, int E,
                                                                       int k, int renorm) {
-    using Ring = RouteRing<TF, NF>;
-    constexpr int TOK = 16 * TF, NW = kRouteWaves, NT = NW * 64, FPW = NF / NW, S = Ring::kStages, P = Ring::kCopies;
-    static_assert(NF % NW == 0, "whole fragments of experts per wavefront");
+    using Ring = RouteRing<TF, NF, STAGES, KSPLIT>;
+    constexpr int TOK = 16 * TF, NW = kRouteWaves, NT = NW * 64, RW = Ring::kWaves, FPW = NF / RW, S = STAGES, P = Ring::kCopies;
+    static_assert(NF % RW == 0, "whole fragments of experts per wavefront");
     extern __shared__ __attribute__((aligned(16))) unsigned char route_lds[];
     const int Ep = route_row_stride(E, NF);
     float* L = reinterpret_cast<float*>(route_lds + Ring::kBytes);
@@ -192,17 +198,22 @@ __global__ __launch_bounds__(kRouteWaves * 64) void route_bf16_kernel(const uint
     const int t0 = blockIdx.x * TOK;
     for (int e = threadIdx.x; e < E; e += NT) hist[e] = 0;
 
-    const int ksteps = d >> 5, nstages = (ksteps + 1) >> 1;
-    const uint32_t ring0 = lds_address(route_lds);
-    // copies: this wavefront's p-th takes the rows 8 * (wave + NW * p) ... + 7 of a stage, tokens first
+    // the ring's stages of the contraction: all of them, or this wavefront's share
+    static_assert(KSPLIT == 1 || RW == 1, "one ring, or one per wavefront");
+    const int rw = KSPLIT == 1 ? wave : 0, part = KSPLIT == 1 ? 0 : wave;
+    const int per_ring = (((d >> 5) + 1) / 2 + KSPLIT - 1) / KSPLIT;
+    const int j0 = part * per_ring, ksteps = (d >> 5) - 2 * j0, nstages = min((ksteps + 1) >> 1, per_ring);     // <= 0: none
+    unsigned char* ring = route_lds + part * Ring::kRingBytes;
+    const uint32_t ring0 = lds_address(ring);
+    // copies: this wavefront's p-th takes the rows 8 * (rw + RW * p) ... + 7 of a stage, tokens first
     const int piece = (lane & 7) ^ (lane >> 3);
     for (int ec = 0; ec < E; ec += 16 * NF) {
         const uint16_t* src[P];
 #pragma unroll
         for (int p = 0; p < P; ++p) {
-            const int row = 8 * (wave + NW * p) + (lane >> 3);
-            src[p] = row < TOK ? x + static_cast<size_t>(min(t0 + row, T - 1)) * d
-                               : wg + static_cast<size_t>(min(ec + row - TOK, E - 1)) * d;
+            const int row = 8 * (rw + RW * p) + (lane >> 3);
+            src[p] = (row < TOK ? x + static_cast<size_t>(min(t0 + row, T - 1)) * d
+                                : wg + static_cast<size_t>(min(ec + row - TOK, E - 1)) * d) + j0 * 64;
         }
         auto stage_in = [&](int j) {
             // a last stage of one 32-k step: its second half is read again from the first, and not used
@@ -211,10 +222,10 @@ __global__ __launch_bounds__(kRouteWaves * 64) void route_bf16_kernel(const uint
 #pragma unroll
             for (int p = 0; p < P; ++p) {
                 if constexpr (DIRECT) {
-                    copy16_to_lds(src[p] + j * 64 + q * 8, base + (wave + NW * p) * 1024);
+                    copy16_to_lds(src[p] + j * 64 + q * 8, base + (rw + RW * p) * 1024);
                 } else {
                     const u32x4_any v = *reinterpret_cast<const u32x4_any*>(src[p] + j * 64 + q * 8);
-                    *reinterpret_cast<uint4*>(route_lds + (j % S) * Ring::kStageBytes + (wave + NW * p) * 1024 + lane * 16) =
+                    *reinterpret_cast<uint4*>(ring + (j % S) * Ring::kStageBytes + (rw + RW * p) * 1024 + lane * 16) =
                         uint4{v[0], v[1], v[2], v[3]};
                 }
             }
@@ -237,18 +248,19 @@ __global__ __launch_bounds__(kRouteWaves * 64) void route_bf16_kernel(const uint
             first[nf] = f32x4{0.f, 0.f, 0.f, 0.f};
             if (bias != nullptr) {
 #pragma unroll
-                for (int i = 0; i < 4; ++i) first[nf][i] = bias[min(ec + (wave * FPW + nf) * 16 + g * 4 + i, E - 1)];
+                for (int i = 0; i < 4; ++i) first[nf][i] = bias[min(ec + (rw * FPW + nf) * 16 + g * 4 + i, E - 1)];
             }
         }
         auto step = [&](int j, auto parity) {
             constexpr int C = 2 * decltype(parity)::value;
             // Stage j has landed for every wavefront, and nobody reads stage j - 1 any more: the reads are waited for here,
             // because nothing else keeps the matrix instructions that consume them in front of the barrier.
-            if (j + S - 2 < nstages) __builtin_amdgcn_s_waitcnt(0x0F70 | ((S - 2) * P));
+            if (j + S - 2 < nstages) __builtin_amdgcn_s_waitcnt(Ring::kWait);
             else __builtin_amdgcn_s_waitcnt(0x0F70);
-            asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+            if constexpr (RW > 1) asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+            else asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
             if (j + S - 1 < nstages) stage_in(j + S - 1);
-            const unsigned char* st = route_lds + (j % S) * Ring::kStageBytes;
+            const unsigned char* st = ring + (j % S) * Ring::kStageBytes;
             const int halves = 2 * j + 1 < ksteps ? 2 : 1;
 #pragma unroll
             for (int h = 0; h < 2; ++h) {
@@ -257,7 +269,7 @@ __global__ __launch_bounds__(kRouteWaves * 64) void route_bf16_kernel(const uint
                 bf16x8 a[FPW], b[TF];
 #pragma unroll
                 for (int nf = 0; nf < FPW; ++nf)
-                    a[nf] = *reinterpret_cast<const bf16x8*>(st + (TOK + (wave * FPW + nf) * 16) * 128 + at);
+                    a[nf] = *reinterpret_cast<const bf16x8*>(st + (TOK + (rw * FPW + nf) * 16) * 128 + at);
 #pragma unroll
                 for (int tf = 0; tf < TF; ++tf) b[tf] = *reinterpret_cast<const bf16x8*>(st + tf * 16 * 128 + at);
 #pragma unroll
@@ -279,11 +291,18 @@ __global__ __launch_bounds__(kRouteWaves * 64) void route_bf16_kernel(const uint
         asm volatile("s_nop 7\n\ts_nop 7");
         __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-        for (int nf = 0; nf < FPW; ++nf)
+        for (int q = 0; q < KSPLIT; ++q) {                 // shares of the contraction in order
+            if (part == q) {
 #pragma unroll
-            for (int tf = 0; tf < TF; ++tf)
-                *reinterpret_cast<f32x4*>(L + (tf * 16 + r) * Ep + ec + (wave * FPW + nf) * 16 + g * 4) =
-                    (first[nf] + acc[0][nf][tf]) + acc[1][nf][tf] + (acc[2][nf][tf] + acc[3][nf][tf]);
+                for (int nf = 0; nf < FPW; ++nf)
+#pragma unroll
+                    for (int tf = 0; tf < TF; ++tf) {
+                        f32x4* p = reinterpret_cast<f32x4*>(L + (tf * 16 + r) * Ep + ec + (rw * FPW + nf) * 16 + g * 4);
+                        *p = ((q == 0 ? first[nf] : *p) + acc[0][nf][tf]) + acc[1][nf][tf] + (acc[2][nf][tf] + acc[3][nf][tf]);
+                    }
+            }
+            if (q + 1 < KSPLIT) __syncthreads();
+        }
     }
     __syncthreads();
 
@@ -645,21 +664,26 @@ hipError_t launch_mask_out(const uint8_t* mask_or_null, uint8_t* dst, int E, hip
 // Tokens per routing block and fragments of experts taken at a time, from the shape alone.  More tokens per block read the
 // gate matrix fewer times, as long as the chip is one round of blocks: with 313 blocks of 16 tokens on 256 CUs, 5003 tokens
 // took 42 us, with 157 of 32 tokens 31 us (128 experts, d = 2048, an earlier form of the kernel).
+// Two fragments (up to 32 experts) mean that the wavefronts split the contraction, each with a ring of its own: side by side
+// in one ring, two or three of them would work on experts that do not exist, and every stage waits for the block.  That pays
+// from d = 1024 on (16 experts, tokens x d, with dispatch: 1000 x 2048 14.9 -> 11.2 us, 1000 x 4096 21.4 -> 13.2, 8300 x 2048 22.7 ->
+// 18.9, 8300 x 768 15.9 -> 16.1); past 64 tokens per CU two blocks of 64 tokens share a CU and hide it (20000 x 2048 38 against 28 us).
 struct RouteCfg { int tok, nf; };
 static RouteCfg route_cfg(const moe_shape& s) {
     RouteCfg c{16, 1};
     if (s.dtype != MOE_BF16) return c;
-    c.nf = s.E > 64 ? 8 : 4;
+    const int cus = device_cu_count();
+    c.nf = s.E > 64 ? 8 : (s.E > 32 || s.d_model < 1024 || s.T > 64 * cus ? 4 : 2);
     if (route_is_split(s)) return c;                       // the split path works in chunks of 16 tokens
-    if (s.T > 32 * device_cu_count() && s.E <= 128) c.tok = 64;
-    else if (s.T > 16 * device_cu_count() && s.E <= 256) c.tok = 32;
+    if (s.T > 32 * cus && s.E <= 128) c.tok = 64;
+    else if (s.T > 16 * cus && s.E <= 256) c.tok = 32;
     return c;
 }
 
 int route_chunk_tokens(const moe_shape& s) { return route_cfg(s).tok; }
 
-// Most dynamic LDS a routing kernel asks for: a ring of 4 stages of 160 rows (80 KiB) next to the logits of 16 tokens x
-// 1024 experts and the histogram.
+// Most dynamic LDS a routing kernel asks for: four rings of three stages of 96 rows (144 KiB) next to the logits of 64 tokens
+// x 32 experts, or one of four stages of 160 rows (80 KiB) next to those of 16 tokens x 1024 experts; and the histogram.
 constexpr size_t kRouteLdsMax = kLdsPerCu;
 
 template <typename ST>
@@ -678,12 +702,14 @@ static hipError_t launch_route_kernel(RouteKernel<ST> kern, int tok, int nf, siz
     return hipGetLastError();
 }
 
-template <int TF, int NF>
+template <int TF, int NF, int STAGES, int KSPLIT>
 static hipError_t launch_route_bf16(const moe_shape& s, const void* x, const void* w_gate, const float* bias, int32_t* idx,
                                     float* gate, float* margin, int32_t* chunk_hist, hipStream_t st) {
-    const bool aligned = ((reinterpret_cast<uintptr_t>(x) | reinterpret_cast<uintptr_t>(w_gate)) & 15) == 0;     // rows are 64 k bytes
-    return launch_route_kernel<uint16_t>(aligned ? route_bf16_kernel<TF, NF, true> : route_bf16_kernel<TF, NF, false>, 16 * TF, NF,
-                                         RouteRing<TF, NF>::kBytes, s, x, w_gate, bias, idx, gate, margin, chunk_hist, st);
+    // whole rows are multiples of 64 bytes
+    const bool aligned = ((reinterpret_cast<uintptr_t>(x) | reinterpret_cast<uintptr_t>(w_gate)) & 15) == 0;
+    auto kern = aligned ? route_bf16_kernel<TF, NF, STAGES, KSPLIT, true> : route_bf16_kernel<TF, NF, STAGES, KSPLIT, false>;
+    return launch_route_kernel<uint16_t>(kern, 16 * TF, NF, RouteRing<TF, NF, STAGES, KSPLIT>::kBytes, s, x, w_gate, bias, idx,
+                                         gate, margin, chunk_hist, st);
 }
 
 template <typename Kernel>
@@ -692,10 +718,10 @@ static hipError_t configure_route(Kernel kern) {
                                static_cast<int>(kRouteLdsMax));
 }
 
-template <int TF, int NF>
+template <int TF, int NF, int STAGES, int KSPLIT>
 static hipError_t configure_route_bf16() {
-    const hipError_t e = configure_route(route_bf16_kernel<TF, NF, true>);
-    return e != hipSuccess ? e : configure_route(route_bf16_kernel<TF, NF, false>);
+    const hipError_t e = configure_route(route_bf16_kernel<TF, NF, STAGES, KSPLIT, true>);
+    return e != hipSuccess ? e : configure_route(route_bf16_kernel<TF, NF, STAGES, KSPLIT, false>);
 }
 
 // Few tokens (a decode step): the gate product is one skinny GEMM whose cost is reading the gate weights, and
@@ -874,12 +900,16 @@ constexpr size_t kTopkFinalizeLdsMax = static_cast<size_t>(64) * (kTopkFinalizeM
 hipError_t configure_route_kernels(int) {
     hipError_t e;
     if ((e = configure_route(route_f32_kernel)) != hipSuccess) return e;
-    if ((e = configure_route_bf16<1, 4>()) != hipSuccess) return e;
-    if ((e = configure_route_bf16<2, 4>()) != hipSuccess) return e;
-    if ((e = configure_route_bf16<4, 4>()) != hipSuccess) return e;
-    if ((e = configure_route_bf16<1, 8>()) != hipSuccess) return e;
-    if ((e = configure_route_bf16<2, 8>()) != hipSuccess) return e;
-    if ((e = configure_route_bf16<4, 8>()) != hipSuccess) return e;
+    if ((e = configure_route_bf16<1, 4, 4, 1>()) != hipSuccess) return e;
+    if ((e = configure_route_bf16<2, 4, 4, 1>()) != hipSuccess) return e;
+    if ((e = configure_route_bf16<4, 4, 4, 1>()) != hipSuccess) return e;
+    if ((e = configure_route_bf16<4, 4, 3, 1>()) != hipSuccess) return e;
+    if ((e = configure_route_bf16<1, 2, 4, 4>()) != hipSuccess) return e;
+    if ((e = configure_route_bf16<2, 2, 4, 4>()) != hipSuccess) return e;
+    if ((e = configure_route_bf16<4, 2, 3, 4>()) != hipSuccess) return e;
+    if ((e = configure_route_bf16<1, 8, 4, 1>()) != hipSuccess) return e;
+    if ((e = configure_route_bf16<2, 8, 4, 1>()) != hipSuccess) return e;
+    if ((e = configure_route_bf16<4, 8, 4, 1>()) != hipSuccess) return e;
     if ((e = configure_route(route_topk_kernel)) != hipSuccess) return e;
     return hipFuncSetAttribute(reinterpret_cast<const void*>(route_topk_finalize_kernel),
                                hipFuncAttributeMaxDynamicSharedMemorySize, static_cast<int>(kTopkFinalizeLdsMax));
@@ -909,12 +939,20 @@ hipError_t launch_route_fused(const moe_shape& s, const void* x, const void* w_g
         return launch_route_small(s, x, w_gate, bias, idx, gate, margin, chunk_hist, gate_part_ws, st);
     const RouteCfg c = route_cfg(s);
     switch (c.tok + c.nf) {
-        case 64 + 8: return launch_route_bf16<4, 8>(s, x, w_gate, bias, idx, gate, margin, chunk_hist, st);
-        case 32 + 8: return launch_route_bf16<2, 8>(s, x, w_gate, bias, idx, gate, margin, chunk_hist, st);
-        case 16 + 8: return launch_route_bf16<1, 8>(s, x, w_gate, bias, idx, gate, margin, chunk_hist, st);
-        case 64 + 4: return launch_route_bf16<4, 4>(s, x, w_gate, bias, idx, gate, margin, chunk_hist, st);
-        case 32 + 4: return launch_route_bf16<2, 4>(s, x, w_gate, bias, idx, gate, margin, chunk_hist, st);
-        default: return launch_route_bf16<1, 4>(s, x, w_gate, bias, idx, gate, margin, chunk_hist, st);
+        case 64 + 8: return launch_route_bf16<4, 8, 4, 1>(s, x, w_gate, bias, idx, gate, margin, chunk_hist, st);
+        case 32 + 8: return launch_route_bf16<2, 8, 4, 1>(s, x, w_gate, bias, idx, gate, margin, chunk_hist, st);
+        case 16 + 8: return launch_route_bf16<1, 8, 4, 1>(s, x, w_gate, bias, idx, gate, margin, chunk_hist, st);
+        case 64 + 2: return launch_route_bf16<4, 2, 3, 4>(s, x, w_gate, bias, idx, gate, margin, chunk_hist, st);
+        case 32 + 2: return launch_route_bf16<2, 2, 4, 4>(s, x, w_gate, bias, idx, gate, margin, chunk_hist, st);
+        case 16 + 2: return launch_route_bf16<1, 2, 4, 4>(s, x, w_gate, bias, idx, gate, margin, chunk_hist, st);
+        case 64 + 4:
+            // more than a round of blocks: three stages, so that two blocks fit a CU (8 experts, 20000 x 768 26.5 -> 19.0 us); up to
+            // a round, four (8300 x 768 16.5 -> 15.9)
+            if (s.T > 64 * device_cu_count())
+                return launch_route_bf16<4, 4, 3, 1>(s, x, w_gate, bias, idx, gate, margin, chunk_hist, st);
+            return launch_route_bf16<4, 4, 4, 1>(s, x, w_gate, bias, idx, gate, margin, chunk_hist, st);
+        case 32 + 4: return launch_route_bf16<2, 4, 4, 1>(s, x, w_gate, bias, idx, gate, margin, chunk_hist, st);
+        default: return launch_route_bf16<1, 4, 4, 1>(s, x, w_gate, bias, idx, gate, margin, chunk_hist, st);
     }
 }
 

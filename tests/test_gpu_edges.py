@@ -130,7 +130,8 @@ def route_against_oracle(moe, T, d, E, k, x_at=0, wg_at=0, seed=0):
         return flat[at:at + a.size].view(a.shape)
 
     shape = moe.make_shape(T, d, 32, E, k, "bf16", True)
-    idx, w, margin = torch.empty((T, k), dtype=torch.int32, device="cuda"), torch.empty((T, k), device="cuda"), torch.empty(T, device="cuda")
+    idx = torch.empty((T, k), dtype=torch.int32, device="cuda")
+    w, margin = torch.empty((T, k), device="cuda"), torch.empty(T, device="cuda")
     counts, offsets = (torch.empty(n, dtype=torch.int32, device="cuda") for n in (E, E + 1))
     ws = torch.full((moe.moe_workspace_bytes(shape),), 0xFF, dtype=torch.uint8, device="cuda")
     moe.moe_route(shape, dev(x, x_at), dev(wg, wg_at), torch.from_numpy(b).cuda(), idx, w, margin, counts, offsets, -1, None, ws)
@@ -146,8 +147,12 @@ def route_against_oracle(moe, T, d, E, k, x_at=0, wg_at=0, seed=0):
 
 # bf16 routing: every form of the kernel (16, 32 or 64 tokens by 64 or 128 experts at a time; on 256 CUs 32 tokens from 4097
 # tokens on and 64 from 8193), ragged token counts, contractions that go round the ring of four stages of 64 k more than once
-# and end in half a stage, one that is half a stage, expert counts that take a second pass, and the few-token path
-@pytest.mark.parametrize("T,d,E,k", [(65, 352, 60, 2), (700, 320, 129, 4), (300, 608, 1024, 8), (4100, 352, 60, 2), (5003, 352, 128, 2),
+# and end in half a stage, one that is half a stage, expert counts that take a second pass, and the few-token path; up to 32
+# experts from d = 1024 on, where the wavefronts share the contraction (equally, unequally, with a half stage in the last share),
+# and more than 64 tokens per CU
+@pytest.mark.parametrize("T,d,E,k", [(65, 1024, 32, 2), (700, 1056, 9, 1), (4100, 1120, 17, 2), (8192, 1184, 3, 2), (8300, 1056, 31, 4),
+                                     (17000, 1024, 8, 1), (17000, 160, 40, 2), (65, 352, 60, 2), (700, 320, 129, 4),
+                                     (300, 608, 1024, 8), (4100, 352, 60, 2), (5003, 352, 128, 2),
                                      (4500, 352, 200, 3), (8192, 96, 64, 1), (8300, 352, 40, 2), (8300, 544, 128, 2),
                                      (8300, 352, 200, 1), (9000, 32, 20, 2), (33, 352, 60, 2), (64, 96, 300, 2)])
 def test_bf16_route(gpu_lib, T, d, E, k):
@@ -158,7 +163,7 @@ def test_bf16_route(gpu_lib, T, d, E, k):
 # the same from operands that are views into larger buffers, 2, 4 and 8 bytes off a 16-byte line
 @pytest.mark.parametrize("x_at,wg_at", [(0, 1), (4, 0), (1, 2)])
 @pytest.mark.parametrize("T,d,E,k", [(70, 352, 60, 2), (700, 320, 129, 4), (4100, 352, 60, 2), (5003, 96, 128, 2), (8300, 352, 40, 2),
-                                     (8300, 32, 100, 1), (33, 96, 60, 2)])
+                                     (8300, 32, 100, 1), (33, 96, 60, 2), (300, 1056, 30, 2), (4100, 1120, 8, 1), (8300, 1056, 12, 2)])
 def test_bf16_route_unaligned(gpu_lib, T, d, E, k, x_at, wg_at):
     say(f"[case] bf16 route T={T} d={d} E={E}, operands {x_at} and {wg_at} elements off")
     route_against_oracle(gpu_lib, T, d, E, k, x_at, wg_at)
