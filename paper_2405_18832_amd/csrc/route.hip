@@ -759,7 +759,7 @@ __global__ __launch_bounds__(64) void gate_partial_kernel(const uint16_t* __rest
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
         const int e = nb * 16 + g * 4 + i;
-        if (t < T && e < E) dst[e] = acc[i];               // rows of padding are not read again
+        if (t < T && e < E) dst[e] = acc[i];               // rows of padding are not read
     }
 }
 
@@ -777,15 +777,16 @@ __global__ __launch_bounds__(256) void route_topk_kernel(const float* __restrict
     const int t0 = blockIdx.x * 16;
     for (int e = threadIdx.x; e < E; e += 256) hist[e] = 0;
     // 4 logits per thread and pass: their 4 * kGateSplit partial sums are loaded before any is added (a wait
-    // per logit otherwise: this kernel is two blocks of pure latency on the decode path)
-    for (int i0 = threadIdx.x; i0 < 16 * E; i0 += 4 * 256) {
+    // per logit otherwise: this kernel is two blocks of pure latency on the decode path).  Only the rows of tokens that exist
+    // have been written.
+    const int logits = min(16, T - t0) * E;
+    for (int i0 = threadIdx.x; i0 < logits; i0 += 4 * 256) {
         float p[4][kGateSplit];
         float b[4];
 #pragma unroll
         for (int u = 0; u < 4; ++u) {
-            const int i = min(i0 + u * 256, 16 * E - 1);   // past the end: re-read, not stored
-            const int tl = i / E, e = i - tl * E;
-            const int t = min(t0 + tl, Tpad - 1);
+            const int i = min(i0 + u * 256, logits - 1);   // past the end: re-read, not stored
+            const int tl = i / E, e = i - tl * E, t = t0 + tl;
             b[u] = bias ? bias[e] : 0.f;
 #pragma unroll
             for (int ks = 0; ks < kGateSplit; ++ks) p[u][ks] = part[(static_cast<size_t>(ks) * Tpad + t) * E + e];
@@ -793,7 +794,7 @@ __global__ __launch_bounds__(256) void route_topk_kernel(const float* __restrict
 #pragma unroll
         for (int u = 0; u < 4; ++u) {
             const int i = i0 + u * 256;
-            if (i >= 16 * E) break;
+            if (i >= logits) break;
             const int tl = i / E, e = i - tl * E;
             float s = b[u];
 #pragma unroll
