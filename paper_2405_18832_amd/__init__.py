@@ -136,8 +136,12 @@ def _nbytes(t) -> int:
 def _stream(stream) -> Optional[int]:
     if stream is None:
         import torch
-        # the handle itself: building a torch.cuda.Stream around it takes 2.7 us, a tenth of a small layer's host time
-        return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device()) or None
+        # the handle itself: building a torch.cuda.Stream around it takes 2.7 us, a tenth of a small layer's host time; the
+        # call is not part of torch's public interface, so a torch without it goes the long way
+        raw = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+        if raw is not None:
+            return raw(torch.cuda.current_device()) or None
+        stream = torch.cuda.current_stream()
     if isinstance(stream, int):
         return stream or None
     return stream.cuda_stream or None

@@ -243,3 +243,19 @@ def test_tiled_kernel_min_rows_half_tiles():
     s = shape(T=4096, d_model=96, d_ff=384, E=128, k=1)              # 3 column tiles: 85
     assert line(s, [128] + [70] * 84) == 65
     assert line(s, [128] + [70] * 85) == 128
+
+
+@pytest.mark.parametrize("private", [True, False])
+def test_current_stream_handle(monkeypatch, private):
+    """The default stream argument: torch's raw handle of the current device's stream, or the public way where torch has none."""
+    import types
+
+    import torch
+    monkeypatch.setattr(torch.cuda, "current_device", lambda: 3)
+    monkeypatch.setattr(torch.cuda, "current_stream", lambda: types.SimpleNamespace(cuda_stream=0x40))
+    if private:
+        monkeypatch.setattr(torch._C, "_cuda_getCurrentRawStream", lambda dev: 0x10 * dev, raising=False)
+    else:
+        monkeypatch.delattr(torch._C, "_cuda_getCurrentRawStream", raising=False)
+    assert moe._stream(None) == (0x30 if private else 0x40)
+    assert moe._stream(types.SimpleNamespace(cuda_stream=0)) is None and moe._stream(0x50) == 0x50
