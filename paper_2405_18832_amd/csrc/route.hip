@@ -79,6 +79,10 @@ __device__ __forceinline__ void topk_row(float* __restrict__ row, int E, int k, 
         better(row_rot<2>(bv), row_rot<2>(bi));
         better(row_rot<1>(bv), row_rot<1>(bi));
         bi = min(bi, E - 1);          // NaN logits must not produce an out-of-range expert
+        if constexpr (V == 0) {       // lanes that hold a NaN see another winner: the first lane's counts, which retires it below
+            bv = __shfl(bv, 0, 16);
+            bi = __shfl(bi, 0, 16);
+        }
         if (j == 0) {
             vmax = bv;
             float part = 0.f;

@@ -160,6 +160,33 @@ def test_bf16_route(gpu_lib, T, d, E, k):
     route_against_oracle(gpu_lib, T, d, E, k)
 
 
+# a token whose logits are all NaN: no maximum exists, every slot holds expert 0 and a NaN weight, whatever the number of
+# experts (64, 128 and 256 are kept in registers, more are not), and other tokens are as without it
+@pytest.mark.parametrize("T,E", [(40, 20), (40, 100), (40, 200), (40, 300), (100, 100), (100, 300)])
+def test_nan_token(gpu_lib, T, E):
+    say(f"[case] NaN token T={T} E={E}")
+    moe, d, k, bad = gpu_lib, 64, 3, 7
+    gen = torch.Generator(device="cuda").manual_seed(E)
+    x, wg = (torch.randn((n, d), device="cuda", generator=gen).to(torch.bfloat16) for n in (T, E))
+    shape = moe.make_shape(T, d, 32, E, k, "bf16", False)
+    ws = torch.empty(moe.moe_workspace_bytes(shape), dtype=torch.uint8, device="cuda")
+
+    def route(x):
+        idx, w = torch.empty((T, k), dtype=torch.int32, device="cuda"), torch.empty((T, k), device="cuda")
+        counts, offsets = (torch.empty(n, dtype=torch.int32, device="cuda") for n in (E, E + 1))
+        moe.moe_route(shape, x, wg, None, idx, w, None, counts, offsets, -1, None, ws)
+        torch.cuda.synchronize()
+        assert torch.equal(counts.cpu().long(), torch.bincount(idx.cpu().flatten().long(), minlength=E))
+        return idx, w
+
+    idx, w = route(x)
+    x[bad, 5] = float("nan")
+    idx2, w2 = route(x)
+    assert idx2[bad].tolist() == [0] * k and bool(torch.isnan(w2[bad]).all())
+    others = torch.arange(T, device="cuda") != bad
+    assert torch.equal(idx[others], idx2[others]) and torch.equal(w[others], w2[others])
+
+
 # the same from operands that are views into larger buffers, 2, 4 and 8 bytes off a 16-byte line
 @pytest.mark.parametrize("x_at,wg_at", [(0, 1), (4, 0), (1, 2)])
 @pytest.mark.parametrize("T,d,E,k", [(70, 352, 60, 2), (700, 320, 129, 4), (4100, 352, 60, 2), (5003, 96, 128, 2), (8300, 352, 40, 2),
