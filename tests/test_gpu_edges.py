@@ -16,8 +16,18 @@ def say(*a):
     print(*a, file=sys.stderr, flush=True)
 
 
-def ffn_rows(moe, rows, d, f, dtype, activation="relu", biases=False, seed=0, mask=None):
-    """moe_expert_ffn over experts with the given row counts; returns (y, the oracle's y at storage precision)."""
+def placed(a, at):
+    """The tensor `a`, or a copy of it that starts `at` elements into its allocation."""
+    if at == 0:
+        return a
+    flat = torch.empty(a.numel() + at, dtype=a.dtype, device=a.device)
+    flat[at:] = a.flatten()
+    return flat[at:].view(a.shape)
+
+
+def ffn_rows(moe, rows, d, f, dtype, activation="relu", biases=False, seed=0, mask=None, at=0):
+    """moe_expert_ffn over experts with the given row counts, tokens, weights and results `at` elements into their
+    allocations; returns (y, the oracle's y at storage precision)."""
     from paper_2405_18832_amd.device_layer import to_device
     E, A = len(rows), int(sum(rows))
     rng = np.random.default_rng([seed, d, f, E, A])
@@ -30,12 +40,12 @@ def ffn_rows(moe, rows, d, f, dtype, activation="relu", biases=False, seed=0, ma
     packed = []
     for which, w in ((1, w1), (2, w2)):
         src = dev(w, dtype)
-        packed.append(torch.empty_like(src))
+        packed.append(placed(torch.empty_like(src), at))
         moe.moe_pack_weights(shape, which, src, packed[-1])
-    y = torch.full((A, d), float("nan"), dtype=torch.float32, device="cuda")
+    y = placed(torch.full((A, d), float("nan"), dtype=torch.float32, device="cuda"), at)
     ws = torch.full((moe.moe_workspace_bytes(shape),), 0xFF, dtype=torch.uint8, device="cuda")
     m = None if mask is None else torch.tensor(mask, dtype=torch.uint8, device="cuda")
-    moe.moe_expert_ffn_biased(shape, dev(x, dtype), packed[0], dev(b1, "f32"), packed[1], dev(b2, "f32"),
+    moe.moe_expert_ffn_biased(shape, placed(dev(x, dtype), at), packed[0], dev(b1, "f32"), packed[1], dev(b2, "f32"),
                               torch.from_numpy(offsets).cuda(), m, y, ws)
     torch.cuda.synchronize()
     ref = np.full((A, d), np.nan)
@@ -63,6 +73,14 @@ def check(y, ref, tol):
 def test_f32_ffn_row_tiles(gpu_lib, d, f):
     say(f"[case] f32 ffn d={d} f={f}")
     check(*ffn_rows(gpu_lib, [1, 16, 0, 17, 33, 64, 65, 130], d, f, "f32", "gelu", biases=True), 1e-5)
+
+
+# the same from base addresses that are 4, 8 and 12 bytes off a 16-byte line, with row pitches of 16 bytes
+@pytest.mark.parametrize("at", [1, 2, 3])
+@pytest.mark.parametrize("d,f", [(20, 36), (128, 160)])
+def test_f32_ffn_unaligned(gpu_lib, d, f, at):
+    say(f"[case] f32 ffn d={d} f={f}, {at} elements off")
+    check(*ffn_rows(gpu_lib, [1, 17, 40, 64, 65], d, f, "f32", "gelu", biases=True, at=at), 1e-5)
 
 
 def test_f32_ffn_few_rows_masked(gpu_lib):
@@ -95,11 +113,8 @@ def test_f32_ffn_rounding(gpu_lib, d, f):
     assert err <= 1.05 * bar
 
 
-# fp32 routing: contraction remainders and expert counts around one fragment of 16
-@pytest.mark.parametrize("T,d,E", [(1, 7, 3), (17, 16, 16), (33, 50, 17), (40, 260, 40)])
-def test_f32_route(gpu_lib, T, d, E):
-    say(f"[case] f32 route T={T} d={d} E={E}")
-    moe, k = gpu_lib, 2
+def f32_route_against_oracle(moe, T, d, E, at=0):
+    k = 2
     rng = np.random.default_rng([T, d, E])
     x, wg = rng.standard_normal((T, d), dtype=np.float32), rng.standard_normal((E, d), dtype=np.float32)
     b = rng.standard_normal(E, dtype=np.float32)
@@ -108,13 +123,28 @@ def test_f32_route(gpu_lib, T, d, E):
     w, margin = torch.empty((T, k), device="cuda"), torch.empty(T, device="cuda")
     counts, offsets = (torch.empty(n, dtype=torch.int32, device="cuda") for n in (E, E + 1))
     ws = torch.empty(moe.moe_workspace_bytes(shape), dtype=torch.uint8, device="cuda")
-    moe.moe_route(shape, *(torch.from_numpy(a).cuda() for a in (x, wg, b)), idx, w, margin, counts, offsets, -1, None, ws)
+    x_dev, wg_dev = (placed(torch.from_numpy(a).cuda(), at) for a in (x, wg))
+    moe.moe_route(shape, x_dev, wg_dev, torch.from_numpy(b).cuda(), idx, w, margin, counts, offsets, -1, None, ws)
     torch.cuda.synchronize()
     r = orc.route(x, wg, b, k, True)
     ok = r["margin"] >= 1e-4
     assert np.array_equal(idx.cpu().numpy()[ok], r["idx"][ok])
     assert np.allclose(w.cpu().numpy()[ok], r["g"][ok], rtol=2e-4)
     assert np.array_equal(counts.cpu().numpy(), np.bincount(idx.cpu().numpy().ravel(), minlength=E))
+
+
+# fp32 routing: contraction remainders and expert counts around one fragment of 16
+@pytest.mark.parametrize("T,d,E", [(1, 7, 3), (17, 16, 16), (33, 50, 17), (40, 260, 40)])
+def test_f32_route(gpu_lib, T, d, E):
+    say(f"[case] f32 route T={T} d={d} E={E}")
+    f32_route_against_oracle(gpu_lib, T, d, E)
+
+
+# the same from base addresses that are 4 and 8 bytes off a 16-byte line
+@pytest.mark.parametrize("at", [1, 2])
+def test_f32_route_unaligned(gpu_lib, at):
+    say(f"[case] f32 route, operands {at} elements off")
+    f32_route_against_oracle(gpu_lib, 33, 64, 17, at)
 
 
 def route_against_oracle(moe, T, d, E, k, x_at=0, wg_at=0, seed=0):
@@ -124,11 +154,7 @@ def route_against_oracle(moe, T, d, E, k, x_at=0, wg_at=0, seed=0):
     wg = wl.round_to_storage(rng.standard_normal((E, d), dtype=np.float32) * np.float32(d ** -0.5), "bf16")
     b = rng.standard_normal(E, dtype=np.float32)
 
-    def dev(a, at):
-        flat = torch.empty(a.size + 64, dtype=torch.bfloat16, device="cuda")
-        flat[at:at + a.size] = torch.from_numpy(a).cuda().flatten().to(torch.bfloat16)
-        return flat[at:at + a.size].view(a.shape)
-
+    dev = lambda a, at: placed(torch.from_numpy(a).cuda().to(torch.bfloat16), at)
     shape = moe.make_shape(T, d, 32, E, k, "bf16", True)
     idx = torch.empty((T, k), dtype=torch.int32, device="cuda")
     w, margin = torch.empty((T, k), device="cuda"), torch.empty(T, device="cuda")
@@ -219,9 +245,12 @@ def test_unit_choice(gpu_lib, rows, d, f, act):
 
 
 # counting sort: one block, a block per 16 or 4 chunks, and slot bases through memory, at the sizes where one form gives way to
-# the next (4096 assignments for moe_permute; 256 experts; 64 k histogram entries or 1024 chunks), by itself and in the layer
+# the next (4096 assignments for moe_permute; 256 experts; 64 k histogram entries or 1024 chunks), by itself and in the layer.
+# Past 64 k entries: the layer with chunks of 16 tokens and 257 experts, moe_permute with chunks of 256 assignments and 1024
+# experts (placed from the caller's offsets).  70000 x 3 makes 1094 chunks in the layer.
 @pytest.mark.parametrize("T,E,k", [(1, 1, 1), (64, 256, 8), (64, 257, 2), (65, 256, 8), (2048, 40, 2), (2049, 40, 2),
-                                   (4000, 257, 3), (4096, 256, 1), (4112, 256, 1), (5000, 1024, 2), (70000, 3, 1)])
+                                   (4000, 257, 3), (4080, 257, 1), (4096, 256, 1), (4100, 257, 1), (4112, 256, 1), (5000, 1024, 2),
+                                   (16384, 1024, 1), (16641, 1024, 1), (70000, 3, 1)])
 def test_places(gpu_lib, T, E, k):
     say(f"[case] places T={T} E={E} k={k}")
     moe, d = gpu_lib, 32

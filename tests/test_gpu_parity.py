@@ -77,8 +77,9 @@ EXTRA = {
     "all_to_one": wl.MoEConfig("all_to_one", T=200, d_model=64, d_ff=128, E=8, k=1, dtype="bf16",
                                renormalize=False, seed=17, zipf_s=40.0),
     "switch_large_skew_matched": wl.matched_noise(wl.CONFIGS["switch_large_skew"]),
-    # token counts between the presets: the routing kernel's 32-tokens-per-block form (8192 ... 16383 tokens on a
-    # 256-CU device) and a top-1 layer of that size (folded output, tiled and streaming experts together)
+    # token counts between the presets: the routing kernel's 64-tokens-per-block form in less than a round of blocks
+    # (8193 ... 16383 tokens on a 256-CU device) and a top-1 layer of that size (folded output, tiled and streaming experts
+    # together)
     "tokens_8k": wl.MoEConfig("tokens_8k", T=8192 + 40, d_model=128, d_ff=256, E=96, k=2, dtype="bf16",
                               renormalize=True, seed=41, zipf_s=1.1, gate_std=0.3),
     # several full scheduling rounds of the tiled kernel, compared in full: about 65 row tiles x 8 column tiles
