@@ -180,65 +180,6 @@ __device__ __forceinline__ void store_folded_pair(uint16_t* out, int t, float w,
     __builtin_nontemporal_store(hi[1], q + 3);
 }
 
-// ---- outputs of the tiled product's 32 x 32 accumulators (v_mfma_f32_32x32x16_bf16) --------------------
-// Lane l of a wavefront holds, for token row l % 32 of the block, the output columns n0 + 8 q + 4 (l / 32) + i
-// in accumulator register 4 q + i (q, i = 0 ... 3): four groups of four consecutive columns.
-
-// First product: activation, bf16, into the blocked h.  The 32 columns of the block are one k-step group of h
-// (64 bytes per row).  After rounding, lanes l and l + 32 (same row) trade two of their four column groups with
-// v_permlane32_swap, which leaves the lower lane with columns 0 ... 15 and the upper lane with 16 ... 31: 32
-// contiguous bytes per lane, and the wavefront's two stores cover 2 KiB of consecutive rows.  Called by a whole
-// wavefront (no divergence around it); `row_ok`: the lane's row exists.
-template <int FIRST>
-__device__ __forceinline__ void store_h_block32(void* outp, int row, bool row_ok, int n0, int N, const float* bias,
-                                                const f32x16& acc) {
-    static_assert(FIRST != 0, "first product only");
-    constexpr int ACT = FIRST == kFirstGelu ? MOE_ACT_GELU : MOE_ACT_RELU;
-    const int L = (threadIdx.x & 63) >> 5;
-    uint32_t lo[4], hi[4];
-#pragma unroll
-    for (int q = 0; q < 4; ++q) {
-        f32x4 v = f32x4{acc[4 * q], acc[4 * q + 1], acc[4 * q + 2], acc[4 * q + 3]};
-        if (bias != nullptr) v += *reinterpret_cast<const f32x4*>(bias + n0 + 8 * q + 4 * L);
-        const f32x4 z = activate4<ACT>(v);
-        lo[q] = pack_bf16x2(z[0], z[1]);
-        hi[q] = pack_bf16x2(z[2], z[3]);
-    }
-    const auto s0 = __builtin_amdgcn_permlane32_swap(lo[0], lo[2], false, false);
-    const auto s1 = __builtin_amdgcn_permlane32_swap(hi[0], hi[2], false, false);
-    const auto s2 = __builtin_amdgcn_permlane32_swap(lo[1], lo[3], false, false);
-    const auto s3 = __builtin_amdgcn_permlane32_swap(hi[1], hi[3], false, false);
-    if (!row_ok) return;
-    uint4* q = reinterpret_cast<uint4*>(static_cast<uint16_t*>(outp) + h_index(row, n0 + 16 * L, N >> 5));
-    q[0] = uint4{s0[0], s1[0], s0[1], s1[1]};
-    q[1] = uint4{s2[0], s3[0], s2[1], s3[1]};
-}
-
-// Second product whose rows are the layer output (FoldOut): gate weight times the row, one rounding to bf16
-// (what the combine step does for a token with a single expert), the same lane exchange, 32 contiguous bytes
-// of out[t] per lane; not read again by the layer: non-temporal.
-__device__ __forceinline__ void store_folded_block32(uint16_t* out, int t, float w, bool row_ok, int n0, int N,
-                                                     const float* bias, const f32x16& acc) {
-    const int L = (threadIdx.x & 63) >> 5;
-    uint32_t lo[4], hi[4];
-#pragma unroll
-    for (int q = 0; q < 4; ++q) {
-        f32x4 v = f32x4{acc[4 * q], acc[4 * q + 1], acc[4 * q + 2], acc[4 * q + 3]};
-        if (bias != nullptr) v += *reinterpret_cast<const f32x4*>(bias + n0 + 8 * q + 4 * L);
-        lo[q] = pack_bf16x2(fmaf(w, v[0], 0.f), fmaf(w, v[1], 0.f));
-        hi[q] = pack_bf16x2(fmaf(w, v[2], 0.f), fmaf(w, v[3], 0.f));
-    }
-    const auto s0 = __builtin_amdgcn_permlane32_swap(lo[0], lo[2], false, false);
-    const auto s1 = __builtin_amdgcn_permlane32_swap(hi[0], hi[2], false, false);
-    const auto s2 = __builtin_amdgcn_permlane32_swap(lo[1], lo[3], false, false);
-    const auto s3 = __builtin_amdgcn_permlane32_swap(hi[1], hi[3], false, false);
-    if (!row_ok) return;
-    uint32_t* q = reinterpret_cast<uint32_t*>(out + static_cast<size_t>(t) * N + n0 + 16 * L);
-    const uint32_t v8[8] = {s0[0], s1[0], s0[1], s1[1], s2[0], s3[0], s2[1], s3[1]};
-#pragma unroll
-    for (int i = 0; i < 8; ++i) __builtin_nontemporal_store(v8[i], q + i);     // merged into two 16-byte stores
-}
-
 // Adds up the partial tiles that a tiled product of grid G left behind and writes the output rows.
 // Called by every thread of `nblocks` blocks of the following kernel, `block` being the caller's rank among
 // them.  A wavefront takes four consecutive rows of a
