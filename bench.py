@@ -77,15 +77,15 @@ class HipEvents:
 # HBM-side bytes per launch of the expert-FFN kernels, from rocprofv3 --pmc FETCH_SIZE / WRITE_SIZE runs
 # (summaries and commands: profiles/<workload>_full_layer.txt).  Valid only for the kernel sources they
 # were taken with: reported as null once one of the sources below has changed.
-TRAFFIC_SOURCES = {"ffn.hip": "3244c151d56e3a52", "ffn_tile.hip": "436f9bad48effd6a",
-                   "tile_schedule.hpp": "9fe1793c9c6ad92e", "common.hpp": "7306a852dfe63120"}
+TRAFFIC_SOURCES = {"ffn.hip": "e287ddaf173d7838", "ffn_tile.hip": "4e2254c6d6b31764",
+                   "tile_schedule.hpp": "825bbd1186462090", "common.hpp": "502c460aa16ad314"}
 TRAFFIC_BYTES = {
-    ("switch_base", "stream_w1"): 316526015, ("switch_base", "stream_w2"): 320342552,
-    ("switch_large_skew", "stream_w1"): 68335790, ("switch_large_skew", "stream_w2"): 141349222,
-    ("switch_large_skew", "tile_w1"): 90878013, ("switch_large_skew", "tile_w2"): 133077616,
-    ("nllb_decode", "stream_w1"): 1643615820, ("nllb_decode", "stream_w2"): 1645576598,
-    ("nllb_prefill_skew", "stream_w1"): 913815377, ("nllb_prefill_skew", "stream_w2"): 972053271,
-    ("nllb_prefill_skew", "tile_w1"): 2556990570, ("nllb_prefill_skew", "tile_w2"): 2389242192,
+    ("switch_base", "stream_w1"): 316691612, ("switch_base", "stream_w2"): 320477437,
+    ("switch_large_skew", "stream_w1"): 68377579, ("switch_large_skew", "stream_w2"): 68483072,
+    ("switch_large_skew", "tile_w1"): 90894997, ("switch_large_skew", "tile_w2"): 123045815,
+    ("nllb_decode", "stream_w1"): 1643759594, ("nllb_decode", "stream_w2"): 1645698647,
+    ("nllb_prefill_skew", "stream_w1"): 913896996, ("nllb_prefill_skew", "stream_w2"): 972128547,
+    ("nllb_prefill_skew", "tile_w1"): 2619195259, ("nllb_prefill_skew", "tile_w2"): 2400065106,
 }
 
 
