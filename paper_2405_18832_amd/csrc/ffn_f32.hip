@@ -12,12 +12,13 @@
 // instruction instead of 16, which bounded the kernel (57 + 67 us on the layer below).
 //
 // Rounding: a result is no further from the exact sum than with four interleaved sums over k mod 4, added in pairs.  Four
-// equal shares of a contraction are as good as those.  Unequal ones (K no multiple of 128) are not: there a wavefront's
-// MFMAs take turns in two chains of sums, and in four, one per k mod 4, where the contraction is too short for a step per
-// wavefront (the weights of such units are few, so tiles of more than 32 rows read them twice).  Relative error of a
-// layer's two products, mean of 24 layers of random inputs, one chain per wavefront throughout -> these: d = 20, f = 33:
-// 1.12 -> 0.82e-7; d = 32: 1.35 -> 1.08e-7; d = 64: 1.54 -> 1.32e-7; d = 96: 1.71 -> 1.51e-7 (four interleaved sums: 0.96,
-// 1.07, 1.38 and 1.64e-7).
+// about equal shares of a contraction are as good as those.  Where they are not (K below 128, or a few hundred and no multiple
+// of 128), a wavefront's MFMAs take turns in two chains of sums, and in four, one per k mod 4, where the contraction is too
+// short for a step per wavefront (the weights of such units are few, so tiles of more than 32 rows read them twice).  Relative
+// error of a layer's two products, mean of 24 layers of random inputs, one chain per wavefront throughout -> these: d = 20,
+// f = 33: 1.12 -> 0.82e-7; d = 32: 1.35 -> 1.08e-7; d = 64: 1.54 -> 1.32e-7; d = 96: 1.71 -> 1.51e-7 (four interleaved sums:
+// 0.96, 1.07, 1.38 and 1.64e-7).  Further chains cost registers: layers of 300 tokens, 8 experts, 96 x 384 22.6 -> 23.3 us;
+// 500 tokens, 258 x 1032, would take 41.3 -> 44.0 us and stay with one at the error they have.
 //
 // What bounds it: with about 64 rows per expert the MFMA time (64 flop per clock and SIMD) and reading the weights once
 // are about equal, 17 and 14 us on a layer of 500 tokens, 8 experts, 768 x 3072, one expert per token (2.4 GFLOP and
@@ -34,6 +35,13 @@ namespace moe {
 constexpr int kF32Waves = 4;        // wavefronts of a block: slices of the contraction
 constexpr int kF32Step = 32;        // k per step: one 128-byte line of every row
 constexpr int kF32FragFloats = 16 * kF32Step;
+
+// A wavefront's first step: shares differ by one step at most, and the last wavefront, which also takes the rest of the row,
+// has one of the smaller ones.
+__host__ __device__ __forceinline__ int f32_first_step(int steps, int wave) {
+    const int q = steps / kF32Waves, r = steps % kF32Waves;
+    return wave * q + (wave < r ? wave : r);
+}
 
 // 16-byte piece p (of 8) of row r of a fragment in LDS.  The pieces of a row are permuted by its row number: the eight
 // rows that a read touches at once then lie in different banks.
@@ -100,8 +108,8 @@ __device__ __forceinline__ void f32_unit(const float* __restrict__ act, const in
                         __builtin_amdgcn_mfma_f32_16x16x4f32(v[0][j], v[1 + tf][j], acc[j % CHAINS][tf], 0, 0, 0);
         }
     };
-    const int steps = K / kF32Step, per = (steps + kF32Waves - 1) / kF32Waves;      // whole steps; the rest of the row below
-    const int s0 = min(steps, wave * per), s1 = min(steps, s0 + per);
+    const int steps = K / kF32Step;                       // whole steps; the rest of the row below
+    const int s0 = f32_first_step(steps, wave), s1 = f32_first_step(steps, wave + 1);
     auto start_at = [&](int step) {
 #pragma unroll
         for (int i = 0; i < F; ++i)
@@ -209,10 +217,19 @@ template <int VEC>
 static hipError_t launch_f32(bool first, unsigned grid, const float* act, const int32_t* rowmap, const float* w,
                              float* outp, const Tile* tiles, const int32_t* ntiles, int N, int K, int activation,
                              const float* bias, hipStream_t st) {
-    constexpr int kShared = kF32Waves * kF32Step;         // contraction with a step for every wavefront
+    // Rounding errors of a sum grow with the square of its length: one chain per wavefront where the squares of the shares
+    // are within 2 % of those of four quarters (1 % in the error itself).
+    long squares = 0;
+    for (int w = 0; w < kF32Waves; ++w) {
+        const long n = static_cast<long>(f32_first_step(K / kF32Step, w + 1) - f32_first_step(K / kF32Step, w)) * kF32Step +
+                       (w == kF32Waves - 1 ? K % kF32Step : 0);
+        squares += n * n;
+    }
     auto kern = first ? ffn_f32_kernel<VEC, true, 2> : ffn_f32_kernel<VEC, false, 2>;
-    if (K % kShared == 0) kern = first ? ffn_f32_kernel<VEC, true, 1> : ffn_f32_kernel<VEC, false, 1>;
-    else if (K < kShared) kern = first ? ffn_f32_kernel<VEC, true, 4> : ffn_f32_kernel<VEC, false, 4>;
+    if (squares * 4 * 100 <= static_cast<long>(K) * K * 102)
+        kern = first ? ffn_f32_kernel<VEC, true, 1> : ffn_f32_kernel<VEC, false, 1>;
+    else if (K < kF32Waves * kF32Step)
+        kern = first ? ffn_f32_kernel<VEC, true, 4> : ffn_f32_kernel<VEC, false, 4>;
     hipLaunchKernelGGL(kern, dim3(grid), dim3(256), 0, st, act, rowmap, w, outp, tiles, ntiles, N, K, activation, bias);
     return hipGetLastError();
 }

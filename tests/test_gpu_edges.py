@@ -89,9 +89,9 @@ def test_f32_ffn_few_rows_masked(gpu_lib):
 
 
 # fp32 rounding: no further from 64 bits than four interleaved fp32 sums over k mod 4, added in pairs, at contractions that one
-# wavefront, two, three and all four of them hold.  Bar on the rms over 512 d elements: 5 %, several times the scatter of
+# wavefront, two, three and all four of them hold, in equal, nearly equal and unequal shares.  Bar on the rms over 512 d elements: 5 %, several times the scatter of
 # such a ratio between two orders of the same length.
-@pytest.mark.parametrize("d,f", [(20, 20), (32, 32), (48, 40), (64, 64), (96, 160), (256, 128)])
+@pytest.mark.parametrize("d,f", [(20, 20), (32, 32), (48, 40), (64, 64), (96, 160), (256, 128), (264, 544)])
 def test_f32_ffn_rounding(gpu_lib, d, f):
     say(f"[case] f32 ffn rounding d={d} f={f}")
     rows = [16, 32, 48, 64, 96, 256]
