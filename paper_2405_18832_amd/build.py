@@ -10,7 +10,7 @@ ROOT = os.path.dirname(PKG)
 CSRC = os.path.join(PKG, "csrc")
 OBJ = os.path.join(PKG, "_build")
 LIB = os.path.join(PKG, "libmoe_ffn_gfx950.so")
-SOURCES = ["api.hip", "route.hip", "permute.hip", "ffn.hip", "ffn_tile.hip", "ffn_f32.hip", "combine.hip"]
+SOURCES = ["api.hip", "route.hip", "permute.hip", "ffn.hip", "ffn_tile.hip", "ffn_f32.hip", "ffn_few.hip", "combine.hip"]
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 FLAGS = ["-O3", "-std=c++17", "--offload-arch=gfx950", "-fPIC", "-fno-gpu-rdc",
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",

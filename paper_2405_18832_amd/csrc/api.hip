@@ -338,6 +338,14 @@ moe_status moe_layer_forward_biased(const moe_shape* shape, const void* x, const
                                            at<Tile>(ws, L.tiles_half), at<int32_t>(ws, L.ntiles),
                                            at<float>(ws, L.partials));
     hipError_t e;
+    if (used == nullptr && layer_is_few(*shape)) {
+        if (hot_mask_out != nullptr && launch_mask_out(nullptr, hot_mask_out, shape->E, hs) != hipSuccess) return MOE_ERR_HIP;
+        float* part = at<float>(ws, L.gate_part);
+        e = launch_gate_partial(*shape, x, w_gate, part, hs);
+        if (e != hipSuccess) return MOE_ERR_HIP;
+        return from_hip(launch_few_products(*shape, x, gate_bias, part, w1, w2, b1, b2, idx, gate, cnt, offsets,
+                                            perm, inv, tokmap, at<void>(ws, L.h), out, hs));
+    }
     const int tok = route_chunk_tokens(*shape);
     const PlaceArgs place{idx, perm, inv, tokmap, shape->T * shape->k, shape->k, tok * shape->k};
     e = launch_route_finalize(*shape, x, w_gate, gate_bias, idx, gate, nullptr, hist, at<float>(ws, L.gate_part), cnt,

@@ -478,10 +478,17 @@ hipError_t launch_expert_ffn(const moe_shape& s, const void* x_perm, const void*
 hipError_t launch_combine(const moe_shape& s, const float* y_perm, const int32_t* inv_perm,
                           const int32_t* idx, const float* gate, const uint8_t* mask, void* out,
                           hipStream_t st);
+hipError_t launch_gate_partial(const moe_shape& s, const void* x, const void* w_gate, float* part, hipStream_t st);
+bool layer_is_few(const moe_shape& s);
+hipError_t launch_few_products(const moe_shape& s, const void* x, const float* gate_bias, const float* gate_part, const void* w1,
+                               const void* w2, const float* b1, const float* b2, int32_t* idx, float* gate, int32_t* counts,
+                               int32_t* offsets, int32_t* perm, int32_t* inv_perm, int32_t* tokmap, void* h, void* out,
+                               hipStream_t st);
 hipError_t launch_pack(const moe_shape& s, int which, const void* src, void* dst, hipStream_t st);
 hipError_t launch_mask_out(const uint8_t* mask_or_null, uint8_t* dst, int E, hipStream_t st);
 
 void set_profile_events(const hipEvent_t* five_events_or_null);
+hipError_t mark_profile_event(int i, hipStream_t st);     // records the caller's event i, if there is one
 
 // number of compute units of the current device (cached)
 int device_cu_count();

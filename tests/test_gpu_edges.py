@@ -222,6 +222,67 @@ def test_bf16_route_unaligned(gpu_lib, T, d, E, k, x_at, wg_at):
     route_against_oracle(gpu_lib, T, d, E, k, x_at, wg_at)
 
 
+# layers of at most 8 tokens, which are routed inside the first product and combined inside the second: one assignment up to a
+# wavefront of them, contractions of an odd number of 32-k steps, of fewer pairs of steps than wavefronts and of many, units of 16
+# columns and of 64 (the last three shapes), and a token of NaN logits, whose 8 slots all name expert 0 and give it more rows than
+# a tile holds.  Values against the oracle at storage precision; bar: the output's one rounding to bf16 (2^-8) and rare hidden
+# values at a rounding boundary.  Routing and places also against the general path, which a mask of ones takes.
+@pytest.mark.parametrize("nan_token", [False, True])
+@pytest.mark.parametrize("T,d,f,E,k", [(1, 32, 32, 1, 1), (1, 96, 96, 5, 3), (3, 160, 544, 256, 2), (5, 352, 608, 40, 2),
+                                       (8, 64, 1056, 8, 8), (7, 2048, 256, 20, 2), (2, 64, 8192, 30, 1), (8, 64, 1024, 64, 4),
+                                       (4, 96, 3072, 64, 3)])
+def test_few_tokens(gpu_lib, T, d, f, E, k, nan_token):
+    say(f"[case] few tokens T={T} d={d} f={f} E={E} k={k} nan={nan_token}")
+    moe = gpu_lib
+    from paper_2405_18832_amd.device_layer import to_device
+    rng = np.random.default_rng([T, d, f, E, k])
+    draw = lambda shape, s: wl.round_to_storage(rng.standard_normal(shape, dtype=np.float32) * np.float32(s), "bf16")
+    x, wg, w1, w2 = draw((T, d), 1.0), draw((E, d), d ** -0.5), draw((E, f, d), d ** -0.5), draw((E, d, f), f ** -0.5)
+    bg, b1, b2 = draw((E,), 0.5), draw((E, f), 0.25), draw((E, d), 0.25)
+    bad = T // 2 if nan_token else -1
+    if nan_token:
+        x[bad, d // 2] = np.nan
+    act = "gelu" if T % 2 else "relu"
+    shape = moe.make_shape(T, d, f, E, k, "bf16", True, {"relu": 0, "gelu": 1}[act])
+    dev = lambda a, dt: to_device(a, dt, "cuda")
+    xd, wgd, bgd, b1d, b2d = dev(x, "bf16"), dev(wg, "bf16"), dev(bg, "f32"), dev(b1, "f32"), dev(b2, "f32")
+    p1, p2 = torch.empty((E, d * f), dtype=torch.bfloat16, device="cuda"), torch.empty((E, d * f), dtype=torch.bfloat16, device="cuda")
+    moe.moe_pack_weights(shape, 1, dev(w1, "bf16"), p1)
+    moe.moe_pack_weights(shape, 2, dev(w2, "bf16"), p2)
+    ws = torch.full((moe.moe_workspace_bytes(shape),), 0xFF, dtype=torch.uint8, device="cuda")
+
+    def layer(mask, by_products=True):
+        out = torch.full((T, d), 7.0, dtype=torch.bfloat16, device="cuda")
+        i32 = lambda *s: torch.full(s, -1, dtype=torch.int32, device="cuda")
+        more = (i32(T, k), torch.zeros((T, k), device="cuda"), i32(E), i32(T * k), torch.zeros(E, dtype=torch.uint8, device="cuda"))
+        moe.moe_layer_forward_biased(shape, xd, wgd, bgd, p1, b1d, p2, b2d, mask, -1, out, *(more if by_products else (None,) * 5), ws=ws)
+        torch.cuda.synchronize()
+        return out, more
+
+    out, few = layer(None)
+    general, gen = layer(torch.ones(E, dtype=torch.uint8, device="cuda"))
+    others = np.arange(T) != bad
+    for a, b in zip(few, gen):
+        assert torch.equal(a.view(torch.uint8), b.view(torch.uint8))
+    bare, _ = layer(None, by_products=False)               # none of the optional outputs
+    assert torch.equal(bare.view(torch.int16), out.view(torch.int16))
+    idx, g = few[0].cpu().numpy(), few[1].cpu().numpy().astype(np.float64)
+    r = orc.route(np.where(np.isnan(x), 0, x), wg, bg, k, True)
+    ok = others & (r["margin"] >= 1e-4)
+    assert np.array_equal(idx[ok], r["idx"][ok])
+    ref = np.zeros((T, d))
+    for t in np.flatnonzero(others):
+        for j in range(k):
+            e = idx[t, j]
+            ref[t] += g[t, j] * orc.expert_ffn(x[t:t + 1], w1[e], w2[e], "bf16", act, b1[e], b2[e])[0]
+    got = out.float().cpu().numpy().astype(np.float64)
+    if others.any():
+        err = float(orc.rel_error_rows(got[others], ref[others]).max())
+        say(f"[edges] element-wise max {err:.3e}")
+        assert err <= 1e-2
+    assert not nan_token or np.isnan(got[bad]).all()
+
+
 # tiled kernels: experts around their 128- and 256-row tiles, columns that are no multiple of a tile's, contractions of one
 # step, of fewer steps than the LDS ring holds, and long enough to be cut; the last shape has few large units in one product
 # and many in the other.  Bar: y against the oracle that rounds the hidden activation once, as the kernels do; what is left
