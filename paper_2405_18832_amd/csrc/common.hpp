@@ -54,7 +54,7 @@ struct Tile {
 constexpr int kBigTileRows = 256;
 constexpr int kBigMinRows = 128;
 // The same experts are listed in tiles of kHalfTileRows rows too, for products whose large tiles are too few to
-// occupy the chip (tiled_product_is_fine in tile_schedule.hpp).
+// occupy the chip (tiled_product_units in tile_schedule.hpp).
 constexpr int kHalfTileRows = 128;
 constexpr int kHalfCount = 4;           // int of the `ntiles` array that holds their number
 // Experts between one streaming tile and kBigMinRows rows would have their weights streamed once per
@@ -187,12 +187,14 @@ struct TileLists {
     Tile* small_tiles;     // capacity A / small_rows + E
     Tile* big_tiles;       // capacity A / kBigTileRows + E (unused when big_min == 0)
     Tile* half_tiles;      // the same experts in tiles of kHalfTileRows rows, capacity A / kHalfTileRows + E
-    int32_t* ntiles;       // [0] small count, [1] big count, [2], [3] part counters of the tiled products, [4] half count
+    int32_t* ntiles;       // [0] small count, [1] big count, [2], [3] part counters of the tiled products, [4] half count, [8] and
+                           // [16]: the TileSchedule of the first and of the second product (if big_min > 0)
     float* partials;       // kSplitSlots partial tiles (nullptr when big_min == 0)
     int small_rows;        // rows per small tile
     int big_min;           // experts with >= big_min rows are "big"; 0 = none
     int join_tiles;        // tiles of big experts from which the mid-sized experts join them (tiled_min_rows); 0 = never
     int join_half_tiles;   // half-sized tiles, with the mid-sized experts', up to which they do
+    int d_model, d_ff, cus;       // what the schedules depend on besides the tiles
 };
 
 #ifdef __HIPCC__
@@ -312,38 +314,6 @@ __device__ __forceinline__ void write_tiles(Tile* __restrict__ out, int e, int r
         const uint64_t hi = static_cast<uint32_t>(__builtin_amdgcn_readlane(static_cast<int>(at >> 32), src));
         Tile* o = reinterpret_cast<Tile*>(lo | hi << 32);
         for (int i = threadIdx.x & 63; i < n; i += 64) o[i] = Tile{ee, r0 + i * rows, min(rows, mm - i * rows), 0};
-    }
-}
-
-// Called by all 1024 threads of a block, thread e owning expert e (row0, m rows; m = 0 when the
-// expert is empty or masked out).  `big_at_min`, `half_joined`: the block's sums of big_tiles_at_min and half_tiles_joined.
-// `tmp` is an LDS array of >= 48 ints.
-__device__ __forceinline__ void emit_tiles(int e, int row0, int m, int big_at_min, int half_joined, const TileLists tl,
-                                           int32_t* tmp) {
-    if (tl.big_min <= 0) {                                 // no large experts possible: one list (uniform)
-        const int nt[1] = {(m + tl.small_rows - 1) / tl.small_rows};
-        int incl[1], total[1];
-        block_scan_1024(nt, incl, total, tmp);
-        write_tiles(tl.small_tiles + incl[0] - nt[0], e, row0, m, tl.small_rows, nt[0]);
-        if (e == 0) {
-            tl.ntiles[0] = total[0];
-            tl.ntiles[1] = tl.ntiles[kHalfCount] = 0;
-        }
-        return;
-    }
-    const bool big = m >= tiled_min_rows(big_at_min, tl.join_tiles, half_joined, tl.join_half_tiles);
-    const int nt[3] = {big ? 0 : (m + tl.small_rows - 1) / tl.small_rows, big ? (m + kBigTileRows - 1) / kBigTileRows : 0,
-                       big ? (m + kHalfTileRows - 1) / kHalfTileRows : 0};
-    int incl[3], total[3];
-    block_scan_1024(nt, incl, total, tmp);
-    write_tiles(tl.small_tiles + incl[0] - nt[0], e, row0, m, tl.small_rows, nt[0]);
-    write_tiles(tl.big_tiles + incl[1] - nt[1], e, row0, m, kBigTileRows, nt[1]);
-    write_tiles(tl.half_tiles + incl[2] - nt[2], e, row0, m, kHalfTileRows, nt[2]);
-    if (e == 0) {
-        tl.ntiles[0] = total[0];
-        tl.ntiles[1] = total[1];
-        tl.ntiles[kHalfCount] = total[2];
-        tl.ntiles[kSplitCounter] = tl.ntiles[kSplitCounter + 1] = 0;
     }
 }
 #endif

@@ -230,10 +230,10 @@ __global__ __launch_bounds__(256) void ffn_stream_kernel(const uint16_t* __restr
         const int idle = stride - nbu;                    // blocks with pb >= nbu have no unit (balance is off here)
         if (idle * 4 >= stride) {
             if (pb >= nbu)
-                finish_tiled_product<FIRST, FOLD>(big_tiles, half_tiles, ntiles_p, partials, outp, N, K >> 5, cus, bias, fold,
+                finish_tiled_product<FIRST, FOLD>(big_tiles, half_tiles, ntiles_p, partials, outp, N, cus, bias, fold,
                                                   pb - nbu, idle);
         } else {
-            finish_tiled_product<FIRST, FOLD>(big_tiles, half_tiles, ntiles_p, partials, outp, N, K >> 5, cus, bias, fold,
+            finish_tiled_product<FIRST, FOLD>(big_tiles, half_tiles, ntiles_p, partials, outp, N, cus, bias, fold,
                                               static_cast<int>(blockIdx.x), static_cast<int>(gridDim.x));
         }
     }
@@ -468,6 +468,9 @@ TileLists ffn_tile_lists(const moe_shape& s, Tile* small_ws, Tile* big_ws, Tile*
     l.big_min = (s.dtype == MOE_BF16 && s.T >= kBigMinRows) ? kBigMinRows : 0;
     l.partials = l.big_min > 0 ? partials_ws : nullptr;
     l.join_tiles = l.big_min > 0 ? tiled_join_tiles(s) : 0;
+    l.d_model = s.d_model;
+    l.d_ff = s.d_ff;
+    l.cus = tile_product_grid();
     l.join_half_tiles = tile_product_grid() / ((std::max(s.d_model, s.d_ff) + FineUnits::kCols - 1) / FineUnits::kCols);
     return l;
 }

@@ -15,7 +15,11 @@
 // 4 weight fragments (MFMA A operand) x 8 row fragments (B operand) of 16x16x32 per 32-k step,
 // 128 accumulator registers.
 //
-// Fine units, for products whose big units would leave much of the chip idle (tiled_product_is_fine): 128 x 128, the
+// Narrow units, where big ones would leave up to half of the chip idle (tiled_product_units): 256 x 128, wavefronts 4 x 2 of
+// 64 x 64 each.  Bound by the copies like the fine ones below (24 KB per step, about 48 GB/s per CU), with a quarter less of them
+// per output and no exchange: 8 experts of 137 ... 228 rows, 768 x 3072, GeLU, first product 29.7 -> 25.4 us.
+//
+// Fine units, for products whose big units would leave most of the chip idle: 128 x 128, the
 // 8 wavefronts as two groups of four (64 x 64 each) that take half of the contraction each, through a ring of their own
 // with stages half the size, and add up in LDS.  A CU can pull about 35 GB/s from beyond its L2 however much it has in
 // flight, so a handful of big units is bound by the CUs they run on, not by memory or matrix units.  Per output they copy
@@ -41,12 +45,14 @@ constexpr int kWaves = 8;           // wavefronts of a block
 constexpr int kRingBytes = kStages * 2 * kBigTileRows * kTK * 2;   // 128 KiB of stages
 constexpr int kTileLds = kRingBytes + 32 * 1024;                   // and where the groups of a fine unit exchange sums
 
-// Wait until at most `stages` stages' worth of this wavefront's copies (4 each) are still in flight.
+// Wait until at most `stages` stages' worth of this wavefront's copies (COPIES each, 3 or 4) are still in flight.
+template <int COPIES>
 __device__ __forceinline__ void wait_copies(int stages) {
-    if (stages >= 3) __builtin_amdgcn_s_waitcnt(0x0F7C);         // vmcnt(12)
-    else if (stages == 2) __builtin_amdgcn_s_waitcnt(0x0F78);    // vmcnt(8)
-    else if (stages == 1) __builtin_amdgcn_s_waitcnt(0x0F74);    // vmcnt(4)
-    else __builtin_amdgcn_s_waitcnt(0x0F70);                     // vmcnt(0)
+    static_assert(COPIES <= 5, "vmcnt up to 15 sits in the low four bits");
+    if (stages >= 3) __builtin_amdgcn_s_waitcnt(0x0F70 + 3 * COPIES);
+    else if (stages == 2) __builtin_amdgcn_s_waitcnt(0x0F70 + 2 * COPIES);
+    else if (stages == 1) __builtin_amdgcn_s_waitcnt(0x0F70 + COPIES);
+    else __builtin_amdgcn_s_waitcnt(0x0F70);
 }
 
 // Register fragments of one wavefront: the 4 weight fragments of a stage, double-buffered over stages,
@@ -79,25 +85,28 @@ __device__ __forceinline__ void mfma_pair(const bf16x8 (&w)[4], const bf16x8 (&x
 template <int FIRST, typename Units>
 __device__ __forceinline__ void run_units(const uint16_t* __restrict__ act, const int32_t* __restrict__ rowmap,
                                           const uint16_t* __restrict__ wpk, void* __restrict__ outp,
-                                          const Tile* __restrict__ tiles, const int ntiles,
+                                          const Tile* __restrict__ tiles, const TileSchedule& sch,
                                           int32_t* __restrict__ part_counter, float* __restrict__ partials, int N, int K,
                                           int act_kmajor, const float* __restrict__ bias, const FoldOut& fold,
                                           unsigned char* smem) {
     constexpr bool FINE = Units::kGroups == 2;
     constexpr int kTM = Units::kRows, kTN = Units::kCols;
     constexpr int kGroupWaves = kWaves / Units::kGroups;
-    constexpr int WN = kTN / 64;                        // wavefronts of a group side by side; two in the row direction
-    constexpr int RF = kTM / 32;                        // row fragments of a wavefront
-    constexpr int kOperandBytes = kTM * kTK * 2;        // per operand and stage (kTM == kTN)
-    constexpr int kStageBytes = 2 * kOperandBytes;
-    static_assert(kTM == kTN && kGroupWaves == 2 * WN && kTM / 16 == 2 * kGroupWaves, "two fragments per wavefront and copy");
-    static_assert(Units::kGroups * kStages * kStageBytes == kRingBytes, "the groups' rings fill the LDS");
+    constexpr int WN = kTN / 64;                        // wavefronts of a group side by side
+    constexpr int WM = kGroupWaves / WN;                // and in the row direction
+    constexpr int RF = kTM / WM / 16;                   // row fragments of a wavefront
+    constexpr bool FOUR = RF == 4;                      // 64 x 64 per wavefront, else 128 x 64
+    constexpr int kRowBytes = kTM * kTK * 2;            // rows of a stage; the weights lie behind them
+    constexpr int kStageBytes = kRowBytes + kTN * kTK * 2;
+    constexpr int RC = kTM / 16 / kGroupWaves, WC = kTN / 16 / kGroupWaves;    // row and weight fragments a wavefront copies per stage
+    static_assert((RF == 4 || RF == 8) && RC == 2 && (WC == 1 || WC == 2), "the shapes the loop is written for");
+    static_assert(Units::kGroups * kStages * kStageBytes <= kRingBytes, "the groups' rings fit into the LDS");
     // between units, when no stage is in use, the first word of the ring passes the next part's number on
     int* next_part = reinterpret_cast<int*>(smem);
     f32x4* exchange = reinterpret_cast<f32x4*>(smem + kRingBytes);
     const int block_wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int group = FINE ? block_wave / kGroupWaves : 0;
-    // stage st of a group: kTM / 16 row fragments at ring + st * kStageBytes, as many weight fragments behind them
+    // stage st of a group: kTM / 16 row fragments at ring + st * kStageBytes, kTN / 16 weight fragments behind them
     unsigned char* ring = smem + group * (kStages * kStageBytes);
 
     const int t = threadIdx.x, wave = block_wave % kGroupWaves, lane = t & 63;
@@ -105,13 +114,12 @@ __device__ __forceinline__ void run_units(const uint16_t* __restrict__ act, cons
     const int r = lane & 15, g = lane >> 4;
     const int nblk = N >> 4, kblk = K >> 5;
     const int G = gridDim.x;
-    // LDS byte address of the first of the two fragments that this wavefront copies in, stage 0
-    const uint32_t copy_base = lds_address(ring) + 2 * wave * 1024;
+    // LDS byte address of the first row fragment that this wavefront copies in, stage 0, and where its weight fragments lie from there
+    const uint32_t copy_base = lds_address(ring) + RC * wave * 1024, weights_at = kRowBytes - (RC - WC) * wave * 1024;
 
     // Blocks are handed to the 8 XCDs round-robin, and each XCD has its own L2: block b takes position pb
     // of a round, so that the blocks of one XCD hold G / 8 consecutive units, a GM x GN patch whose
     // activation panels that L2 serves GN times and whose weight panels GM times.
-    const TileSchedule sch = tile_schedule<Units>(ntiles, N, kblk, G, partials != nullptr);
     const int pb = (G % 8 == 0) ? static_cast<int>(blockIdx.x & 7) * (G >> 3) + static_cast<int>(blockIdx.x >> 3)
                                 : static_cast<int>(blockIdx.x);
     const int nleft = sch.R * sch.split;                // parts of the left-over units
@@ -175,20 +183,19 @@ __device__ __forceinline__ void run_units(const uint16_t* __restrict__ act, cons
         return w;
     };
 
-    // 4 copies per wavefront and stage; stages are copied in order, so the pointers just advance.
-    // This wavefront stages fragments 2*wave and 2*wave+1 of each operand.  A lane fetches the 16
+    // RC + WC copies per wavefront and stage; stages are copied in order, so the pointers just advance.  A lane fetches the 16
     // bytes that belong at its own slot of the fragment: row (lane % 16), k-group (lane / 16).
-    const uint16_t* arow[2];
-    const uint16_t* brow[2];
+    const uint16_t* arow[RC];
+    const uint16_t* brow[WC];
     const size_t kstride = act_kmajor ? kStepStride : 32;   // elements per k-step
     auto copy_piece = [&](int st, int q) {             // q = 0 ... 3: row fragment 0, weight 0, row 1, weight 1
         const int i = q >> 1;
         if ((q & 1) == 0) {
             copy16_to_lds(arow[i], copy_base + st * kStageBytes + i * 1024);
             arow[i] += kstride;
-        } else {
-            copy16_to_lds(brow[i], copy_base + st * kStageBytes + kOperandBytes + i * 1024);
-            brow[i] += 512;
+        } else if (i < WC) {
+            copy16_to_lds(brow[i % WC], copy_base + st * kStageBytes + weights_at + i * 1024);
+            brow[i % WC] += 512;
         }
     };
     auto stage_in = [&](int st) {
@@ -198,13 +205,16 @@ __device__ __forceinline__ void run_units(const uint16_t* __restrict__ act, cons
     // Point the copies at a unit's first k-step.
     auto point_copies_at = [&](const Unit& w) {
 #pragma unroll
-        for (int i = 0; i < 2; ++i) {
-            int row = w.tl.row0 + min((2 * wave + i) * 16 + r, w.tl.rows - 1);
+        for (int i = 0; i < RC; ++i) {
+            int row = w.tl.row0 + min((RC * wave + i) * 16 + r, w.tl.rows - 1);
             if (rowmap != nullptr) row = rowmap[row];
             // operand rows are row-major (the caller's x or x_perm) or k-step-major (h, gathered x)
             arow[i] = act_kmajor ? act + h_index(row, w.kb0 * 32 + g * 8, kblk)
                                  : act + static_cast<size_t>(row) * K + static_cast<size_t>(w.kb0) * 32 + g * 8;
-            const int nb = min(w.nt * (kTN / 16) + 2 * wave + i, nblk - 1);
+        }
+#pragma unroll
+        for (int i = 0; i < WC; ++i) {
+            const int nb = min(w.nt * (kTN / 16) + WC * wave + i, nblk - 1);
             brow[i] = wpk + ((static_cast<size_t>(w.tl.expert) * nblk + nb) * kblk + w.kb0) * 512 + lane * 8;
         }
     };
@@ -222,7 +232,7 @@ __device__ __forceinline__ void run_units(const uint16_t* __restrict__ act, cons
             if (sidx < w.nk) stage_in((slot + sidx) % kStages);
     };
 
-    const int wave_w = kOperandBytes + (wn * 4 * 64 + lane) * 16, wave_x = (wm * RF * 64 + lane) * 16;
+    const int wave_w = kRowBytes + (wn * 4 * 64 + lane) * 16, wave_x = (wm * RF * 64 + lane) * 16;
     Unit cur = unit_at(0);
     if (cur.valid) start_unit(cur);
     for (int it = 0; cur.valid; ++it) {
@@ -235,7 +245,7 @@ __device__ __forceinline__ void run_units(const uint16_t* __restrict__ act, cons
         // The next unit's first stages go out during this unit's last iterations, in the slots that fall free
         // there, when the unit is known by then, needs no row lookups (a vector load here would make the
         // compiler wait for every copy in flight) and both units are at least as long as the ring is deep.
-        const bool ahead = !FINE && next_known && nxt.valid && rowmap == nullptr && nk >= kAhead && nxt.nk >= kAhead;
+        const bool ahead = !FOUR && next_known && nxt.valid && rowmap == nullptr && nk >= kAhead && nxt.nk >= kAhead;
         f32x4 acc[4][RF];
 #pragma unroll
         for (int nf = 0; nf < 4; ++nf)
@@ -263,7 +273,7 @@ __device__ __forceinline__ void run_units(const uint16_t* __restrict__ act, cons
             if (more) {
                 // stages j + 2 ... j + kAhead - 1 (as far as they exist) may stay in flight; with the next unit's
                 // stages behind them that is always kAhead - 2 stages' worth
-                wait_copies((STEADY || ahead) ? kAhead - 2 : min(j + kAhead - 1, nk - 1) - (j + 1));
+                wait_copies<RC + WC>((STEADY || ahead) ? kAhead - 2 : min(j + kAhead - 1, nk - 1) - (j + 1));
                 asm volatile("s_barrier" ::: "memory");
             } else if (ahead) {
                 asm volatile("s_barrier" ::: "memory");   // the slot of stage j - 1 is about to be refilled
@@ -273,9 +283,9 @@ __device__ __forceinline__ void run_units(const uint16_t* __restrict__ act, cons
             // the four copies of stage j + kAhead are issued between the first MFMAs, whose execution
             // covers the scalar and address arithmetic of the copies
             const bool refill = (more && (STEADY || j + kAhead < nk)) || (!STEADY && ahead && j + kAhead >= nk);
-            // Fine units: both row pairs of stage j are in registers, and the second group of MFMAs covers the reads of
+            // 64 x 64: both row pairs of stage j are in registers, and the second group of MFMAs covers the reads of
             // stage j + 1 into the other buffers.
-            const bf16x8 (&x0)[2] = fr.x[FINE ? 2 * C : 0];
+            const bf16x8 (&x0)[2] = fr.x[FOUR ? 2 * C : 0];
 #pragma unroll
             for (int nf = 0; nf < 4; ++nf) {
                 __builtin_amdgcn_sched_barrier(0);
@@ -285,7 +295,7 @@ __device__ __forceinline__ void run_units(const uint16_t* __restrict__ act, cons
                 if (refill) copy_piece(slot_free, nf);
             }
             __builtin_amdgcn_sched_barrier(0);
-            if constexpr (FINE) {
+            if constexpr (FOUR) {
                 if (more) {
                     lds_read_w(fr.w[C ^ 1], st_nxt + wave_w);
                     lds_read_x(fr.x[2 * (C ^ 1)], st_nxt + wave_x, 0);
@@ -318,12 +328,12 @@ __device__ __forceinline__ void run_units(const uint16_t* __restrict__ act, cons
         // The first waits may also wait for the previous unit's output stores, which were issued after this
         // unit's first copies and count in vmcnt like them: never too short, since no more than the given
         // number of operations stays outstanding and the copies complete in order.
-        wait_copies(min(kAhead, nk) - 1);                  // stage 0 has landed ...
+        wait_copies<RC + WC>(min(kAhead, nk) - 1);                  // stage 0 has landed ...
         asm volatile("s_barrier" ::: "memory");           // ... for every wavefront
         lds_read_w(fr.w[0], ring + slot * kStageBytes + wave_w);
         lds_read_x(fr.x[0], ring + slot * kStageBytes + wave_x, 0);
         lds_read_x(fr.x[1], ring + slot * kStageBytes + wave_x, 1);
-        if constexpr (!FINE) lds_read_x(fr.x[2], ring + slot * kStageBytes + wave_x, 2);
+        if constexpr (!FOUR) lds_read_x(fr.x[2], ring + slot * kStageBytes + wave_x, 2);
         int j = 0;
         for (; j + 1 + kAhead < nk; j += 2) {
             iterate(std::integral_constant<int, 0>{}, std::true_type{}, j);
@@ -354,7 +364,7 @@ __device__ __forceinline__ void run_units(const uint16_t* __restrict__ act, cons
             }
         }
         constexpr int OF = RF / Units::kGroups;            // row fragments of output per wavefront, from the first on:
-        const int lr0 = wm * (kTM / 2) + group * OF * 16;
+        const int lr0 = wm * (RF * 16) + group * OF * 16;
 
         // The next unit's first copies go out before this unit's output is stored: the copies' latency and
         // the stores overlap, and the load of the next tile's descriptor does not wait behind the stores.
@@ -425,15 +435,20 @@ __global__ __launch_bounds__(kWaves * 64, 2) void ffn_tile_kernel(const uint16_t
                                                                   float* __restrict__ partials, int N, int K, int act_kmajor,
                                                                   const float* __restrict__ bias, const FoldOut fold) {
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
-    const int ntiles = ntiles_p[1];
-    if (ntiles <= 0) return;                            // no large expert in this call (block-uniform)
-    const int nhalf = ntiles_p[kHalfCount];
-    if (tiled_product_is_fine(ntiles, nhalf, N, gridDim.x, FIRST == kFirstGelu))
-        run_units<FIRST, FineUnits>(act, rowmap, wpk, outp, half_tiles, nhalf, part_counter, partials, N, K,
-                                    act_kmajor, bias, fold, smem);
+    // the grid is the number of CUs that the schedule was made for
+    const TileSchedule sch = *reinterpret_cast<const TileSchedule*>(ntiles_p + kScheduleAt + (FIRST != 0 ? 0 : kScheduleInts));
+    if (ntiles_p[1] <= 0) return;                       // no large expert in this call (block-uniform)
+    // Big units first: their loop is the one that matters most, and its place in the code makes a difference (with the other shapes
+    // in front of them the first product of 16384 tokens x 2048 x 8192, k = 2, took 888 us instead of 878).
+    if (sch.shape == UnitShape::kBig)
+        run_units<FIRST, BigUnits>(act, rowmap, wpk, outp, big_tiles, sch, part_counter, partials, N, K, act_kmajor, bias, fold,
+                                   smem);
+    else if (sch.shape == UnitShape::kFine)
+        run_units<FIRST, FineUnits>(act, rowmap, wpk, outp, half_tiles, sch, part_counter, partials, N, K, act_kmajor, bias, fold,
+                                    smem);
     else
-        run_units<FIRST, BigUnits>(act, rowmap, wpk, outp, big_tiles, ntiles, part_counter, partials, N, K, act_kmajor, bias,
-                                   fold, smem);
+        run_units<FIRST, NarrowUnits>(act, rowmap, wpk, outp, big_tiles, sch, part_counter, partials, N, K, act_kmajor, bias, fold,
+                                      smem);
 }
 
 template <int FIRST>

@@ -1,4 +1,4 @@
-// Schedule of the LDS-tiled product over the (row tile, column tile) units of the large experts, shared
+// Schedule of the LDS-tiled product over the (row tile, column tile) units of the large experts, made with the tile lists and read
 // by the kernel that runs it (ffn_tile.hip) and the kernel that finishes it (ffn.hip).
 //
 // All units cost the same.  G blocks run U / G full rounds of whole units in a fixed, XCD-aware order.
@@ -20,7 +20,7 @@ constexpr int kMaxSplit = 8;        // parts per left-over unit, at most ...
 #define MOE_MIN_SPLIT_STEPS_FINE 24
 #endif
 
-// The two shapes of a unit: rows x columns of its output, the groups of wavefronts that share its contraction inside the
+// The shapes of a unit: rows x columns of its output, the groups of wavefronts that share its contraction inside the
 // block (each adds up an equal run of its 32-k steps), and the fewest steps of a part.
 struct BigUnits {
     static constexpr int kRows = kBigTileRows, kCols = 256, kGroups = 1, kMinSplitSteps = MOE_MIN_SPLIT_STEPS;
@@ -28,38 +28,49 @@ struct BigUnits {
 struct FineUnits {
     static constexpr int kRows = kHalfTileRows, kCols = 128, kGroups = 2, kMinSplitSteps = MOE_MIN_SPLIT_STEPS_FINE;
 };
+struct NarrowUnits {
+    static constexpr int kRows = kBigTileRows, kCols = 128, kGroups = 1, kMinSplitSteps = MOE_MIN_SPLIT_STEPS;
+};
 
-// Which of them a product runs in.  Fine ones where they are at most one round: the big units would leave most of the chip
-// idle, or be half empty (experts of up to 128 rows).  Between one round of fine units and half a round of big ones neither
-// is better as such: it depends on how the left-over units of either happen to be cut, and big units copy half as much.
-// There fine units are taken for the first product of GeLU layers only, whose epilogue all CUs work on then instead of
-// those that have a big unit.  Measured in us, fine / big, with the pass that adds up parts, tiles of 256 rows: 64 units of 24,
-// 32, 64 and 128 steps 24 / 34, 26 / 37, 31 / 46 and 57 / 67; 96 units of 24, 32, 64 and 128 steps 35 / 34, 40 / 38, 56 / 56 and
-// 92 / 89; 120 units of 32 and 128 steps 42 / 39 and 106 / 101; tiles of 137 rows, 72 units of 48 steps 38 / 45, 96 of 128 94 / 81,
-// 120 of 32 42 / 37.  GeLU: 72, 96 and 120 units of 24 steps 36 / 41, 38 / 42 and 41 / 42; 96 of 32 43 / 45; 144 of 24 48 / 43.
-inline __host__ __device__ bool tiled_product_is_fine(long big_tiles, long half_tiles, int N, int cus, bool gelu) {
-    if (half_tiles * ((N + FineUnits::kCols - 1) / FineUnits::kCols) <= cus) return true;
-    return gelu && big_tiles * ((N + BigUnits::kCols - 1) / BigUnits::kCols) * 2 < cus;
+// Which of them a product of `kblk` 32-k steps runs in.  Fine ones where they are at most one round: the big units would leave
+// most of the chip idle, or be half empty (experts of up to 128 rows).  Narrow ones where these are at most one round (65 to 128
+// full-width units: big units would run on that many of 256 CUs, or be cut along K and added up afterwards), unless the contraction
+// is so long that the cut units win: a step takes about 0.5 us in a narrow unit and 0.7 in a big one.  Big units that can be cut in
+// three win from about 100 steps on, those cut in two from about 190; and with few row tiles the narrow units of an XCD share too
+// little of their rows.  us, big or fine units before -> narrow units, both products' worth of adding up included, tiles of 256 rows:
+// 96 units of 24 steps 35 -> 31 (137 rows 33 -> 25), 112 of 32 39 -> 35, 72 of 48 48 -> 41, 80 of 64 51 -> 49, 112 of 64 66 -> 57, 112 of
+// 96 85 -> 69, 96 of 128 95 -> 84, 124 of 128 110 -> 96; and 68 of 128 73 -> 76, 3 x 32 of 128 96 -> 103, 96 of 192 115 -> 117, 80 of 256
+// 126 -> 143.  GeLU: 96 of 24 39 -> 34 (137 rows 33 -> 27), 112 of 64 65 -> 60 (62 -> 43).
+enum class UnitShape { kBig, kNarrow, kFine };
+inline __host__ __device__ UnitShape tiled_product_units(long big_tiles, long half_tiles, int N, int kblk, int cus) {
+    if (half_tiles * ((N + FineUnits::kCols - 1) / FineUnits::kCols) <= cus) return UnitShape::kFine;
+    if (big_tiles * ((N + NarrowUnits::kCols - 1) / NarrowUnits::kCols) > cus) return UnitShape::kBig;
+    const bool cut_in_two = big_tiles * ((N + BigUnits::kCols - 1) / BigUnits::kCols) * 3 > cus;
+    return kblk <= 96 || (kblk <= 128 && cut_in_two && big_tiles >= 8) ? UnitShape::kNarrow : UnitShape::kBig;
 }
 
 struct TileSchedule {
+    UnitShape shape;
     int ntiles, ntn;    // row tiles, column tiles
     int rounds, R;      // full rounds of G units; units left over
     int split;          // parts per left-over unit (1: not cut, written directly)
     int GM, GN;         // patch of consecutive units: GM row tiles x GN column tiles
 };
+constexpr int kScheduleAt = 8, kScheduleInts = 8;      // in the `ntiles` array, one per product
+static_assert(sizeof(TileSchedule) == kScheduleInts * 4, "as laid out in the array");
 
 #ifdef __HIPCC__
 template <typename Units>
-__device__ __forceinline__ TileSchedule tile_schedule(int ntiles, int N, int kblk, int G, bool have_partials) {
+__device__ __forceinline__ TileSchedule schedule_of(UnitShape shape, int ntiles, int N, int kblk, int G) {
     TileSchedule s;
+    s.shape = shape;
     s.ntiles = ntiles;
     s.ntn = (N + Units::kCols - 1) / Units::kCols;
     const int U = ntiles * s.ntn;
     s.rounds = U / G;
     s.R = U - s.rounds * G;
     s.split = 1;
-    if (s.R > 0 && have_partials) {
+    if (s.R > 0 && shape != UnitShape::kNarrow) {          // narrow units are more than half a round: never cut
         constexpr int slots = kSplitSlots * (kBigTileRows * 256 / (Units::kRows * Units::kCols));
         const int by_blocks = G / s.R, by_steps = kblk / Units::kMinSplitSteps, by_slots = slots / s.R;
         s.split = min(min(by_blocks, kMaxSplit), min(by_steps, by_slots));
@@ -68,6 +79,51 @@ __device__ __forceinline__ TileSchedule tile_schedule(int ntiles, int N, int kbl
     s.GN = min(s.ntn, 8);
     s.GM = (G % 8 == 0 && (G / 8) % s.GN == 0) ? (G / 8) / s.GN : 1;
     return s;
+}
+
+__device__ __forceinline__ TileSchedule product_schedule(int big_tiles, int half_tiles, int N, int kblk, int G) {
+    const UnitShape shape = tiled_product_units(big_tiles, half_tiles, N, kblk, G);
+    if (shape == UnitShape::kFine) return schedule_of<FineUnits>(shape, half_tiles, N, kblk, G);
+    if (shape == UnitShape::kNarrow) return schedule_of<NarrowUnits>(shape, big_tiles, N, kblk, G);
+    return schedule_of<BigUnits>(shape, big_tiles, N, kblk, G);
+}
+
+// Called by all 1024 threads of a block, thread e owning expert e (row0, m rows; m = 0 when the
+// expert is empty or masked out).  `big_at_min`, `half_joined`: the block's sums of big_tiles_at_min and half_tiles_joined.
+// `tmp` is an LDS array of >= 48 ints.
+__device__ __forceinline__ void emit_tiles(int e, int row0, int m, int big_at_min, int half_joined, const TileLists tl,
+                                           int32_t* tmp) {
+    if (tl.big_min <= 0) {                                 // no large experts possible: one list (uniform)
+        const int nt[1] = {(m + tl.small_rows - 1) / tl.small_rows};
+        int incl[1], total[1];
+        block_scan_1024(nt, incl, total, tmp);
+        write_tiles(tl.small_tiles + incl[0] - nt[0], e, row0, m, tl.small_rows, nt[0]);
+        if (e == 0) {
+            tl.ntiles[0] = total[0];
+            tl.ntiles[1] = tl.ntiles[kHalfCount] = 0;
+        }
+        return;
+    }
+    const bool big = m >= tiled_min_rows(big_at_min, tl.join_tiles, half_joined, tl.join_half_tiles);
+    const int nt[3] = {big ? 0 : (m + tl.small_rows - 1) / tl.small_rows, big ? (m + kBigTileRows - 1) / kBigTileRows : 0,
+                       big ? (m + kHalfTileRows - 1) / kHalfTileRows : 0};
+    int incl[3], total[3];
+    block_scan_1024(nt, incl, total, tmp);
+    write_tiles(tl.small_tiles + incl[0] - nt[0], e, row0, m, tl.small_rows, nt[0]);
+    write_tiles(tl.big_tiles + incl[1] - nt[1], e, row0, m, kBigTileRows, nt[1]);
+    write_tiles(tl.half_tiles + incl[2] - nt[2], e, row0, m, kHalfTileRows, nt[2]);
+    if (e == 0) {
+        tl.ntiles[0] = total[0];
+        tl.ntiles[1] = total[1];
+        tl.ntiles[kHalfCount] = total[2];
+        tl.ntiles[kSplitCounter] = tl.ntiles[kSplitCounter + 1] = 0;
+    }
+    // by the last wavefront, which has few tiles to write; both kernels of a product would else begin with these divisions
+    if (e >= 1022) {
+        const bool second = e == 1023;
+        *reinterpret_cast<TileSchedule*>(tl.ntiles + kScheduleAt + (second ? kScheduleInts : 0)) =
+            product_schedule(total[1], total[2], second ? tl.d_model : tl.d_ff, (second ? tl.d_ff : tl.d_model) >> 5, tl.cus);
+    }
 }
 
 // Unit u of the ntiles x ntn grid.  Units are numbered so that a run of consecutive units is a compact
@@ -188,14 +244,10 @@ __device__ __forceinline__ void store_folded_pair(uint16_t* out, int t, float w,
 // 4 x split loads of partial sums go out together (one row at a time, with a lookup per element, the pass was a
 // chain of dependent trips to memory: 35 of the 50 us of the kernel that did it on the Switch-large preset).
 template <typename Units, int FIRST, bool FOLD>
-__device__ __forceinline__ void finish_split_units(const Tile* __restrict__ big_tiles, int ntiles_big,
+__device__ __forceinline__ void finish_split_units(const TileSchedule& s, const Tile* __restrict__ tiles,
                                                    const float* __restrict__ partials, void* __restrict__ outp,
-                                                   int N, int kblk, int G,
-                                                   const float* __restrict__ bias, const FoldOut fold, int block,
+                                                   int N, int G, const float* __restrict__ bias, const FoldOut fold, int block,
                                                    int nblocks) {
-    if (ntiles_big <= 0 || partials == nullptr) return;
-    const TileSchedule s = tile_schedule<Units>(ntiles_big, N, kblk, G, true);
-    if (s.split < 2) return;
     constexpr int kLoads = 4;                                    // 16-byte loads per lane and part
     constexpr int kRowLanes = Units::kCols / 4;                  // lanes of a row: 64 (big units) or 32
     constexpr int kRowsPerLoad = kWave / kRowLanes;
@@ -210,7 +262,7 @@ __device__ __forceinline__ void finish_split_units(const Tile* __restrict__ big_
         const int ru = i / kGroups, lr0 = (i % kGroups) * (kLoads * kRowsPerLoad) + sub;
         int mt, nt;
         unit_of(s, s.rounds * G + ru, mt, nt);
-        const Tile tl = big_tiles[mt];
+        const Tile tl = tiles[mt];
         if (lr0 - sub >= tl.rows) continue;
         const int c = nt * Units::kCols + lane * 4;
         const float* base = partials + static_cast<size_t>(ru) * s.split * kTileFloats + static_cast<size_t>(lr0) * Units::kCols + lane * 4;
@@ -245,13 +297,14 @@ __device__ __forceinline__ void finish_split_units(const Tile* __restrict__ big_
 template <int FIRST, bool FOLD>
 __device__ __forceinline__ void finish_tiled_product(const Tile* __restrict__ big_tiles, const Tile* __restrict__ half_tiles,
                                                      const int32_t* __restrict__ ntiles, const float* __restrict__ partials,
-                                                     void* __restrict__ outp, int N, int kblk, int cus,
-                                                     const float* __restrict__ bias, const FoldOut& fold, int block, int nblocks) {
-    if (tiled_product_is_fine(ntiles[1], ntiles[kHalfCount], N, cus, FIRST == kFirstGelu))
-        finish_split_units<FineUnits, FIRST, FOLD>(half_tiles, ntiles[kHalfCount], partials, outp, N, kblk, cus, bias, fold,
-                                                   block, nblocks);
+                                                     void* __restrict__ outp, int N, int cus, const float* __restrict__ bias,
+                                                     const FoldOut& fold, int block, int nblocks) {
+    const TileSchedule s = *reinterpret_cast<const TileSchedule*>(ntiles + kScheduleAt + (FIRST != 0 ? 0 : kScheduleInts));
+    if (ntiles[1] <= 0 || s.split < 2) return;
+    if (s.shape == UnitShape::kFine)
+        finish_split_units<FineUnits, FIRST, FOLD>(s, half_tiles, partials, outp, N, cus, bias, fold, block, nblocks);
     else
-        finish_split_units<BigUnits, FIRST, FOLD>(big_tiles, ntiles[1], partials, outp, N, kblk, cus, bias, fold, block, nblocks);
+        finish_split_units<BigUnits, FIRST, FOLD>(s, big_tiles, partials, outp, N, cus, bias, fold, block, nblocks);
 }
 #endif
 

@@ -295,11 +295,11 @@ def test_tiled_ffn_row_tiles(gpu_lib, d, f):
 
 # experts of 65 ... 127 rows next to a large one: as many as join the tiled kernel (256 CUs: 8 half-sized tiles at 4096 columns)
 # and one more, which leaves them to the streaming kernel; and products just inside and outside one round of the tiled kernel's
-# 128 x 128 units (with GeLU: half a round of its 256 x 256 units).  Bar as above.
+# 128 x 128 units, and of its 256 x 128 units, with contractions shorter than the ring and longer than 96 steps.  Bar as above.
 @pytest.mark.parametrize("act", ["relu", "gelu"])
 @pytest.mark.parametrize("rows,d,f", [([128] + 7 * [100], 64, 4096), ([128] + 8 * [100], 64, 4096), ([256] + 6 * [65, 0], 4096, 32),
                                       (8 * [129], 64, 2048), (8 * [129] + [128], 64, 2048), (15 * [256], 96, 2048),
-                                      (16 * [130], 96, 2048)])
+                                      (16 * [130], 96, 2048), (17 * [129], 1024, 160), (22 * [130], 1024, 3104)])
 def test_unit_choice(gpu_lib, rows, d, f, act):
     say(f"[case] unit choice {len(rows)} experts d={d} f={f} {act}")
     check(*ffn_rows(gpu_lib, rows, d, f, "bf16", act, biases=True), 4e-3)
