@@ -253,41 +253,47 @@ __device__ __forceinline__ void place_chunk(const int32_t* __restrict__ idx, con
     }
 }
 
-// Inclusive prefix sums of N values at once over the 1024 threads of a block (thread e contributes v[i]) and their
-// totals: shuffles inside each wavefront, one LDS round for the 16 wavefront totals.  `tmp` is an LDS array of
-// >= 16 * N ints; two barriers, whatever N.
+// Inclusive prefix sum over the lanes of a wavefront, all of them active: inside the rows of 16, then from row to row (DPP moves,
+// no LDS traffic).
+__device__ __forceinline__ int wave_scan(int v) {
+    v += __builtin_amdgcn_update_dpp(0, v, 0x111, 0xF, 0xF, false);        // from 1, 2, 4 and 8 lanes below in the row
+    v += __builtin_amdgcn_update_dpp(0, v, 0x112, 0xF, 0xF, false);
+    v += __builtin_amdgcn_update_dpp(0, v, 0x114, 0xF, 0xF, false);
+    v += __builtin_amdgcn_update_dpp(0, v, 0x118, 0xF, 0xF, false);
+    v += __builtin_amdgcn_update_dpp(0, v, 0x142, 0xA, 0xF, false);        // the last lane of rows 0 and 2 to rows 1 and 3
+    v += __builtin_amdgcn_update_dpp(0, v, 0x143, 0xC, 0xF, false);        // lane 31 to rows 2 and 3
+    return v;
+}
+
+// Inclusive prefix sums of N values at once over the threads of a block's first `nw` wavefronts (thread e contributes v[i]) and their
+// totals.  Called by all threads of the block; the other wavefronts only meet the barrier and get nothing: a block of 16 wavefronts
+// that all went through this for the one or two that hold experts was bound by issuing it.  `tmp`: 16 * N ints of LDS, for
+// this call alone.
 template <int N>
-__device__ __forceinline__ void block_scan_1024(const int (&v)[N], int (&incl)[N], int (&total)[N], int32_t* tmp) {
+__device__ __forceinline__ void block_scan(const int (&v)[N], int (&incl)[N], int (&total)[N], int32_t* tmp, int nw) {
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
 #pragma unroll
-    for (int i = 0; i < N; ++i) incl[i] = v[i];
-#pragma unroll
-    for (int s = 1; s < 64; s <<= 1) {
+    for (int i = 0; i < N; ++i) incl[i] = total[i] = 0;
+    if (wave < nw) {
 #pragma unroll
         for (int i = 0; i < N; ++i) {
-            const int o = __shfl_up(incl[i], s);
-            if (lane >= s) incl[i] += o;
+            incl[i] = wave_scan(v[i]);
+            if (lane == 63) tmp[i * 16 + wave] = incl[i];
         }
-    }
-    __syncthreads();                       // tmp may still be read from a previous call
-    if (lane == 63) {
-#pragma unroll
-        for (int i = 0; i < N; ++i) tmp[i * 16 + wave] = incl[i];
     }
     __syncthreads();
+    if (wave < nw) {
+        for (int w = 0; w < nw; ++w) {
 #pragma unroll
-    for (int i = 0; i < N; ++i) {
-        int base = 0, sum = 0;
-#pragma unroll
-        for (int w = 0; w < 16; ++w) {
-            const int t = tmp[i * 16 + w];
-            if (w < wave) base += t;
-            sum += t;
+            for (int i = 0; i < N; ++i) {
+                const int t = tmp[i * 16 + w];
+                if (w < wave) incl[i] += t;
+                total[i] += t;
+            }
         }
-        incl[i] += base;
-        total[i] = sum;
     }
 }
+constexpr int kScanInts = 96;           // LDS of two scans of three values
 
 // what an expert of m rows contributes to the two sums that tiled_min_rows is asked with
 inline __host__ __device__ int big_tiles_at_min(int m, const TileLists& tl) {

@@ -58,7 +58,7 @@ hipError_t launch_pack(const moe_shape& s, int which, const void* src, void* dst
 __global__ __launch_bounds__(1024) void build_tiles_kernel(const int32_t* __restrict__ offsets,
                                                            const uint8_t* __restrict__ mask, int E, int A,
                                                            const TileLists lists) {
-    __shared__ int32_t scan[48];
+    __shared__ int32_t scan[kScanInts];
     const int e = threadIdx.x;
     int row0 = 0, m = 0;
     bool bad = false;
@@ -74,8 +74,8 @@ __global__ __launch_bounds__(1024) void build_tiles_kernel(const int32_t* __rest
     if (__syncthreads_or(bad ? 1 : 0)) m = 0;
     const int v[2] = {big_tiles_at_min(m, lists), half_tiles_joined(m, lists)};
     int incl[2], total[2];
-    block_scan_1024(v, incl, total, scan);
-    emit_tiles(e, row0, m, total[0], total[1], lists, scan);
+    block_scan(v, incl, total, scan, (E + 63) >> 6);
+    emit_tiles(e, E, row0, m, total[0], total[1], lists, scan + 48);
 }
 
 // The same unit when all four wavefronts of the block share the tile's rows over the same k range

@@ -344,7 +344,7 @@ __device__ __forceinline__ void sum_chunks(const int32_t* __restrict__ chunk_his
 }
 
 // counts, offsets, hot mask and tile lists from the token counts, by a block of 1024 threads, thread e owning expert e
-// with `mine` tokens.  `cnt` (2 * MOE_MAX_E ints) and `scan` (48 ints) are LDS scratch.  Any output pointer may be NULL.
+// with `mine` tokens.  `cnt` (2 * MOE_MAX_E ints) and `scan` (kScanInts) are LDS scratch.  Any output pointer may be NULL.
 // `mask_copy`: a second place for the hot mask (the caller's output buffer, which later kernels of the call must not depend
 // on: the caller may write to it as soon as the call has returned).  Returns the expert's first row.
 __device__ __forceinline__ int finalize_outputs(int mine, int E, int32_t* __restrict__ counts, int32_t* __restrict__ offsets,
@@ -381,7 +381,7 @@ __device__ __forceinline__ int finalize_outputs(int mine, int E, int32_t* __rest
     if (want_tiles && lists.big_min > 0) {                 // uniform
         const int v[3] = {mine, on ? big_tiles_at_min(mine, lists) : 0, on ? half_tiles_joined(mine, lists) : 0};
         int incl[3], total[3];
-        block_scan_1024(v, incl, total, scan);
+        block_scan(v, incl, total, scan, (E + 63) >> 6);
         row0 = incl[0] - mine;
         rows = total[0];
         at_min = total[1];
@@ -389,7 +389,7 @@ __device__ __forceinline__ int finalize_outputs(int mine, int E, int32_t* __rest
     } else {
         const int v[1] = {mine};
         int incl[1], total[1];
-        block_scan_1024(v, incl, total, scan);
+        block_scan(v, incl, total, scan, (E + 63) >> 6);
         row0 = incl[0] - mine;
         rows = total[0];
     }
@@ -398,7 +398,7 @@ __device__ __forceinline__ int finalize_outputs(int mine, int E, int32_t* __rest
         if (offsets) offsets[e] = row0;
     }
     if (e == 0 && offsets) offsets[E] = rows;
-    if (want_tiles) emit_tiles(e, row0, on ? mine : 0, at_min, joined, lists, scan);     // uniform: a kernel argument
+    if (want_tiles) emit_tiles(e, E, row0, on ? mine : 0, at_min, joined, lists, scan + 48);     // uniform: a kernel argument
     return row0;
 }
 
@@ -423,7 +423,7 @@ __global__ __launch_bounds__(1024) void dispatch_kernel(const int32_t* __restric
                                                         const int want_tiles, const PlaceArgs place) {
     extern __shared__ int32_t next_all[];
     __shared__ int32_t groups[2048];
-    __shared__ int32_t scan[48];
+    __shared__ int32_t scan[kScanInts];
     const int e = threadIdx.x;
     int total, before;
     if (finalize && blockIdx.x == 0) {
@@ -450,7 +450,7 @@ __global__ __launch_bounds__(1024) void dispatch_kernel(const int32_t* __restric
         } else {
             const int v[1] = {total};
             int incl[1], all[1];
-            block_scan_1024(v, incl, all, scan);
+            block_scan(v, incl, all, scan, (E + 63) >> 6);
             at = incl[0] - total;
         }
         at += before;
@@ -475,7 +475,7 @@ __global__ __launch_bounds__(1024) void scan_finalize_kernel(int32_t* __restrict
                                                              const uint8_t* __restrict__ mask_in, const TileLists lists,
                                                              const int want_tiles) {
     __shared__ int32_t groups[2048];
-    __shared__ int32_t scan[48];
+    __shared__ int32_t scan[kScanInts];
     int total, before;
     sum_chunks(chunk_hist, nchunks, E, 0, groups, total, before);
     __syncthreads();
@@ -740,7 +740,7 @@ __global__ __launch_bounds__(1024) void route_topk_finalize_kernel(const float* 
     int32_t* hist = reinterpret_cast<int32_t*>(lds + 64 * Ep);
     int32_t* experts = hist + 4 * E;
     __shared__ int32_t cnt[2 * MOE_MAX_E];
-    __shared__ int32_t scan[48];
+    __shared__ int32_t scan[kScanInts];
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
     const int nchunks = Tpad >> 4;                         // <= 4
     for (int i = threadIdx.x; i < 4 * E; i += 1024) hist[i] = 0;

@@ -88,15 +88,18 @@ __device__ __forceinline__ TileSchedule product_schedule(int big_tiles, int half
     return schedule_of<BigUnits>(shape, big_tiles, N, kblk, G);
 }
 
-// Called by all 1024 threads of a block, thread e owning expert e (row0, m rows; m = 0 when the
+// Called by all 1024 threads of a block, thread e owning expert e < E (row0, m rows; m = 0 when the
 // expert is empty or masked out).  `big_at_min`, `half_joined`: the block's sums of big_tiles_at_min and half_tiles_joined.
-// `tmp` is an LDS array of >= 48 ints.
-__device__ __forceinline__ void emit_tiles(int e, int row0, int m, int big_at_min, int half_joined, const TileLists tl,
+// `tmp`: 48 ints of LDS.
+__device__ __forceinline__ void emit_tiles(int e, int E, int row0, int m, int big_at_min, int half_joined, const TileLists tl,
                                            int32_t* tmp) {
+    const int nw = (E + 63) >> 6, wave = threadIdx.x >> 6;
+    const int small = (m + tl.small_rows - 1) >> __builtin_ctz(tl.small_rows);         // 16, 32 or 64 rows
     if (tl.big_min <= 0) {                                 // no large experts possible: one list (uniform)
-        const int nt[1] = {(m + tl.small_rows - 1) / tl.small_rows};
+        const int nt[1] = {small};
         int incl[1], total[1];
-        block_scan_1024(nt, incl, total, tmp);
+        block_scan(nt, incl, total, tmp, nw);
+        if (wave >= nw) return;                            // no barrier from here on
         write_tiles(tl.small_tiles + incl[0] - nt[0], e, row0, m, tl.small_rows, nt[0]);
         if (e == 0) {
             tl.ntiles[0] = total[0];
@@ -105,24 +108,33 @@ __device__ __forceinline__ void emit_tiles(int e, int row0, int m, int big_at_mi
         return;
     }
     const bool big = m >= tiled_min_rows(big_at_min, tl.join_tiles, half_joined, tl.join_half_tiles);
-    const int nt[3] = {big ? 0 : (m + tl.small_rows - 1) / tl.small_rows, big ? (m + kBigTileRows - 1) / kBigTileRows : 0,
+    const int nt[3] = {big ? 0 : small, big ? (m + kBigTileRows - 1) / kBigTileRows : 0,
                        big ? (m + kHalfTileRows - 1) / kHalfTileRows : 0};
     int incl[3], total[3];
-    block_scan_1024(nt, incl, total, tmp);
-    write_tiles(tl.small_tiles + incl[0] - nt[0], e, row0, m, tl.small_rows, nt[0]);
-    write_tiles(tl.big_tiles + incl[1] - nt[1], e, row0, m, kBigTileRows, nt[1]);
-    write_tiles(tl.half_tiles + incl[2] - nt[2], e, row0, m, kHalfTileRows, nt[2]);
-    if (e == 0) {
-        tl.ntiles[0] = total[0];
-        tl.ntiles[1] = total[1];
-        tl.ntiles[kHalfCount] = total[2];
-        tl.ntiles[kSplitCounter] = tl.ntiles[kSplitCounter + 1] = 0;
+    block_scan(nt, incl, total, tmp, nw);
+    if (wave < nw) {
+        write_tiles(tl.small_tiles + incl[0] - nt[0], e, row0, m, tl.small_rows, nt[0]);
+        write_tiles(tl.big_tiles + incl[1] - nt[1], e, row0, m, kBigTileRows, nt[1]);
+        write_tiles(tl.half_tiles + incl[2] - nt[2], e, row0, m, kHalfTileRows, nt[2]);
+        if (e == 0) {
+            tl.ntiles[0] = total[0];
+            tl.ntiles[1] = total[1];
+            tl.ntiles[kHalfCount] = total[2];
+            tl.ntiles[kSplitCounter] = tl.ntiles[kSplitCounter + 1] = 0;
+        }
     }
-    // by the last wavefront, which has few tiles to write; both kernels of a product would else begin with these divisions
-    if (e >= 1022) {
-        const bool second = e == 1023;
-        *reinterpret_cast<TileSchedule*>(tl.ntiles + kScheduleAt + (second ? kScheduleInts : 0)) =
-            product_schedule(total[1], total[2], second ? tl.d_model : tl.d_ff, (second ? tl.d_ff : tl.d_model) >> 5, tl.cus);
+    // The schedules, by a wavefront without experts if there is one: all kernels of both products would else begin with these
+    // divisions.
+    if (wave == min(nw, 15)) {
+        int big_tiles = 0, half_tiles = 0;
+        for (int w = 0; w < nw; ++w) {
+            big_tiles += tmp[16 + w];
+            half_tiles += tmp[32 + w];
+        }
+        const int lane = threadIdx.x & 63;
+        if (lane < 2)
+            *reinterpret_cast<TileSchedule*>(tl.ntiles + kScheduleAt + lane * kScheduleInts) = product_schedule(
+                big_tiles, half_tiles, lane ? tl.d_model : tl.d_ff, (lane ? tl.d_ff : tl.d_model) >> 5, tl.cus);
     }
 }
 
