@@ -359,9 +359,11 @@ moe_status moe_layer_forward_biased(const moe_shape* shape, const void* x, const
     if (shape->T == 0) return MOE_OK;
     // One expert per token and every expert running: each row of the permuted order is the whole output of
     // its token, so the second product scales it by the gate weight and writes `out` directly (Section 2.1's
-    // combine step without the fp32 round trip through memory); otherwise a combine pass follows.
-    const bool folded = shape->k == 1 && used == nullptr && shape->dtype == MOE_BF16;
-    const FoldOut fold{folded ? static_cast<uint16_t*>(out) : nullptr, tokmap, gate};
+    // combine step without the fp32 round trip through memory); otherwise a combine pass follows.  fp32 products store
+    // 16 bytes only where their output is aligned to that, and load their operands no wider: `out` elsewhere is left to combine.
+    const bool folded = shape->k == 1 && used == nullptr &&
+                        (shape->dtype == MOE_BF16 || reinterpret_cast<uintptr_t>(out) % 16 == 0);
+    const FoldOut fold{folded ? out : nullptr, tokmap, gate};
     if (layer_gathers_kmajor(*shape)) {
         // layers large enough for the tiled kernel: one pass gathers the token rows into the k-step-major
         // layout that lets both kernels fetch operand rows as full cache lines

@@ -406,10 +406,10 @@ hipError_t launch_route_fused(const moe_shape& s, const void* x, const void* w_g
                               hipStream_t st);
 // Top-1 layers without an expert mask: the second product writes the layer output itself.  Row p of the
 // permuted order belongs to token tokmap[p] and to nobody else, so out[tokmap[p]] = gate[tokmap[p]] * y[p],
-// rounded to bf16, is the combine step's result for that token (same operations, same rounding) and the
-// fp32 rows of y never go to memory.  out == nullptr: the product writes y as usual.
+// rounded to the storage type, is the combine step's result for that token (same operations, same rounding) and the
+// rows of y never go to memory.  out == nullptr: the product writes y as usual.
 struct FoldOut {
-    uint16_t* out;           // [T, N] bf16
+    void* out;               // [T, N] of the storage type
     const int32_t* tokmap;   // [A]
     const float* gate;       // [T] (k = 1)
 };
@@ -442,7 +442,7 @@ hipError_t launch_tile_product(bool first, const uint16_t* act, const int32_t* r
 int tile_product_grid();
 hipError_t launch_f32_product(bool first, const float* act, const int32_t* rowmap, const float* w, float* outp,
                               const Tile* tiles, const int32_t* ntiles, long max_tiles, int N, int K, int activation,
-                              const float* bias, hipStream_t st);
+                              const float* bias, const FoldOut& fold, hipStream_t st);
 hipError_t launch_permute(const moe_shape& s, const void* x, const int32_t* idx,
                           const int32_t* offsets, int32_t* perm, int32_t* inv_perm, void* x_perm,
                           int32_t* hist_ws, hipStream_t st);

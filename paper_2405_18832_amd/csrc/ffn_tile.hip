@@ -408,7 +408,7 @@ __device__ __forceinline__ void run_units(const uint16_t* __restrict__ act, cons
                         for (int m = 0; m < 2; ++m) {
                             const int nb = cur.nt * (kTN / 16) + wn * 4 + 2 * m;
                             if (nb >= nblk) continue;                   // wave-uniform
-                            store_folded_pair(fold.out, ftok, fw, ok, nb * 16, N, be, acc[2 * m][tf], acc[2 * m + 1][tf]);
+                            store_folded_pair(static_cast<uint16_t*>(fold.out), ftok, fw, ok, nb * 16, N, be, acc[2 * m][tf], acc[2 * m + 1][tf]);
                         }
                     } else {
 #pragma unroll

@@ -94,7 +94,7 @@ __device__ __forceinline__ void store_group(void* __restrict__ outp, const Tile 
             for (int m = 0; m < 2; ++m) {
                 const int nb = ng * 4 + 2 * m;
                 if (nb >= nblk) continue;                  // wave-uniform
-                store_folded_pair(fold.out, ftok[tf], fw[tf], ok, nb * 16, N, be, acc[2 * m][tf], acc[2 * m + 1][tf]);
+                store_folded_pair(static_cast<uint16_t*>(fold.out), ftok[tf], fw[tf], ok, nb * 16, N, be, acc[2 * m][tf], acc[2 * m + 1][tf]);
             }
         } else {
 #pragma unroll

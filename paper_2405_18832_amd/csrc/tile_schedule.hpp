@@ -297,7 +297,7 @@ __device__ __forceinline__ void finish_split_units(const TileSchedule& s, const 
             const int lr = lr0 + q * kRowsPerLoad;
             if (lr >= tl.rows || c >= N) continue;
             if constexpr (FOLD) {
-                store_folded(fold.out, tok[q], fold.gate[tok[q]], c, N, be, sum[q]);
+                store_folded(static_cast<uint16_t*>(fold.out), tok[q], fold.gate[tok[q]], c, N, be, sum[q]);
             } else {
                 store_out<FIRST>(outp, tl.row0 + lr, c, N, be, sum[q]);
             }

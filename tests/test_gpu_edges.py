@@ -373,3 +373,27 @@ def test_derived_mask_output_is_not_read_back(gpu_lib, T, E, k):
     torch.cuda.synchronize()
     assert int(written.sum()) == E // 3 and int(mask.sum()) == 0
     assert torch.equal(out.view(torch.int16), want.view(torch.int16))
+
+
+# fp32 layers of one expert per token, whose second product stores the layer's output itself: tiles of 1, 16, 17, 64 and 65 rows,
+# the three widths of loads, sums in four, two and one chains, columns that end inside a unit, tokens without numbers, and an output
+# that is not 16-byte aligned.  The same sums, one multiply and one rounding as with combine, which a mask of ones takes: bit for bit.
+@pytest.mark.parametrize("at", [0, 1])
+@pytest.mark.parametrize("T,d,f,E", [(1, 32, 33, 1), (17, 20, 33, 1), (64, 64, 96, 1), (65, 33, 70, 1), (200, 66, 160, 5),
+                                     (500, 258, 512, 8)])
+def test_f32_top1_output(gpu_lib, T, d, f, E, at):
+    say(f"[case] f32 top-1 output T={T} d={d} f={f} E={E}, output {at} elements off")
+    moe = gpu_lib
+    gen = torch.Generator(device="cuda").manual_seed(T + d + f)
+    new = lambda *s: torch.randn(s, device="cuda", generator=gen)
+    x, wg, bg, w1, b1, w2, b2 = new(T, d), new(E, d), new(E), new(E, f, d), new(E, f), new(E, d, f), new(E, d)
+    x[T // 2, 0] = float("nan")
+    shape = moe.make_shape(T, d, f, E, 1, "f32", False, 1)
+    ws = torch.full((moe.moe_workspace_bytes(shape),), 0xFF, dtype=torch.uint8, device="cuda")
+    outs = []
+    for mask in (None, torch.ones(E, dtype=torch.uint8, device="cuda")):
+        buf = torch.full((at + T * d + 8,), 7.0, device="cuda")
+        moe.moe_layer_forward_biased(shape, x, wg, bg, w1, b1, w2, b2, mask, -1, buf[at:at + T * d].view(T, d), ws=ws)
+        torch.cuda.synchronize()
+        outs.append(torch.where(buf.isnan(), 8.0, buf).view(torch.int32))
+    assert torch.equal(outs[0], outs[1])
