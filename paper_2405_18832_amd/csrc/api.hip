@@ -346,6 +346,24 @@ moe_status moe_layer_forward_biased(const moe_shape* shape, const void* x, const
         return from_hip(launch_few_products(*shape, x, gate_bias, part, w1, w2, b1, b2, idx, gate, cnt, offsets,
                                             perm, inv, tokmap, at<void>(ws, L.h), out, hs));
     }
+    // One expert per token and every expert running: each row of the permuted order is the whole output of
+    // its token, so the second product scales it by the gate weight and writes `out` directly (Section 2.1's
+    // combine step without the fp32 round trip through memory); otherwise a combine pass follows.  fp32 products store
+    // 16 bytes only where their output is aligned to that, and load their operands no wider: `out` elsewhere is left to combine.
+    const bool folded = shape->k == 1 && used == nullptr &&
+                        (shape->dtype == MOE_BF16 || reinterpret_cast<uintptr_t>(out) % 16 == 0);
+    const FoldOut fold{folded ? out : nullptr, tokmap, gate};
+    if (used == nullptr && layer_sorts_in_first(*shape)) {
+        if (hot_mask_out != nullptr && launch_mask_out(nullptr, hot_mask_out, shape->E, hs) != hipSuccess) return MOE_ERR_HIP;
+        e = launch_route_fused(*shape, x, w_gate, gate_bias, idx, gate, nullptr, hist, at<float>(ws, L.gate_part), hs);
+        if (e != hipSuccess) return MOE_ERR_HIP;
+        float* y = at<float>(ws, L.y_perm);
+        e = launch_f32_sorted_products(*shape, static_cast<const float*>(x), idx, static_cast<const float*>(w1),
+                                       static_cast<const float*>(w2), b1, b2, cnt, offsets, perm, inv, tokmap, lists,
+                                       at<float>(ws, L.h), y, fold, hs);
+        if (e != hipSuccess) return MOE_ERR_HIP;
+        return folded ? MOE_OK : from_hip(launch_combine(*shape, y, inv, idx, gate, nullptr, out, hs));
+    }
     const int tok = route_chunk_tokens(*shape);
     const PlaceArgs place{idx, perm, inv, tokmap, shape->T * shape->k, shape->k, tok * shape->k};
     e = launch_route_finalize(*shape, x, w_gate, gate_bias, idx, gate, nullptr, hist, at<float>(ws, L.gate_part), cnt,
@@ -357,13 +375,6 @@ moe_status moe_layer_forward_biased(const moe_shape* shape, const void* x, const
         if (e != hipSuccess) return MOE_ERR_HIP;
     }
     if (shape->T == 0) return MOE_OK;
-    // One expert per token and every expert running: each row of the permuted order is the whole output of
-    // its token, so the second product scales it by the gate weight and writes `out` directly (Section 2.1's
-    // combine step without the fp32 round trip through memory); otherwise a combine pass follows.  fp32 products store
-    // 16 bytes only where their output is aligned to that, and load their operands no wider: `out` elsewhere is left to combine.
-    const bool folded = shape->k == 1 && used == nullptr &&
-                        (shape->dtype == MOE_BF16 || reinterpret_cast<uintptr_t>(out) % 16 == 0);
-    const FoldOut fold{folded ? out : nullptr, tokmap, gate};
     if (layer_gathers_kmajor(*shape)) {
         // layers large enough for the tiled kernel: one pass gathers the token rows into the k-step-major
         // layout that lets both kernels fetch operand rows as full cache lines

@@ -443,6 +443,11 @@ int tile_product_grid();
 hipError_t launch_f32_product(bool first, const float* act, const int32_t* rowmap, const float* w, float* outp,
                               const Tile* tiles, const int32_t* ntiles, long max_tiles, int N, int K, int activation,
                               const float* bias, const FoldOut& fold, hipStream_t st);
+bool layer_sorts_in_first(const moe_shape& s);
+hipError_t launch_f32_sorted_products(const moe_shape& s, const float* x, const int32_t* idx, const float* w1, const float* w2,
+                                      const float* b1, const float* b2, int32_t* counts, int32_t* offsets, int32_t* perm,
+                                      int32_t* inv_perm, int32_t* tokmap, const TileLists& lists, float* h, float* y_perm,
+                                      const FoldOut& fold, hipStream_t st);
 hipError_t launch_permute(const moe_shape& s, const void* x, const int32_t* idx,
                           const int32_t* offsets, int32_t* perm, int32_t* inv_perm, void* x_perm,
                           int32_t* hist_ws, hipStream_t st);

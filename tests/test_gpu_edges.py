@@ -397,3 +397,33 @@ def test_f32_top1_output(gpu_lib, T, d, f, E, at):
         torch.cuda.synchronize()
         outs.append(torch.where(buf.isnan(), 8.0, buf).view(torch.int32))
     assert torch.equal(outs[0], outs[1])
+
+
+# fp32 layers whose first product sorts the assignments: groups of 64 assignments and 256 threads with and without a rest, the most
+# assignments and experts and one more (which take the general path), column groups that are and are not a multiple of 8, a token of
+# NaN logits whose slots all name expert 0.  The same order and sums as the general path, which a mask of ones takes: bit for bit.
+@pytest.mark.parametrize("T,d,f,E,k", [(1, 32, 16, 1, 1), (64, 64, 256, 8, 2), (63, 33, 70, 5, 1), (65, 130, 128, 33, 1),
+                                       (128, 20, 144, 64, 8), (129, 64, 32, 8, 8), (256, 66, 40, 4, 4), (1024, 32, 144, 64, 1),
+                                       (1025, 32, 64, 64, 1), (300, 32, 64, 65, 2), (3, 96, 2048, 3, 3)])
+def test_f32_sort_in_first_product(gpu_lib, T, d, f, E, k):
+    say(f"[case] f32 sort in first product T={T} d={d} f={f} E={E} k={k}")
+    moe = gpu_lib
+    gen = torch.Generator(device="cuda").manual_seed(T + d + f)
+    new = lambda *s: torch.randn(s, device="cuda", generator=gen)
+    x, wg, bg, w1, b1, w2, b2 = new(T, d), new(E, d), new(E), new(E, f, d), new(E, f), new(E, d, f), new(E, d)
+    x[T // 2, 0] = float("nan")
+    shape = moe.make_shape(T, d, f, E, k, "f32", True, 1)
+    ws = torch.full((moe.moe_workspace_bytes(shape),), 0xFF, dtype=torch.uint8, device="cuda")
+
+    def layer(mask, by_products=True):
+        i32 = lambda *s: torch.full(s, -1, dtype=torch.int32, device="cuda")
+        more = (i32(T, k), torch.zeros((T, k), device="cuda"), i32(E), i32(T * k), torch.zeros(E, dtype=torch.uint8, device="cuda"))
+        out = torch.full((T, d), 7.0, device="cuda")
+        moe.moe_layer_forward_biased(shape, x, wg, bg, w1, b1, w2, b2, mask, -1, out, *(more if by_products else (None,) * 5), ws=ws)
+        torch.cuda.synchronize()
+        return [torch.where(a.isnan(), 8.0, a) if a.is_floating_point() else a for a in (out, *more)]
+
+    few, general = layer(None), layer(torch.ones(E, dtype=torch.uint8, device="cuda"))
+    for a, b in zip(few, general):
+        assert torch.equal(a.view(torch.uint8), b.view(torch.uint8))
+    assert torch.equal(layer(None, by_products=False)[0], few[0])
