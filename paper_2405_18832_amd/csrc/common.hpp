@@ -188,7 +188,7 @@ struct TileLists {
     Tile* big_tiles;       // capacity A / kBigTileRows + E (unused when big_min == 0)
     Tile* half_tiles;      // the same experts in tiles of kHalfTileRows rows, capacity A / kHalfTileRows + E
     int32_t* ntiles;       // [0] small count, [1] big count, [2], [3] part counters of the tiled products, [4] half count, [8] and
-                           // [16]: the TileSchedule of the first and of the second product (if big_min > 0)
+                           // [20]: the TileSchedule of the first and of the second product (if big_min > 0)
     float* partials;       // kSplitSlots partial tiles (nullptr when big_min == 0)
     int small_rows;        // rows per small tile
     int big_min;           // experts with >= big_min rows are "big"; 0 = none

@@ -82,6 +82,16 @@ __device__ __forceinline__ void mfma_pair(const bf16x8 (&w)[4], const bf16x8 (&x
     }
 }
 
+// Partial sums of a narrow unit's contraction: no fewer than in the units that would run without narrow ones, because the rounding
+// error of a sum grows with its length.  Those were big ones, cut or not (sch.sums), or, for the first product of a GeLU layer, fine
+// ones, which add up two halves, the left-over ones of them cut again from 48 steps on.
+// fp32 rows of 72 narrow units against 64 bits, relative error: 64 steps in one sum 9.1e-8, in two 6.7e-8; 96 in one 11.6e-8, in three
+// 7.1e-8.
+template <int FIRST>
+__device__ __forceinline__ int narrow_sums(const TileSchedule& sch, int kblk) {
+    return FIRST == kFirstGelu ? max(sch.sums, kblk < 2 * FineUnits::kMinSplitSteps ? min(kblk, 2) : 4) : sch.sums;
+}
+
 template <int FIRST, typename Units>
 __device__ __forceinline__ void run_units(const uint16_t* __restrict__ act, const int32_t* __restrict__ rowmap,
                                           const uint16_t* __restrict__ wpk, void* __restrict__ outp,
@@ -90,6 +100,7 @@ __device__ __forceinline__ void run_units(const uint16_t* __restrict__ act, cons
                                           int act_kmajor, const float* __restrict__ bias, const FoldOut& fold,
                                           unsigned char* smem) {
     constexpr bool FINE = Units::kGroups == 2;
+    constexpr bool NARROW = std::is_same_v<Units, NarrowUnits>;
     constexpr int kTM = Units::kRows, kTN = Units::kCols;
     constexpr int kGroupWaves = kWaves / Units::kGroups;
     constexpr int WN = kTN / 64;                        // wavefronts of a group side by side
@@ -123,6 +134,7 @@ __device__ __forceinline__ void run_units(const uint16_t* __restrict__ act, cons
     const int pb = (G % 8 == 0) ? static_cast<int>(blockIdx.x & 7) * (G >> 3) + static_cast<int>(blockIdx.x >> 3)
                                 : static_cast<int>(blockIdx.x);
     const int nleft = sch.R * sch.split;                // parts of the left-over units
+    const int sums = narrow_sums<FIRST>(sch, kblk);     // of a narrow unit
 
     // A unit of work: (row tile mt, column tile nt) over k-steps [kb0, kb0 + nk), whole (nparts == 1) or
     // one of nparts parts of a left-over unit.
@@ -251,6 +263,29 @@ __device__ __forceinline__ void run_units(const uint16_t* __restrict__ act, cons
         for (int nf = 0; nf < 4; ++nf)
 #pragma unroll
             for (int tf = 0; tf < RF; ++tf) acc[nf][tf] = f32x4{0.f, 0.f, 0.f, 0.f};
+        // Narrow units: the contraction is added up in `sums` about equal runs of steps, one after the other, and these in order.
+        f32x4 done[NARROW ? 4 : 1][NARROW ? RF : 1];
+        int run = 1, run_end = NARROW ? nk / sums : 0;
+        if constexpr (NARROW) {
+#pragma unroll
+            for (int nf = 0; nf < 4; ++nf)
+#pragma unroll
+                for (int tf = 0; tf < RF; ++tf) done[nf][tf] = f32x4{0.f, 0.f, 0.f, 0.f};
+        }
+        auto end_run = [&](int j) {
+            if constexpr (NARROW) {
+                if (j != run_end || run == sums) return;    // block-uniform
+#pragma unroll
+                for (int nf = 0; nf < 4; ++nf)
+#pragma unroll
+                    for (int tf = 0; tf < RF; ++tf) {
+                        done[nf][tf] += acc[nf][tf];
+                        acc[nf][tf] = f32x4{0.f, 0.f, 0.f, 0.f};
+                    }
+                ++run;
+                run_end = nk * run / sums;
+            }
+        };
         StageFrags fr;
         // One stage of 32 k, software-pipelined across stages so that the MFMA pipe never waits for LDS.
         // The iteration for stage j starts by making sure that stage j + 1 has landed for every wavefront
@@ -265,6 +300,7 @@ __device__ __forceinline__ void run_units(const uint16_t* __restrict__ act, cons
         auto iterate = [&](auto cbuf, auto steady, int j) {
             constexpr int C = decltype(cbuf)::value;
             constexpr bool STEADY = decltype(steady)::value;
+            end_run(j);
             const int slot_next = slot + 1 == kStages ? 0 : slot + 1;
             const int slot_free = slot == 0 ? kStages - 1 : slot - 1;          // held stage j - 1
             const unsigned char* st_cur = ring + slot * kStageBytes;
@@ -346,6 +382,12 @@ __device__ __forceinline__ void run_units(const uint16_t* __restrict__ act, cons
         if (j + 3 < nk) iterate(std::integral_constant<int, 1>{}, std::false_type{}, j + 3);
         if (j + 4 < nk) iterate(std::integral_constant<int, 0>{}, std::false_type{}, j + 4);
 
+        if constexpr (NARROW) {
+#pragma unroll
+            for (int nf = 0; nf < 4; ++nf)
+#pragma unroll
+                for (int tf = 0; tf < RF; ++tf) acc[nf][tf] = done[nf][tf] + acc[nf][tf];
+        }
         if constexpr (FINE) {
             // the second group may have one step and so one barrier less
             for (int i = cur.longest - max(nk, 1); i > 0; --i) asm volatile("s_barrier" ::: "memory");

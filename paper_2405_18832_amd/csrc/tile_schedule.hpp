@@ -55,8 +55,10 @@ struct TileSchedule {
     int rounds, R;      // full rounds of G units; units left over
     int split;          // parts per left-over unit (1: not cut, written directly)
     int GM, GN;         // patch of consecutive units: GM row tiles x GN column tiles
+    int sums;           // narrow units: partial sums of the contraction that an output is added up from (run_units)
+    int pad[3];
 };
-constexpr int kScheduleAt = 8, kScheduleInts = 8;      // in the `ntiles` array, one per product
+constexpr int kScheduleAt = 8, kScheduleInts = 12;     // in the `ntiles` array, one per product
 static_assert(sizeof(TileSchedule) == kScheduleInts * 4, "as laid out in the array");
 
 #ifdef __HIPCC__
@@ -69,7 +71,11 @@ __device__ __forceinline__ TileSchedule schedule_of(UnitShape shape, int ntiles,
     const int U = ntiles * s.ntn;
     s.rounds = U / G;
     s.R = U - s.rounds * G;
-    s.split = 1;
+    s.split = s.sums = 1;
+    if (shape == UnitShape::kNarrow) {                     // as many as big units would have been cut into
+        const int big = ntiles * ((N + BigUnits::kCols - 1) / BigUnits::kCols);
+        s.sums = max(1, min(G / max(big, 1), min(kMaxSplit, kblk / BigUnits::kMinSplitSteps)));
+    }
     if (s.R > 0 && shape != UnitShape::kNarrow) {          // narrow units are more than half a round: never cut
         constexpr int slots = kSplitSlots * (kBigTileRows * 256 / (Units::kRows * Units::kCols));
         const int by_blocks = G / s.R, by_steps = kblk / Units::kMinSplitSteps, by_slots = slots / s.R;

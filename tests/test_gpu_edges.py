@@ -305,6 +305,55 @@ def test_unit_choice(gpu_lib, rows, d, f, act):
     check(*ffn_rows(gpu_lib, rows, d, f, "bf16", act, biases=True), 4e-3)
 
 
+def ffn_on_device(moe, rows, x, w1, w2, act="relu"):
+    """fp32 rows of moe_expert_ffn over bf16 tensors: x [A, d], w1 [E, f, d], w2 [E, d, f]."""
+    E, f, d = w1.shape
+    shape = moe.make_shape(sum(rows), d, f, E, 1, "bf16", False, {"relu": 0, "gelu": 1}[act])
+    p1, p2 = torch.empty_like(w1), torch.empty_like(w2)
+    moe.moe_pack_weights(shape, 1, w1.contiguous(), p1)
+    moe.moe_pack_weights(shape, 2, w2.contiguous(), p2)
+    offsets = torch.tensor([0] + list(rows), dtype=torch.int32).cumsum(0, dtype=torch.int32).cuda()
+    y = torch.full((sum(rows), d), float("nan"), device="cuda")
+    ws = torch.full((moe.moe_workspace_bytes(shape),), 0xFF, dtype=torch.uint8, device="cuda")
+    moe.moe_expert_ffn(shape, x.contiguous(), p1, p2, offsets, None, y, ws)
+    torch.cuda.synchronize()
+    return y
+
+
+# 256 x 128 units add a contraction up in as many partial sums as full-width units would have been cut into (none is longer than
+# those): their rows are the fp32 sums, in order, of calls over a run of 32 steps each, bit for bit.  Integers that the first product
+# adds up exactly make h the same in all calls.
+@pytest.mark.parametrize("E,m,d,runs", [(9, 256, 2048, 2), (10, 250, 2048, 3), (14, 256, 2048, 2)])
+def test_narrow_units_partial_sums(gpu_lib, E, m, d, runs):
+    say(f"[case] partial sums of narrow units, {E} x {m} rows d={d}, {runs} runs")
+    gen = torch.Generator(device="cuda").manual_seed(E * m)
+    whole = lambda lo, hi, *s: torch.randint(lo, hi, s, device="cuda", generator=gen).to(torch.bfloat16)
+    f = 1024 * runs
+    x, w1 = whole(-2, 3, E * m, d), whole(-1, 2, E, f, d)
+    w2 = (torch.randn((E, d, f), device="cuda", generator=gen) * f ** -0.5).to(torch.bfloat16)
+    y = ffn_on_device(gpu_lib, E * [m], x, w1, w2)
+    parts = [ffn_on_device(gpu_lib, E * [m], x, w1[:, i:i + 1024], w2[:, :, i:i + 1024]) for i in range(0, f, 1024)]
+    want = parts[0]
+    for p in parts[1:]:
+        want = want + p
+    assert torch.equal(y, want)
+
+
+# GeLU: the first product of all experts at once (256 x 128 units) and of two experts at a time (128 x 128 units, each two halves of the
+# contraction) round the same sums.  The second product only picks columns of h.
+@pytest.mark.parametrize("m,d", [(256, 768), (188, 1024)])
+def test_narrow_units_gelu_sums(gpu_lib, m, d):
+    say(f"[case] GeLU sums of narrow units, {m} rows d={d}")
+    E, f = 24, 1024
+    gen = torch.Generator(device="cuda").manual_seed(m)
+    x = torch.randn((E * m, d), device="cuda", generator=gen).to(torch.bfloat16)
+    w1 = (torch.randn((E, f, d), device="cuda", generator=gen) * d ** -0.5).to(torch.bfloat16)
+    w2 = torch.eye(f, device="cuda", dtype=torch.bfloat16)[torch.randperm(f, device="cuda", generator=gen)[:d]].expand(E, d, f)
+    y = ffn_on_device(gpu_lib, E * [m], x, w1, w2, "gelu")
+    two = [ffn_on_device(gpu_lib, 2 * [m], x[e * m:(e + 2) * m], w1[e:e + 2], w2[e:e + 2], "gelu") for e in range(0, E, 2)]
+    assert torch.equal(y, torch.cat(two))
+
+
 # counting sort: one block, a block per 16 or 4 chunks, and slot bases through memory, at the sizes where one form gives way to
 # the next (4096 assignments for moe_permute; 256 experts; 64 k histogram entries or 1024 chunks), by itself and in the layer.
 # Past 64 k entries: the layer with chunks of 16 tokens and 257 experts, moe_permute with chunks of 256 assignments and 1024
