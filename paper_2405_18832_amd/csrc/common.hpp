@@ -195,6 +195,7 @@ struct TileLists {
     int join_tiles;        // tiles of big experts from which the mid-sized experts join them (tiled_min_rows); 0 = never
     int join_half_tiles;   // half-sized tiles, with the mid-sized experts', up to which they do
     int d_model, d_ff, cus;       // what the schedules depend on besides the tiles
+    bool gelu;
 };
 
 #ifdef __HIPCC__

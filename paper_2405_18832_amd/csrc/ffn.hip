@@ -471,6 +471,7 @@ TileLists ffn_tile_lists(const moe_shape& s, Tile* small_ws, Tile* big_ws, Tile*
     l.d_model = s.d_model;
     l.d_ff = s.d_ff;
     l.cus = tile_product_grid();
+    l.gelu = s.activation == MOE_ACT_GELU;
     l.join_half_tiles = tile_product_grid() / ((std::max(s.d_model, s.d_ff) + FineUnits::kCols - 1) / FineUnits::kCols);
     return l;
 }

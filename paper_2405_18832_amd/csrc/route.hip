@@ -884,7 +884,7 @@ static hipError_t launch_dispatch_pw(const int32_t* chunk_hist, int nchunks, int
 static hipError_t launch_dispatch(int32_t* chunk_hist, int nchunks, int E, const int32_t* offsets_in, bool finalize,
                                   int32_t* counts, int32_t* offsets, int H, uint8_t* hot_mask, uint8_t* mask_copy,
                                   const uint8_t* mask_in, const TileLists* lists, const PlaceArgs* place, hipStream_t st) {
-    const TileLists none{nullptr, nullptr, nullptr, nullptr, nullptr, 16, 0, 0, 0, 0, 0, 1};
+    const TileLists none{nullptr, nullptr, nullptr, nullptr, nullptr, 16, 0, 0, 0, 0, 0, 1, false};
     const PlaceArgs no_place{nullptr, nullptr, nullptr, nullptr, 0, 1, 1};
     const TileLists& tl = lists ? *lists : none;
     const bool tiles = lists != nullptr;
@@ -928,7 +928,7 @@ hipError_t launch_route_finalize(const moe_shape& s, const void* x, const void* 
             if (err != hipSuccess) return err;
             // at most kTopkFinalizeLdsMax: the limit configure_route_kernels has raised this kernel to
             const size_t lds = static_cast<size_t>(64) * (s.E + 1) * 4 + static_cast<size_t>(4) * s.E * 4 + static_cast<size_t>(64) * s.k * 4;
-            const TileLists none{nullptr, nullptr, nullptr, nullptr, nullptr, 16, 0, 0, 0, 0, 0, 1};
+            const TileLists none{nullptr, nullptr, nullptr, nullptr, nullptr, 16, 0, 0, 0, 0, 0, 1, false};
             const PlaceArgs no_place{nullptr, nullptr, nullptr, nullptr, 0, 1, 1};
             hipLaunchKernelGGL(route_topk_finalize_kernel, dim3(1), dim3(1024), lds, st, gate_part_ws, bias, idx, gate,
                                margin, s.T, s.E, s.k, s.renormalize, Tpad, counts, offsets, H, hot_mask, mask_copy,

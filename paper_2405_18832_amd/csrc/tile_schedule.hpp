@@ -37,16 +37,26 @@ struct NarrowUnits {
 // full-width units: big units would run on that many of 256 CUs, or be cut along K and added up afterwards), unless the contraction
 // is so long that the cut units win: a step takes about 0.5 us in a narrow unit and 0.7 in a big one.  Big units that can be cut in
 // three win from about 100 steps on, those cut in two from about 190; and with few row tiles the narrow units of an XCD share too
-// little of their rows.  us, big or fine units before -> narrow units, both products' worth of adding up included, tiles of 256 rows:
-// 96 units of 24 steps 35 -> 31 (137 rows 33 -> 25), 112 of 32 39 -> 35, 72 of 48 48 -> 41, 80 of 64 51 -> 49, 112 of 64 66 -> 57, 112 of
-// 96 85 -> 69, 96 of 128 95 -> 84, 124 of 128 110 -> 96; and 68 of 128 73 -> 76, 3 x 32 of 128 96 -> 103, 96 of 192 115 -> 117, 80 of 256
-// 126 -> 143.  GeLU: 96 of 24 39 -> 34 (137 rows 33 -> 27), 112 of 64 65 -> 60 (62 -> 43).
+// little of their rows: sooner.  Else big ones, but fine ones for the first product of a GeLU layer with less than half a round of
+// big units, whose epilogue all CUs work on then instead of those that have a big unit; up to 85 big units these are ahead of the
+// narrow ones too from about 60 steps on.
+// us, what ran without narrow units -> narrow, the pass that adds up parts included, tiles of 256 rows: 96 units of 24 steps
+// 39 -> 31 (188 rows 35 -> 28), 112 of 32 44 -> 37, 72 of 36 42 -> 32, 80 of 64 55 -> 46, 112 of 64 65 -> 52, 108 of 96 80 -> 68, 96 of 128
+// 88 -> 81, 128 of 128 104 -> 90; not taken, with few row tiles and up to 85 units: 72 of 96 56.8 -> 62.7 (140 rows), 72 of 72
+// 62 -> 64, 72 of 128 71 -> 75; nor 3 x 32 of 128 96 -> 103, 96 of 192 115 -> 117, 80 of 256 126 -> 143.
+// GeLU first products: 96 of 24 44 -> 36, 128 of 64 75 -> 55, 112 of 128 107 -> 89; fine, not narrow: 72 of 63 0.88, 77 of 77 0.94,
+// 69 of 92 0.80, 88 of 96 and 4 row tiles 0.94 of the time; fine, not big: 80 of 144 (130 rows) 73 and 79, 75 of 171 (196 rows) 82 and
+// 95, 72 of 131 70 and 79 (full row tiles and long contractions are the other way: 112 of 256 184 and 157).
 enum class UnitShape { kBig, kNarrow, kFine };
-inline __host__ __device__ UnitShape tiled_product_units(long big_tiles, long half_tiles, int N, int kblk, int cus) {
+inline __host__ __device__ UnitShape tiled_product_units(long big_tiles, long half_tiles, int N, int kblk, int cus, bool gelu) {
     if (half_tiles * ((N + FineUnits::kCols - 1) / FineUnits::kCols) <= cus) return UnitShape::kFine;
-    if (big_tiles * ((N + NarrowUnits::kCols - 1) / NarrowUnits::kCols) > cus) return UnitShape::kBig;
-    const bool cut_in_two = big_tiles * ((N + BigUnits::kCols - 1) / BigUnits::kCols) * 3 > cus;
-    return kblk <= 96 || (kblk <= 128 && cut_in_two && big_tiles >= 8) ? UnitShape::kNarrow : UnitShape::kBig;
+    const long big_units = big_tiles * ((N + BigUnits::kCols - 1) / BigUnits::kCols);
+    if (big_tiles * ((N + NarrowUnits::kCols - 1) / NarrowUnits::kCols) <= cus) {
+        const bool cut_in_three = big_units * 3 <= cus;
+        const int longest = cut_in_three ? (gelu ? 56 : big_tiles >= 9 ? 96 : 70) : (big_tiles >= 8 ? 128 : gelu ? 80 : 96);
+        if (kblk <= longest) return UnitShape::kNarrow;
+    }
+    return gelu && big_units * 2 < cus ? UnitShape::kFine : UnitShape::kBig;
 }
 
 struct TileSchedule {
@@ -87,8 +97,8 @@ __device__ __forceinline__ TileSchedule schedule_of(UnitShape shape, int ntiles,
     return s;
 }
 
-__device__ __forceinline__ TileSchedule product_schedule(int big_tiles, int half_tiles, int N, int kblk, int G) {
-    const UnitShape shape = tiled_product_units(big_tiles, half_tiles, N, kblk, G);
+__device__ __forceinline__ TileSchedule product_schedule(int big_tiles, int half_tiles, int N, int kblk, int G, bool gelu) {
+    const UnitShape shape = tiled_product_units(big_tiles, half_tiles, N, kblk, G, gelu);
     if (shape == UnitShape::kFine) return schedule_of<FineUnits>(shape, half_tiles, N, kblk, G);
     if (shape == UnitShape::kNarrow) return schedule_of<NarrowUnits>(shape, big_tiles, N, kblk, G);
     return schedule_of<BigUnits>(shape, big_tiles, N, kblk, G);
@@ -140,7 +150,8 @@ __device__ __forceinline__ void emit_tiles(int e, int E, int row0, int m, int bi
         const int lane = threadIdx.x & 63;
         if (lane < 2)
             *reinterpret_cast<TileSchedule*>(tl.ntiles + kScheduleAt + lane * kScheduleInts) = product_schedule(
-                big_tiles, half_tiles, lane ? tl.d_model : tl.d_ff, (lane ? tl.d_ff : tl.d_model) >> 5, tl.cus);
+                big_tiles, half_tiles, lane ? tl.d_model : tl.d_ff, (lane ? tl.d_ff : tl.d_model) >> 5, tl.cus,
+                lane == 0 && tl.gelu);
     }
 }
 
