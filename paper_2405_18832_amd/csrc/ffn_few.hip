@@ -67,7 +67,9 @@ struct FewRoute {
 };
 
 // First product.  A unit is 64 columns of a tile, or 16 where those are fewer than the CUs; the four wavefronts split the
-// contraction.  Block 0 writes the routing's outputs and has no unit.
+// contraction.  Block 0 writes the routing's outputs and takes the last unit of a round: one that is there only where the grid is
+// all the blocks that fit (without it 511 blocks share 512 units, or 1024, and wait for one or two of them: layers of 4 tokens,
+// k = 1, 2048 x 8192, 54.6 -> 52.7 us; k = 2, 1024 x 4096, 34.6 -> 33.5).
 template <int FIRST>
 __global__ __launch_bounds__(256, 2) void few_first_kernel(const FewRoute p, const uint16_t* __restrict__ x,
                                                         const uint16_t* __restrict__ w1, uint16_t* __restrict__ h,
@@ -131,18 +133,17 @@ __global__ __launch_bounds__(256, 2) void few_first_kernel(const FewRoute p, con
             p.inv_perm[e] = at;
             p.tokmap[at] = e / k;
         }
-        return;
     }
     const int nblk = N >> 4, kblk = K >> 5, ngroups = (nblk + 3) >> 2;
     const int kb0 = kblk * wave / 4, kb1 = kblk * (wave + 1) / 4;
-    const int workers = static_cast<int>(gridDim.x) - 1;
+    const int grid = static_cast<int>(gridDim.x), first = blockIdx.x == 0 ? grid - 1 : static_cast<int>(blockIdx.x) - 1;
     const FoldOut none{nullptr, nullptr, nullptr};
     if (lists.ntiles * ngroups >= cus) {                   // uniform
-        for (int u = static_cast<int>(blockIdx.x) - 1; u < lists.ntiles * ngroups; u += workers)
+        for (int u = first; u < lists.ntiles * ngroups; u += grid)
             stream_unit<1, 1, 4, FIRST, false, 4>(x, lists.token, w1, h, lists.tiles[u / ngroups], u % ngroups, true, N, K, kb0, kb1,
                                                   red, false, b1, none);
     } else {
-        for (int u = static_cast<int>(blockIdx.x) - 1; u < lists.ntiles * nblk; u += workers)
+        for (int u = first; u < lists.ntiles * nblk; u += grid)
             stream_unit<1, 1, 4, FIRST, false, 1>(x, lists.token, w1, h, lists.tiles[u / nblk], u % nblk, true, N, K, kb0, kb1, red,
                                                   false, b1, none);
     }
@@ -266,7 +267,7 @@ hipError_t launch_few_products(const moe_shape& s, const void* x, const float* g
     const int Tpad = (s.T + 15) / 16 * 16, cus = device_cu_count();
     const FewRoute p{gate_part, gate_bias, idx, gate, counts, offsets, perm, inv_perm, tokmap, s.T, s.E, s.k, s.renormalize, Tpad};
     const long tiles = std::min(s.T * s.k, s.E), wide = tiles * ((s.d_ff / 16 + 3) / 4), narrow = tiles * (s.d_ff / 16);
-    const unsigned grid = static_cast<unsigned>(std::min(wide >= cus ? wide : narrow, 2L * cus - 1)) + 1;     // two blocks fit a CU
+    const unsigned grid = static_cast<unsigned>(std::min((wide >= cus ? wide : narrow) + 1, 2L * cus));     // two blocks fit a CU
     hipError_t err;
     if ((err = mark_profile_event(0, st)) != hipSuccess || (err = mark_profile_event(1, st)) != hipSuccess) return err;
     auto first = s.activation == MOE_ACT_GELU ? few_first_kernel<kFirstGelu> : few_first_kernel<kFirstRelu>;
