@@ -163,7 +163,9 @@ __global__ __launch_bounds__(kFewWaves * 64) void few_second_kernel(const uint16
                                                                     const float* __restrict__ b2, uint16_t* __restrict__ out,
                                                                     int T, int E, int k, int N, int K) {
     __shared__ FewLists lists;
-    __shared__ float sums[kFewWaves][kFewAssignments][2][8];           // [wavefront][row][k-step of a pair][column]
+    // [wavefront][row][k-step of a pair][column]; written 16 bytes at a time
+    __shared__ __attribute__((aligned(16))) float sums[kFewWaves][kFewAssignments][2][8];
+    static_assert(__alignof__(sums) >= alignof(f32x4), "stored as f32x4");
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63, r = lane & 15, g = lane >> 4;
     const int A = T * k, nblk = N >> 4, kblk = K >> 5;
     __shared__ int32_t experts[kFewAssignments];
