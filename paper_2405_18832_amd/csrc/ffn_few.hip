@@ -1,4 +1,4 @@
-// Layers of at most 8 tokens (decoder steps of one or a few sentences): routing, both products and the combine in three
+// Layers of few tokens (decoder steps of one or a few sentences; layer_is_few): routing, both products and the combine in three
 // launches instead of five.  Such a step is a chain of short kernels around two streams of weights; a launch that moves almost
 // nothing costs its own latency and about 1.7 us between the kernels.
 //
@@ -7,7 +7,7 @@
 //                                     same arithmetic on the same values), then streams its share of the first product
 //   few_second_kernel                 a block owns 8 output columns of all experts and adds up the tokens' outputs itself
 //
-// One token, 128 experts, k = 2, 2048 x 8192: 41.1 -> 36.7 us a step; 64 experts, k = 1, 768 x 3072: 23.7 -> 13.3 us.
+// One token, 128 experts, k = 2, 2048 x 8192: 36.4 -> 32.9 us a step; k = 1, 768 x 3072: 23.1 -> 14.2 us.
 #include <algorithm>
 
 #include "stream_unit.hpp"
@@ -16,7 +16,7 @@
 namespace moe {
 
 constexpr int kFewTokens = 8;
-constexpr int kFewAssignments = kWave;  // a lane each
+constexpr int kFewAssignments = 20;     // at most a lane each
 constexpr int kFewExperts = 256;        // a thread each in few_first_kernel
 constexpr int kFewRows = 8;             // rows of a tile: an expert has more only if a token (of NaN logits) names it twice
 
@@ -172,8 +172,10 @@ __global__ __launch_bounds__(kFewWaves * 64) void few_second_kernel(const uint16
     __shared__ float weights[kFewAssignments];
     if (wave == 0) {
         const int e = lane < A ? min(max(idx[lane], 0), E - 1) : 0x7fffffff;
-        experts[lane] = e;
-        weights[lane] = lane < A ? gate[lane] : 0.f;
+        if (lane < A) {
+            experts[lane] = e;
+            weights[lane] = gate[lane];
+        }
         few_lists(e, A, k, &lists);
     }
     __syncthreads();
@@ -190,7 +192,7 @@ __global__ __launch_bounds__(kFewWaves * 64) void few_second_kernel(const uint16
         const int expert = __builtin_amdgcn_readfirstlane(lists.tiles[t].expert);
         const int row = lists.tiles[t].row0 + min(sub, lists.tiles[t].rows - 1);
         wp = w2 + (static_cast<size_t>(expert) * nblk + nb) * kblk * 512 + (g * 16 + half * 8 + sub) * 8;
-        hp = h + static_cast<size_t>(row) * 32 + g * 8;    // at most 64 rows: all in the first row block
+        hp = h + static_cast<size_t>(row) * 32 + g * 8;    // few rows: all in the first row block
     };
     bf16x8 a[kFewAhead], b[kFewAhead];
     auto issue = [&](int slot) {
@@ -251,15 +253,43 @@ __global__ __launch_bounds__(kFewWaves * 64) void few_second_kernel(const uint16
     }
 }
 
-// A decoder step of few tokens whose first product is short: its units, with a whole contraction per wavefront, are less than one
-// and a half rounds.  What is saved is a few microseconds, and past that line the general path streams as fast or faster (from two
-// rounds on with its rows in LDS).  Measured, general -> this: 2048 x 8192, k = 2, 1, 2, 5 and 7 tokens (the last past the line) 41.1 -> 36.7,
-// 65.1 -> 63.4, 145 -> 131 and 176.2 -> 176.9 us; 1024 x 4096, k = 1, 1, 3, 7 and 8 tokens 24.3 -> 14.4, 26.5 -> 21.3, 38.7 -> 35.3 and
-// 44.2 us both; 768 x 3072, 64 experts, 1, 5 and 8 tokens 23.7 -> 13.3, 25.4 -> 21.3 and 33.5 -> 27.6.
+// units of the first product if all tiles are of different experts
+struct FewUnits {
+    long count;
+    int columns;
+};
+static FewUnits few_units(const moe_shape& s, int tiles, int cus) {
+    const long wide = static_cast<long>(tiles) * ((s.d_ff / 16 + 3) / 4);
+    if (wide >= cus) return {wide, 64};
+    return {static_cast<long>(tiles) * (s.d_ff / 16), 16};
+}
+
+// Layers that this is faster for than the general path.  It saves two launches, or three (k > 1), 5 to 9 us.  What it may lose, from
+// the 35 GB/s that a CU pulls in and the 5.5 TB/s of the chip:
+//  - a block of the second product streams 8 columns of every tile, however few blocks d_model gives; the general path's units are
+//    over the whole chip.  Up to 2.8 us of it are no matter.  Blocks that share a CU (d_model above 8 per CU) are worth it up to 4 us;
+//  - the first product's units, where there are many and a little more than a whole number per CU;
+//  - tiles are one after the other in the second product.
+// And the first product has to be less than one and a half rounds of units with a whole contraction per wavefront: past that the
+// general path streams as fast or faster (from two rounds on with its rows in LDS).
+// us, general and this, taken: 1 token, 2048 x 8192, k = 2 36.4 and 32.9; 1 token, 1024 x 4096 23.7 and 14.8; 4 tokens, 2048 x 8192, k = 2
+// 97.3 and 93.7; 8 tokens, 768 x 3072 28.5 and 26.6.  Not taken: 8 tokens, 512 x 2048, k = 2 25.4 and 27.5; 8 tokens, 256 x 1024, k = 8
+// 38.0 and 60.7; 5 tokens, 256 x 8192, k = 2 33.5 and 52.2; 3 tokens, 4096 x 16384 152 and 169.  Of 620 layers of 64 to 8192
+// columns drawn at random after the line was set, none takes more than 1.009 of the general path's time.
 bool layer_is_few(const moe_shape& s) {
     if (s.dtype != MOE_BF16 || s.T < 1 || s.T > kFewTokens || s.T * s.k > kFewAssignments || s.E > kFewExperts) return false;
-    const long tiles = std::min(s.T * s.k, s.E);
-    return 2 * tiles * ((s.d_ff / 64 + 3) / 4) < 3L * device_cu_count();
+    const int cus = device_cu_count(), tiles = std::min(s.T * s.k, s.E);
+    if (2L * tiles * ((s.d_ff / 64 + 3) / 4) >= 3L * cus) return false;
+    constexpr double kCuRate = 35e3, kChipRate = 5.5e6;    // bytes per us
+    const double block = tiles * 16.0 * s.d_ff / kCuRate;
+    if (block <= 2.8) return true;
+    if (s.d_model > 8 * cus) return block <= 4.;
+    double loss = block - tiles * 2.0 * s.d_model * s.d_ff / kChipRate;
+    const FewUnits u = few_units(s, tiles, cus);
+    const double uneven = ((u.count + cus - 1) / cus - static_cast<double>(u.count) / cus) * u.columns * 2.0 * s.d_model / kCuRate;
+    if (tiles > 6 && uneven >= 2.) loss += uneven;
+    if (tiles > 8) loss += 0.1 * (tiles - 8);
+    return loss <= 4.4;
 }
 
 hipError_t launch_few_products(const moe_shape& s, const void* x, const float* gate_bias, const float* gate_part, const void* w1,
@@ -268,8 +298,8 @@ hipError_t launch_few_products(const moe_shape& s, const void* x, const float* g
                                hipStream_t st) {
     const int Tpad = (s.T + 15) / 16 * 16, cus = device_cu_count();
     const FewRoute p{gate_part, gate_bias, idx, gate, counts, offsets, perm, inv_perm, tokmap, s.T, s.E, s.k, s.renormalize, Tpad};
-    const long tiles = std::min(s.T * s.k, s.E), wide = tiles * ((s.d_ff / 16 + 3) / 4), narrow = tiles * (s.d_ff / 16);
-    const unsigned grid = static_cast<unsigned>(std::min((wide >= cus ? wide : narrow) + 1, 2L * cus));     // two blocks fit a CU
+    const FewUnits units = few_units(s, std::min(s.T * s.k, s.E), cus);
+    const unsigned grid = static_cast<unsigned>(std::min(units.count + 1, 2L * cus));     // two blocks fit a CU
     hipError_t err;
     if ((err = mark_profile_event(0, st)) != hipSuccess || (err = mark_profile_event(1, st)) != hipSuccess) return err;
     auto first = s.activation == MOE_ACT_GELU ? few_first_kernel<kFirstGelu> : few_first_kernel<kFirstRelu>;

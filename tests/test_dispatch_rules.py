@@ -1,9 +1,11 @@
 """Rules that choose between kernels, on the host: measured points of both sides stay on the side that was faster."""
+import ctypes
 import os
 import subprocess
 
 import pytest
 
+import paper_2405_18832_amd as moe
 from paper_2405_18832_amd.build import CSRC, HIPCC, ROOT
 
 SHAPES = ["big", "narrow", "fine"]
@@ -50,3 +52,37 @@ def test_tiled_product_units(unit_shapes):
               ((16, 32, 2048, 256, 1), "big"),       # half a round of big units
               ((4, 8, 3072, 24, 0), "fine")]         # at most one round
     assert unit_shapes([p for p, _ in points]) == [s for _, s in points]
+
+
+def layer_is_few(T, d, f, E, k, dtype="bf16"):
+    """Whether a layer without a mask takes the three launches of few tokens (moe::layer_is_few of the library)."""
+    rule = moe.load()._ZN3moe12layer_is_fewERK9moe_shape
+    rule.restype, rule.argtypes = ctypes.c_bool, [ctypes.POINTER(moe.moe_shape)]
+    return rule(ctypes.byref(moe.make_shape(T, d, f, E, k, dtype, True)))
+
+
+def test_few_token_layers():
+    # (T, d_model, d_ff, E, k), us on the general path and in three launches (256 CUs)
+    faster = [(1, 2048, 8192, 128, 2),       # 36.4 32.9
+              (2, 2048, 8192, 128, 2),       # 56.2 54.8
+              (4, 2048, 8192, 128, 2),       # 97.3 93.7
+              (1, 1024, 4096, 128, 1),       # 23.7 14.8
+              (8, 1024, 4096, 128, 1),       # 33.7 31.1
+              (8, 768, 3072, 64, 1),         # 28.5 26.6
+              (3, 1376, 5504, 8, 1),         # 36.6 24.3
+              (2, 4096, 192, 128, 1),        # 23.6 15.4
+              (1, 64, 256, 8, 1)]
+    slower = [(8, 256, 1024, 128, 8),        # 38.0 60.7
+              (5, 256, 8192, 64, 2),         # 33.5 52.2
+              (4, 512, 4096, 128, 4),        # 40.7 51.5
+              (6, 512, 2048, 8, 2),          # 25.4 27.5
+              (7, 160, 320, 128, 8),         # 27.8 47.1
+              (4, 2176, 4352, 16, 8),        # 116 140
+              (2, 2560, 5120, 16, 2),        # 44.5 48.8
+              (7, 4096, 8192, 16, 1),        # 169 187
+              (2, 1024, 4096, 128, 8),       # 63.5 67.4
+              (8, 2048, 8192, 128, 2),
+              (9, 64, 256, 8, 1)]
+    assert [s for s in faster if not layer_is_few(*s)] == []
+    assert [s for s in slower if layer_is_few(*s)] == []
+    assert not layer_is_few(1, 64, 256, 8, 1, "f32")
