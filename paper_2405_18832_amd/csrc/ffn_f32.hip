@@ -48,8 +48,14 @@ __host__ __device__ __forceinline__ int f32_first_step(int steps, int wave) {
 // rows that a read touches at once then lie in different banks.
 __device__ __forceinline__ int f32_slot(int r, int p) { return r * kF32Step + ((p ^ (r & 7)) << 2); }
 
+// A second product's output: rows of y, the layer output itself (FoldOut), or either as the launch says.  The last takes a register for
+// the token's number: with two chains 18 spilled instead of 13 (layers of 2000 tokens, 16 experts, k = 2, 320 x 288 57.9 -> 59.1 us), so
+// only kernels of one chain, which have one to spare, leave it to the launch (500 tokens, 8 experts, k = 2, 768 x 3072: 156.8 us so,
+// 158.9 as a kernel for rows of y alone).
+enum F32Fold { kF32Rows, kF32Folded, kF32Either };
+
 // CHAINS: accumulators per output, taken in turn by the four MFMAs of 16 k
-template <int TFC, int CHAINS, int VEC, bool FIRST>
+template <int TFC, int CHAINS, int VEC, bool FIRST, int FOLD>
 __device__ __forceinline__ void f32_unit(const float* __restrict__ act, const int32_t* __restrict__ rowmap,
                                          const float* __restrict__ w, float* __restrict__ outp, const Tile tl,
                                          const int n0, const int N, const int K, const int activation,
@@ -72,11 +78,14 @@ __device__ __forceinline__ void f32_unit(const float* __restrict__ act, const in
                 src[i][h] = act + static_cast<size_t>(row) * K + lpiece * 4;
             }
         }
-    // A folded output (FoldOut): the token of the row that this lane stores, looked up here and its gate weight at the end of the
-    // contraction, so that neither is waited for.  Whole layers, us, with combine -> this: 500 tokens, 8 experts, 768 x 3072
+    // A folded output: the token of the row that this lane stores, looked up here and its gate weight at the end of the contraction, so
+    // that neither is waited for.  Whole layers, us, with combine -> this: 500 tokens, 8 experts, 768 x 3072
     // 100.2 -> 95.5; 300 tokens, 8 experts, 256 x 1024 29.4 -> 25.2; 16 tokens, 4 experts, 64 x 256 21.2 -> 16.6.
-    int orow = tl.row0 + min(wave * 16 + r, tl.rows - 1);
-    if (!FIRST && fold.out != nullptr) orow = fold.tokmap[orow];
+    static_assert(!FIRST || FOLD == kF32Rows, "second products only");
+    const bool folded = FOLD == kF32Folded || (FOLD == kF32Either && fold.out != nullptr);
+    constexpr bool EARLY = FIRST || CHAINS == 1 || FOLD != kF32Rows;      // the row's number: a register during the contraction
+    int orow = EARLY ? tl.row0 + min(wave * 16 + r, tl.rows - 1) : 0;
+    if (FOLD != kF32Rows && folded) orow = fold.tokmap[orow];
     f32x4 acc[CHAINS][TFC];
 #pragma unroll
     for (int c = 0; c < CHAINS; ++c)
@@ -145,7 +154,7 @@ __device__ __forceinline__ void f32_unit(const float* __restrict__ act, const in
         fma();
     }
     float gate = 1.f;
-    if (!FIRST && fold.out != nullptr) gate = fold.gate[orow];
+    if (FOLD != kF32Rows && folded) gate = fold.gate[orow];
     f32x4* red = reinterpret_cast<f32x4*>(lds);
     __syncthreads();                                      // the operands in LDS give way to the partial sums
 
@@ -164,13 +173,13 @@ __device__ __forceinline__ void f32_unit(const float* __restrict__ act, const in
         const f32x4* part = red + wave * 64 + lane;
         f32x4 v = (part[0] + part[TFC * 64]) + (part[2 * TFC * 64] + part[3 * TFC * 64]);
         if (lr < tl.rows) {
-            float* o = outp + static_cast<size_t>(orow) * N + n;
+            float* o = outp + static_cast<size_t>(EARLY ? orow : tl.row0 + lr) * N + n;
             const float* be = bias ? bias + static_cast<size_t>(tl.expert) * N + n : nullptr;
 #pragma unroll
             for (int q = 0; q < 4; ++q) {
                 if (n + q < N && be != nullptr) v[q] += be[q];
                 if (FIRST) v[q] = activate(v[q], activation);
-                if (!FIRST && fold.out != nullptr) v[q] = fmaf(gate, v[q], 0.f);     // what combine_kernel computes
+                if (folded) v[q] = fmaf(gate, v[q], 0.f);     // what combine_kernel computes
             }
             if (VEC == 4 && (N & 3) == 0) {               // out rows are then 16-byte aligned (see launch_f32_product)
                 if (n < N) *reinterpret_cast<f32x4*>(o) = v;
@@ -291,7 +300,7 @@ static_assert(kF32SortTiles <= 256, "a thread per tile");
 // At least 4 wavefronts per SIMD: the turn through LDS and the start of a unit are covered by the other blocks' MFMAs.  3 with the
 // lists of SORT in LDS.
 struct F32NoSort {};
-template <int VEC, bool FIRST, int CHAINS, bool SORT>
+template <int VEC, bool FIRST, int CHAINS, bool SORT, int FOLD>
 __global__ __launch_bounds__(256, SORT ? 3 : 4) void ffn_f32_kernel(const float* __restrict__ act,
                                                                  const int32_t* __restrict__ rowmap,
                                                                  const float* __restrict__ w, float* __restrict__ outp,
@@ -323,18 +332,18 @@ __global__ __launch_bounds__(256, SORT ? 3 : 4) void ffn_f32_kernel(const float*
         const int n0 = (g0 + u % ng) * 16;
         if constexpr (CHAINS < 4) {
             switch ((tl.rows + 15) >> 4) {                // exact number of row fragments: a fixed number of loads per step
-                case 1: f32_unit<1, CHAINS, VEC, FIRST>(act, rowmap, w, outp, tl, n0, N, K, activation, bias, fold, lds); break;
-                case 2: f32_unit<2, CHAINS, VEC, FIRST>(act, rowmap, w, outp, tl, n0, N, K, activation, bias, fold, lds); break;
-                case 3: f32_unit<3, CHAINS, VEC, FIRST>(act, rowmap, w, outp, tl, n0, N, K, activation, bias, fold, lds); break;
-                default: f32_unit<4, CHAINS, VEC, FIRST>(act, rowmap, w, outp, tl, n0, N, K, activation, bias, fold, lds); break;
+                case 1: f32_unit<1, CHAINS, VEC, FIRST, FOLD>(act, rowmap, w, outp, tl, n0, N, K, activation, bias, fold, lds); break;
+                case 2: f32_unit<2, CHAINS, VEC, FIRST, FOLD>(act, rowmap, w, outp, tl, n0, N, K, activation, bias, fold, lds); break;
+                case 3: f32_unit<3, CHAINS, VEC, FIRST, FOLD>(act, rowmap, w, outp, tl, n0, N, K, activation, bias, fold, lds); break;
+                default: f32_unit<4, CHAINS, VEC, FIRST, FOLD>(act, rowmap, w, outp, tl, n0, N, K, activation, bias, fold, lds); break;
             }
         } else {                                          // four chains of more than two fragments do not fit the registers
             for (int r0 = 0; r0 < tl.rows; r0 += 32) {
                 const Tile part{tl.expert, tl.row0 + r0, min(32, tl.rows - r0), 0};
                 if (part.rows <= 16)
-                    f32_unit<1, CHAINS, VEC, FIRST>(act, rowmap, w, outp, part, n0, N, K, activation, bias, fold, lds);
+                    f32_unit<1, CHAINS, VEC, FIRST, FOLD>(act, rowmap, w, outp, part, n0, N, K, activation, bias, fold, lds);
                 else
-                    f32_unit<2, CHAINS, VEC, FIRST>(act, rowmap, w, outp, part, n0, N, K, activation, bias, fold, lds);
+                    f32_unit<2, CHAINS, VEC, FIRST, FOLD>(act, rowmap, w, outp, part, n0, N, K, activation, bias, fold, lds);
             }
         }
     }
@@ -359,14 +368,20 @@ static int f32_width(int K, const void* act, const void* w, const void* outp) {
     return K % 4 == 0 && bases % 16 == 0 ? 4 : K % 2 == 0 && bases % 8 == 0 ? 2 : 1;
 }
 
+template <int VEC, bool FIRST>
+static auto f32_kernel(int K, bool folded) {
+    constexpr int kEither = FIRST ? kF32Rows : kF32Either, kFolded = FIRST ? kF32Rows : kF32Folded;
+    const int chains = f32_chains(K);
+    if (chains == 1) return ffn_f32_kernel<VEC, FIRST, 1, false, kEither>;
+    if (chains == 4) return folded ? ffn_f32_kernel<VEC, FIRST, 4, false, kFolded> : ffn_f32_kernel<VEC, FIRST, 4, false, kF32Rows>;
+    return folded ? ffn_f32_kernel<VEC, FIRST, 2, false, kFolded> : ffn_f32_kernel<VEC, FIRST, 2, false, kF32Rows>;
+}
+
 template <int VEC>
 static hipError_t launch_f32(bool first, unsigned grid, const float* act, const int32_t* rowmap, const float* w,
                              float* outp, const Tile* tiles, const int32_t* ntiles, int N, int K, int activation,
                              const float* bias, const FoldOut& fold, hipStream_t st) {
-    const int chains = f32_chains(K);
-    auto kern = first ? ffn_f32_kernel<VEC, true, 2, false> : ffn_f32_kernel<VEC, false, 2, false>;
-    if (chains == 1) kern = first ? ffn_f32_kernel<VEC, true, 1, false> : ffn_f32_kernel<VEC, false, 1, false>;
-    if (chains == 4) kern = first ? ffn_f32_kernel<VEC, true, 4, false> : ffn_f32_kernel<VEC, false, 4, false>;
+    auto kern = first ? f32_kernel<VEC, true>(K, false) : f32_kernel<VEC, false>(K, fold.out != nullptr);
     hipLaunchKernelGGL(kern, dim3(grid), dim3(256), 0, st, act, rowmap, w, outp, tiles, ntiles, N, K, activation, bias, fold,
                        F32NoSort{});
     return hipGetLastError();
@@ -403,9 +418,9 @@ template <int VEC>
 static hipError_t launch_f32_sort(const F32Sort& p, unsigned grid, const float* x, const float* w1, float* h, int N, int K,
                                   int activation, const float* b1, hipStream_t st) {
     const int chains = f32_chains(K);
-    auto kern = ffn_f32_kernel<VEC, true, 2, true>;
-    if (chains == 1) kern = ffn_f32_kernel<VEC, true, 1, true>;
-    if (chains == 4) kern = ffn_f32_kernel<VEC, true, 4, true>;
+    auto kern = ffn_f32_kernel<VEC, true, 2, true, kF32Rows>;
+    if (chains == 1) kern = ffn_f32_kernel<VEC, true, 1, true, kF32Rows>;
+    if (chains == 4) kern = ffn_f32_kernel<VEC, true, 4, true, kF32Rows>;
     hipLaunchKernelGGL(kern, dim3(grid), dim3(256), 0, st, x, nullptr, w1, h, nullptr, nullptr, N, K, activation, b1,
                        FoldOut{nullptr, nullptr, nullptr}, p);
     return hipGetLastError();

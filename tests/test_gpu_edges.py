@@ -449,13 +449,15 @@ def test_derived_mask_output_is_not_read_back(gpu_lib, T, E, k):
 
 
 # fp32 layers of one expert per token, whose second product stores the layer's output itself: tiles of 1, 16, 17, 64 and 65 rows,
-# the three widths of loads, sums in four, two and one chains, columns that end inside a unit, tokens without numbers, and an output
-# that is not 16-byte aligned.  The same sums, one multiply and one rounding as with combine, which a mask of ones takes: bit for bit.
-@pytest.mark.parametrize("at", [0, 1])
-@pytest.mark.parametrize("T,d,f,E", [(1, 32, 33, 1), (17, 20, 33, 1), (64, 64, 96, 1), (65, 33, 70, 1), (200, 66, 160, 5),
-                                     (500, 258, 512, 8)])
-def test_f32_top1_output(gpu_lib, T, d, f, E, at):
-    say(f"[case] f32 top-1 output T={T} d={d} f={f} E={E}, output {at} elements off")
+# the three widths of loads, sums in four, two and one chains, columns that end inside a unit, tokens without numbers; the first six
+# with the assignments sorted inside the first product (`sorts`), the others past the limits of that.  An output that is not 16-byte
+# aligned is left to combine, as is a layer with a mask of ones: the same sums, one multiply and one rounding, bit for bit.
+@pytest.mark.parametrize("T,d,f,E,sorts", [(1, 32, 33, 1, True), (17, 20, 33, 1, True), (64, 64, 96, 1, True), (65, 33, 70, 1, True),
+                                           (200, 66, 160, 5, True), (500, 258, 512, 8, True), (300, 33, 71, 65, False),
+                                           (330, 34, 70, 66, False), (300, 20, 72, 70, False), (1025, 36, 128, 16, False),
+                                           (1000, 66, 1042, 16, False), (900, 33, 1044, 14, False), (950, 130, 2049, 9, False)])
+def test_f32_top1_output(gpu_lib, T, d, f, E, sorts):
+    say(f"[case] f32 top-1 output T={T} d={d} f={f} E={E}")
     moe = gpu_lib
     gen = torch.Generator(device="cuda").manual_seed(T + d + f)
     new = lambda *s: torch.randn(s, device="cuda", generator=gen)
@@ -463,22 +465,36 @@ def test_f32_top1_output(gpu_lib, T, d, f, E, at):
     x[T // 2, 0] = float("nan")
     shape = moe.make_shape(T, d, f, E, 1, "f32", False, 1)
     ws = torch.full((moe.moe_workspace_bytes(shape),), 0xFF, dtype=torch.uint8, device="cuda")
-    outs = []
-    for mask in (None, torch.ones(E, dtype=torch.uint8, device="cuda")):
+    ones = torch.ones(E, dtype=torch.uint8, device="cuda")
+
+    def call(mask, out):
+        moe.moe_layer_forward_biased(shape, x, wg, bg, w1, b1, w2, b2, mask, -1, out, ws=ws)
+
+    outs, kernels = [], []
+    for mask, at in ((None, 0), (None, 1), (ones, 0), (ones, 1)):
         buf = torch.full((at + T * d + 8,), 7.0, device="cuda")
-        moe.moe_layer_forward_biased(shape, x, wg, bg, w1, b1, w2, b2, mask, -1, buf[at:at + T * d].view(T, d), ws=ws)
+        call(mask, buf[at:at + T * d].view(T, d))
         torch.cuda.synchronize()
-        outs.append(torch.where(buf.isnan(), 8.0, buf).view(torch.int32))
-    assert torch.equal(outs[0], outs[1])
+        assert bool((buf[:at] == 7.0).all()) and bool((buf[at + T * d:] == 7.0).all())
+        outs.append(torch.where(buf.isnan(), 8.0, buf)[at:at + T * d].view(torch.int32))
+        kernels.append(launches(lambda: call(mask, buf[at:at + T * d].view(T, d))))
+    for o in outs[1:]:
+        assert torch.equal(outs[0], o)
+    # with a mask: routing, dispatch, two products, combine; the fold saves the last, sorting the second
+    assert kernels == [4 - sorts, 5 - sorts, 5, 5]
 
 
 # fp32 layers whose first product sorts the assignments: groups of 64 assignments and 256 threads with and without a rest, the most
-# assignments and experts and one more (which take the general path), column groups that are and are not a multiple of 8, a token of
-# NaN logits whose slots all name expert 0.  The same order and sums as the general path, which a mask of ones takes: bit for bit.
-@pytest.mark.parametrize("T,d,f,E,k", [(1, 32, 16, 1, 1), (64, 64, 256, 8, 2), (63, 33, 70, 5, 1), (65, 130, 128, 33, 1),
-                                       (128, 20, 144, 64, 8), (129, 64, 32, 8, 8), (256, 66, 40, 4, 4), (1024, 32, 144, 64, 1),
-                                       (1025, 32, 64, 64, 1), (300, 32, 64, 65, 2), (3, 96, 2048, 3, 3)])
-def test_f32_sort_in_first_product(gpu_lib, T, d, f, E, k):
+# assignments and experts and one more (which take the general path), column groups that are and are not a multiple of 8, more units in
+# an XCD's slice than its even share, a token of NaN logits whose slots all name expert 0.  The same order and sums as the general
+# path, which a mask of ones takes: bit for bit.  Order and values also by themselves: perm is the stable sort of the experts, and
+# the output the oracle's; bar of the fp32 FFN tests above.
+@pytest.mark.parametrize("T,d,f,E,k,sorts", [(1, 32, 16, 1, 1, True), (64, 64, 256, 8, 2, True), (63, 33, 70, 5, 1, True),
+                                             (65, 130, 128, 33, 1, True), (128, 20, 144, 64, 8, True), (129, 64, 32, 8, 8, False),
+                                             (128, 64, 32, 8, 8, True), (256, 66, 40, 4, 4, True), (1024, 32, 144, 64, 1, True),
+                                             (1025, 32, 64, 64, 1, False), (300, 32, 64, 65, 2, False), (3, 96, 2048, 3, 3, True),
+                                             (20, 464, 1312, 8, 2, True), (33, 80, 300, 32, 2, True)])
+def test_f32_sort_in_first_product(gpu_lib, T, d, f, E, k, sorts):
     say(f"[case] f32 sort in first product T={T} d={d} f={f} E={E} k={k}")
     moe = gpu_lib
     gen = torch.Generator(device="cuda").manual_seed(T + d + f)
@@ -487,6 +503,7 @@ def test_f32_sort_in_first_product(gpu_lib, T, d, f, E, k):
     x[T // 2, 0] = float("nan")
     shape = moe.make_shape(T, d, f, E, k, "f32", True, 1)
     ws = torch.full((moe.moe_workspace_bytes(shape),), 0xFF, dtype=torch.uint8, device="cuda")
+    ones = torch.ones(E, dtype=torch.uint8, device="cuda")
 
     def layer(mask, by_products=True):
         i32 = lambda *s: torch.full(s, -1, dtype=torch.int32, device="cuda")
@@ -496,7 +513,23 @@ def test_f32_sort_in_first_product(gpu_lib, T, d, f, E, k):
         torch.cuda.synchronize()
         return [torch.where(a.isnan(), 8.0, a) if a.is_floating_point() else a for a in (out, *more)]
 
-    few, general = layer(None), layer(torch.ones(E, dtype=torch.uint8, device="cuda"))
+    few, general = layer(None), layer(ones)
     for a, b in zip(few, general):
         assert torch.equal(a.view(torch.uint8), b.view(torch.uint8))
     assert torch.equal(layer(None, by_products=False)[0], few[0])
+    scratch = torch.empty_like(few[0])
+    kernels = [launches(lambda: moe.moe_layer_forward_biased(shape, x, wg, bg, w1, b1, w2, b2, m, -1, scratch, ws=ws))
+               for m in (None, ones)]
+    assert kernels == [5 - sorts - (k == 1), 5]
+    idx, g = few[1].cpu().numpy(), few[2].cpu().numpy().astype(np.float64)
+    assert np.array_equal(few[4].cpu().numpy(), np.argsort(idx.ravel(), kind="stable"))
+    assert np.array_equal(few[3].cpu().numpy(), np.bincount(idx.ravel(), minlength=E))
+    host = [t.cpu().numpy() for t in (x, w1, w2, b1, b2)]
+    ref = np.zeros((T, d))
+    for e in range(E):
+        t, j = np.nonzero((idx == e) & (np.arange(T) != T // 2)[:, None])
+        if len(t):
+            ref[t] += g[t, j, None] * orc.expert_ffn(host[0][t], host[1][e], host[2][e], None, "gelu", host[3][e], host[4][e])
+    others = np.arange(T) != T // 2
+    if others.any():
+        assert float(orc.rel_error_rows(few[0].cpu().numpy().astype(np.float64)[others], ref[others]).max()) <= 1e-5
