@@ -103,6 +103,14 @@ def recorded_traffic(workload: str, share: str, tag: str):
     return TRAFFIC_BYTES.get((workload, tag))
 
 
+def layer_is_few(shape) -> bool:
+    """Whether a layer without a mask runs in the three launches of few tokens (the library's own rule, csrc/ffn_few.hip)."""
+    import paper_2405_18832_amd as moe
+    rule = moe.load()._ZN3moe12layer_is_fewERK9moe_shape
+    rule.restype, rule.argtypes = ctypes.c_bool, [ctypes.POINTER(moe.moe_shape)]
+    return bool(rule(ctypes.byref(shape)))
+
+
 def describe(cfg) -> str:
     return (f"{cfg.name}: T={cfg.T} d_model={cfg.d_model} d_ff={cfg.d_ff} E={cfg.E} top-{cfg.k} "
             f"{'renormalised' if cfg.renormalize else 'raw-prob'} gates, {cfg.dtype}, seed {cfg.seed}"
@@ -311,16 +319,21 @@ def measure(name: str, share: str, K: int, W: int, copies_arg: int = 0, cpu_base
     names = ["ffn_tile_kernel (x.W1 product, large experts)", "ffn_stream_kernel (x.W1 product, small experts)",
              "ffn_tile_kernel (h.W2 product, large experts)", "ffn_stream_kernel (h.W2 product, small experts)"]
     tags = ["tile_w1", "stream_w1", "tile_w2", "stream_w2"]
+    few = not hot and layer_is_few(L.shape)                  # the call above: no mask
+    if few:                                                  # routing in the first product, combine in the second
+        names[1], names[3] = "few_first_kernel (top-k and x.W1 product)", "few_second_kernel (h.W2 product and combine)"
     kern = []
     for j in range(4):
         rows, wb = (rows_b, wb_b) if j % 2 == 0 else (rows_s, wb_s)
         io = rows * d * (es if j < 2 else 4)                 # rows in (first product) / fp32 rows out (second)
+        if few and j % 2:                                    # tokens in and h out / h in and tokens out
+            io = cfg.T * d * es + rows * f * es
         kern.append(dict(name=names[j], tag=tags[j], us=float(seg[:, j].mean()), us_min=float(seg[:, j].min()),
                          us_raw=float(seg_raw[:, j].mean()), bytes=wb + io, flops=2.0 * rows * d * f))
     kd = max(kern, key=lambda q: q["us"])
     t_flop = kd["flops"] / (PEAK_BF16_TFLOPS * 1e12)
     t_byte = kd["bytes"] / (PEAK_HBM_GBPS * 1e9)
-    traffic = recorded_traffic(name, share, kd["tag"])
+    traffic = None if few else recorded_traffic(name, share, kd["tag"])
     if cfg.dtype != "bf16" or kd["us"] <= 0:
         roof = None
     elif t_flop > t_byte:

@@ -259,6 +259,9 @@ int32_t moe_tiled_kernel_min_rows(const moe_shape* shape, const int32_t* rows_ho
  *   [0] before the first product (x.W1^T, ReLU) of the large experts' tiled kernel (if launched),
  *   [1] after it, [2] after the first product of the small experts' weight-streaming kernel,
  *   [3] after the second product (h.W2^T) of the tiled kernel, [4] after that of the streaming kernel.
+ * Layers without a mask that fuse steps record the same events around fewer kernels: bf16 layers of few tokens do the top-k and the
+ * dispatch inside the first product and the combine inside the second ([1] - [2] and [3] - [4]), small fp32 layers the dispatch
+ * inside the first product, and layers of one expert per token the combine inside the second product.
  * The handles are copied; the array need not outlive the call.  Process-global (all devices, all threads) and
  * not thread-safe: set it only while no other thread is inside an expert-FFN call.
  */

@@ -7,8 +7,8 @@
 namespace moe {
 
 // One wavefront per token and run of `cols` columns (blockIdx.y; the whole row when there are many tokens,
-// 64 * VEC columns each when there are few: a decoder step's handful of tokens would otherwise walk their rows
-// step after step in one wavefront each, 5.4 us for one token of 2048 columns); a lane owns 4 consecutive
+// 64 * VEC columns each when there are few: a handful of tokens would otherwise walk their rows step after step in one
+// wavefront each, 5.4 us for one token of 2048 columns); a lane owns 4 consecutive
 // columns per 256-column step, reads them as one 16-byte piece from each of the token's k rows of y_perm and
 // keeps the sum in fp32.
 template <typename ST, int VEC>

@@ -287,8 +287,10 @@ template <int TFMAX, int KSPLIT, int FIRST, bool FOLD>
 int StreamKernelInfo<TFMAX, KSPLIT, FIRST, FOLD>::per_cu[kMaxDevices] = {0};
 
 // Second product of a layer of at most 16 tokens when its experts are so few that groups of 64 columns leave
-// most CUs without a unit (one decoder token with two experts: 64 units): a unit is one 16-column block, the
-// four wavefronts of a block split the contraction as usual and keep 16 KiB-steps of weights in flight each.
+// most CUs without a unit (one token with two experts, 2048 columns: 64 units): a unit is one 16-column block, the
+// four wavefronts of a block split the contraction as usual and keep 16 KiB-steps of weights in flight each.  Layers of few
+// tokens without a mask go to ffn_few.hip instead where that is faster; what comes here has a mask, is called step by step, or has
+// more tokens, experts or bytes per column than pay there.
 __global__ __launch_bounds__(256) void ffn_stream_narrow_kernel(const uint16_t* __restrict__ act,
                                                                 const uint16_t* __restrict__ wpk,
                                                                 void* __restrict__ outp,
