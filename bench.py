@@ -77,15 +77,16 @@ class HipEvents:
 # HBM-side bytes per launch of the expert-FFN kernels, from rocprofv3 --pmc FETCH_SIZE / WRITE_SIZE runs
 # (summaries and commands: profiles/<workload>_full_layer.txt).  Valid only for the kernel sources they
 # were taken with: reported as null once one of the sources below has changed.
-TRAFFIC_SOURCES = {"ffn.hip": "e287ddaf173d7838", "ffn_tile.hip": "4e2254c6d6b31764",
-                   "tile_schedule.hpp": "825bbd1186462090", "common.hpp": "502c460aa16ad314"}
+TRAFFIC_SOURCES = {"ffn.hip": "4f15afd4b8392328", "ffn_tile.hip": "5021647b0f1d9f16",
+                   "tile_schedule.hpp": "36f55c1699316219", "common.hpp": "95950a7d8edbf8f0",
+                   "stream_unit.hpp": "9122e21b36072d9c"}
 TRAFFIC_BYTES = {
-    ("switch_base", "stream_w1"): 316691612, ("switch_base", "stream_w2"): 320477437,
-    ("switch_large_skew", "stream_w1"): 68377579, ("switch_large_skew", "stream_w2"): 68483072,
-    ("switch_large_skew", "tile_w1"): 90894997, ("switch_large_skew", "tile_w2"): 123045815,
-    ("nllb_decode", "stream_w1"): 1643759594, ("nllb_decode", "stream_w2"): 1645698647,
-    ("nllb_prefill_skew", "stream_w1"): 913896996, ("nllb_prefill_skew", "stream_w2"): 972128547,
-    ("nllb_prefill_skew", "tile_w1"): 2619195259, ("nllb_prefill_skew", "tile_w2"): 2400065106,
+    ("switch_base", "stream_w1"): 316646208, ("switch_base", "stream_w2"): 320449534,
+    ("switch_large_skew", "stream_w1"): 68340751, ("switch_large_skew", "stream_w2"): 68447863,
+    ("switch_large_skew", "tile_w1"): 90911347, ("switch_large_skew", "tile_w2"): 123025513,
+    ("nllb_decode", "stream_w1"): 1643741396, ("nllb_decode", "stream_w2"): 1645692016,
+    ("nllb_prefill_skew", "stream_w1"): 913872865, ("nllb_prefill_skew", "stream_w2"): 972124232,
+    ("nllb_prefill_skew", "tile_w1"): 2567193098, ("nllb_prefill_skew", "tile_w2"): 2395759912,
 }
 
 
