@@ -71,8 +71,10 @@ def test_few_token_layers():
               (8, 768, 3072, 64, 1),         # 28.5 26.6
               (3, 1376, 5504, 8, 1),         # 36.6 24.3
               (2, 4096, 192, 128, 1),        # 23.6 15.4
+              (7, 896, 2496, 63, 1),         # 30.2 25.9
               (1, 64, 256, 8, 1)]
     slower = [(8, 256, 1024, 128, 8),        # 38.0 60.7
+              (7, 640, 2560, 128, 1),        # 26.2 27.0
               (5, 256, 8192, 64, 2),         # 33.5 52.2
               (4, 512, 4096, 128, 4),        # 40.7 51.5
               (6, 512, 2048, 8, 2),          # 25.4 27.5
