@@ -320,6 +320,11 @@ def measure(name: str, share: str, K: int, W: int, copies_arg: int = 0, cpu_base
     names = ["ffn_tile_kernel (x.W1 product, large experts)", "ffn_stream_kernel (x.W1 product, small experts)",
              "ffn_tile_kernel (h.W2 product, large experts)", "ffn_stream_kernel (h.W2 product, small experts)"]
     tags = ["tile_w1", "stream_w1", "tile_w2", "stream_w2"]
+    one_kernel = min_rows > 0                                # large and small experts in one kernel per product
+    if one_kernel:
+        names[0], names[2] = "ffn_product_kernel (x.W1 product)", "ffn_product_kernel (h.W2 product)"
+        tags[0], tags[2] = "w1", "w2"
+        rows_b, wb_b = rows_b + rows_s, wb_b + wb_s
     few = not hot and layer_is_few(L.shape)                  # the call above: no mask
     if few:                                                  # routing in the first product, combine in the second
         names[1], names[3] = "few_first_kernel (top-k and x.W1 product)", "few_second_kernel (h.W2 product and combine)"

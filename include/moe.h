@@ -240,9 +240,9 @@ moe_status moe_combine(const moe_shape* shape, const float* y_perm, const int32_
                        void* out, void* stream);
 
 /*
- * For tools that attribute time or bytes to the two kernels of the expert FFN (the paper's compute-bound and
- * memory-bound experts, Section 3.1): the smallest number of rows with which an expert's rows are run by the
- * LDS-tiled kernels rather than the weight-streaming one in a call where the experts have `rows_host[e]` rows
+ * For tools that attribute time or bytes to the two kinds of units of the expert FFN (the paper's compute-bound and
+ * memory-bound experts, Section 3.1): the smallest number of rows with which an expert's rows are run in
+ * LDS-tiled units rather than weight-streaming ones in a call where the experts have `rows_host[e]` rows
  * (HOST array [E]; 0 for experts that are empty or masked out).  It is 128, or one more than a streaming tile
  * holds when the experts of 128 rows and more already fill the tiled kernel for a round, or when they and the
  * smaller ones together are at most a round of its smaller units; 0 when the shape
@@ -256,9 +256,9 @@ int32_t moe_tiled_kernel_min_rows(const moe_shape* shape, const int32_t* rows_ho
  * about an expert's cost product by product, Section 2.2 and Eq. 3-4).  `events` is a HOST array of
  * five hipEvent_t created by the caller (entries may be NULL), or NULL to stop.  Until the next call,
  * every expert-FFN launch (from moe_expert_ffn or moe_layer_forward) records, on the launch's stream:
- *   [0] before the first product (x.W1^T, ReLU) of the large experts' tiled kernel (if launched),
- *   [1] after it, [2] after the first product of the small experts' weight-streaming kernel,
- *   [3] after the second product (h.W2^T) of the tiled kernel, [4] after that of the streaming kernel.
+ *   [0] before the first product (x.W1^T, activation), [2] after it, [4] after the second (h.W2^T); bf16 layers of at least
+ *   128 tokens run each product as one kernel, for large and small experts, with [1] and [3] at its end, too; other layers
+ *   run the weight-streaming kernels alone, between [1] = [0] and [2] and between [3] = [2] and [4].
  * Layers without a mask that fuse steps record the same events around fewer kernels: bf16 layers of few tokens do the top-k and the
  * dispatch inside the first product and the combine inside the second ([1] - [2] and [3] - [4]), small fp32 layers the dispatch
  * inside the first product, and layers of one expert per token the combine inside the second product.

@@ -73,11 +73,18 @@ inline __host__ __device__ int tiled_min_rows(int big_tiles_at_min, int join_til
     if (big_tiles_at_min > 0 && half_tiles_joined <= join_half_tiles) return kJoinMinRows;
     return kBigMinRows;
 }
-// The LDS-tiled kernel cuts the units of its last, partly filled round along K; the parts leave fp32
-// partial tiles (kBigTileRows x 256) in the workspace and are handed out through a counter.
+// The units of the last, partly filled round of tiled units are cut along K; the parts are handed out through a counter and leave
+// fp32 partial tiles (kBigTileRows x 256) in the workspace.
 constexpr int kSplitSlots = 256;        // partial tiles in the workspace
 constexpr int kSplitCounter = 2;        // ints [2] and [3] of the `ntiles` array: the part counters of the
                                         // first and of the second product
+// Counters of a layer that may have large experts, behind the first 64 ints of the `ntiles` array, zero when its products start:
+// per product, the streaming units taken from each of 8 runs (a 128-byte line each: every XCD counts in its own), and how many
+// of the two sums that meet at a node have got there (join_parts in ffn_tile.hip)
+constexpr int kTakenStride = 32, kTakenAt = 64, kJoinedAt = kTakenAt + 2 * 8 * kTakenStride;
+constexpr int kListCounters = 2 * 8 * kTakenStride + 2 * kSplitSlots;
+constexpr int kListThreads = 1024;      // threads of the block that makes the lists
+static_assert(kListCounters == kListThreads, "a thread each clears them");
 
 // trailing activation of the first linear layer (Section 3.4): 0 = ReLU, 1 = GeLU in its defining form
 // z * Phi(z) = 0.5 z (1 + erf(z / sqrt 2))
@@ -328,7 +335,7 @@ __device__ __forceinline__ void write_tiles(Tile* __restrict__ out, int e, int r
 // ---- workspace ----------------------------------------------------------------
 struct WsLayout {
     size_t hist;       // int32 [ceil(T/16), E]  chunk histograms / slot bases of the counting sort
-    size_t ntiles;     // int32 [64]  ([0] = tiles of small experts, [1] = of large experts, [2], [3] counters)
+    size_t ntiles;     // int32 [64 + kListCounters, or 64 without large experts]  ([0] = tiles of small experts, [1] = of large experts, [2], [3] counters)
     size_t tiles;      // Tile [A/16 + E + 1]   row tiles of the weight-streaming kernel
     size_t tiles_big;  // Tile [A/256 + E + 1]  row tiles of the LDS-tiled kernel
     size_t tiles_half; // Tile [A/128 + E + 1]  the same rows in the half-sized tiles of that kernel (if an expert can have them)
@@ -371,10 +378,10 @@ inline WsLayout ws_layout(const moe_shape& s) {
         return at;
     };
     L.hist = take(((static_cast<size_t>(s.T) + 15) / 16 + 1) * E * 4);
-    L.ntiles = take(64 * 4);
+    const bool big = s.dtype == MOE_BF16 && s.T >= kBigMinRows;
+    L.ntiles = take((64 + (big ? kListCounters : 0)) * 4);
     L.tiles = take((A / 16 + E + 1) * sizeof(Tile));
     L.tiles_big = take((A / 256 + E + 1) * sizeof(Tile));
-    const bool big = s.dtype == MOE_BF16 && s.T >= kBigMinRows;
     L.tiles_half = take(big ? (A / kHalfTileRows + E + 1) * sizeof(Tile) : 0);
     const size_t Ab = (A + kRowBlock - 1) / kRowBlock * kRowBlock;     // the blocked layouts hold whole row blocks
     L.h = take(Ab * s.d_ff * es);
@@ -437,7 +444,7 @@ hipError_t launch_expert_products(const moe_shape& s, const void* act, const int
                                   void* h_ws, const TileLists& lists, const FoldOut& fold, hipStream_t st);
 bool layer_gathers_kmajor(const moe_shape& s);
 hipError_t launch_gather_kmajor(const moe_shape& s, const void* x, const int32_t* tokmap, void* xk, hipStream_t st);
-hipError_t launch_tile_product(bool first, const uint16_t* act, const int32_t* rowmap, const uint16_t* wpk,
+hipError_t launch_tiled_product(bool first, int ksplit, const uint16_t* act, const int32_t* rowmap, const uint16_t* wpk,
                                void* outp, const TileLists& lists, int N, int K, bool act_kmajor, int activation,
                                const float* bias, const FoldOut& fold, hipStream_t st);
 int tile_product_grid();

@@ -78,113 +78,6 @@ __global__ __launch_bounds__(1024) void build_tiles_kernel(const int32_t* __rest
     emit_tiles(e, E, row0, m, total[0], total[1], lists, scan + 48);
 }
 
-// The same unit when all four wavefronts of the block share the tile's rows over the same k range
-// (KSPLIT = 1: the block covers four column groups): the rows are copied once per block into LDS, in
-// MFMA-fragment order, instead of being fetched by every wavefront at every k-step.  That takes the
-// row operand out of the vector-memory queue that the weights stream through (one quarter of the
-// requests, issued once, asynchronously) and out of the registers that hold loads in flight.
-// `tok_lds` holds TFC * K / 32 fragments of 1 KiB: fragment (tf, kb) at (tf * K / 32 + kb) * 1024.
-template <int TFC, int FIRST, bool FOLD>
-__device__ __forceinline__ void stream_unit_lds(const uint16_t* __restrict__ act,
-                                                const int32_t* __restrict__ rowmap,
-                                                const uint16_t* __restrict__ wpk, void* __restrict__ outp,
-                                                const Tile tl, const int ng, const bool active, const int N,
-                                                const int K, const bool act_kmajor,
-                                                const float* __restrict__ bias, unsigned char* tok_lds,
-                                                const FoldOut& fold) {
-    constexpr int PF = MOE_PF_LDS;
-    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-    const int r = lane & 15, g = lane >> 4;
-    const int nblk = N >> 4, kblk = K >> 5;
-    f32x4 acc[4][TFC];
-#pragma unroll
-    for (int nf = 0; nf < 4; ++nf)
-#pragma unroll
-        for (int tf = 0; tf < TFC; ++tf) acc[nf][tf] = f32x4{0.f, 0.f, 0.f, 0.f};
-
-    int ftok[TFC];
-    float fw[TFC];
-    fold_rows<TFC, FOLD>(fold, tl, ftok, fw);
-    // the token rows behind the lane's permuted positions: fetched before the barrier, whose wait hides them
-    int rows_of[TFC];
-#pragma unroll
-    for (int tf = 0; tf < TFC; ++tf) {
-        rows_of[tf] = tl.row0 + min(tf * 16 + r, tl.rows - 1);
-        if (rowmap != nullptr) rows_of[tf] = rowmap[rows_of[tf]];
-    }
-    // every wavefront has finished reading the previous unit's rows
-    asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
-    // rows -> LDS: wavefront w copies the fragments (tf, kb) with kb = w, w + 4, ...; a lane fetches the
-    // 16 bytes of its own slot: row (lane % 16), k-group (lane / 16)
-    const size_t kstride = act_kmajor ? kStepStride : 32;   // elements per k-step
-    const uint32_t lds0 = lds_address(tok_lds);
-#pragma unroll
-    for (int tf = 0; tf < TFC; ++tf) {
-        const int row = rows_of[tf];
-        const uint16_t* ap =
-            act_kmajor ? act + h_index(row, g * 8, kblk) : act + static_cast<size_t>(row) * K + g * 8;
-        for (int kb = wave; kb < kblk; kb += 4) copy16_to_lds(ap + kb * kstride, lds0 + (tf * kblk + kb) * 1024);
-    }
-
-    const uint16_t* wp[4];
-#pragma unroll
-    for (int nf = 0; nf < 4; ++nf) {
-        const int nb = min(ng * 4 + nf, nblk - 1);
-        wp[nf] = wpk + (static_cast<size_t>(tl.expert) * nblk + nb) * kblk * 512 + lane * 8;
-    }
-    bf16x8 a[PF][4];
-    auto issue = [&](int slot, int kb) {
-#pragma unroll
-        for (int nf = 0; nf < 4; ++nf)
-            a[slot][nf] = *reinterpret_cast<const bf16x8*>(wp[nf] + static_cast<size_t>(kb) * 512);
-    };
-    if (active) {
-#pragma unroll
-        for (int p = 0; p < PF; ++p) issue(p, min(p, kblk - 1));   // past the end: re-read, never used
-    }
-    // The row copies were issued before the weight loads, and loads complete in order: they have landed
-    // once at most the weight loads are outstanding ... for every wavefront.
-    if (active) __builtin_amdgcn_s_waitcnt(vmcnt_imm(PF * 4));
-    else __builtin_amdgcn_s_waitcnt(0x0F70);
-    asm volatile("s_barrier" ::: "memory");
-
-    if (active) {
-        const unsigned char* bl = tok_lds + lane * 16;
-        auto fma = [&](int slot, int kb) {
-            bf16x8 b[TFC];
-#pragma unroll
-            for (int tf = 0; tf < TFC; ++tf) b[tf] = *reinterpret_cast<const bf16x8*>(bl + (tf * kblk + kb) * 1024);
-#pragma unroll
-            for (int tf = 0; tf < TFC; ++tf)
-#pragma unroll
-                for (int nf = 0; nf < 4; ++nf)
-                    acc[nf][tf] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[slot][nf], b[tf], acc[nf][tf], 0, 0, 0);
-        };
-        int kb = 0;
-        for (; kb + 2 * PF <= kblk; kb += PF) {
-#pragma unroll
-            for (int p = 0; p < PF; ++p) {
-                fma(p, kb + p);
-                issue(p, kb + p + PF);
-            }
-        }
-        if (kb + PF < kblk) {
-#pragma unroll
-            for (int p = 0; p < PF; ++p) {
-                fma(p, kb + p);
-                issue(p, min(kb + p + PF, kblk - 1));
-            }
-            kb += PF;
-        }
-#pragma unroll
-        for (int p = 0; p < PF; ++p)
-            if (kb + p < kblk) fma(p, kb + p);
-
-        const float* be = bias ? bias + static_cast<size_t>(tl.expert) * N : nullptr;
-        store_group<TFC, FIRST, FOLD>(outp, tl, ng, nblk, N, be, acc, fold, ftok, fw);
-    }
-}
-
 template <int TFMAX, int KSPLIT, int FIRST, bool FOLD>
 __global__ __launch_bounds__(256) void ffn_stream_kernel(const uint16_t* __restrict__ act,
                                                          const int32_t* __restrict__ rowmap,
@@ -193,15 +86,12 @@ __global__ __launch_bounds__(256) void ffn_stream_kernel(const uint16_t* __restr
                                                          const Tile* __restrict__ tiles,
                                                          const int32_t* __restrict__ ntiles_p, int N,
                                                          int K, int balance,
-                                                         const Tile* __restrict__ big_tiles,
-                                                         const Tile* __restrict__ half_tiles,
-                                                         const float* __restrict__ partials, int cus,
                                                          int act_kmajor, int rows_in_lds,
                                                          const float* __restrict__ bias, const FoldOut fold) {
     extern __shared__ __attribute__((aligned(16))) unsigned char tok_lds[];
     constexpr int NGB = 4 / KSPLIT;   // n-groups (of 64 columns) per block
     __shared__ f32x4 red[KSPLIT > 1 ? (KSPLIT - 1) * NGB * 4 * TFMAX * 64 : 1];
-    const int wave = threadIdx.x >> 6;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int ks = wave % KSPLIT, ngs = wave / KSPLIT;
     const int nblk = N >> 4, kblk = K >> 5;
     const int ngroups = (nblk + 3) >> 2;
@@ -223,20 +113,6 @@ __global__ __launch_bounds__(256) void ffn_stream_kernel(const uint16_t* __restr
     // fetched into that L2 once instead of into all eight.
     const int pb = (stride % 8 == 0) ? static_cast<int>(blockIdx.x & 7) * (stride >> 3) + static_cast<int>(blockIdx.x >> 3)
                                      : static_cast<int>(blockIdx.x);
-    // First the rows that the tiled kernel before this one left as partial tiles (large experts; no overlap
-    // with the rows of the small experts below).  When at least a quarter of the blocks have no streaming unit
-    // they do it, side by side with the others' streaming; else everybody does, before streaming.
-    if (partials != nullptr) {
-        const int idle = stride - nbu;                    // blocks with pb >= nbu have no unit (balance is off here)
-        if (idle * 4 >= stride) {
-            if (pb >= nbu)
-                finish_tiled_product<FIRST, FOLD>(big_tiles, half_tiles, ntiles_p, partials, outp, N, cus, bias, fold,
-                                                  pb - nbu, idle);
-        } else {
-            finish_tiled_product<FIRST, FOLD>(big_tiles, half_tiles, ntiles_p, partials, outp, N, cus, bias, fold,
-                                              static_cast<int>(blockIdx.x), static_cast<int>(gridDim.x));
-        }
-    }
     for (int base = 0; base < nbu; base += stride) {
         const int bu = base + pb;
         if (bu >= nbu) break;                             // block-uniform
@@ -247,23 +123,23 @@ __global__ __launch_bounds__(256) void ffn_stream_kernel(const uint16_t* __restr
         if (KSPLIT == 1 && rows_in_lds) {
             const bool km = act_kmajor != 0;
             if (TFMAX >= 4 && tfc == 4)
-                stream_unit_lds<4, FIRST, FOLD>(act, rowmap, wpk, outp, tl, ng, active, N, K, km, bias, tok_lds, fold);
+                stream_unit_lds<4, FIRST, FOLD>(act, rowmap, wpk, outp, tl, ng, active, N, K, km, bias, tok_lds, fold, wave);
             else if (TFMAX >= 4 && tfc == 3)
-                stream_unit_lds<3, FIRST, FOLD>(act, rowmap, wpk, outp, tl, ng, active, N, K, km, bias, tok_lds, fold);
+                stream_unit_lds<3, FIRST, FOLD>(act, rowmap, wpk, outp, tl, ng, active, N, K, km, bias, tok_lds, fold, wave);
             else if (TFMAX >= 2 && tfc == 2)
-                stream_unit_lds<2, FIRST, FOLD>(act, rowmap, wpk, outp, tl, ng, active, N, K, km, bias, tok_lds, fold);
+                stream_unit_lds<2, FIRST, FOLD>(act, rowmap, wpk, outp, tl, ng, active, N, K, km, bias, tok_lds, fold, wave);
             else
-                stream_unit_lds<1, FIRST, FOLD>(act, rowmap, wpk, outp, tl, ng, active, N, K, km, bias, tok_lds, fold);
+                stream_unit_lds<1, FIRST, FOLD>(act, rowmap, wpk, outp, tl, ng, active, N, K, km, bias, tok_lds, fold, wave);
             continue;
         }
         if (TFMAX >= 4 && tfc == 4)
-            stream_unit<4, TFMAX, KSPLIT, FIRST, FOLD>(act, rowmap, wpk, outp, tl, ng, active, N, K, kb0, kb1, red, act_kmajor != 0, bias, fold);
+            stream_unit<4, TFMAX, KSPLIT, FIRST, FOLD>(act, rowmap, wpk, outp, tl, ng, active, N, K, kb0, kb1, red, act_kmajor != 0, bias, fold, wave);
         else if (TFMAX >= 4 && tfc == 3)
-            stream_unit<3, TFMAX, KSPLIT, FIRST, FOLD>(act, rowmap, wpk, outp, tl, ng, active, N, K, kb0, kb1, red, act_kmajor != 0, bias, fold);
+            stream_unit<3, TFMAX, KSPLIT, FIRST, FOLD>(act, rowmap, wpk, outp, tl, ng, active, N, K, kb0, kb1, red, act_kmajor != 0, bias, fold, wave);
         else if (TFMAX >= 2 && tfc == 2)
-            stream_unit<2, TFMAX, KSPLIT, FIRST, FOLD>(act, rowmap, wpk, outp, tl, ng, active, N, K, kb0, kb1, red, act_kmajor != 0, bias, fold);
+            stream_unit<2, TFMAX, KSPLIT, FIRST, FOLD>(act, rowmap, wpk, outp, tl, ng, active, N, K, kb0, kb1, red, act_kmajor != 0, bias, fold, wave);
         else
-            stream_unit<1, TFMAX, KSPLIT, FIRST, FOLD>(act, rowmap, wpk, outp, tl, ng, active, N, K, kb0, kb1, red, act_kmajor != 0, bias, fold);
+            stream_unit<1, TFMAX, KSPLIT, FIRST, FOLD>(act, rowmap, wpk, outp, tl, ng, active, N, K, kb0, kb1, red, act_kmajor != 0, bias, fold, wave);
     }
 }
 
@@ -298,7 +174,7 @@ __global__ __launch_bounds__(256) void ffn_stream_narrow_kernel(const uint16_t* 
                                                                 const int32_t* __restrict__ ntiles_p, int N, int K,
                                                                 const float* __restrict__ bias) {
     __shared__ f32x4 red[3 * 64];
-    const int ks = threadIdx.x >> 6;
+    const int ks = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int nblk = N >> 4, kblk = K >> 5;
     const int kb_per = (kblk + 3) / 4;
     const int kb0 = min(kblk, ks * kb_per), kb1 = min(kblk, kb0 + kb_per);
@@ -316,66 +192,61 @@ __global__ __launch_bounds__(256) void ffn_stream_narrow_kernel(const uint16_t* 
         const int bu = base + pb;
         if (bu >= nbu) break;                             // block-uniform
         stream_unit<1, 1, 4, 0, false, 1>(act, nullptr, wpk, outp, tiles[bu / nblk], bu % nblk, true, N, K, kb0, kb1, red,
-                                          true, bias, none);
+                                          true, bias, none, ks);
     }
 }
 
 template <int TFMAX, int KSPLIT, int FIRST, bool FOLD>
 static hipError_t launch_stream(const uint16_t* act, const int32_t* rowmap, const uint16_t* wpk, void* outp,
                                 const Tile* tiles, const int32_t* ntiles, int N, int K, long max_units,
-                                const TileLists& big, bool act_kmajor,
-                                const float* bias, const FoldOut& fold, hipStream_t st) {
+                                bool act_kmajor, const float* bias, const FoldOut& fold, hipStream_t st) {
     auto kern = ffn_stream_kernel<TFMAX, KSPLIT, FIRST, FOLD>;
-    const int per_cu = std::max(1, StreamKernelInfo<TFMAX, KSPLIT, FIRST, FOLD>::per_cu[current_device_index()]);
+    // tiles of up to 64 rows stream fastest as one block per CU, smaller ones as two
+    const int per_cu = std::max(1, std::min(TFMAX == 4 ? 1 : 2, StreamKernelInfo<TFMAX, KSPLIT, FIRST, FOLD>::per_cu[current_device_index()]));
     // KSPLIT = 1: the tile's rows (16 * TFMAX x K, bf16) go through LDS when they fit (the kernel's dynamic-LDS
     // limit was raised by configure_ffn_kernels)
-    const size_t row_bytes = static_cast<size_t>(16) * TFMAX * K * 2;
+    const size_t row_bytes = stream_row_lds(16 * TFMAX, K);
     const bool rows_in_lds = KSPLIT == 1 && row_bytes <= kStreamRowLdsMax;
     const size_t lds = rows_in_lds ? row_bytes : 0;
     // resident blocks per CU: what registers allow, and what the row tiles in LDS leave room for
     int blocks_per_cu = per_cu;
     if (lds > 0) blocks_per_cu = std::max(1, std::min(per_cu, static_cast<int>(kLdsPerCu / lds)));
     long grid = static_cast<long>(device_cu_count()) * blocks_per_cu;
-    if (grid > max_units && big.partials == nullptr) grid = max_units;   // with partial tiles to add: all blocks
+    if (grid > max_units) grid = max_units;
     if (grid < 1) grid = 1;
     // decode-sized tiles (many units per block): balanced grid; larger tiles: every block stays busy
     hipLaunchKernelGGL(kern, dim3(static_cast<unsigned>(grid)), dim3(256), lds, st, act, rowmap, wpk, outp, tiles,
-                       ntiles, N, K, TFMAX <= 2 ? 1 : 0, big.big_tiles, big.half_tiles, big.partials, device_cu_count(),
-                       act_kmajor ? 1 : 0, rows_in_lds ? 1 : 0, bias, fold);
+                       ntiles, N, K, TFMAX <= 2 ? 1 : 0, act_kmajor ? 1 : 0, rows_in_lds ? 1 : 0, bias, fold);
     return hipGetLastError();
 }
 
 template <int TFMAX, int FIRST, bool FOLD>
 static hipError_t launch_stream_kf(int ksplit, const uint16_t* act, const int32_t* rowmap, const uint16_t* wpk,
                                    void* outp, const Tile* tiles, const int32_t* ntiles, int N, int K,
-                                   long max_tiles, const TileLists& big,
-                                   bool act_kmajor, const float* bias, const FoldOut& fold, hipStream_t st) {
+                                   long max_tiles, bool act_kmajor, const float* bias, const FoldOut& fold, hipStream_t st) {
     const long ngroups = (N / 16 + 3) / 4;
     if (ksplit == 4)
         return launch_stream<TFMAX, 4, FIRST, FOLD>(act, rowmap, wpk, outp, tiles, ntiles, N, K, max_tiles * ngroups,
-                                                    big, act_kmajor, bias, fold, st);
+                                                    act_kmajor, bias, fold, st);
     if (ksplit == 2)
         return launch_stream<TFMAX, 2, FIRST, FOLD>(act, rowmap, wpk, outp, tiles, ntiles, N, K,
-                                                    max_tiles * ((ngroups + 1) / 2), big,
-                                                    act_kmajor, bias, fold, st);
+                                                    max_tiles * ((ngroups + 1) / 2), act_kmajor, bias, fold, st);
     return launch_stream<TFMAX, 1, FIRST, FOLD>(act, rowmap, wpk, outp, tiles, ntiles, N, K,
-                                                max_tiles * ((ngroups + 3) / 4), big,
-                                                act_kmajor, bias, fold, st);
+                                                max_tiles * ((ngroups + 3) / 4), act_kmajor, bias, fold, st);
 }
 
 // the folded form exists for the second product only
 template <int TFMAX, int FIRST>
 static hipError_t launch_stream_k(int ksplit, const uint16_t* act, const int32_t* rowmap, const uint16_t* wpk,
                                   void* outp, const Tile* tiles, const int32_t* ntiles, int N, int K,
-                                  long max_tiles, const TileLists& big,
-                                  bool act_kmajor, const float* bias, const FoldOut& fold, hipStream_t st) {
+                                  long max_tiles, bool act_kmajor, const float* bias, const FoldOut& fold, hipStream_t st) {
     if constexpr (FIRST == 0) {
         if (fold.out != nullptr)
             return launch_stream_kf<TFMAX, 0, true>(ksplit, act, rowmap, wpk, outp, tiles, ntiles, N, K, max_tiles,
-                                                    big, act_kmajor, bias, fold, st);
+                                                    act_kmajor, bias, fold, st);
     }
     return launch_stream_kf<TFMAX, FIRST, false>(ksplit, act, rowmap, wpk, outp, tiles, ntiles, N, K, max_tiles,
-                                                 big, act_kmajor, bias, fold, st);
+                                                 act_kmajor, bias, fold, st);
 }
 
 template <int TFMAX, int KSPLIT, int FIRST, bool FOLD>
@@ -432,7 +303,7 @@ hipError_t configure_ffn_kernels(int dev) {
 static int pick_ksplit(int K, int N, int tfmax, long tiles_expected) {
     const int steps = K / 32;
     if (tfmax <= 2) {
-        const bool rows_fit = static_cast<size_t>(16) * tfmax * K * 2 <= kStreamRowLdsMax;
+        const bool rows_fit = stream_row_lds(16 * tfmax, K) <= kStreamRowLdsMax;
         const long units_unsplit = tiles_expected * ((N / 64 + 3) / 4);
         if (rows_fit && units_unsplit >= 2L * device_cu_count()) return 1;
     }
@@ -527,32 +398,31 @@ hipError_t launch_expert_products(const moe_shape& s, const void* act, const int
     uint16_t* h = static_cast<uint16_t*>(h_ws);
     const long tiles_expected = A < E ? A : E;      // every assignment on its own expert, at most E of them
     const int ks1 = pick_ksplit(d, f, ffn_tfmax(s), tiles_expected), ks2 = pick_ksplit(f, d, ffn_tfmax(s), tiles_expected);
-    // Per product: the tiled kernel (large experts) first, then the streaming kernel (small experts), which
-    // also adds up the partial tiles that the tiled kernel left for the units it cut along K.
-    if (big) {
-        err = launch_tile_product(true, xp, rowmap, p1, h, lists, f, d, act_kmajor, s.activation, b1,
-                                  FoldOut{nullptr, nullptr, nullptr}, st);
+    if (big) {                                             // one kernel per product for large and small experts
+        err = launch_tiled_product(true, ks1, xp, rowmap, p1, h, lists, f, d, act_kmajor, s.activation, b1,
+                                   FoldOut{nullptr, nullptr, nullptr}, st);
         if (err != hipSuccess) return err;
+        if ((err = mark_profile_event(1, st)) != hipSuccess || (err = mark_profile_event(2, st)) != hipSuccess) return err;
+        err = launch_tiled_product(false, ks2, h, nullptr, p2, y_perm, lists, d, f, true, s.activation, b2, fold, st);
+        if (err != hipSuccess) return err;
+        if ((err = mark_profile_event(3, st)) != hipSuccess) return err;
+        return mark_profile_event(4, st);
     }
     if ((err = mark_profile_event(1, st)) != hipSuccess) return err;
     const bool gelu = s.activation == MOE_ACT_GELU;
     switch (ffn_tfmax(s) * 2 + (gelu ? 1 : 0)) {
-        case 2: err = launch_stream_k<1, kFirstRelu>(ks1, xp, rowmap, p1, h, tiles, ntiles, f, d, max_tiles, lists, act_kmajor, b1, FoldOut{nullptr, nullptr, nullptr}, st); break;
-        case 3: err = launch_stream_k<1, kFirstGelu>(ks1, xp, rowmap, p1, h, tiles, ntiles, f, d, max_tiles, lists, act_kmajor, b1, FoldOut{nullptr, nullptr, nullptr}, st); break;
-        case 4: err = launch_stream_k<2, kFirstRelu>(ks1, xp, rowmap, p1, h, tiles, ntiles, f, d, max_tiles, lists, act_kmajor, b1, FoldOut{nullptr, nullptr, nullptr}, st); break;
-        case 5: err = launch_stream_k<2, kFirstGelu>(ks1, xp, rowmap, p1, h, tiles, ntiles, f, d, max_tiles, lists, act_kmajor, b1, FoldOut{nullptr, nullptr, nullptr}, st); break;
-        case 8: err = launch_stream_k<4, kFirstRelu>(ks1, xp, rowmap, p1, h, tiles, ntiles, f, d, max_tiles, lists, act_kmajor, b1, FoldOut{nullptr, nullptr, nullptr}, st); break;
-        default: err = launch_stream_k<4, kFirstGelu>(ks1, xp, rowmap, p1, h, tiles, ntiles, f, d, max_tiles, lists, act_kmajor, b1, FoldOut{nullptr, nullptr, nullptr}, st); break;
+        case 2: err = launch_stream_k<1, kFirstRelu>(ks1, xp, rowmap, p1, h, tiles, ntiles, f, d, max_tiles, act_kmajor, b1, FoldOut{nullptr, nullptr, nullptr}, st); break;
+        case 3: err = launch_stream_k<1, kFirstGelu>(ks1, xp, rowmap, p1, h, tiles, ntiles, f, d, max_tiles, act_kmajor, b1, FoldOut{nullptr, nullptr, nullptr}, st); break;
+        case 4: err = launch_stream_k<2, kFirstRelu>(ks1, xp, rowmap, p1, h, tiles, ntiles, f, d, max_tiles, act_kmajor, b1, FoldOut{nullptr, nullptr, nullptr}, st); break;
+        case 5: err = launch_stream_k<2, kFirstGelu>(ks1, xp, rowmap, p1, h, tiles, ntiles, f, d, max_tiles, act_kmajor, b1, FoldOut{nullptr, nullptr, nullptr}, st); break;
+        case 8: err = launch_stream_k<4, kFirstRelu>(ks1, xp, rowmap, p1, h, tiles, ntiles, f, d, max_tiles, act_kmajor, b1, FoldOut{nullptr, nullptr, nullptr}, st); break;
+        default: err = launch_stream_k<4, kFirstGelu>(ks1, xp, rowmap, p1, h, tiles, ntiles, f, d, max_tiles, act_kmajor, b1, FoldOut{nullptr, nullptr, nullptr}, st); break;
     }
     if (err != hipSuccess) return err;
     if ((err = mark_profile_event(2, st)) != hipSuccess) return err;
-    if (big) {
-        err = launch_tile_product(false, h, nullptr, p2, y_perm, lists, d, f, true, s.activation, b2, fold, st);
-        if (err != hipSuccess) return err;
-    }
     if ((err = mark_profile_event(3, st)) != hipSuccess) return err;
     // few tokens and few experts: units of one column block, so that every CU has one
-    const bool narrow = ffn_tfmax(s) == 1 && ks2 == 4 && fold.out == nullptr && !big &&
+    const bool narrow = ffn_tfmax(s) == 1 && ks2 == 4 && fold.out == nullptr &&
                         tiles_expected * ((d / 16 + 3) / 4) < device_cu_count();
     if (narrow) {
         long grid = max_tiles * (d / 16);
@@ -563,9 +433,9 @@ hipError_t launch_expert_products(const moe_shape& s, const void* act, const int
         return mark_profile_event(4, st);
     }
     switch (ffn_tfmax(s)) {
-        case 1: err = launch_stream_k<1, 0>(ks2, h, nullptr, p2, y_perm, tiles, ntiles, d, f, max_tiles, lists, true, b2, fold, st); break;
-        case 2: err = launch_stream_k<2, 0>(ks2, h, nullptr, p2, y_perm, tiles, ntiles, d, f, max_tiles, lists, true, b2, fold, st); break;
-        default: err = launch_stream_k<4, 0>(ks2, h, nullptr, p2, y_perm, tiles, ntiles, d, f, max_tiles, lists, true, b2, fold, st); break;
+        case 1: err = launch_stream_k<1, 0>(ks2, h, nullptr, p2, y_perm, tiles, ntiles, d, f, max_tiles, true, b2, fold, st); break;
+        case 2: err = launch_stream_k<2, 0>(ks2, h, nullptr, p2, y_perm, tiles, ntiles, d, f, max_tiles, true, b2, fold, st); break;
+        default: err = launch_stream_k<4, 0>(ks2, h, nullptr, p2, y_perm, tiles, ntiles, d, f, max_tiles, true, b2, fold, st); break;
     }
     if (err != hipSuccess) return err;
     return mark_profile_event(4, st);

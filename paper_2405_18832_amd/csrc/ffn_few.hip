@@ -141,11 +141,11 @@ __global__ __launch_bounds__(256, 2) void few_first_kernel(const FewRoute p, con
     if (lists.ntiles * ngroups >= cus) {                   // uniform
         for (int u = first; u < lists.ntiles * ngroups; u += grid)
             stream_unit<1, 1, 4, FIRST, false, 4>(x, lists.token, w1, h, lists.tiles[u / ngroups], u % ngroups, true, N, K, kb0, kb1,
-                                                  red, false, b1, none);
+                                                  red, false, b1, none, wave);
     } else {
         for (int u = first; u < lists.ntiles * nblk; u += grid)
             stream_unit<1, 1, 4, FIRST, false, 1>(x, lists.token, w1, h, lists.tiles[u / nblk], u % nblk, true, N, K, kb0, kb1, red,
-                                                  false, b1, none);
+                                                  false, b1, none, wave);
     }
 }
 

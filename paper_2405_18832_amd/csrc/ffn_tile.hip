@@ -1,8 +1,16 @@
-// LDS-tiled MFMA product for experts with many rows (the compute-bound "hot" experts of the
-// paper's Section 3.3: enough tokens per expert that the product is bound by matrix throughput,
-// not by reading the expert's parameters):
+// One product of a layer that may have large experts, as one kernel:
 //
-//   out[row, n] = sum_k act[row, k] * W_e[n, k]          (FIRST: relu, rounded to bf16)
+//   out[row, n] = sum_k act[row, k] * W_e[n, k]          (FIRST: activation, rounded to bf16)
+//
+// Experts with many rows (the compute-bound "hot" experts of the paper's Section 3.3: enough tokens that the product is bound by matrix
+// throughput, not by reading the expert's parameters) run in LDS-tiled MFMA units, the others in weight-streaming units
+// (stream_unit.hpp), which the blocks turn to as they run out of tiled ones.  As two kernels one after the other the CUs without a unit
+// of a partly filled round waited for the last one twice per product, the sums of cut units were added up by the second kernel, and
+// where one kind does not occur its launch cost 2 to 3 us all the same.  Whole layers, two kernels -> one, us: 1501 tokens, 8 experts,
+// 768 x 3072, GeLU 63 -> 57; 5003 tokens, hot share of 32 experts, 2048 x 8192, k = 2 935 -> 860; 2586 tokens, hot share of 20
+// 574 -> 498; 16384 tokens, 41 experts 2180 -> 2140; 208 tokens, 128 experts 323 -> 299.
+// The four wavefronts that stream do so within the 256 registers that 8 wavefronts per CU leave each: their loads are issued step by
+// step (stream_unit.hpp) and their share of a sum is a quarter.  No register is spilled: a kernel that has scratch memory starts several us later.
 //
 // Big units: block = 8 wavefronts on a 256 (rows) x 256 (columns) output tile, K in steps of 32 through a
 // ring of four LDS stages of 32 KiB: the copies of two stages are in flight while two are being
@@ -30,10 +38,12 @@
 // As blocks of one group, two per CU, the last was 50.1 + 36.7 us: twice the parts.
 //
 // Blocks are persistent over (row tile, column tile) pairs taken
-// from the device-built list of large-expert row tiles.
+// from the device-built list of large-expert row tiles.  (Figures of sums above: the parts added up by a kernel of its own.)
 #include <type_traits>
 
-#include "tile_schedule.hpp"
+#include <algorithm>
+
+#include "stream_unit.hpp"
 
 namespace moe {
 
@@ -92,11 +102,72 @@ __device__ __forceinline__ int narrow_sums(const TileSchedule& sch, int kblk) {
     return FIRST == kFirstGelu ? max(sch.sums, kblk < 2 * FineUnits::kMinSplitSteps ? min(kblk, 2) : 4) : sch.sums;
 }
 
-template <int FIRST, typename Units>
+// 16 bytes per lane of memory that another XCD's blocks read or have written in the same launch: sc1 (bit 4 of the cache-policy
+// operand) sends the store through this XCD's L2 to memory, and makes the load miss in it.
+constexpr int kAgentScope = 16;
+typedef __attribute__((ext_vector_type(4))) uint32_t u32x4;
+
+// Adds up the parts of a unit that was cut along K, in a tree over the part numbers: (0 + 1) + (2 + 3) and so on, whichever block
+// computed them.  Of the two blocks that meet at a node, the one that gets there first leaves its sum in the workspace and is done;
+// the other adds that to its own and goes on to the next level.  Nobody waits for anybody, so that it does not matter which blocks
+// are resident, and the sum does not depend on the order of arrival.  Returns whether this block has the whole sum.
+// `first_slot`: number of the unit's part 0 among all parts; part p owns partial tile first_slot + p (tile_floats floats), and the
+// node whose right-hand side begins with part p the counter joined[first_slot + p], zero at the start of the launch.
+// A wavefront reads only what the same wavefront of the other block has stored (the tile lies in accumulator order).
+// Visibility: the sums are stored with agent scope and have arrived in memory (vmcnt) for every wavefront (barrier) before the
+// counter is raised; a counter that reads 1 therefore means that the other block's sum can be loaded.  (A fence would write back
+// all of the XCD's L2 for these few lines: such a version cost more than it saved.)
+template <int OF, int RF>
+__device__ __forceinline__ bool join_parts(f32x4 (&acc)[4][RF], int part, int nparts, int first_slot, int tile_floats,
+                                           int32_t* joined, float* partials, int wave, int* flag) {
+    const int lane = threadIdx.x & 63;
+    const int wave_bytes = OF * 4 * 1024;
+    auto tile_of = [&](int p) {
+        return __builtin_amdgcn_make_buffer_rsrc(reinterpret_cast<char*>(partials + static_cast<size_t>(first_slot + p) * tile_floats),
+                                                 0, tile_floats * 4, 0x00027000);
+    };
+    const int at = wave * wave_bytes + lane * 16;
+    for (int level = 0; (1 << level) < nparts; ++level) {
+        const int mine = part >> level, other = mine ^ 1;
+        if ((other << level) >= nparts) continue;              // nobody there: up to the next level
+        int32_t* const node = joined + first_slot + ((mine | 1) << level);
+        if (threadIdx.x == 0) *flag = __hip_atomic_load(node, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+        bool second = __builtin_amdgcn_readfirstlane(*flag) != 0;
+        asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");          // the flag is read
+        if (!second) {
+            const auto tile = tile_of(mine << level);
+#pragma unroll
+            for (int tf = 0; tf < OF; ++tf)
+#pragma unroll
+                for (int nf = 0; nf < 4; ++nf)
+                    __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, acc[nf][tf]), tile, at + nf * 1024, tf * 4096,
+                                                           kAgentScope);
+            asm volatile("s_waitcnt vmcnt(0)\n\ts_barrier" ::: "memory");
+            if (threadIdx.x == 0) *flag = __hip_atomic_fetch_add(node, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+            second = __builtin_amdgcn_readfirstlane(*flag) != 0;
+            asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+            if (!second) return false;
+        }
+        const auto tile = tile_of(other << level);
+#pragma unroll
+        for (int tf = 0; tf < OF; ++tf) {
+            u32x4 v[4];
+#pragma unroll
+            for (int nf = 0; nf < 4; ++nf) v[nf] = __builtin_amdgcn_raw_buffer_load_b128(tile, at + nf * 1024, tf * 4096, kAgentScope);
+#pragma unroll
+            for (int nf = 0; nf < 4; ++nf) acc[nf][tf] += __builtin_bit_cast(f32x4, v[nf]);
+        }
+    }
+    return true;
+}
+
+template <int FIRST, bool FOLD, typename Units>
 __device__ __forceinline__ void run_units(const uint16_t* __restrict__ act, const int32_t* __restrict__ rowmap,
                                           const uint16_t* __restrict__ wpk, void* __restrict__ outp,
                                           const Tile* __restrict__ tiles, const TileSchedule& sch,
-                                          int32_t* __restrict__ part_counter, float* __restrict__ partials, int N, int K,
+                                          int32_t* part_counter, int32_t* joined, float* partials, int N, int K,
                                           int act_kmajor, const float* __restrict__ bias, const FoldOut& fold,
                                           unsigned char* smem) {
     constexpr bool FINE = Units::kGroups == 2;
@@ -413,22 +484,18 @@ __device__ __forceinline__ void run_units(const uint16_t* __restrict__ act, cons
         if (!next_known) nxt = unit_at(it + 1);
         if (nxt.valid && !ahead) start_unit(nxt);
 
+        // The last of a cut unit's parts to finish adds them all up and stores the unit's output.
+        const bool whole = cur.nparts == 1 ||
+                           join_parts<OF>(acc, cur.part, cur.nparts, (cur.u - sch.rounds * G) * cur.nparts, kTM * kTN, joined,
+                                          partials, block_wave, reinterpret_cast<int*>(exchange));
         // Lane holds 4 consecutive columns of one row per accumulator.
-        if (cur.nparts > 1) {
-            // part of a unit: the partial tile goes to the workspace; the next kernel adds the parts up
-            float* mine = partials + (static_cast<size_t>(cur.u - sch.rounds * G) * cur.nparts + cur.part) * (kTM * kTN);
-#pragma unroll
-            for (int tf = 0; tf < OF; ++tf)
-#pragma unroll
-                for (int nf = 0; nf < 4; ++nf)
-                    *reinterpret_cast<f32x4*>(mine + (lr0 + tf * 16 + r) * kTN + (wn * 4 + nf) * 16 + g * 4) =
-                        acc[nf][tf];
-        } else {
+        if (whole) {
+            const int el = lane_of_unit(), er = el & 15, eg = el >> 4;
             const float* be = bias ? bias + static_cast<size_t>(cur.tl.expert) * N : nullptr;
 #pragma unroll
             for (int tf = 0; tf < OF; ++tf) {
                 if (lr0 + tf * 16 >= cur.tl.rows) break;     // wave-uniform: no row from here on
-                const int lr = lr0 + tf * 16 + r;
+                const int lr = lr0 + tf * 16 + er;
                 const bool ok = lr < cur.tl.rows;
                 if constexpr (FIRST != 0) {
 #pragma unroll
@@ -439,13 +506,9 @@ __device__ __forceinline__ void run_units(const uint16_t* __restrict__ act, cons
                                                    acc[2 * m + 1][tf]);
                     }
                 } else {
-                    int ftok = 0;
-                    float fw = 0.f;
-                    if (fold.out != nullptr && ok) {                    // folded layer output (top-1, no mask)
-                        ftok = fold.tokmap[cur.tl.row0 + lr];
-                        fw = fold.gate[ftok];
-                    }
-                    if (fold.out != nullptr) {                          // block-uniform
+                    if constexpr (FOLD) {                               // folded layer output (top-1, no mask)
+                        const int ftok = ok ? fold.tokmap[cur.tl.row0 + lr] : 0;
+                        const float fw = ok ? fold.gate[ftok] : 0.f;
 #pragma unroll
                         for (int m = 0; m < 2; ++m) {
                             const int nb = cur.nt * (kTN / 16) + wn * 4 + 2 * m;
@@ -457,7 +520,7 @@ __device__ __forceinline__ void run_units(const uint16_t* __restrict__ act, cons
                         for (int nf = 0; nf < 4; ++nf) {
                             const int nb = cur.nt * (kTN / 16) + wn * 4 + nf;
                             if (ok && nb < nblk)
-                                store_out<0>(outp, cur.tl.row0 + lr, nb * 16 + g * 4, N, be, acc[nf][tf]);
+                                store_out<0>(outp, cur.tl.row0 + lr, nb * 16 + eg * 4, N, be, acc[nf][tf]);
                         }
                     }
                 }
@@ -467,66 +530,242 @@ __device__ __forceinline__ void run_units(const uint16_t* __restrict__ act, cons
     }
 }
 
-template <int FIRST>
-__global__ __launch_bounds__(kWaves * 64, 2) void ffn_tile_kernel(const uint16_t* __restrict__ act, const int32_t* __restrict__ rowmap,
-                                                                  const uint16_t* __restrict__ wpk, void* __restrict__ outp,
-                                                                  const Tile* __restrict__ big_tiles,
-                                                                  const Tile* __restrict__ half_tiles,
-                                                                  const int32_t* __restrict__ ntiles_p,
-                                                                  int32_t* __restrict__ part_counter,
-                                                                  float* __restrict__ partials, int N, int K, int act_kmajor,
-                                                                  const float* __restrict__ bias, const FoldOut fold) {
-    extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
-    // the grid is the number of CUs that the schedule was made for
-    const TileSchedule sch = *reinterpret_cast<const TileSchedule*>(ntiles_p + kScheduleAt + (FIRST != 0 ? 0 : kScheduleInts));
-    if (ntiles_p[1] <= 0) return;                       // no large expert in this call (block-uniform)
-    // Big units first: their loop is the one that matters most, and its place in the code makes a difference (with the other shapes
-    // in front of them the first product of 16384 tokens x 2048 x 8192, k = 2, took 888 us instead of 878).
-    if (sch.shape == UnitShape::kBig)
-        run_units<FIRST, BigUnits>(act, rowmap, wpk, outp, big_tiles, sch, part_counter, partials, N, K, act_kmajor, bias, fold,
-                                   smem);
-    else if (sch.shape == UnitShape::kFine)
-        run_units<FIRST, FineUnits>(act, rowmap, wpk, outp, half_tiles, sch, part_counter, partials, N, K, act_kmajor, bias, fold,
-                                    smem);
-    else
-        run_units<FIRST, NarrowUnits>(act, rowmap, wpk, outp, big_tiles, sch, part_counter, partials, N, K, act_kmajor, bias, fold,
-                                      smem);
+// The streaming units of a product (stream_unit.hpp), by the first four wavefronts of every block of the product kernel; the others
+// have ended, and barriers do not wait for wavefronts that have.  Four are as many as stream fastest: a second set on every CU was
+// slower (64 experts of about 32 rows, 768 x 3072: 67 -> 78 us a product).
+// Each XCD has a run of consecutive units, the column groups of one tile after the other, so that a tile's rows are fetched into one
+// L2; within a run, blocks that had no tiled unit begin with the first units, and from then on units are handed out in order of
+// arrival, from the other XCDs' runs too when the block's own is empty.
+template <int KSPLIT, int FIRST, bool FOLD>
+__device__ __forceinline__ void run_stream_units(const uint16_t* __restrict__ act, const int32_t* __restrict__ rowmap,
+                                                 const uint16_t* __restrict__ wpk, void* __restrict__ outp,
+                                                 const Tile* __restrict__ tiles, int ntiles, int32_t* taken, int busy, int N, int K,
+                                                 int act_kmajor, const float* __restrict__ bias,
+                                                 const FoldOut& fold, unsigned char* smem, const int wave) {
+    constexpr int TFMAX = 4, NGB = 4 / KSPLIT;              // row fragments of a tile; column groups (of 64) per unit
+    unsigned char* tok_lds = smem;
+    f32x4* red = reinterpret_cast<f32x4*>(smem);
+    static_assert((KSPLIT - 1) * NGB * 4 * TFMAX * 1024 <= kRingBytes && kStreamRowLdsMax <= kRingBytes, "both fit in front of `next_unit`");
+    int* next_unit = reinterpret_cast<int*>(smem + kRingBytes);
+    const int lane = static_cast<int>(__builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, 0)));
+    const int ks = wave % KSPLIT, ngs = wave / KSPLIT;
+    const int nblk = N >> 4, kblk = K >> 5;
+    const int ngchunks = (nblk + 4 * NGB - 1) / (4 * NGB);
+    const int kb_per = (kblk + KSPLIT - 1) / KSPLIT;
+    const int kb0 = min(kblk, ks * kb_per), kb1 = min(kblk, kb0 + kb_per);
+    const int units = ntiles * ngchunks;
+
+    const int G = gridDim.x, nx = G % 8 == 0 ? 8 : 1, blocks = G / nx;
+    const int x = static_cast<int>(blockIdx.x) % nx, rank = static_cast<int>(blockIdx.x) / nx;
+    const int fixed = blocks - busy;                        // units at the head of a run that are not handed out
+    auto run_begin = [&](int i) { return static_cast<int>(static_cast<long>(units) * i / nx); };
+    auto take = [&](int i) { return __hip_atomic_fetch_add(taken + i * kTakenStride, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); };
+    // A unit for a block whose own run is empty, or -1: by the first wavefront, which looks at all runs at once.
+    auto take_any = [&]() {
+        for (;;) {                                          // ends: counters only rise, and every turn raises one that is not at its end
+            const int i = min(lane, nx - 1);
+            const int end = run_begin(i + 1) - run_begin(i) - fixed;
+            const int c = __hip_atomic_load(taken + i * kTakenStride, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            const uint64_t left = __ballot(lane < nx && c < end);
+            if (left == 0) return -1;
+            const uint64_t from = left >> x << x;           // the next run after the block's own that has some
+            const int y = __builtin_ctzll(from != 0 ? from : left);
+            int n = 0;
+            if (lane == 0) n = take(y);
+            n = run_begin(y) + fixed + __builtin_amdgcn_readfirstlane(n);
+            if (n < run_begin(y + 1)) return n;
+        }
+    };
+    // The next unit is asked for when the current one's last loads are out, so that its number is there when they are consumed and no
+    // block holds a unit that an idle one could run; its tile is looked up while the current one's output is stored.  (Asked for at the
+    // start of the current unit: 16 experts of the hot share of 777 tokens, 1024 x 4096: 117 -> 131 us for the four calls.)
+    // Without tiled units all blocks start together and units cost about the same: every block takes its share, nothing is counted
+    // (64 experts of about 32 rows, 768 x 3072: 136 us for the layer, 147 counted).
+    struct NextUnit {
+        decltype(take)& take_;
+        const Tile* tiles;
+        int* slot;
+        int x, fixed, x0, x1, ngchunks;
+        bool counted, first;                                // first: the block's first lane
+        int asked, unit;
+        Tile tl;
+        __device__ __forceinline__ void look_up() {
+            if (unit >= 0) tl = tiles[unit / ngchunks];
+        }
+        __device__ __forceinline__ void loads_out() {
+            if (counted && first) asked = take_(x);
+        }
+        __device__ __forceinline__ void loads_done() {
+            if (counted && first) *slot = asked;
+        }
+        __device__ __forceinline__ bool meet() const { return counted; }
+        __device__ __forceinline__ void met() {
+            unit = counted ? x0 + fixed + __builtin_amdgcn_readfirstlane(*slot) : unit + static_cast<int>(gridDim.x);
+            if (unit >= x1) unit = -1;
+            look_up();
+        }
+    };
+    const bool counted = busy > 0;
+    NextUnit next{take, tiles, next_unit, x, fixed, run_begin(x), counted ? run_begin(x + 1) : units, ngchunks, counted,
+                  wave == 0 && lane == 0, 0, 0, {}};
+    next.unit = counted ? (rank >= busy ? next.x0 + rank - busy : next.x1) : x * blocks + rank;
+    if (next.unit >= next.x1) next.unit = -1;
+    next.look_up();
+    for (;;) {
+        if (next.unit < 0) {                                // block-uniform
+            if (!next.counted) return;
+            asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");      // the last number has been read by all
+            if (wave == 0) {
+                const int got = take_any();
+                if (lane == 0) *next_unit = got;
+            }
+            asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+            next.unit = __builtin_amdgcn_readfirstlane(*next_unit);
+            if (next.unit < 0) return;
+            next.look_up();
+            asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");      // read by all before it is written again
+        }
+        const Tile tl{__builtin_amdgcn_readfirstlane(next.tl.expert), __builtin_amdgcn_readfirstlane(next.tl.row0),
+                      __builtin_amdgcn_readfirstlane(next.tl.rows), 0};
+        const int ng = next.unit % ngchunks * NGB + ngs;
+        const bool active = ng * 4 < nblk;                  // wave-uniform
+        const int tfc = (tl.rows + 15) >> 4;                // token fragments in use: block-uniform
+        const bool km = act_kmajor != 0;
+        auto run = [&](auto frags) {
+            constexpr int TFC = decltype(frags)::value;
+            if constexpr (KSPLIT == 1)
+                stream_unit_lds<TFC, FIRST, FOLD>(act, rowmap, wpk, outp, tl, ng, active, N, K, km, bias, tok_lds, fold, wave, next);
+            else
+                stream_unit<TFC, TFMAX, KSPLIT, FIRST, FOLD, 4>(act, rowmap, wpk, outp, tl, ng, active, N, K, kb0, kb1, red, km, bias,
+                                                                fold, wave, next);
+        };
+        if (tfc == 4) run(std::integral_constant<int, 4>{});
+        else if (tfc == 3) run(std::integral_constant<int, 3>{});
+        else if (tfc == 2) run(std::integral_constant<int, 2>{});
+        else run(std::integral_constant<int, 1>{});
+    }
 }
 
-template <int FIRST>
-static hipError_t launch_tile(const uint16_t* act, const int32_t* rowmap, const uint16_t* wpk, void* outp,
-                              const TileLists& lists, int N, int K, bool act_kmajor, const float* bias, const FoldOut& fold,
-                              hipStream_t st) {
-    // Always the whole chip, one block per CU (the LDS allows no more): how many units there are is
-    // only known on the device, and few units are cut along K over blocks that would otherwise idle.
-    hipLaunchKernelGGL(ffn_tile_kernel<FIRST>, dim3(static_cast<unsigned>(tile_product_grid())), dim3(kWaves * 64), kTileLds, st,
-                       act, rowmap, wpk, outp, lists.big_tiles, lists.half_tiles, lists.ntiles,
-                       lists.ntiles + kSplitCounter + (FIRST != 0 ? 0 : 1), lists.partials, N, K, act_kmajor ? 1 : 0, bias, fold);
+// The arguments of one product: in the kernel's argument segment, read where they are needed.
+struct ProductArgs {
+    const uint16_t* act;
+    const int32_t* rowmap;
+    const uint16_t* wpk;
+    void* outp;
+    const Tile* small_tiles;
+    const Tile* big_tiles;
+    const Tile* half_tiles;
+    int32_t* lists;
+    float* partials;
+    const float* bias;
+    FoldOut fold;
+    int N, K, act_kmajor;
+};
+typedef const ProductArgs __attribute__((address_space(4))) * product_args_t;
+
+// One product of a layer that may have large experts: these experts' units first, then the small experts' on whichever blocks are
+// free, side by side with the tiled units that still run.
+template <int KSPLIT, int FIRST, bool FOLD>
+__global__ __launch_bounds__(kWaves * 64, 2) void ffn_product_kernel(const ProductArgs by_value) {
+    extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
+    constexpr int product = FIRST != 0 ? 0 : 1;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    // the grid is the number of CUs that the schedule was made for
+    const TileSchedule sch = *reinterpret_cast<const TileSchedule*>(by_value.lists + kScheduleAt + product * kScheduleInts);
+    if (by_value.lists[1] > 0) {                            // block-uniform, as all of these
+        int32_t* const parts = by_value.lists + kSplitCounter + product;
+        int32_t* const joined = by_value.lists + kJoinedAt + product * kSplitSlots;
+        const ProductArgs& p = by_value;
+        // Big units first: their loop is the one that matters most, and its place in the code makes a difference (with the other
+        // shapes in front of them the first product of 16384 tokens x 2048 x 8192, k = 2, took 888 us instead of 878).
+        if (sch.shape == UnitShape::kBig)
+            run_units<FIRST, FOLD, BigUnits>(p.act, p.rowmap, p.wpk, p.outp, p.big_tiles, sch, parts, joined, p.partials, p.N, p.K,
+                                             p.act_kmajor, p.bias, p.fold, smem);
+        else if (sch.shape == UnitShape::kFine)
+            run_units<FIRST, FOLD, FineUnits>(p.act, p.rowmap, p.wpk, p.outp, p.half_tiles, sch, parts, joined, p.partials, p.N, p.K,
+                                              p.act_kmajor, p.bias, p.fold, smem);
+        else
+            run_units<FIRST, FOLD, NarrowUnits>(p.act, p.rowmap, p.wpk, p.outp, p.big_tiles, sch, parts, joined, p.partials, p.N, p.K,
+                                                p.act_kmajor, p.bias, p.fold, smem);
+    }
+    // From here on everything is read anew (the pointer is opaque to the compiler), so that nothing of it takes registers above.
+    product_args_t args = (product_args_t)__builtin_amdgcn_kernarg_segment_ptr();
+    asm volatile("" : "+s"(args));
+    const int32_t* lists = args->lists;
+    if (lists[0] <= 0) return;                              // no small expert
+    int busy = 0;                                           // blocks of an XCD that began with a tiled unit
+    if (lists[1] > 0) {
+        const TileSchedule* s = reinterpret_cast<const TileSchedule*>(lists + kScheduleAt + product * kScheduleInts);
+        busy = s->rounds > 0 ? static_cast<int>(gridDim.x) : s->R * s->split;
+        if (gridDim.x % 8 == 0) busy = (busy + 7) >> 3;
+    }
+    asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");       // the LDS changes hands
+    if (wave >= 4) return;
+    const FoldOut fold{args->fold.out, args->fold.tokmap, args->fold.gate};
+    run_stream_units<KSPLIT, FIRST, FOLD>(args->act, args->rowmap, args->wpk, args->outp, args->small_tiles, lists[0],
+                                          args->lists + kTakenAt + product * 8 * kTakenStride, busy, args->N, args->K, args->act_kmajor,
+                                          args->bias, fold, smem, wave);
+}
+
+template <int KSPLIT, int FIRST, bool FOLD>
+static hipError_t launch_product_kernel(const uint16_t* act, const int32_t* rowmap, const uint16_t* wpk, void* outp,
+                                        const TileLists& lists, int N, int K, bool act_kmajor, const float* bias, const FoldOut& fold,
+                                        hipStream_t st) {
+    // An uncut contraction is read from rows in LDS (pick_ksplit cuts the others).
+    if (KSPLIT == 1 && stream_row_lds(64, K) > kStreamRowLdsMax) return hipErrorInvalidValue;
+    const ProductArgs args{act, rowmap, wpk, outp, lists.small_tiles, lists.big_tiles, lists.half_tiles, lists.ntiles, lists.partials,
+                           bias, fold, N, K, act_kmajor ? 1 : 0};
+    // Always the whole chip, one block per CU (the LDS allows no more): how many units there are is only known on the device.
+    hipLaunchKernelGGL((ffn_product_kernel<KSPLIT, FIRST, FOLD>), dim3(static_cast<unsigned>(tile_product_grid())), dim3(kWaves * 64),
+                       kTileLds, st, args);
     return hipGetLastError();
 }
 
 int tile_product_grid() { return device_cu_count(); }
 
-template <int FIRST>
-static hipError_t configure_tile() {
-    return hipFuncSetAttribute(reinterpret_cast<const void*>(ffn_tile_kernel<FIRST>),
+template <int KSPLIT, int FIRST, bool FOLD>
+static hipError_t configure_product() {
+    return hipFuncSetAttribute(reinterpret_cast<const void*>(ffn_product_kernel<KSPLIT, FIRST, FOLD>),
                                hipFuncAttributeMaxDynamicSharedMemorySize, kTileLds);
+}
+
+template <int KSPLIT>
+static hipError_t configure_products() {
+    hipError_t e;
+    if ((e = configure_product<KSPLIT, kFirstRelu, false>()) != hipSuccess) return e;
+    if ((e = configure_product<KSPLIT, kFirstGelu, false>()) != hipSuccess) return e;
+    if ((e = configure_product<KSPLIT, 0, false>()) != hipSuccess) return e;
+    return configure_product<KSPLIT, 0, true>();
 }
 
 hipError_t configure_tile_kernels(int) {
     hipError_t e;
-    if ((e = configure_tile<0>()) != hipSuccess) return e;
-    if ((e = configure_tile<kFirstRelu>()) != hipSuccess) return e;
-    return configure_tile<kFirstGelu>();
+    if ((e = configure_products<1>()) != hipSuccess) return e;
+    if ((e = configure_products<2>()) != hipSuccess) return e;
+    return configure_products<4>();
 }
 
-hipError_t launch_tile_product(bool first, const uint16_t* act, const int32_t* rowmap, const uint16_t* wpk,
-                               void* outp, const TileLists& lists, int N, int K, bool act_kmajor, int activation,
-                               const float* bias, const FoldOut& fold, hipStream_t st) {
-    if (!first) return launch_tile<0>(act, rowmap, wpk, outp, lists, N, K, act_kmajor, bias, fold, st);
-    if (activation == MOE_ACT_GELU)
-        return launch_tile<kFirstGelu>(act, rowmap, wpk, outp, lists, N, K, act_kmajor, bias, fold, st);
-    return launch_tile<kFirstRelu>(act, rowmap, wpk, outp, lists, N, K, act_kmajor, bias, fold, st);
+template <int KSPLIT>
+static hipError_t launch_product_split(bool first, const uint16_t* act, const int32_t* rowmap, const uint16_t* wpk, void* outp,
+                                       const TileLists& lists, int N, int K, bool act_kmajor, int activation, const float* bias,
+                                       const FoldOut& fold, hipStream_t st) {
+    if (first && activation == MOE_ACT_GELU)
+        return launch_product_kernel<KSPLIT, kFirstGelu, false>(act, rowmap, wpk, outp, lists, N, K, act_kmajor, bias, fold, st);
+    if (first)
+        return launch_product_kernel<KSPLIT, kFirstRelu, false>(act, rowmap, wpk, outp, lists, N, K, act_kmajor, bias, fold, st);
+    if (fold.out != nullptr)
+        return launch_product_kernel<KSPLIT, 0, true>(act, rowmap, wpk, outp, lists, N, K, act_kmajor, bias, fold, st);
+    return launch_product_kernel<KSPLIT, 0, false>(act, rowmap, wpk, outp, lists, N, K, act_kmajor, bias, fold, st);
+}
+
+hipError_t launch_tiled_product(bool first, int ksplit, const uint16_t* act, const int32_t* rowmap, const uint16_t* wpk,
+                                void* outp, const TileLists& lists, int N, int K, bool act_kmajor, int activation,
+                                const float* bias, const FoldOut& fold, hipStream_t st) {
+    if (ksplit == 4)
+        return launch_product_split<4>(first, act, rowmap, wpk, outp, lists, N, K, act_kmajor, activation, bias, fold, st);
+    if (ksplit == 2)
+        return launch_product_split<2>(first, act, rowmap, wpk, outp, lists, N, K, act_kmajor, activation, bias, fold, st);
+    return launch_product_split<1>(first, act, rowmap, wpk, outp, lists, N, K, act_kmajor, activation, bias, fold, st);
 }
 
 }  // namespace moe

@@ -1,12 +1,10 @@
-// Schedule of the LDS-tiled product over the (row tile, column tile) units of the large experts, made with the tile lists and read
-// by the kernel that runs it (ffn_tile.hip) and the kernel that finishes it (ffn.hip).
+// Schedule of the LDS-tiled units, (row tile, column tile) pairs of the large experts, made with the tile lists and read by the kernel
+// that runs them (ffn_tile.hip).
 //
 // All units cost the same.  G blocks run U / G full rounds of whole units in a fixed, XCD-aware order.
 // The R = U mod G units left over would keep R blocks busy for a whole round and the rest of the chip
 // idle, so each of them is cut along K into `split` parts; blocks take parts from a counter as they
-// become free, and every part leaves an fp32 partial tile in the workspace.  The partial tiles are added
-// up in part order -- whichever block computed them -- by the next kernel on the stream: the kernel
-// boundary makes them visible across the XCDs' L2s without any fence.
+// become free, and the sums of a unit's parts meet in the workspace, in a tree over the part numbers (join_parts).
 #pragma once
 #include "common.hpp"
 
@@ -73,7 +71,7 @@ static_assert(sizeof(TileSchedule) == kScheduleInts * 4, "as laid out in the arr
 
 #ifdef __HIPCC__
 template <typename Units>
-__device__ __forceinline__ TileSchedule schedule_of(UnitShape shape, int ntiles, int N, int kblk, int G) {
+__device__ __forceinline__ TileSchedule schedule_of(UnitShape shape, int ntiles, int N, int kblk, int G, bool uncut) {
     TileSchedule s;
     s.shape = shape;
     s.ntiles = ntiles;
@@ -86,7 +84,7 @@ __device__ __forceinline__ TileSchedule schedule_of(UnitShape shape, int ntiles,
         const int big = ntiles * ((N + BigUnits::kCols - 1) / BigUnits::kCols);
         s.sums = max(1, min(G / max(big, 1), min(kMaxSplit, kblk / BigUnits::kMinSplitSteps)));
     }
-    if (s.R > 0 && shape != UnitShape::kNarrow) {          // narrow units are more than half a round: never cut
+    if (s.R > 0 && shape != UnitShape::kNarrow && !(uncut && s.rounds > 0)) {          // narrow units are more than half a round: never cut
         constexpr int slots = kSplitSlots * (kBigTileRows * 256 / (Units::kRows * Units::kCols));
         const int by_blocks = G / s.R, by_steps = kblk / Units::kMinSplitSteps, by_slots = slots / s.R;
         s.split = min(min(by_blocks, kMaxSplit), min(by_steps, by_slots));
@@ -97,11 +95,18 @@ __device__ __forceinline__ TileSchedule schedule_of(UnitShape shape, int ntiles,
     return s;
 }
 
-__device__ __forceinline__ TileSchedule product_schedule(int big_tiles, int half_tiles, int N, int kblk, int G, bool gelu) {
-    const UnitShape shape = tiled_product_units(big_tiles, half_tiles, N, kblk, G, gelu);
-    if (shape == UnitShape::kFine) return schedule_of<FineUnits>(shape, half_tiles, N, kblk, G);
-    if (shape == UnitShape::kNarrow) return schedule_of<NarrowUnits>(shape, big_tiles, N, kblk, G);
-    return schedule_of<BigUnits>(shape, big_tiles, N, kblk, G);
+// `small_tiles`: row tiles of the small experts, whose streaming fills the blocks without a left-over unit.  When there is more of it
+// than a left-over unit takes (about 0.95 us per 32-k step, while the chip streams 5.5 TB/s of the tiles' weights), the units of a
+// first product stay whole: cutting them costs every part's block 7 to 10 us for its partial tile.  (5003 tokens, k = 2, hot
+// share of 32 experts, 2048 x 8192: 380 -> 373 us.)  A second product's are cut all the same, their rows leave in fp32, and a long
+// sum is further from the exact one than the sum of its parts.
+__device__ __forceinline__ TileSchedule product_schedule(int big_tiles, int half_tiles, int small_tiles, int N, int kblk, int G,
+                                                         bool first, bool gelu) {
+    const UnitShape shape = tiled_product_units(big_tiles, half_tiles, N, kblk, G, first && gelu);
+    const bool uncut = first && static_cast<long>(small_tiles) * N >= 102400;
+    if (shape == UnitShape::kFine) return schedule_of<FineUnits>(shape, half_tiles, N, kblk, G, uncut);
+    if (shape == UnitShape::kNarrow) return schedule_of<NarrowUnits>(shape, big_tiles, N, kblk, G, uncut);
+    return schedule_of<BigUnits>(shape, big_tiles, N, kblk, G, uncut);
 }
 
 // Called by all 1024 threads of a block, thread e owning expert e < E (row0, m rows; m = 0 when the
@@ -123,6 +128,7 @@ __device__ __forceinline__ void emit_tiles(int e, int E, int row0, int m, int bi
         }
         return;
     }
+    tl.ntiles[kTakenAt + threadIdx.x] = 0;                 // all counters: kListThreads of them
     const bool big = m >= tiled_min_rows(big_at_min, tl.join_tiles, half_joined, tl.join_half_tiles);
     const int nt[3] = {big ? 0 : small, big ? (m + kBigTileRows - 1) / kBigTileRows : 0,
                        big ? (m + kHalfTileRows - 1) / kHalfTileRows : 0};
@@ -142,16 +148,17 @@ __device__ __forceinline__ void emit_tiles(int e, int E, int row0, int m, int bi
     // The schedules, by a wavefront without experts if there is one: all kernels of both products would else begin with these
     // divisions.
     if (wave == min(nw, 15)) {
-        int big_tiles = 0, half_tiles = 0;
+        int small_tiles = 0, big_tiles = 0, half_tiles = 0;
         for (int w = 0; w < nw; ++w) {
+            small_tiles += tmp[w];
             big_tiles += tmp[16 + w];
             half_tiles += tmp[32 + w];
         }
         const int lane = threadIdx.x & 63;
         if (lane < 2)
             *reinterpret_cast<TileSchedule*>(tl.ntiles + kScheduleAt + lane * kScheduleInts) = product_schedule(
-                big_tiles, half_tiles, lane ? tl.d_model : tl.d_ff, (lane ? tl.d_ff : tl.d_model) >> 5, tl.cus,
-                lane == 0 && tl.gelu);
+                big_tiles, half_tiles, small_tiles, lane ? tl.d_model : tl.d_ff, (lane ? tl.d_ff : tl.d_model) >> 5, tl.cus,
+                lane == 0, tl.gelu);
     }
 }
 
@@ -166,6 +173,14 @@ __device__ __forceinline__ void unit_of(const TileSchedule& s, int u, int& mt, i
     const int chunk = v / (s.GM * wn), slot = v - chunk * (s.GM * wn);
     mt = chunk * s.GM + slot / wn;                      // < ntiles, also in a last, shorter chunk
     nt = cg * s.GN + slot % wn;
+}
+
+// The lane's number, opaque to the compiler: what follows from it is worked out per unit instead of being kept in registers (and
+// spilled) from before the loop over units, for every variant of the unit.
+__device__ __forceinline__ int lane_of_unit() {
+    int lane = static_cast<int>(__builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, 0)));
+    asm volatile("" : "+v"(lane));
+    return lane;
 }
 
 // 4 values of one output row, columns n ... n + 3 (n a multiple of 4).  FIRST != 0 (first product; the value
@@ -218,7 +233,7 @@ template <int FIRST, bool STREAMED>
 __device__ __forceinline__ void store_h_pair(void* outp, int row, bool row_ok, int n0, int N,
                                              const float* bias, f32x4 v0, f32x4 v1) {
     static_assert(FIRST != 0, "first product only");
-    const int g = (threadIdx.x & 63) >> 4;
+    const int g = lane_of_unit() >> 4;
     if (bias != nullptr) {
         v0 += *reinterpret_cast<const f32x4*>(bias + n0 + g * 4);
         v1 += *reinterpret_cast<const f32x4*>(bias + n0 + 16 + g * 4);
@@ -247,7 +262,7 @@ __device__ __forceinline__ void store_h_pair(void* outp, int row, bool row_ok, i
 // not read again by the layer: non-temporal.
 __device__ __forceinline__ void store_folded_pair(uint16_t* out, int t, float w, bool row_ok, int n0, int N,
                                                   const float* bias, f32x4 v0, f32x4 v1) {
-    const int g = (threadIdx.x & 63) >> 4;
+    const int g = lane_of_unit() >> 4;
     if (bias != nullptr) {
         v0 += *reinterpret_cast<const f32x4*>(bias + n0 + g * 4);
         v1 += *reinterpret_cast<const f32x4*>(bias + n0 + 16 + g * 4);
@@ -265,76 +280,6 @@ __device__ __forceinline__ void store_folded_pair(uint16_t* out, int t, float w,
     __builtin_nontemporal_store(hi[1], q + 3);
 }
 
-// Adds up the partial tiles that a tiled product of grid G left behind and writes the output rows.
-// Called by every thread of `nblocks` blocks of the following kernel, `block` being the caller's rank among
-// them.  A wavefront takes four consecutive rows of a
-// cut unit at a time (a row of a unit is 256 columns: 4 per lane): what is the same for the whole row -- the unit,
-// its row tile, for a folded output the row's token and gate weight -- is looked up once per wavefront, and the
-// 4 x split loads of partial sums go out together (one row at a time, with a lookup per element, the pass was a
-// chain of dependent trips to memory: 35 of the 50 us of the kernel that did it on the Switch-large preset).
-template <typename Units, int FIRST, bool FOLD>
-__device__ __forceinline__ void finish_split_units(const TileSchedule& s, const Tile* __restrict__ tiles,
-                                                   const float* __restrict__ partials, void* __restrict__ outp,
-                                                   int N, int G, const float* __restrict__ bias, const FoldOut fold, int block,
-                                                   int nblocks) {
-    constexpr int kLoads = 4;                                    // 16-byte loads per lane and part
-    constexpr int kRowLanes = Units::kCols / 4;                  // lanes of a row: 64 (big units) or 32
-    constexpr int kRowsPerLoad = kWave / kRowLanes;
-    constexpr int kGroups = Units::kRows / (kLoads * kRowsPerLoad);     // row groups per unit
-    constexpr size_t kTileFloats = static_cast<size_t>(Units::kRows) * Units::kCols;
-    const int lane = (threadIdx.x & 63) % kRowLanes, sub = (threadIdx.x & 63) / kRowLanes;
-    const int waves_per_block = blockDim.x >> 6;
-    const int first = __builtin_amdgcn_readfirstlane(block * waves_per_block + static_cast<int>(threadIdx.x >> 6));
-    const int nwaves = nblocks * waves_per_block;
-    const int total = s.R * kGroups;
-    for (int i = first; i < total; i += nwaves) {              // wave-uniform
-        const int ru = i / kGroups, lr0 = (i % kGroups) * (kLoads * kRowsPerLoad) + sub;
-        int mt, nt;
-        unit_of(s, s.rounds * G + ru, mt, nt);
-        const Tile tl = tiles[mt];
-        if (lr0 - sub >= tl.rows) continue;
-        const int c = nt * Units::kCols + lane * 4;
-        const float* base = partials + static_cast<size_t>(ru) * s.split * kTileFloats + static_cast<size_t>(lr0) * Units::kCols + lane * 4;
-        f32x4 sum[kLoads];
-        int tok[kLoads];
-#pragma unroll
-        for (int q = 0; q < kLoads; ++q) {
-            const int lr = lr0 + q * kRowsPerLoad;
-            sum[q] = *reinterpret_cast<const f32x4*>(base + q * kRowsPerLoad * Units::kCols);
-            tok[q] = (FOLD && lr < tl.rows) ? fold.tokmap[tl.row0 + lr] : 0;
-        }
-        for (int p = 1; p < s.split; ++p) {                    // in part order, whichever block computed the parts
-#pragma unroll
-            for (int q = 0; q < kLoads; ++q)
-                sum[q] += *reinterpret_cast<const f32x4*>(base + static_cast<size_t>(p) * kTileFloats + q * kRowsPerLoad * Units::kCols);
-        }
-        const float* be = bias ? bias + static_cast<size_t>(tl.expert) * N : nullptr;
-#pragma unroll
-        for (int q = 0; q < kLoads; ++q) {
-            const int lr = lr0 + q * kRowsPerLoad;
-            if (lr >= tl.rows || c >= N) continue;
-            if constexpr (FOLD) {
-                store_folded(static_cast<uint16_t*>(fold.out), tok[q], fold.gate[tok[q]], c, N, be, sum[q]);
-            } else {
-                store_out<FIRST>(outp, tl.row0 + lr, c, N, be, sum[q]);
-            }
-        }
-    }
-}
-
-// after a tiled product: whichever units it ran in
-template <int FIRST, bool FOLD>
-__device__ __forceinline__ void finish_tiled_product(const Tile* __restrict__ big_tiles, const Tile* __restrict__ half_tiles,
-                                                     const int32_t* __restrict__ ntiles, const float* __restrict__ partials,
-                                                     void* __restrict__ outp, int N, int cus, const float* __restrict__ bias,
-                                                     const FoldOut& fold, int block, int nblocks) {
-    const TileSchedule s = *reinterpret_cast<const TileSchedule*>(ntiles + kScheduleAt + (FIRST != 0 ? 0 : kScheduleInts));
-    if (ntiles[1] <= 0 || s.split < 2) return;
-    if (s.shape == UnitShape::kFine)
-        finish_split_units<FineUnits, FIRST, FOLD>(s, half_tiles, partials, outp, N, cus, bias, fold, block, nblocks);
-    else
-        finish_split_units<BigUnits, FIRST, FOLD>(s, big_tiles, partials, outp, N, cus, bias, fold, block, nblocks);
-}
 #endif
 
 }  // namespace moe

@@ -329,6 +329,22 @@ def test_unit_choice(gpu_lib, rows, d, f, act):
     check(*ffn_rows(gpu_lib, rows, d, f, "bf16", act, biases=True), 4e-3)
 
 
+# one kernel per product for large and small experts: streaming units alone, in more rounds than one, with contractions of an odd number
+# of steps from rows in LDS (up to all 128 KiB) and split over two and four wavefronts; fine units cut into 3, 5, 7 and 8 parts (48, 72, ...
+# steps), with no streaming units, with a few and with more than there are blocks; big units left over after a full round, cut and, where
+# there is enough to stream, whole.  Row tiles of 1 to 4 fragments, and of 1 and 64 rows.  Bar as above.
+SMALL_ROWS = [1, 16, 17, 32, 33, 48, 49, 64, 63]
+
+
+@pytest.mark.parametrize("rows,d,f", [(SMALL_ROWS, 992, 1056), (5 * SMALL_ROWS, 96, 3104), (SMALL_ROWS, 1056, 96),
+                                      ([130], 64, 2304), ([130] + SMALL_ROWS, 64, 3840), ([129, 200] + SMALL_ROWS, 96, 5376),
+                                      ([130] + 12 * SMALL_ROWS, 160, 6144), ([2400] + SMALL_ROWS, 256, 7168),
+                                      ([2400] + 4 * SMALL_ROWS, 288, 7200), (9 * [256] + SMALL_ROWS, 2048, 288)])
+def test_product_units(gpu_lib, rows, d, f):
+    say(f"[case] product units {len(rows)} experts, largest {max(rows)} rows, d={d} f={f}")
+    check(*ffn_rows(gpu_lib, rows, d, f, "bf16", "relu", biases=True), 4e-3)
+
+
 def ffn_on_device(moe, rows, x, w1, w2, act="relu"):
     """fp32 rows of moe_expert_ffn over bf16 tensors: x [A, d], w1 [E, f, d], w2 [E, d, f]."""
     E, f, d = w1.shape
