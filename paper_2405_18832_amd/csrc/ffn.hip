@@ -201,8 +201,9 @@ static hipError_t launch_stream(const uint16_t* act, const int32_t* rowmap, cons
                                 const Tile* tiles, const int32_t* ntiles, int N, int K, long max_units,
                                 bool act_kmajor, const float* bias, const FoldOut& fold, hipStream_t st) {
     auto kern = ffn_stream_kernel<TFMAX, KSPLIT, FIRST, FOLD>;
-    // tiles of up to 64 rows stream fastest as one block per CU, smaller ones as two
-    const int per_cu = std::max(1, std::min(TFMAX == 4 ? 1 : 2, StreamKernelInfo<TFMAX, KSPLIT, FIRST, FOLD>::per_cu[current_device_index()]));
+    // Tiles of more than 16 rows stream fastest as one block per CU, though the registers allow three (23 tokens, 128 experts,
+    // 1024 x 4096: 80 us, 84 as two), the smallest as two.
+    const int per_cu = std::max(1, std::min(TFMAX == 1 ? 2 : 1, StreamKernelInfo<TFMAX, KSPLIT, FIRST, FOLD>::per_cu[current_device_index()]));
     // KSPLIT = 1: the tile's rows (16 * TFMAX x K, bf16) go through LDS when they fit (the kernel's dynamic-LDS
     // limit was raised by configure_ffn_kernels)
     const size_t row_bytes = stream_row_lds(16 * TFMAX, K);

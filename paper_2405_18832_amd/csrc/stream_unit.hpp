@@ -1,4 +1,6 @@
 #pragma once
+#include <type_traits>
+
 #include "tile_schedule.hpp"
 
 namespace moe {
@@ -131,6 +133,10 @@ __device__ __forceinline__ void store_share(void* __restrict__ outp, const Tile 
     }
 }
 
+// Whole loops of a unit (Hooks given: the product kernel, whose wavefronts have 256 registers) issue a step's loads right behind the
+// MFMAs that free their registers.  Left to itself the compiler gathers the loads of several steps, which takes up to 350 registers;
+// the kernels that have those are as fast either way and keep its order.
+
 // What else a wavefront does at three points of a unit: when its last load is out, when that has arrived, and when all wavefronts of
 // the block have got there, before the unit's output is stored.
 struct NoHooks {
@@ -152,6 +158,7 @@ __device__ __forceinline__ void stream_unit(const uint16_t* __restrict__ act,
                                             Hooks&& hooks = {}) {
     constexpr int PF = GW == 4 ? StreamPF<TFC>::value : MOE_PF_NARROW;
     constexpr int NGB = 4 / KSPLIT;
+    constexpr bool STEPWISE = !std::is_same_v<std::remove_reference_t<Hooks>, NoHooks>;
     const int lane = lane_of_unit();
     const int r = lane & 15, g = lane >> 4;
     const int ks = KSPLIT == 1 ? 0 : wave % KSPLIT, ngs = wave / KSPLIT;
@@ -210,18 +217,18 @@ __device__ __forceinline__ void stream_unit(const uint16_t* __restrict__ act,
 #pragma unroll
             for (int p = 0; p < PF; ++p) {
                 fma(p);
-                __builtin_amdgcn_sched_barrier(0);
+                if (STEPWISE) __builtin_amdgcn_sched_barrier(0);
                 issue(p, kb + p + PF);
-                __builtin_amdgcn_sched_barrier(0);
+                if (STEPWISE) __builtin_amdgcn_sched_barrier(0);
             }
         }
         if (kb + PF < kb1) {                               // one partial round of refills
 #pragma unroll
             for (int p = 0; p < PF; ++p) {
                 fma(p);
-                __builtin_amdgcn_sched_barrier(0);
+                if (STEPWISE) __builtin_amdgcn_sched_barrier(0);
                 issue(p, min(kb + p + PF, kb1 - 1));
-                __builtin_amdgcn_sched_barrier(0);
+                if (STEPWISE) __builtin_amdgcn_sched_barrier(0);
             }
             kb += PF;
         }
@@ -320,6 +327,7 @@ __device__ __forceinline__ void stream_unit_lds(const uint16_t* __restrict__ act
                                                 const FoldOut& fold, const int wave,
                                                 Hooks&& hooks = {}) {
     constexpr int PF = MOE_PF_LDS;
+    constexpr bool STEPWISE = !std::is_same_v<std::remove_reference_t<Hooks>, NoHooks>;
     const int lane = lane_of_unit();
     const int r = lane & 15, g = lane >> 4;
     const int nblk = N >> 4, kblk = K >> 5;
@@ -411,18 +419,18 @@ __device__ __forceinline__ void stream_unit_lds(const uint16_t* __restrict__ act
 #pragma unroll
             for (int p = 0; p < PF; ++p) {
                 fma(p, kb + p);
-                __builtin_amdgcn_sched_barrier(0);
+                if (STEPWISE) __builtin_amdgcn_sched_barrier(0);
                 issue(p, kb + p + PF);
-                __builtin_amdgcn_sched_barrier(0);
+                if (STEPWISE) __builtin_amdgcn_sched_barrier(0);
             }
         }
         if (kb + PF < kblk) {
 #pragma unroll
             for (int p = 0; p < PF; ++p) {
                 fma(p, kb + p);
-                __builtin_amdgcn_sched_barrier(0);
+                if (STEPWISE) __builtin_amdgcn_sched_barrier(0);
                 issue(p, min(kb + p + PF, kblk - 1));
-                __builtin_amdgcn_sched_barrier(0);
+                if (STEPWISE) __builtin_amdgcn_sched_barrier(0);
             }
             kb += PF;
         }
