@@ -67,6 +67,7 @@ hipError_t ensure_ready() {
     if (g_device_ready[dev].load(std::memory_order_acquire)) return hipSuccess;
     if ((e = configure_ffn_kernels(dev)) != hipSuccess) return e;
     if ((e = configure_tile_kernels(dev)) != hipSuccess) return e;
+    if ((e = configure_f32_kernels()) != hipSuccess) return e;
     if ((e = configure_route_kernels(dev)) != hipSuccess) return e;
     // this device's copy of the scratch array (each GPU has its own, at its own address)
     void* p = nullptr;

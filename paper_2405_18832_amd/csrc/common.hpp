@@ -448,7 +448,7 @@ hipError_t launch_tiled_product(bool first, int ksplit, const uint16_t* act, con
                                void* outp, const TileLists& lists, int N, int K, bool act_kmajor, int activation,
                                const float* bias, const FoldOut& fold, hipStream_t st);
 int tile_product_grid();
-hipError_t launch_f32_product(bool first, const float* act, const int32_t* rowmap, const float* w, float* outp,
+hipError_t launch_f32_product(bool first, long rows, const float* act, const int32_t* rowmap, const float* w, float* outp,
                               const Tile* tiles, const int32_t* ntiles, long max_tiles, int N, int K, int activation,
                               const float* bias, const FoldOut& fold, hipStream_t st);
 bool layer_sorts_in_first(const moe_shape& s);
@@ -493,6 +493,7 @@ hipError_t ensure_ready();                       // api.hip
 int current_device_index();                      // api.hip: hipGetDevice clamped to [0, kMaxDevices)
 hipError_t configure_ffn_kernels(int dev);       // ffn.hip
 hipError_t configure_tile_kernels(int dev);      // ffn_tile.hip
+hipError_t configure_f32_kernels();              // ffn_f32.hip
 hipError_t configure_route_kernels(int dev);     // route.hip
 
 }  // namespace moe

@@ -382,12 +382,12 @@ hipError_t launch_expert_products(const moe_shape& s, const void* act, const int
 
     if (s.dtype == MOE_F32) {
         if ((err = mark_profile_event(1, st)) != hipSuccess) return err;
-        err = launch_f32_product(true, static_cast<const float*>(act), rowmap, static_cast<const float*>(w1),
+        err = launch_f32_product(true, A, static_cast<const float*>(act), rowmap, static_cast<const float*>(w1),
                                  static_cast<float*>(h_ws), tiles, ntiles, max_tiles, f, d, s.activation, b1,
                                  FoldOut{nullptr, nullptr, nullptr}, st);
         if (err != hipSuccess) return err;
         if ((err = mark_profile_event(2, st)) != hipSuccess || (err = mark_profile_event(3, st)) != hipSuccess) return err;
-        err = launch_f32_product(false, static_cast<const float*>(h_ws), nullptr, static_cast<const float*>(w2), y_perm,
+        err = launch_f32_product(false, A, static_cast<const float*>(h_ws), nullptr, static_cast<const float*>(w2), y_perm,
                                  tiles, ntiles, max_tiles, d, f, s.activation, b2, fold, st);
         if (err != hipSuccess) return err;
         return mark_profile_event(4, st);

@@ -193,6 +193,147 @@ __device__ __forceinline__ void f32_unit(const float* __restrict__ act, const in
     __syncthreads();                                      // LDS may be reused
 }
 
+// The same product for layers of many rows per expert, where reading the token rows again for every 16 columns bounds the units above
+// (64 rows: 40 bytes per clock and CU at the full matrix rate, which is what a CU can pull from its L2).  A unit is one row tile x 32
+// columns: two groups of two wavefronts take half of the contraction each, through rings of their own in LDS, and a wavefront of a group
+// 16 columns; the rows of a step are in LDS once for both.  Everything is copied straight into LDS a line per eight lanes, in the
+// layout that f32_slot describes: 12 KiB per 32 k and group, 24 bytes per clock and CU.  Two blocks fit a CU; blocks are one unit long, and
+// the hardware hands them out as CUs fall free.  (With a ring of two stages, three blocks to a CU: 39 -> 43 us on the layer below.)
+// Rounding: two chains of sums per half, four in all, as good as those above.
+// Rows and columns past the end are copies of the last one and not stored.  K a multiple of 32, everything 16-byte aligned.
+constexpr int kWideStages = 3, kWideCols = 32;
+template <int TFC>
+constexpr int wide_stage_bytes() { return (2 + TFC) * kF32FragFloats * 4; }              // of a group
+
+template <int TFC, bool FIRST, bool FOLDED>
+__device__ __forceinline__ void f32_wide_unit(const float* __restrict__ act, const int32_t* __restrict__ rowmap,
+                                              const float* __restrict__ w, float* __restrict__ outp, const Tile tl, const int n0,
+                                              const int N, const int K, const int activation, const float* __restrict__ bias,
+                                              const FoldOut& fold, float* lds) {
+    constexpr int kFrags = 2 + TFC, kCopies = 2 * kFrags / 2;      // fragments of a stage; 1-KiB copies of a stage per wavefront of the group
+    constexpr int kStage = wide_stage_bytes<TFC>();
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63, r = lane & 15, g = lane >> 4;
+    const int group = wave >> 1, col = wave & 1;
+    const int lrow = lane >> 3, piece = ((lane & 7) ^ lrow) * 4;   // copies: 8 rows x 128 bytes; the row's piece that belongs at the lane's slot
+    const int steps = K / kF32Step, half = (steps + 1) >> 1;
+    const int s0 = group ? half : 0, n = group ? steps - half : half;
+    unsigned char* const ring = reinterpret_cast<unsigned char*>(lds) + group * (kWideStages * kStage);
+    const uint32_t ring_at = lds_address(ring);
+    // Copy c of the group: half c % 2 of fragment c / 2 (0, 1: weights of the two column blocks); wavefront `col` does c = 2 q + col.
+    const float* src[kCopies];
+#pragma unroll
+    for (int q = 0; q < kCopies; ++q) {
+        const int fr = col * 8 + lrow;                     // row of the fragment
+        if (q < 2) {
+            src[q] = w + (static_cast<size_t>(tl.expert) * N + min(n0 + q * 16 + fr, N - 1)) * K + s0 * kF32Step + piece;
+        } else {
+            int row = tl.row0 + min((q - 2) * 16 + fr, tl.rows - 1);
+            if (rowmap != nullptr) row = rowmap[row];
+            src[q] = act + static_cast<size_t>(row) * K + s0 * kF32Step + piece;
+        }
+    }
+    auto copy_stage = [&](int slot) {
+#pragma unroll
+        for (int q = 0; q < kCopies; ++q) {
+            copy16_to_lds(src[q], ring_at + slot * kStage + (2 * q + col) * 1024);
+            src[q] += kF32Step;
+        }
+    };
+    f32x4 acc[2][TFC];
+#pragma unroll
+    for (int c = 0; c < 2; ++c)
+#pragma unroll
+        for (int tf = 0; tf < TFC; ++tf) acc[c][tf] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int s = 0; s < kWideStages - 1; ++s)
+        if (s < n) copy_stage(s);
+    int slot = 0;
+    for (int s = 0; s < half; ++s) {                       // the second group may have a step less: it only meets the barriers then
+        // own copies of step s have landed (those of one later step may be under way), then everybody's
+        if (s + 1 < n) __builtin_amdgcn_s_waitcnt(0x0F70 + kCopies);
+        else __builtin_amdgcn_s_waitcnt(0x0F70);
+        asm volatile("s_barrier" ::: "memory");            // also: step s - 1 has been read by all, its slot is free
+        const int free_slot = slot == 0 ? kWideStages - 1 : slot - 1;
+        if (s + kWideStages - 1 < n) copy_stage(free_slot);
+        if (s < n) {
+            const float* st = reinterpret_cast<const float*>(ring + slot * kStage);
+            f32x4 wv[2], xv[2][TFC];                       // all reads at once: the second half's are covered by the first half's MFMAs
+#pragma unroll
+            for (int q = 0; q < 2; ++q) {
+                const int at = f32_slot(r, q * 4 + g);
+                wv[q] = *reinterpret_cast<const f32x4*>(st + col * kF32FragFloats + at);
+#pragma unroll
+                for (int tf = 0; tf < TFC; ++tf) xv[q][tf] = *reinterpret_cast<const f32x4*>(st + (2 + tf) * kF32FragFloats + at);
+            }
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int q = 0; q < 2; ++q)
+#pragma unroll
+                for (int j = 0; j < 4; ++j)
+#pragma unroll
+                    for (int tf = 0; tf < TFC; ++tf)
+                        acc[j & 1][tf] = __builtin_amdgcn_mfma_f32_16x16x4f32(wv[q][j], xv[q][tf][j], acc[j & 1][tf], 0, 0, 0);
+            // the reads of this step are done before the next barrier lets its slot be filled
+            asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+        }
+        slot = slot + 1 == kWideStages ? 0 : slot + 1;
+    }
+    __syncthreads();                                       // the operands in LDS give way to the partial sums
+    // of its columns, the first group keeps the even row fragments and the second the odd ones
+    f32x4* const red = reinterpret_cast<f32x4*>(lds);
+#pragma unroll
+    for (int tf = 0; tf < TFC; ++tf) {
+        acc[0][tf] += acc[1][tf];
+        if ((tf & 1) != group) red[(col * TFC + tf) * 64 + lane] = acc[0][tf];
+    }
+    __syncthreads();
+    const int n1 = n0 + col * 16 + g * 4;
+    const float* be = bias ? bias + static_cast<size_t>(tl.expert) * N + n1 : nullptr;
+#pragma unroll
+    for (int tf = 0; tf < TFC; ++tf) {
+        const int lr = tf * 16 + r;
+        if ((tf & 1) != group || lr >= tl.rows || n1 >= N) continue;
+        const f32x4 other = red[(col * TFC + tf) * 64 + lane];
+        f32x4 v = group == 0 ? acc[0][tf] + other : other + acc[0][tf];
+        if (be != nullptr) v += *reinterpret_cast<const f32x4*>(be);
+        int orow = tl.row0 + lr;
+        float gate = 1.f;
+        if (FOLDED) {
+            orow = fold.tokmap[orow];
+            gate = fold.gate[orow];
+        }
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            if (FIRST) v[q] = activate(v[q], activation);
+            if (FOLDED) v[q] = fmaf(gate, v[q], 0.f);      // what combine_kernel computes
+        }
+        *reinterpret_cast<f32x4*>(outp + static_cast<size_t>(orow) * N + n1) = v;
+    }
+}
+
+template <bool FIRST, bool FOLDED>
+__global__ __launch_bounds__(256, 2) void ffn_f32_wide_kernel(const float* __restrict__ act, const int32_t* __restrict__ rowmap,
+                                                              const float* __restrict__ w, float* __restrict__ outp,
+                                                              const Tile* __restrict__ tiles, const int32_t* __restrict__ ntiles_p,
+                                                              int N, int K, int activation, const float* __restrict__ bias,
+                                                              const FoldOut fold) {
+    extern __shared__ __attribute__((aligned(16))) float wide_lds[];
+    // Block b of an XCD (b % 8) takes a unit of its eighth of the column groups, as in ffn_f32_kernel: each weight enters one L2 only.
+    const int per = ((N + kWideCols - 1) / kWideCols + 7) / 8, u = static_cast<int>(blockIdx.x >> 3);
+    const int cg = static_cast<int>(blockIdx.x & 7) * per + u % per, tile = u / per;
+    if (tile >= ntiles_p[0] || cg * kWideCols >= N) return;
+    const Tile tl = tiles[tile];
+    const int n0 = cg * kWideCols;
+    switch ((tl.rows + 15) >> 4) {
+        case 1: f32_wide_unit<1, FIRST, FOLDED>(act, rowmap, w, outp, tl, n0, N, K, activation, bias, fold, wide_lds); break;
+        case 2: f32_wide_unit<2, FIRST, FOLDED>(act, rowmap, w, outp, tl, n0, N, K, activation, bias, fold, wide_lds); break;
+        case 3: f32_wide_unit<3, FIRST, FOLDED>(act, rowmap, w, outp, tl, n0, N, K, activation, bias, fold, wide_lds); break;
+        default: f32_wide_unit<4, FIRST, FOLDED>(act, rowmap, w, outp, tl, n0, N, K, activation, bias, fold, wide_lds); break;
+    }
+}
+constexpr int kWideLds = 2 * kWideStages * wide_stage_bytes<4>();
+static_assert(2 * kWideLds <= static_cast<int>(kLdsPerCu), "two blocks to a CU");
+
 // SORT: the first product of a small layer, whose blocks sort the assignments by expert themselves: such a layer is a chain of short
 // kernels, each at its launch, and a dispatch step of its own does nothing but that.  Every block reads the tokens' experts (at
 // most kF32SortMax, 4 per thread), ranks them among those of its 64 that name the same expert with one ballot per bit of the
@@ -395,11 +536,42 @@ static long f32_units(long max_tiles, int N) {
     return ngroups >= 8 ? max_tiles * ((ngroups + 7) / 8) * 8 : (max_tiles * ngroups + 7) / 8 * 8;
 }
 
+// Where the wide units are ahead: rows enough per tile to share, and three units for every CU, because a CU with one is bound by the
+// latency of its copies.  us, units above -> wide: 500 tokens, 8 experts, 768 x 3072, first product 45.4 -> 39.0 (1440 units at
+// most), second 46.0 -> 60.9 (360: not taken); 155 tokens, 14 experts, 544 x 2048 (10 rows per tile: not taken) 42.3 -> 47.4 for the layer;
+// 376 tokens, 14 experts, k = 2, 288 x 1024 43.2 -> 41.0.
+constexpr long kWideMinRows = 24, kWideMinUnits = 3;
+static bool f32_is_wide(long rows, long max_tiles, int N, int K, const void* act, const void* w, const void* outp, const float* bias) {
+    const uintptr_t bases = reinterpret_cast<uintptr_t>(act) | reinterpret_cast<uintptr_t>(w) | reinterpret_cast<uintptr_t>(outp) |
+                            reinterpret_cast<uintptr_t>(bias);
+    return K % kF32Step == 0 && K >= 8 * kF32Step && N % 4 == 0 && bases % 16 == 0 && rows >= kWideMinRows * max_tiles &&
+           max_tiles * ((N + kWideCols - 1) / kWideCols) >= kWideMinUnits * device_cu_count();
+}
+
+template <bool FIRST, bool FOLDED>
+static hipError_t configure_wide() {
+    return hipFuncSetAttribute(reinterpret_cast<const void*>(ffn_f32_wide_kernel<FIRST, FOLDED>),
+                               hipFuncAttributeMaxDynamicSharedMemorySize, kWideLds);
+}
+
+hipError_t configure_f32_kernels() {
+    hipError_t e;
+    if ((e = configure_wide<true, false>()) != hipSuccess) return e;
+    if ((e = configure_wide<false, false>()) != hipSuccess) return e;
+    return configure_wide<false, true>();
+}
+
 // fold.out, if not NULL, is the second product's output in place of rows of y: outp is not used then
-hipError_t launch_f32_product(bool first, const float* act, const int32_t* rowmap, const float* w, float* outp,
+hipError_t launch_f32_product(bool first, long rows, const float* act, const int32_t* rowmap, const float* w, float* outp,
                               const Tile* tiles, const int32_t* ntiles, long max_tiles, int N, int K, int activation,
                               const float* bias, const FoldOut& fold, hipStream_t st) {
     if (fold.out != nullptr) outp = static_cast<float*>(fold.out);
+    if (f32_is_wide(rows, max_tiles, N, K, act, w, outp, bias)) {
+        const unsigned blocks = static_cast<unsigned>(max_tiles * (((N + kWideCols - 1) / kWideCols + 7) / 8) * 8);
+        auto kern = first ? ffn_f32_wide_kernel<true, false> : fold.out != nullptr ? ffn_f32_wide_kernel<false, true> : ffn_f32_wide_kernel<false, false>;
+        hipLaunchKernelGGL(kern, dim3(blocks), dim3(256), kWideLds, st, act, rowmap, w, outp, tiles, ntiles, N, K, activation, bias, fold);
+        return hipGetLastError();
+    }
     const long cap = static_cast<long>(device_cu_count()) * 4;
     const unsigned grid = static_cast<unsigned>(std::max(1L, std::min(f32_units(max_tiles, N), cap)));
     switch (f32_width(K, act, w, outp)) {
@@ -453,7 +625,7 @@ hipError_t launch_f32_sorted_products(const moe_shape& s, const float* x, const 
     }
     if (err != hipSuccess) return err;
     if ((err = mark_profile_event(2, st)) != hipSuccess || (err = mark_profile_event(3, st)) != hipSuccess) return err;
-    err = launch_f32_product(false, h, nullptr, w2, y_perm, lists.small_tiles, lists.ntiles,
+    err = launch_f32_product(false, A, h, nullptr, w2, y_perm, lists.small_tiles, lists.ntiles,
                              A / kF32TileRows + std::min(s.E, A), s.d_model, s.d_ff, s.activation, b2, fold, st);
     if (err != hipSuccess) return err;
     return mark_profile_event(4, st);

@@ -102,6 +102,20 @@ def test_f32_ffn_few_rows_masked(gpu_lib):
     check(*ffn_rows(gpu_lib, [3, 9, 4], 64, 96, "f32", mask=[1, 0, 1]), 1e-5)
 
 
+# fp32 products in units of 32 columns (three units for every CU and 24 rows per tile at least): contractions of an even and an odd number
+# of steps, columns that end inside a unit and inside a wavefront's half of it, row tiles of 1 to 4 fragments; first and second product,
+# and second products that store the layer's output (compared with the combine step).  Bar: fp32 sums, 1e-5.
+@pytest.mark.parametrize("d,f", [(256, 1484), (288, 1508), (1484, 256), (1524, 288)])
+def test_f32_wide_units(gpu_lib, d, f):
+    say(f"[case] f32 wide units d={d} f={f}")
+    check(*ffn_rows(gpu_lib, [64, 128, 63, 49, 48, 33, 65, 17, 120], d, f, "f32", "gelu", biases=True), 1e-5)
+
+
+def test_f32_wide_top1_output(gpu_lib):
+    test_f32_top1_output(gpu_lib, 700, 1484, 256, 9, True)
+
+
+
 # fp32 rounding: no further from 64 bits than four interleaved fp32 sums over k mod 4, added in pairs, at contractions that one
 # wavefront, two, three and all four of them hold, in equal, nearly equal and unequal shares.  Bar on the rms over 512 d elements: 5 %, several times the scatter of
 # such a ratio between two orders of the same length.
