@@ -199,7 +199,8 @@ __device__ __forceinline__ void f32_unit(const float* __restrict__ act, const in
 // 16 columns; the rows of a step are in LDS once for both.  Everything is copied straight into LDS a line per eight lanes, in the
 // layout that f32_slot describes: 12 KiB per 32 k and group, 24 bytes per clock and CU.  Two blocks fit a CU; blocks are one unit long, and
 // the hardware hands them out as CUs fall free.  (With a ring of two stages, three blocks to a CU: 39 -> 43 us on the layer below.)
-// Rounding: two chains of sums per half, four in all, as good as those above.
+// Rounding: four chains of sums per half, eight in all, no further from 64 bits than those above (two chains per half were, where those
+// have eight: 288 x 1152 2.5 -> 2.7e-7; with four 2.5e-7).
 // Rows and columns past the end are copies of the last one and not stored.  K a multiple of 32, everything 16-byte aligned.
 constexpr int kWideStages = 3, kWideCols = 32;
 template <int TFC>
@@ -239,9 +240,9 @@ __device__ __forceinline__ void f32_wide_unit(const float* __restrict__ act, con
             src[q] += kF32Step;
         }
     };
-    f32x4 acc[2][TFC];
+    f32x4 acc[4][TFC];
 #pragma unroll
-    for (int c = 0; c < 2; ++c)
+    for (int c = 0; c < 4; ++c)
 #pragma unroll
         for (int tf = 0; tf < TFC; ++tf) acc[c][tf] = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
@@ -272,7 +273,7 @@ __device__ __forceinline__ void f32_wide_unit(const float* __restrict__ act, con
                 for (int j = 0; j < 4; ++j)
 #pragma unroll
                     for (int tf = 0; tf < TFC; ++tf)
-                        acc[j & 1][tf] = __builtin_amdgcn_mfma_f32_16x16x4f32(wv[q][j], xv[q][tf][j], acc[j & 1][tf], 0, 0, 0);
+                        acc[j][tf] = __builtin_amdgcn_mfma_f32_16x16x4f32(wv[q][j], xv[q][tf][j], acc[j][tf], 0, 0, 0);
             // the reads of this step are done before the next barrier lets its slot be filled
             asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
         }
@@ -283,7 +284,7 @@ __device__ __forceinline__ void f32_wide_unit(const float* __restrict__ act, con
     f32x4* const red = reinterpret_cast<f32x4*>(lds);
 #pragma unroll
     for (int tf = 0; tf < TFC; ++tf) {
-        acc[0][tf] += acc[1][tf];
+        acc[0][tf] = (acc[0][tf] + acc[1][tf]) + (acc[2][tf] + acc[3][tf]);
         if ((tf & 1) != group) red[(col * TFC + tf) * 64 + lane] = acc[0][tf];
     }
     __syncthreads();
