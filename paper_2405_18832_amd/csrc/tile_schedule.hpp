@@ -87,7 +87,7 @@ __device__ __forceinline__ TileSchedule schedule_of(UnitShape shape, int ntiles,
     if (s.R > 0 && shape != UnitShape::kNarrow && !(uncut && s.rounds > 0)) {          // narrow units are more than half a round: never cut
         constexpr int slots = kSplitSlots * (kBigTileRows * 256 / (Units::kRows * Units::kCols));
         const int by_blocks = G / s.R, by_steps = kblk / Units::kMinSplitSteps, by_slots = slots / s.R;
-        s.split = min(min(by_blocks, kMaxSplit), min(by_steps, by_slots));
+        s.split = min(min(by_blocks, kMaxSplit), min(by_steps, min(by_slots, kSplitSlots / s.R)));     // kSplitSlots nodes, too
         if (s.split < 2) s.split = 1;
     }
     s.GN = min(s.ntn, 8);
@@ -211,17 +211,6 @@ __device__ __forceinline__ void store_out(void* outp, int row, int n, int N, con
     }
 }
 
-// Second-product output of a row whose layer output is written directly (FoldOut): 4 columns n ... n + 3 of
-// out[t], t and the row's gate weight w looked up by the caller.  fmaf(w, y, 0) and one rounding to bf16: what
-// the combine step does for a token with a single expert.
-__device__ __forceinline__ void store_folded(uint16_t* out, int t, float w, int n, int N, const float* bias, f32x4 v) {
-    if (bias != nullptr) v += *reinterpret_cast<const f32x4*>(bias + n);
-    uint2 pk;
-    pk.x = pack_bf16x2(fmaf(w, v[0], 0.f), fmaf(w, v[1], 0.f));
-    pk.y = pack_bf16x2(fmaf(w, v[2], 0.f), fmaf(w, v[3], 0.f));
-    *reinterpret_cast<uint2*>(out + static_cast<size_t>(t) * N + n) = pk;
-}
-
 // First-product output of two adjacent 16-column blocks (columns n0 ... n0 + 31: one k-step block of h) for
 // the 16 rows of an accumulator pair.  Called by a whole wavefront (no divergence around it): lane (r, g),
 // r = lane % 16 the row, g = lane / 16, holds columns n0 + 4g ... + 3 in v0 and n0 + 16 + 4g ... + 3 in v1.
@@ -256,8 +245,9 @@ __device__ __forceinline__ void store_h_pair(void* outp, int row, bool row_ok, i
     }
 }
 
-// store_folded for two adjacent 16-column blocks (columns n0 ... n0 + 31) of the 16 rows of an accumulator
-// pair, by a whole wavefront, with the lane exchange of store_h_pair: every lane ends up with 8 consecutive
+// Second-product output of rows whose layer output is written directly (FoldOut): columns n0 ... n0 + 31 of out[t] for the 16 rows of an
+// accumulator pair, t and the row's gate weight w looked up by the caller.  fmaf(w, y, 0) and one rounding to bf16: what the
+// combine step does for a token with a single expert.  By a whole wavefront, with the lane exchange of store_h_pair: every lane ends up with 8 consecutive
 // columns of its row, one 16-byte store (64 contiguous bytes per token row and instruction).  The output is
 // not read again by the layer: non-temporal.
 __device__ __forceinline__ void store_folded_pair(uint16_t* out, int t, float w, bool row_ok, int n0, int N,
