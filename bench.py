@@ -81,12 +81,7 @@ TRAFFIC_SOURCES = {"ffn.hip": "4f15afd4b8392328", "ffn_tile.hip": "5021647b0f1d9
                    "tile_schedule.hpp": "36f55c1699316219", "common.hpp": "95950a7d8edbf8f0",
                    "stream_unit.hpp": "9122e21b36072d9c"}
 TRAFFIC_BYTES = {
-    ("switch_base", "stream_w1"): 316646208, ("switch_base", "stream_w2"): 320449534,
-    ("switch_large_skew", "stream_w1"): 68340751, ("switch_large_skew", "stream_w2"): 68447863,
-    ("switch_large_skew", "tile_w1"): 90911347, ("switch_large_skew", "tile_w2"): 123025513,
     ("nllb_decode", "stream_w1"): 1643741396, ("nllb_decode", "stream_w2"): 1645692016,
-    ("nllb_prefill_skew", "stream_w1"): 913872865, ("nllb_prefill_skew", "stream_w2"): 972124232,
-    ("nllb_prefill_skew", "tile_w1"): 2567193098, ("nllb_prefill_skew", "tile_w2"): 2395759912,
 }
 
 
