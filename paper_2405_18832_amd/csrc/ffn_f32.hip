@@ -537,16 +537,21 @@ static long f32_units(long max_tiles, int N) {
     return ngroups >= 8 ? max_tiles * ((ngroups + 7) / 8) * 8 : (max_tiles * ngroups + 7) / 8 * 8;
 }
 
+// Blocks of a product in wide units: one for each, every XCD's eighth of the column groups rounded up.
+static long f32_wide_blocks(long max_tiles, int N) { return max_tiles * (((N + kWideCols - 1) / kWideCols + 7) / 8) * 8; }
+
 // Where the wide units are ahead: rows enough per tile to share, and three units for every CU, because a CU with one is bound by the
 // latency of its copies.  us, units above -> wide: 500 tokens, 8 experts, 768 x 3072, first product 45.4 -> 39.0 (1440 units at
 // most), second 46.0 -> 60.9 (360: not taken); 155 tokens, 14 experts, 544 x 2048 (10 rows per tile: not taken) 42.3 -> 47.4 for the layer;
-// 376 tokens, 14 experts, k = 2, 288 x 1024 43.2 -> 41.0.
-constexpr long kWideMinRows = 24, kWideMinUnits = 3;
-static bool f32_is_wide(long rows, long max_tiles, int N, int K, const void* act, const void* w, const void* outp, const float* bias) {
+// 376 tokens, 14 experts, k = 2, 288 x 1024 43.2 -> 41.0.  A launch holds fewer than 2^32 threads: products of more units run in those
+// above, whose blocks walk through them.
+constexpr long kWideMinRows = 24, kWideMinUnits = 3, kWideThreads = 256, kWideMaxBlocks = 0xffffffffL / kWideThreads;
+bool f32_is_wide(long rows, long max_tiles, int N, int K, const void* act, const void* w, const void* outp, const float* bias) {
     const uintptr_t bases = reinterpret_cast<uintptr_t>(act) | reinterpret_cast<uintptr_t>(w) | reinterpret_cast<uintptr_t>(outp) |
                             reinterpret_cast<uintptr_t>(bias);
     return K % kF32Step == 0 && K >= 8 * kF32Step && N % 4 == 0 && bases % 16 == 0 && rows >= kWideMinRows * max_tiles &&
-           max_tiles * ((N + kWideCols - 1) / kWideCols) >= kWideMinUnits * device_cu_count();
+           max_tiles * ((N + kWideCols - 1) / kWideCols) >= kWideMinUnits * device_cu_count() &&
+           f32_wide_blocks(max_tiles, N) <= kWideMaxBlocks;
 }
 
 template <bool FIRST, bool FOLDED>
@@ -568,9 +573,9 @@ hipError_t launch_f32_product(bool first, long rows, const float* act, const int
                               const float* bias, const FoldOut& fold, hipStream_t st) {
     if (fold.out != nullptr) outp = static_cast<float*>(fold.out);
     if (f32_is_wide(rows, max_tiles, N, K, act, w, outp, bias)) {
-        const unsigned blocks = static_cast<unsigned>(max_tiles * (((N + kWideCols - 1) / kWideCols + 7) / 8) * 8);
+        const unsigned blocks = static_cast<unsigned>(f32_wide_blocks(max_tiles, N));
         auto kern = first ? ffn_f32_wide_kernel<true, false> : fold.out != nullptr ? ffn_f32_wide_kernel<false, true> : ffn_f32_wide_kernel<false, false>;
-        hipLaunchKernelGGL(kern, dim3(blocks), dim3(256), kWideLds, st, act, rowmap, w, outp, tiles, ntiles, N, K, activation, bias, fold);
+        hipLaunchKernelGGL(kern, dim3(blocks), dim3(kWideThreads), kWideLds, st, act, rowmap, w, outp, tiles, ntiles, N, K, activation, bias, fold);
         return hipGetLastError();
     }
     const long cap = static_cast<long>(device_cu_count()) * 4;

@@ -88,3 +88,26 @@ def test_few_token_layers():
     assert [s for s in faster if not layer_is_few(*s)] == []
     assert [s for s in slower if layer_is_few(*s)] == []
     assert not layer_is_few(1, 64, 256, 8, 1, "f32")
+
+
+def f32_is_wide(rows, E, N, K):
+    """Whether an fp32 product of `rows` rows on E experts, all of them 16-byte aligned, runs in units of 32 columns (moe::f32_is_wide)."""
+    rule = moe.load()._ZN3moe11f32_is_wideElliiPKvS1_S1_PKf
+    rule.restype = ctypes.c_bool
+    rule.argtypes = [ctypes.c_long, ctypes.c_long, ctypes.c_int, ctypes.c_int] + 4 * [ctypes.c_void_p]
+    return rule(rows, rows // 64 + min(E, rows), N, K, 0x1000, 0x2000, 0x3000, 0x4000)
+
+
+def test_f32_wide_units():
+    # (rows, experts, columns, contraction) of 256 CUs, us in units of 16 and of 32 columns
+    wide = [(500, 8, 3072, 768),               # 45.4 39.0
+            (752, 14, 1024, 288),              # 43.2 41.0, of the layer
+            ((1 << 21) - 128, 1, 16384, 256)]  # 512 units fewer than 2^24
+    narrow = [(500, 8, 768, 3072),             # 46.0 60.9
+              (155, 14, 2048, 544),            # 42.3 47.4, of the layer
+              ((1 << 21) - 64, 1, 16384, 256), # 2^24 units of 256 threads and more: no launch holds them
+              (1 << 21, 1, 16384, 256),
+              (1 << 24, 8, 2048, 512),
+              ((1 << 30) - 1, 1, 1024, 256)]
+    assert [s for s in wide if not f32_is_wide(*s)] == []
+    assert [s for s in narrow if f32_is_wide(*s)] == []
