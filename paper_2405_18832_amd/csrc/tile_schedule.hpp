@@ -71,7 +71,7 @@ static_assert(sizeof(TileSchedule) == kScheduleInts * 4, "as laid out in the arr
 
 #ifdef __HIPCC__
 template <typename Units>
-__device__ __forceinline__ TileSchedule schedule_of(UnitShape shape, int ntiles, int N, int kblk, int G, bool uncut) {
+__device__ __forceinline__ TileSchedule schedule_of(UnitShape shape, int ntiles, int N, int kblk, int G) {
     TileSchedule s;
     s.shape = shape;
     s.ntiles = ntiles;
@@ -84,7 +84,7 @@ __device__ __forceinline__ TileSchedule schedule_of(UnitShape shape, int ntiles,
         const int big = ntiles * ((N + BigUnits::kCols - 1) / BigUnits::kCols);
         s.sums = max(1, min(G / max(big, 1), min(kMaxSplit, kblk / BigUnits::kMinSplitSteps)));
     }
-    if (s.R > 0 && shape != UnitShape::kNarrow && !(uncut && s.rounds > 0)) {          // narrow units are more than half a round: never cut
+    if (s.R > 0 && shape != UnitShape::kNarrow) {          // narrow units are more than half a round: never cut
         constexpr int slots = kSplitSlots * (kBigTileRows * 256 / (Units::kRows * Units::kCols));
         const int by_blocks = G / s.R, by_steps = kblk / Units::kMinSplitSteps, by_slots = slots / s.R;
         s.split = min(min(by_blocks, kMaxSplit), min(by_steps, min(by_slots, kSplitSlots / s.R)));     // kSplitSlots nodes, too
@@ -95,18 +95,14 @@ __device__ __forceinline__ TileSchedule schedule_of(UnitShape shape, int ntiles,
     return s;
 }
 
-// `small_tiles`: row tiles of the small experts, whose streaming fills the blocks without a left-over unit.  When there is more of it
-// than a left-over unit takes (about 0.95 us per 32-k step, while the chip streams 5.5 TB/s of the tiles' weights), the units of a
-// first product stay whole: cutting them costs every part's block 7 to 10 us for its partial tile.  (5003 tokens, k = 2, hot
-// share of 32 experts, 2048 x 8192: 380 -> 373 us.)  A second product's are cut all the same, their rows leave in fp32, and a long
-// sum is further from the exact one than the sum of its parts.
-__device__ __forceinline__ TileSchedule product_schedule(int big_tiles, int half_tiles, int small_tiles, int N, int kblk, int G,
-                                                         bool first, bool gelu) {
-    const UnitShape shape = tiled_product_units(big_tiles, half_tiles, N, kblk, G, first && gelu);
-    const bool uncut = first && static_cast<long>(small_tiles) * N >= 102400;
-    if (shape == UnitShape::kFine) return schedule_of<FineUnits>(shape, half_tiles, N, kblk, G, uncut);
-    if (shape == UnitShape::kNarrow) return schedule_of<NarrowUnits>(shape, big_tiles, N, kblk, G, uncut);
-    return schedule_of<BigUnits>(shape, big_tiles, N, kblk, G, uncut);
+// Left-over units are cut whatever the small experts leave to stream beside them: a long sum is further from the exact one than the sum
+// of its parts.  (Whole ones of a first product, where streaming fills the chip, gained nothing: a layer of 5003 tokens, k = 2, hot share
+// of 32 experts, 2048 x 8192, 875 us, cut 874.)
+__device__ __forceinline__ TileSchedule product_schedule(int big_tiles, int half_tiles, int N, int kblk, int G, bool gelu) {
+    const UnitShape shape = tiled_product_units(big_tiles, half_tiles, N, kblk, G, gelu);
+    if (shape == UnitShape::kFine) return schedule_of<FineUnits>(shape, half_tiles, N, kblk, G);
+    if (shape == UnitShape::kNarrow) return schedule_of<NarrowUnits>(shape, big_tiles, N, kblk, G);
+    return schedule_of<BigUnits>(shape, big_tiles, N, kblk, G);
 }
 
 // Called by all 1024 threads of a block, thread e owning expert e < E (row0, m rows; m = 0 when the
@@ -148,17 +144,16 @@ __device__ __forceinline__ void emit_tiles(int e, int E, int row0, int m, int bi
     // The schedules, by a wavefront without experts if there is one: all kernels of both products would else begin with these
     // divisions.
     if (wave == min(nw, 15)) {
-        int small_tiles = 0, big_tiles = 0, half_tiles = 0;
+        int big_tiles = 0, half_tiles = 0;
         for (int w = 0; w < nw; ++w) {
-            small_tiles += tmp[w];
             big_tiles += tmp[16 + w];
             half_tiles += tmp[32 + w];
         }
         const int lane = threadIdx.x & 63;
         if (lane < 2)
             *reinterpret_cast<TileSchedule*>(tl.ntiles + kScheduleAt + lane * kScheduleInts) = product_schedule(
-                big_tiles, half_tiles, small_tiles, lane ? tl.d_model : tl.d_ff, (lane ? tl.d_ff : tl.d_model) >> 5, tl.cus,
-                lane == 0, tl.gelu);
+                big_tiles, half_tiles, lane ? tl.d_model : tl.d_ff, (lane ? tl.d_ff : tl.d_model) >> 5, tl.cus,
+                lane == 0 && tl.gelu);
     }
 }
 

@@ -374,6 +374,20 @@ def ffn_on_device(moe, rows, x, w1, w2, act="relu"):
     return y
 
 
+# The rows of a large expert are the same sums whether or not there are small experts to stream: 34 x 8 units, 16 of which are left over
+# after a full round and cut in two.  The second product only picks columns of h.
+def test_cut_units_beside_streaming(gpu_lib):
+    say("[case] cut units beside streaming units")
+    d, f, m, small = 2048, 2048, 34 * 256, 50
+    gen = torch.Generator(device="cuda").manual_seed(m)
+    x = torch.randn((m + small * 64, d), device="cuda", generator=gen).to(torch.bfloat16)
+    w1 = (torch.randn((1 + small, f, d), device="cuda", generator=gen) * d ** -0.5).to(torch.bfloat16)
+    w2 = torch.eye(f, device="cuda", dtype=torch.bfloat16)[torch.randperm(f, device="cuda", generator=gen)[:d]].expand(1 + small, d, f)
+    alone = ffn_on_device(gpu_lib, [m], x[:m], w1[:1], w2[:1])
+    beside = ffn_on_device(gpu_lib, [m] + small * [64], x, w1, w2)
+    assert torch.equal(beside[:m], alone)
+
+
 # 256 x 128 units add a contraction up in as many partial sums as full-width units would have been cut into (none is longer than
 # those): their rows are the fp32 sums, in order, of calls over a run of 32 steps each, bit for bit.  Integers that the first product
 # adds up exactly make h the same in all calls.
