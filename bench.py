@@ -258,28 +258,38 @@ def measure(name: str, share: str, K: int, W: int, copies_arg: int = 0, cpu_base
     ms_step = dt / K * 1e3
     tokens_s = cfg.T * K / dt
 
-    # ---- pass B: same loop with HIP events around each expert-FFN kernel ------------------------
+    # ---- pass B: same loop with HIP events around each expert-FFN product, and around the two kinds of units of each ----------
+    # (bf16 layers of at least 128 tokens run a product as one kernel; the event between the kinds makes it two launches)
     hev = HipEvents()
-    evs = [[hev.create() for _ in range(5)] for _ in range(K)]
-    torch.cuda.synchronize()
-    # Two events recorded back to back, with nothing between them, are already some microseconds apart (the
-    # second event's own packet): that interval is measured after every step, on the same stream, and taken
-    # off each kernel's interval, which then agrees with the kernel durations rocprofv3 reports.
-    gap = [[hev.create(), hev.create()] for _ in range(K)]
     stream = torch.cuda.current_stream().cuda_stream
-    for i in range(K):
-        moe.moe_set_profile_events(evs[i])
-        L.forward(H=H, copy=i)
-        hev.record(gap[i][0], stream)
-        hev.record(gap[i][1], stream)
-    moe.moe_set_profile_events(None)
-    torch.cuda.synchronize()
-    seg_raw = np.array([[hev.elapsed_ms(e[j], e[j + 1]) for j in range(4)] for e in evs]) * 1e3      # us
-    ev_gap = float(np.median([hev.elapsed_ms(a, z) for a, z in gap])) * 1e3
+
+    def between_events(which):
+        """us per step between consecutive events of `which`, us between two events with nothing between them"""
+        evs = [[hev.create() if j in which else None for j in range(5)] for _ in range(K)]
+        torch.cuda.synchronize()
+        # Two events recorded back to back, with nothing between them, are already some microseconds apart (the
+        # second event's own packet): that interval is measured after every step, on the same stream, and taken
+        # off each kernel's interval, which then agrees with the kernel durations rocprofv3 reports.
+        gap = [[hev.create(), hev.create()] for _ in range(K)]
+        for i in range(K):
+            moe.moe_set_profile_events(evs[i])
+            L.forward(H=H, copy=i)
+            hev.record(gap[i][0], stream)
+            hev.record(gap[i][1], stream)
+        moe.moe_set_profile_events(None)
+        torch.cuda.synchronize()
+        us = np.array([[hev.elapsed_ms(e[a], e[b]) for a, b in zip(which, which[1:])] for e in evs]) * 1e3
+        empty = float(np.median([hev.elapsed_ms(a, z) for a, z in gap])) * 1e3
+        for many in evs + gap:
+            for e in many:
+                if e is not None:
+                    hev.destroy(e)
+        return us, empty
+
+    seg_raw, ev_gap = between_events((0, 1, 2, 3, 4))
     seg = np.maximum(seg_raw - ev_gap, 0.0)
-    for e5 in evs + gap:
-        for e in e5:
-            hev.destroy(e)
+    products, products_gap = between_events((0, 2, 4))
+    products = np.maximum(products - products_gap, 0.0).mean(axis=0)
 
     # ---- per-entry-point breakdown (torch events on the same stream) ---------------------------
     def timed(fn, reps=50):
@@ -304,22 +314,18 @@ def measure(name: str, share: str, K: int, W: int, copies_arg: int = 0, cpu_base
               "combine_us": timed(lambda i: L.combine(mask=mask_t), reps)}
 
     # ---- roofline of the dominant kernel ---------------------------------------------------------
-    # Experts with at least `min_rows` rows run in the LDS-tiled kernel, the others in the weight-streaming
-    # kernel (the library says where the line is for these counts; 0: everything streams).
+    # Experts with at least `min_rows` rows run in LDS-tiled units, the others in weight-streaming units (the library says
+    # where the line is for these counts; 0: everything streams).
     d, f = cfg.d_model, cfg.d_ff
     min_rows = moe.moe_tiled_kernel_min_rows(L.shape, [int(c) if r else 0 for c, r in zip(counts, ran)])
     big = ran & (counts >= min_rows) if min_rows > 0 else np.zeros_like(ran)
     smalls = ran & ~big
     rows_s, rows_b = int(counts[smalls].sum()), int(counts[big].sum())
     wb_s, wb_b = int(smalls.sum()) * d * f * es, int(big.sum()) * d * f * es
-    names = ["ffn_tile_kernel (x.W1 product, large experts)", "ffn_stream_kernel (x.W1 product, small experts)",
-             "ffn_tile_kernel (h.W2 product, large experts)", "ffn_stream_kernel (h.W2 product, small experts)"]
+    kernel = "ffn_product_kernel" if min_rows > 0 else "ffn_stream_kernel"
+    names = [f"{kernel} ({p} product, {units})" for p in ("x.W1", "h.W2")
+             for units in ("tiled units: large experts", "streaming units: small experts")]
     tags = ["tile_w1", "stream_w1", "tile_w2", "stream_w2"]
-    one_kernel = min_rows > 0                                # large and small experts in one kernel per product
-    if one_kernel:
-        names[0], names[2] = "ffn_product_kernel (x.W1 product)", "ffn_product_kernel (h.W2 product)"
-        tags[0], tags[2] = "w1", "w2"
-        rows_b, wb_b = rows_b + rows_s, wb_b + wb_s
     few = not hot and layer_is_few(L.shape)                  # the call above: no mask
     if few:                                                  # routing in the first product, combine in the second
         names[1], names[3] = "few_first_kernel (top-k and x.W1 product)", "few_second_kernel (h.W2 product and combine)"
@@ -351,7 +357,9 @@ def measure(name: str, share: str, K: int, W: int, copies_arg: int = 0, cpu_base
         roof.update(kernel=kd["name"], kernel_us=kd["us"], kernel_us_min=kd["us_min"],
                     kernel_us_between_events=kd["us_raw"], empty_event_interval_us=ev_gap,
                     algorithmic_bytes=kd["bytes"], flops=kd["flops"],
-                    ffn_kernels_us={q["tag"]: round(q["us"], 2) for q in kern})
+                    ffn_kernels_us={q["tag"]: round(q["us"], 2) for q in kern},
+                    # both kinds of units side by side, as in the timed steps
+                    ffn_products_us={t: round(float(u), 2) for t, u in zip(("w1", "w2"), products)})
 
     layer_flops = 2.0 * cfg.T * d * cfg.E + 4.0 * A_run * d * f
     layer_bytes = 2 * w_bytes_one + 2 * cfg.T * d * es + d * cfg.E * es

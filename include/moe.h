@@ -256,9 +256,12 @@ int32_t moe_tiled_kernel_min_rows(const moe_shape* shape, const int32_t* rows_ho
  * about an expert's cost product by product, Section 2.2 and Eq. 3-4).  `events` is a HOST array of
  * five hipEvent_t created by the caller (entries may be NULL), or NULL to stop.  Until the next call,
  * every expert-FFN launch (from moe_expert_ffn or moe_layer_forward) records, on the launch's stream:
- *   [0] before the first product (x.W1^T, activation), [2] after it, [4] after the second (h.W2^T); bf16 layers of at least
- *   128 tokens run each product as one kernel, for large and small experts, with [1] and [3] at its end, too; other layers
- *   run the weight-streaming kernels alone, between [1] = [0] and [2] and between [3] = [2] and [4].
+ *   [0] before the first product (x.W1^T, activation), [1] after its LDS-tiled units (the large experts), [2] after its
+ *   weight-streaming units (the small experts), [3] after the tiled units of the second product (h.W2^T), [4] after its
+ *   streaming units.
+ * bf16 layers of at least 128 tokens run a product as one kernel, in which the two kinds overlap.  Where the event between them is
+ * asked for, they run as two, one kind each, with the same results; with events[1] (events[3]) NULL the product stays the one
+ * kernel of calls that nobody profiles.  Other layers have no tiled units: [1] = [0], [3] = [2].
  * Layers without a mask that fuse steps record the same events around fewer kernels: bf16 layers of few tokens do the top-k and the
  * dispatch inside the first product and the combine inside the second ([1] - [2] and [3] - [4]), small fp32 layers the dispatch
  * inside the first product, and layers of one expert per token the combine inside the second product.

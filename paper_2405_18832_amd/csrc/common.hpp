@@ -446,7 +446,8 @@ bool layer_gathers_kmajor(const moe_shape& s);
 hipError_t launch_gather_kmajor(const moe_shape& s, const void* x, const int32_t* tokmap, void* xk, hipStream_t st);
 hipError_t launch_tiled_product(bool first, int ksplit, const uint16_t* act, const int32_t* rowmap, const uint16_t* wpk,
                                void* outp, const TileLists& lists, int N, int K, bool act_kmajor, int activation,
-                               const float* bias, const FoldOut& fold, hipStream_t st);
+                               const float* bias, const FoldOut& fold, int kinds, hipStream_t st);
+constexpr int kTiledUnits = 1, kStreamUnits = 2;        // kinds of units that a launch of a product runs
 int tile_product_grid();
 hipError_t launch_f32_product(bool first, long rows, const float* act, const int32_t* rowmap, const float* w, float* outp,
                               const Tile* tiles, const int32_t* ntiles, long max_tiles, int N, int K, int activation,

@@ -400,14 +400,22 @@ hipError_t launch_expert_products(const moe_shape& s, const void* act, const int
     const long tiles_expected = A < E ? A : E;      // every assignment on its own expert, at most E of them
     const int ks1 = pick_ksplit(d, f, ffn_tfmax(s), tiles_expected), ks2 = pick_ksplit(f, d, ffn_tfmax(s), tiles_expected);
     if (big) {                                             // one kernel per product for large and small experts
-        err = launch_tiled_product(true, ks1, xp, rowmap, p1, h, lists, f, d, act_kmajor, s.activation, b1,
-                                   FoldOut{nullptr, nullptr, nullptr}, st);
-        if (err != hipSuccess) return err;
-        if ((err = mark_profile_event(1, st)) != hipSuccess || (err = mark_profile_event(2, st)) != hipSuccess) return err;
-        err = launch_tiled_product(false, ks2, h, nullptr, p2, y_perm, lists, d, f, true, s.activation, b2, fold, st);
-        if (err != hipSuccess) return err;
-        if ((err = mark_profile_event(3, st)) != hipSuccess) return err;
-        return mark_profile_event(4, st);
+        const FoldOut none{nullptr, nullptr, nullptr};
+        for (const bool first : {true, false}) {
+            auto run = [&](int kinds) {
+                return first ? launch_tiled_product(true, ks1, xp, rowmap, p1, h, lists, f, d, act_kmajor, s.activation, b1, none, kinds, st)
+                             : launch_tiled_product(false, ks2, h, nullptr, p2, y_perm, lists, d, f, true, s.activation, b2, fold, kinds, st);
+            };
+            const int apart = first ? 1 : 3;               // the event between the two kinds of units: a launch each
+            if (g_profile_events[apart] != nullptr) {
+                if ((err = run(kTiledUnits)) != hipSuccess || (err = mark_profile_event(apart, st)) != hipSuccess) return err;
+                err = run(kStreamUnits);
+            } else {
+                err = run(kTiledUnits | kStreamUnits);
+            }
+            if (err != hipSuccess || (err = mark_profile_event(apart + 1, st)) != hipSuccess) return err;
+        }
+        return hipSuccess;
     }
     if ((err = mark_profile_event(1, st)) != hipSuccess) return err;
     const bool gelu = s.activation == MOE_ACT_GELU;

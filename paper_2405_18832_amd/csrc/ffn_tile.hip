@@ -660,11 +660,12 @@ struct ProductArgs {
     const float* bias;
     FoldOut fold;
     int N, K, act_kmajor;
+    int kinds;                          // kTiledUnits, kStreamUnits or both
 };
 typedef const ProductArgs __attribute__((address_space(4))) * product_args_t;
 
 // One product of a layer that may have large experts: these experts' units first, then the small experts' on whichever blocks are
-// free, side by side with the tiled units that still run.
+// free, side by side with the tiled units that still run.  Profiled calls that time the two kinds apart launch it once for each.
 template <int KSPLIT, int FIRST, bool FOLD>
 __global__ __launch_bounds__(kWaves * 64, 2) void ffn_product_kernel(const ProductArgs by_value) {
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
@@ -672,7 +673,7 @@ __global__ __launch_bounds__(kWaves * 64, 2) void ffn_product_kernel(const Produ
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     // the grid is the number of CUs that the schedule was made for
     const TileSchedule sch = *reinterpret_cast<const TileSchedule*>(by_value.lists + kScheduleAt + product * kScheduleInts);
-    if (by_value.lists[1] > 0) {                            // block-uniform, as all of these
+    if (by_value.lists[1] > 0 && (by_value.kinds & kTiledUnits)) {         // block-uniform, as all of these
         int32_t* const parts = by_value.lists + kSplitCounter + product;
         int32_t* const joined = by_value.lists + kJoinedAt + product * kSplitSlots;
         const ProductArgs& p = by_value;
@@ -692,9 +693,10 @@ __global__ __launch_bounds__(kWaves * 64, 2) void ffn_product_kernel(const Produ
     product_args_t args = (product_args_t)__builtin_amdgcn_kernarg_segment_ptr();
     asm volatile("" : "+s"(args));
     const int32_t* lists = args->lists;
-    if (lists[0] <= 0) return;                              // no small expert
+    const int kinds = args->kinds;
+    if (lists[0] <= 0 || !(kinds & kStreamUnits)) return;   // no small expert
     int busy = 0;                                           // blocks of an XCD that began with a tiled unit
-    if (lists[1] > 0) {
+    if (lists[1] > 0 && (kinds & kTiledUnits)) {
         const TileSchedule* s = reinterpret_cast<const TileSchedule*>(lists + kScheduleAt + product * kScheduleInts);
         busy = s->rounds > 0 ? static_cast<int>(gridDim.x) : s->R * s->split;
         if (gridDim.x % 8 == 0) busy = (busy + 7) >> 3;
@@ -710,11 +712,11 @@ __global__ __launch_bounds__(kWaves * 64, 2) void ffn_product_kernel(const Produ
 template <int KSPLIT, int FIRST, bool FOLD>
 static hipError_t launch_product_kernel(const uint16_t* act, const int32_t* rowmap, const uint16_t* wpk, void* outp,
                                         const TileLists& lists, int N, int K, bool act_kmajor, const float* bias, const FoldOut& fold,
-                                        hipStream_t st) {
+                                        int kinds, hipStream_t st) {
     // An uncut contraction is read from rows in LDS (pick_ksplit cuts the others).
     if (KSPLIT == 1 && stream_row_lds(64, K) > kStreamRowLdsMax) return hipErrorInvalidValue;
     const ProductArgs args{act, rowmap, wpk, outp, lists.small_tiles, lists.big_tiles, lists.half_tiles, lists.ntiles, lists.partials,
-                           bias, fold, N, K, act_kmajor ? 1 : 0};
+                           bias, fold, N, K, act_kmajor ? 1 : 0, kinds};
     // Always the whole chip, one block per CU (the LDS allows no more): how many units there are is only known on the device.
     hipLaunchKernelGGL((ffn_product_kernel<KSPLIT, FIRST, FOLD>), dim3(static_cast<unsigned>(tile_product_grid())), dim3(kWaves * 64),
                        kTileLds, st, args);
@@ -748,24 +750,24 @@ hipError_t configure_tile_kernels(int) {
 template <int KSPLIT>
 static hipError_t launch_product_split(bool first, const uint16_t* act, const int32_t* rowmap, const uint16_t* wpk, void* outp,
                                        const TileLists& lists, int N, int K, bool act_kmajor, int activation, const float* bias,
-                                       const FoldOut& fold, hipStream_t st) {
+                                       const FoldOut& fold, int kinds, hipStream_t st) {
     if (first && activation == MOE_ACT_GELU)
-        return launch_product_kernel<KSPLIT, kFirstGelu, false>(act, rowmap, wpk, outp, lists, N, K, act_kmajor, bias, fold, st);
+        return launch_product_kernel<KSPLIT, kFirstGelu, false>(act, rowmap, wpk, outp, lists, N, K, act_kmajor, bias, fold, kinds, st);
     if (first)
-        return launch_product_kernel<KSPLIT, kFirstRelu, false>(act, rowmap, wpk, outp, lists, N, K, act_kmajor, bias, fold, st);
+        return launch_product_kernel<KSPLIT, kFirstRelu, false>(act, rowmap, wpk, outp, lists, N, K, act_kmajor, bias, fold, kinds, st);
     if (fold.out != nullptr)
-        return launch_product_kernel<KSPLIT, 0, true>(act, rowmap, wpk, outp, lists, N, K, act_kmajor, bias, fold, st);
-    return launch_product_kernel<KSPLIT, 0, false>(act, rowmap, wpk, outp, lists, N, K, act_kmajor, bias, fold, st);
+        return launch_product_kernel<KSPLIT, 0, true>(act, rowmap, wpk, outp, lists, N, K, act_kmajor, bias, fold, kinds, st);
+    return launch_product_kernel<KSPLIT, 0, false>(act, rowmap, wpk, outp, lists, N, K, act_kmajor, bias, fold, kinds, st);
 }
 
 hipError_t launch_tiled_product(bool first, int ksplit, const uint16_t* act, const int32_t* rowmap, const uint16_t* wpk,
                                 void* outp, const TileLists& lists, int N, int K, bool act_kmajor, int activation,
-                                const float* bias, const FoldOut& fold, hipStream_t st) {
+                                const float* bias, const FoldOut& fold, int kinds, hipStream_t st) {
     if (ksplit == 4)
-        return launch_product_split<4>(first, act, rowmap, wpk, outp, lists, N, K, act_kmajor, activation, bias, fold, st);
+        return launch_product_split<4>(first, act, rowmap, wpk, outp, lists, N, K, act_kmajor, activation, bias, fold, kinds, st);
     if (ksplit == 2)
-        return launch_product_split<2>(first, act, rowmap, wpk, outp, lists, N, K, act_kmajor, activation, bias, fold, st);
-    return launch_product_split<1>(first, act, rowmap, wpk, outp, lists, N, K, act_kmajor, activation, bias, fold, st);
+        return launch_product_split<2>(first, act, rowmap, wpk, outp, lists, N, K, act_kmajor, activation, bias, fold, kinds, st);
+    return launch_product_split<1>(first, act, rowmap, wpk, outp, lists, N, K, act_kmajor, activation, bias, fold, kinds, st);
 }
 
 }  // namespace moe
