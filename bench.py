@@ -263,33 +263,30 @@ def measure(name: str, share: str, K: int, W: int, copies_arg: int = 0, cpu_base
     hev = HipEvents()
     stream = torch.cuda.current_stream().cuda_stream
 
-    def between_events(which):
-        """us per step between consecutive events of `which`, us between two events with nothing between them"""
-        evs = [[hev.create() if j in which else None for j in range(5)] for _ in range(K)]
-        torch.cuda.synchronize()
-        # Two events recorded back to back, with nothing between them, are already some microseconds apart (the
-        # second event's own packet): that interval is measured after every step, on the same stream, and taken
-        # off each kernel's interval, which then agrees with the kernel durations rocprofv3 reports.
-        gap = [[hev.create(), hev.create()] for _ in range(K)]
-        for i in range(K):
-            moe.moe_set_profile_events(evs[i])
-            L.forward(H=H, copy=i)
-            hev.record(gap[i][0], stream)
-            hev.record(gap[i][1], stream)
-        moe.moe_set_profile_events(None)
-        torch.cuda.synchronize()
-        us = np.array([[hev.elapsed_ms(e[a], e[b]) for a, b in zip(which, which[1:])] for e in evs]) * 1e3
-        empty = float(np.median([hev.elapsed_ms(a, z) for a, z in gap])) * 1e3
-        for many in evs + gap:
-            for e in many:
-                if e is not None:
-                    hev.destroy(e)
-        return us, empty
-
-    seg_raw, ev_gap = between_events((0, 1, 2, 3, 4))
+    # One step with the kinds apart and one with each product as it runs, in turn: clocks move under the power limit.
+    # Two events recorded back to back, with nothing between them, are already some microseconds apart (the
+    # second event's own packet): that interval is measured after every step, on the same stream, and taken
+    # off each kernel's interval, which then agrees with the kernel durations rocprofv3 reports.
+    wanted = [(0, 1, 2, 3, 4), (0, 2, 4)]
+    evs = [[[hev.create() if j in which else None for j in range(5)] for _ in range(K)] for which in wanted]
+    gap = [[hev.create(), hev.create()] for _ in range(2 * K)]
+    torch.cuda.synchronize()
+    for i in range(2 * K):
+        moe.moe_set_profile_events(evs[i % 2][i // 2])
+        L.forward(H=H, copy=i)
+        hev.record(gap[i][0], stream)
+        hev.record(gap[i][1], stream)
+    moe.moe_set_profile_events(None)
+    torch.cuda.synchronize()
+    seg_raw, products = [np.array([[hev.elapsed_ms(e[a], e[b]) for a, b in zip(which, which[1:])] for e in es_]) * 1e3    # us
+                         for which, es_ in zip(wanted, evs)]
+    ev_gap = float(np.median([hev.elapsed_ms(a, z) for a, z in gap])) * 1e3
     seg = np.maximum(seg_raw - ev_gap, 0.0)
-    products, products_gap = between_events((0, 2, 4))
-    products = np.maximum(products - products_gap, 0.0).mean(axis=0)
+    products = np.maximum(products - ev_gap, 0.0).mean(axis=0)
+    for many in evs[0] + evs[1] + gap:
+        for e in many:
+            if e is not None:
+                hev.destroy(e)
 
     # ---- per-entry-point breakdown (torch events on the same stream) ---------------------------
     def timed(fn, reps=50):
