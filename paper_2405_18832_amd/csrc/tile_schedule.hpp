@@ -71,7 +71,7 @@ static_assert(sizeof(TileSchedule) == kScheduleInts * 4, "as laid out in the arr
 
 #ifdef __HIPCC__
 template <typename Units>
-__device__ __forceinline__ TileSchedule schedule_of(UnitShape shape, int ntiles, int N, int kblk, int G) {
+__host__ __device__ __forceinline__ TileSchedule schedule_of(UnitShape shape, int ntiles, int N, int kblk, int G) {
     TileSchedule s;
     s.shape = shape;
     s.ntiles = ntiles;
@@ -98,7 +98,7 @@ __device__ __forceinline__ TileSchedule schedule_of(UnitShape shape, int ntiles,
 // Left-over units are cut whatever the small experts leave to stream beside them: a long sum is further from the exact one than the sum
 // of its parts.  (Whole ones of a first product, where streaming fills the chip, gained nothing: a layer of 5003 tokens, k = 2, hot share
 // of 32 experts, 2048 x 8192, 875 us, cut 874.)
-__device__ __forceinline__ TileSchedule product_schedule(int big_tiles, int half_tiles, int N, int kblk, int G, bool gelu) {
+__host__ __device__ __forceinline__ TileSchedule product_schedule(int big_tiles, int half_tiles, int N, int kblk, int G, bool gelu) {
     const UnitShape shape = tiled_product_units(big_tiles, half_tiles, N, kblk, G, gelu);
     if (shape == UnitShape::kFine) return schedule_of<FineUnits>(shape, half_tiles, N, kblk, G);
     if (shape == UnitShape::kNarrow) return schedule_of<NarrowUnits>(shape, big_tiles, N, kblk, G);

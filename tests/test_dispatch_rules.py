@@ -12,16 +12,19 @@ SHAPES = ["big", "narrow", "fine"]
 
 
 @pytest.fixture(scope="module")
-def unit_shapes(tmp_path_factory):
-    """A function over (big tiles, half tiles, N, k-steps, GeLU first product) points of a 256-CU device."""
+def schedules(tmp_path_factory):
+    """A function over (big tiles, half tiles, N, k-steps, GeLU first product) points of a 256-CU device: (shape of the units, full
+    rounds, units left over, parts of each)."""
     d = tmp_path_factory.mktemp("rules")
     (d / "rules.hip").write_text('''
 #include <cstdio>
 #include "tile_schedule.hpp"
 int main() {
-    long big, half; int n, k, gelu;
-    while (scanf("%ld %ld %d %d %d", &big, &half, &n, &k, &gelu) == 5)
-        printf("%d\\n", static_cast<int>(moe::tiled_product_units(big, half, n, k, 256, gelu != 0)));
+    int big, half, n, k, gelu;
+    while (scanf("%d %d %d %d %d", &big, &half, &n, &k, &gelu) == 5) {
+        const moe::TileSchedule s = moe::product_schedule(big, half, n, k, 256, gelu != 0);
+        printf("%d %d %d %d\\n", static_cast<int>(s.shape), s.rounds, s.R, s.split);
+    }
 }''')
     subprocess.run([HIPCC, "-std=c++17", "--cuda-host-only", "-I", os.path.join(ROOT, "include"), "-I", CSRC,
                     str(d / "rules.hip"), "-o", str(d / "rules")], check=True, capture_output=True)
@@ -29,11 +32,11 @@ int main() {
     def ask(points):
         text = "\n".join(" ".join(str(int(v)) for v in p) for p in points)
         out = subprocess.run([str(d / "rules")], input=text, capture_output=True, text=True, check=True).stdout
-        return [SHAPES[int(v)] for v in out.split()]
+        return [(SHAPES[v[0]], *v[1:]) for v in ([int(t) for t in line.split()] for line in out.splitlines())]
     return ask
 
 
-def test_tiled_product_units(unit_shapes):
+def test_tiled_product_units(schedules):
     # (row tiles of 256 and of 128 rows, columns, 32-k steps, GeLU first product), the faster side and us of the two
     points = [((8, 16, 3072, 24, 0), "narrow"),      # 39 big -> 31
               ((8, 16, 3072, 24, 1), "narrow"),      # 44 fine -> 36
@@ -51,7 +54,18 @@ def test_tiled_product_units(unit_shapes):
               ((12, 24, 1536, 131, 1), "fine"),      # 70 fine, 79 big
               ((16, 32, 2048, 256, 1), "big"),       # half a round of big units
               ((4, 8, 3072, 24, 0), "fine")]         # at most one round
-    assert unit_shapes([p for p, _ in points]) == [s for _, s in points]
+    assert [s[0] for s in schedules([p for p, _ in points])] == [s for _, s in points]
+
+
+def test_product_units_of_the_cases(schedules):
+    """The schedules that the cases of test_gpu_edges.test_product_units are there for."""
+    from test_gpu_edges import PRODUCT_UNITS
+    for rows, d, f, want in PRODUCT_UNITS:
+        least = moe.moe_tiled_kernel_min_rows(moe.make_shape(sum(rows), d, f, len(rows), 1, "bf16", False), rows)
+        large = [r for r in rows if r >= least]
+        big, half = (sum(-(-r // n) for r in large) for n in (256, 128))
+        got = schedules([(big, half, f, d // 32, 0), (big, half, d, f // 32, 0)]) if large else None
+        assert got == want, (rows, d, f, got)
 
 
 def layer_is_few(T, d, f, E, k, dtype="bf16"):
@@ -111,3 +125,12 @@ def test_f32_wide_units():
               ((1 << 30) - 1, 1, 1024, 256)]
     assert [s for s in wide if not f32_is_wide(*s)] == []
     assert [s for s in narrow if f32_is_wide(*s)] == []
+
+
+def test_f32_wide_units_of_the_cases():
+    """The fp32 cases of test_gpu_edges.py that are there for wide units run in them."""
+    import test_gpu_edges as g
+    T, d, f, E, k = g.F32_WIDE_LAYER.values()
+    assert f32_is_wide(T * k, E, f, d) and T * k > 1024          # up to 1024 assignments the first product may sort them instead
+    for K, N in g.F32_WIDE_ROUNDING:
+        assert f32_is_wide(sum(g.F32_WIDE_ROWS), len(g.F32_WIDE_ROWS), N, K)

@@ -115,6 +115,70 @@ def test_f32_wide_top1_output(gpu_lib):
     test_f32_top1_output(gpu_lib, 700, 1484, 256, 9, True)
 
 
+# first products of a layer in such units: token rows through a row map, every token on two experts, with and without a mask.  Bar as above.
+# Columns, contraction, tokens and experts of these and the next are held to those units by test_dispatch_rules.py.
+F32_WIDE_LAYER = dict(T=700, d=288, f=1508, E=9, k=2)
+
+
+@pytest.mark.parametrize("masked", [False, True])
+def test_f32_wide_layer(gpu_lib, masked):
+    say(f"[case] f32 layer in wide units, masked {masked}")
+    moe, (T, d, f, E, k) = gpu_lib, F32_WIDE_LAYER.values()
+    rng = np.random.default_rng(T)
+    draw = lambda s, *shape: rng.standard_normal(shape, dtype=np.float32) * np.float32(s)
+    x, wg, bg = draw(1, T, d), draw(0.05, E, d), draw(0.5, E)
+    w1, b1, w2, b2 = draw(d ** -0.5, E, f, d), draw(0.25, E, f), draw(f ** -0.5, E, d, f), draw(0.25, E, d)
+    mask = (np.arange(E) % 3 != 1).astype(np.uint8) if masked else np.ones(E, dtype=np.uint8)
+    dev = lambda a: torch.from_numpy(a).cuda()
+    shape = moe.make_shape(T, d, f, E, k, "f32", True, 1)
+    out, idx, gate = torch.full((T, d), float("nan"), device="cuda"), torch.empty((T, k), dtype=torch.int32, device="cuda"), torch.empty((T, k), device="cuda")
+    ws = torch.full((moe.moe_workspace_bytes(shape),), 0xFF, dtype=torch.uint8, device="cuda")
+    moe.moe_layer_forward_biased(shape, dev(x), dev(wg), dev(bg), dev(w1), dev(b1), dev(w2), dev(b2), dev(mask) if masked else None, -1, out,
+                                 idx, gate, ws=ws)
+    torch.cuda.synchronize()
+    r = orc.route(x, wg, bg, k, True)
+    ok = r["margin"] >= 1e-4
+    i, g = idx.cpu().numpy(), gate.cpu().numpy().astype(np.float64)
+    assert np.array_equal(i[ok], r["idx"][ok])
+    ref = np.zeros((T, d))
+    for e in np.flatnonzero(mask):
+        t, j = np.nonzero(i == e)
+        ref[t] += g[t, j][:, None] * orc.expert_ffn(x[t], w1[e], w2[e], None, "gelu", b1[e], b2[e])
+    some = ref.any(axis=1)                                 # tokens with an expert that ran
+    check(out.cpu().numpy().astype(np.float64)[some], ref[some], 1e-5)
+    assert not out.cpu().numpy()[~some].any()
+
+
+# rounding of such units, of either product by itself (the other only picks columns): no further from 64 bits than the units of 16
+# columns, which take operands that are 4 bytes off a 16-byte line.  Contractions of equal halves, of halves a step apart, and long ones.
+# Bar on the rms over 500000 elements and more: as above.
+F32_WIDE_ROWS, F32_WIDE_ROUNDING = [640, 640, 592, 177], [(256, 772), (288, 768), (2016, 768)]
+
+
+@pytest.mark.parametrize("first", [True, False])
+@pytest.mark.parametrize("K,N", F32_WIDE_ROUNDING)
+def test_f32_wide_rounding(gpu_lib, K, N, first):
+    say(f"[case] f32 rounding of wide units K={K} N={N} first {first}")
+    moe, rows, E, A = gpu_lib, F32_WIDE_ROWS, len(F32_WIDE_ROWS), sum(F32_WIDE_ROWS)
+    d, f = (K, N) if first else (N, K)
+    gen = torch.Generator(device="cuda").manual_seed(K)
+    new = lambda *s: torch.randn(s, device="cuda", generator=gen)
+    pick = lambda n, m: torch.eye(m, device="cuda")[torch.randint(0, m, (n,), device="cuda", generator=gen)].expand(E, n, m).contiguous()
+    x = new(A, d)
+    w1, w2 = (new(E, f, d), pick(d, f)) if first else (pick(f, d), new(E, d, f))
+    offsets = torch.tensor([0] + rows, dtype=torch.int32).cumsum(0, dtype=torch.int32).cuda()
+    shape = moe.make_shape(A, d, f, E, 1, "f32", False)
+    ws = torch.empty(moe.moe_workspace_bytes(shape), dtype=torch.uint8, device="cuda")
+    lo = offsets.tolist()
+    ref = torch.cat([torch.relu(x[i:j].double() @ w1[e].double().t()) @ w2[e].double().t() for e, (i, j) in enumerate(zip(lo, lo[1:]))])
+    rms = []
+    for at in (0, 1):
+        y = placed(torch.full((A, d), float("nan"), device="cuda"), at)
+        moe.moe_expert_ffn(shape, placed(x, at), placed(w1, at), placed(w2, at), offsets, None, y, ws)
+        rms.append(float((y.double() - ref).square().mean().sqrt()))
+    say(f"[edges] rms error {rms[0]:.4e}, in units of 16 columns {rms[1]:.4e}")
+    assert rms[0] <= 1.05 * rms[1]
+
 
 # fp32 rounding: no further from 64 bits than four interleaved fp32 sums over k mod 4, added in pairs, at contractions that one
 # wavefront, two, three and all four of them hold, in equal, nearly equal and unequal shares.  Bar on the rms over 512 d elements: 5 %, several times the scatter of
@@ -345,33 +409,26 @@ def test_unit_choice(gpu_lib, rows, d, f, act):
 
 # one kernel per product for large and small experts: streaming units alone, in more rounds than one, with contractions of an odd number
 # of steps from rows in LDS (up to all 128 KiB) and split over two and four wavefronts; fine units cut into 3, 5, 7 and 8 parts (48, 72, ...
-# steps), with no streaming units, with a few and with more than there are blocks; big units left over after a full round, cut and, where
-# there is enough to stream, whole.  Row tiles of 1 to 4 fragments, and of 1 and 64 rows.  Bar as above.
+# steps), with no streaming units, with a few and with more than there are blocks; big units left over after full rounds, whole (contractions of 8
+# and 9 steps), cut in two and in three, the last columns of a unit missing.  Row tiles of 1 to 4 fragments, and of 1 and 64 rows.  Bar as above.
+# Last item of a case: units, full rounds, units left over and parts of each, of the two products (test_dispatch_rules.py holds them to that).
 SMALL_ROWS = [1, 16, 17, 32, 33, 48, 49, 64, 63]
+PRODUCT_UNITS = [(SMALL_ROWS, 992, 1056, None), (5 * SMALL_ROWS, 96, 3104, None), (SMALL_ROWS, 1056, 96, None),
+                 ([130], 64, 2304, [("fine", 0, 36, 1), ("fine", 0, 2, 3)]),
+                 ([130] + SMALL_ROWS, 64, 3840, [("fine", 0, 60, 1), ("fine", 0, 2, 5)]),
+                 ([129, 200] + SMALL_ROWS, 96, 5376, [("fine", 0, 168, 1), ("fine", 0, 4, 7)]),
+                 ([130] + 12 * SMALL_ROWS, 160, 6144, [("fine", 0, 96, 1), ("fine", 0, 4, 8)]),
+                 ([2400] + SMALL_ROWS, 256, 7168, [("big", 1, 24, 1), ("fine", 0, 38, 6)]),
+                 ([2400] + 4 * SMALL_ROWS, 288, 7200, [("big", 1, 34, 1), ("fine", 0, 57, 4)]),
+                 (9 * [256] + SMALL_ROWS, 2048, 288, [("fine", 0, 54, 2), ("narrow", 0, 144, 1)]),
+                 ([8700] + SMALL_ROWS, 2112, 2048, [("big", 1, 16, 2), ("big", 1, 50, 2)]),
+                 ([33000] + SMALL_ROWS, 512, 3072, [("big", 6, 12, 1), ("big", 1, 2, 3)])]
 
 
-@pytest.mark.parametrize("rows,d,f", [(SMALL_ROWS, 992, 1056), (5 * SMALL_ROWS, 96, 3104), (SMALL_ROWS, 1056, 96),
-                                      ([130], 64, 2304), ([130] + SMALL_ROWS, 64, 3840), ([129, 200] + SMALL_ROWS, 96, 5376),
-                                      ([130] + 12 * SMALL_ROWS, 160, 6144), ([2400] + SMALL_ROWS, 256, 7168),
-                                      ([2400] + 4 * SMALL_ROWS, 288, 7200), (9 * [256] + SMALL_ROWS, 2048, 288)])
+@pytest.mark.parametrize("rows,d,f", [case[:3] for case in PRODUCT_UNITS])
 def test_product_units(gpu_lib, rows, d, f):
     say(f"[case] product units {len(rows)} experts, largest {max(rows)} rows, d={d} f={f}")
     check(*ffn_rows(gpu_lib, rows, d, f, "bf16", "relu", biases=True), 4e-3)
-
-
-def ffn_on_device(moe, rows, x, w1, w2, act="relu"):
-    """fp32 rows of moe_expert_ffn over bf16 tensors: x [A, d], w1 [E, f, d], w2 [E, d, f]."""
-    E, f, d = w1.shape
-    shape = moe.make_shape(sum(rows), d, f, E, 1, "bf16", False, {"relu": 0, "gelu": 1}[act])
-    p1, p2 = torch.empty_like(w1), torch.empty_like(w2)
-    moe.moe_pack_weights(shape, 1, w1.contiguous(), p1)
-    moe.moe_pack_weights(shape, 2, w2.contiguous(), p2)
-    offsets = torch.tensor([0] + list(rows), dtype=torch.int32).cumsum(0, dtype=torch.int32).cuda()
-    y = torch.full((sum(rows), d), float("nan"), device="cuda")
-    ws = torch.full((moe.moe_workspace_bytes(shape),), 0xFF, dtype=torch.uint8, device="cuda")
-    moe.moe_expert_ffn(shape, x.contiguous(), p1, p2, offsets, None, y, ws)
-    torch.cuda.synchronize()
-    return y
 
 
 # The rows of a large expert are the same sums whether or not there are small experts to stream: 34 x 8 units, 16 of which are left over

@@ -546,8 +546,8 @@ def test_folded_combine_is_the_combine(gpu_lib, name):
     """Top-1 layers without a mask let the second product write the layer output (gate weight times the row,
     rounded once).  With an all-ones mask the same layer takes the separate combine pass (Section 2.1: outputs
     are combined and put back in token order).  Both do the same multiply and the same rounding on the same
-    fp32 rows, so the outputs must agree bit for bit: streaming kernel, tiled kernel and the tiles that are cut
-    along the contraction and added up by the following kernel."""
+    fp32 rows, so the outputs must agree bit for bit: streaming units, tiled units and the tiled units that are cut
+    along the contraction, whose parts meet in the workspace."""
     cfg = CFG(name)
     assert cfg.k == 1
     say(f"[case] folded combine {name}")
