@@ -431,6 +431,21 @@ def test_product_units(gpu_lib, rows, d, f):
     check(*ffn_rows(gpu_lib, rows, d, f, "bf16", "relu", biases=True), 4e-3)
 
 
+def ffn_on_device(moe, rows, x, w1, w2, act="relu"):
+    """fp32 rows of moe_expert_ffn over bf16 tensors: x [A, d], w1 [E, f, d], w2 [E, d, f]."""
+    E, f, d = w1.shape
+    shape = moe.make_shape(sum(rows), d, f, E, 1, "bf16", False, {"relu": 0, "gelu": 1}[act])
+    p1, p2 = torch.empty_like(w1), torch.empty_like(w2)
+    moe.moe_pack_weights(shape, 1, w1.contiguous(), p1)
+    moe.moe_pack_weights(shape, 2, w2.contiguous(), p2)
+    offsets = torch.tensor([0] + list(rows), dtype=torch.int32).cumsum(0, dtype=torch.int32).cuda()
+    y = torch.full((sum(rows), d), float("nan"), device="cuda")
+    ws = torch.full((moe.moe_workspace_bytes(shape),), 0xFF, dtype=torch.uint8, device="cuda")
+    moe.moe_expert_ffn(shape, x.contiguous(), p1, p2, offsets, None, y, ws)
+    torch.cuda.synchronize()
+    return y
+
+
 # The rows of a large expert are the same sums whether or not there are small experts to stream: 34 x 8 units, 16 of which are left over
 # after a full round and cut in two.  The second product only picks columns of h.
 def test_cut_units_beside_streaming(gpu_lib):
