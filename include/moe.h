@@ -244,9 +244,9 @@ moe_status moe_combine(const moe_shape* shape, const float* y_perm, const int32_
  * memory-bound experts, Section 3.1): the smallest number of rows with which an expert's rows are run in
  * LDS-tiled units rather than weight-streaming ones in a call where the experts have `rows_host[e]` rows
  * (HOST array [E]; 0 for experts that are empty or masked out).  It is 128, or one more than a streaming tile
- * holds when the experts of 128 rows and more already fill the tiled kernel for a round, or when they and the
+ * holds when the experts of 128 rows and more already fill a round of tiled units, or when they and the
  * smaller ones together are at most a round of its smaller units; 0 when the shape
- * never uses the tiled kernel (fp32, or fewer than 128 tokens) or on invalid arguments.  The current device's
+ * never has tiled units (fp32, or fewer than 128 tokens) or on invalid arguments.  The current device's
  * size enters (as in the calls themselves).
  */
 int32_t moe_tiled_kernel_min_rows(const moe_shape* shape, const int32_t* rows_host);

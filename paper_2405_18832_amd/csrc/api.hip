@@ -377,7 +377,7 @@ moe_status moe_layer_forward_biased(const moe_shape* shape, const void* x, const
     }
     if (shape->T == 0) return MOE_OK;
     if (layer_gathers_kmajor(*shape)) {
-        // layers large enough for the tiled kernel: one pass gathers the token rows into the k-step-major
+        // layers large enough for tiled units: one pass gathers the token rows into the k-step-major
         // layout that lets both kernels fetch operand rows as full cache lines
         void* xk = at<void>(ws, L.x_kmajor);
         e = launch_gather_kmajor(*shape, x, tokmap, xk, hs);

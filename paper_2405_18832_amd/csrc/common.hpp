@@ -58,15 +58,15 @@ constexpr int kBigMinRows = 128;
 constexpr int kHalfTileRows = 128;
 constexpr int kHalfCount = 4;           // int of the `ntiles` array that holds their number
 // Experts between one streaming tile and kBigMinRows rows would have their weights streamed once per
-// streaming tile; as one mostly empty tile of the tiled kernel they cost about what a single pass over their
-// weights costs -- where the tiled kernel runs anyway and hides the additional units:
+// streaming tile; as one mostly empty tile of tiled units they cost about what a single pass over their
+// weights costs -- where there are rounds of tiled units anyway, which hide the additional units:
 //  - with whole rounds of units, i.e. when the tiles of the experts with kBigMinRows rows already number `join_tiles`
 //    (the host's figure: one full round of units in the narrower product);
 //  - in half-sized units, as long as all of them, `half_tiles_joined` tiles of them and the experts that are large in any
 //    case, are at most one round in the wider product (`join_half_tiles`): then they occupy CUs that would be idle.
 //    (Experts of 327, 112, 85, 71 and 12 times at most 45 rows, 1024 x 4096: streaming 41.8 + 39.8 -> 23.8 + 25.5 us, tiled
 //    15.2 + 14.2 -> 19.6 + 18.6 us.)
-// Else an under-filled tiled kernel would only get longer.
+// Else an under-filled round would only get longer.
 constexpr int kJoinMinRows = 65;
 inline __host__ __device__ int tiled_min_rows(int big_tiles_at_min, int join_tiles, int half_tiles_joined, int join_half_tiles) {
     if (join_tiles > 0 && big_tiles_at_min >= join_tiles) return kJoinMinRows;
@@ -132,7 +132,7 @@ constexpr int kFirstGelu = 2;
 // operand fragment is one contiguous KiB (row-major, each row would contribute half a cache line), a row
 // tile of one k-step is at most two contiguous runs, and consecutive k-steps of a row are 16 KiB apart: a
 // block that walks along K reads one linear stream.  (With the k-step outermost over all A rows, [K / 32][A][32],
-// consecutive steps of a 32 k-row layer were 2 MiB apart and the global-to-LDS copies of the tiled kernel ran
+// consecutive steps of a 32 k-row layer were 2 MiB apart and the global-to-LDS copies of the tiled units ran
 // at two thirds of the rate they reach on a linear stream.)  Element (row, n) of a tensor with `ksteps` = K / 32:
 constexpr int kRowBlock = 256;
 #ifdef __HIPCC__
@@ -336,8 +336,8 @@ __device__ __forceinline__ void write_tiles(Tile* __restrict__ out, int e, int r
 struct WsLayout {
     size_t hist;       // int32 [ceil(T/16), E]  chunk histograms / slot bases of the counting sort
     size_t ntiles;     // int32 [64 + kListCounters, or 64 without large experts]  ([0] = tiles of small experts, [1] = of large experts, [2], [3] counters)
-    size_t tiles;      // Tile [A/16 + E + 1]   row tiles of the weight-streaming kernel
-    size_t tiles_big;  // Tile [A/256 + E + 1]  row tiles of the LDS-tiled kernel
+    size_t tiles;      // Tile [A/16 + E + 1]   row tiles of the streaming units
+    size_t tiles_big;  // Tile [A/256 + E + 1]  row tiles of the big and narrow units
     size_t tiles_half; // Tile [A/128 + E + 1]  the same rows in the half-sized tiles of that kernel (if an expert can have them)
     size_t h;          // dtype [A rounded up to kRowBlock, f]
     size_t idx;        // int32 [A]         -- the rest is used by moe_layer_forward only

@@ -154,7 +154,7 @@ int device_cu_count() {
     return n > 0 ? n : 256;
 }
 
-// resident blocks per CU of a weight-streaming kernel without dynamic LDS, per device
+// resident blocks per CU that the registers of a weight-streaming kernel allow, per device
 template <int TFMAX, int KSPLIT, int FIRST, bool FOLD>
 struct StreamKernelInfo {
     static int per_cu[kMaxDevices];
@@ -201,8 +201,9 @@ static hipError_t launch_stream(const uint16_t* act, const int32_t* rowmap, cons
                                 const Tile* tiles, const int32_t* ntiles, int N, int K, long max_units,
                                 bool act_kmajor, const float* bias, const FoldOut& fold, hipStream_t st) {
     auto kern = ffn_stream_kernel<TFMAX, KSPLIT, FIRST, FOLD>;
-    // Tiles of more than 16 rows stream fastest as one block per CU, though the registers allow three (23 tokens, 128 experts,
-    // 1024 x 4096: 80 us, 84 as two), the smallest as two.
+    // Tiles of more than 16 rows run as one block per CU, though the registers allow three, the smallest as two.  Layers, us, two blocks ->
+    // one: 2048 x 8192, 128 experts, k = 2, 20, 40 and 127 tokens 423, 687, 1229 -> 411, 672, 1206; 1024 x 4096, 128 experts 82.0, 120.0,
+    // 254.8 -> 74.0, 121.7, 247.4; 768 x 3072, 64 experts 44.2, 71.5, 115.6 -> 44.1, 73.6, 109.4; 8 experts (less than a round) the same.
     const int per_cu = std::max(1, std::min(TFMAX == 1 ? 2 : 1, StreamKernelInfo<TFMAX, KSPLIT, FIRST, FOLD>::per_cu[current_device_index()]));
     // KSPLIT = 1: the tile's rows (16 * TFMAX x K, bf16) go through LDS when they fit (the kernel's dynamic-LDS
     // limit was raised by configure_ffn_kernels)
@@ -350,7 +351,7 @@ TileLists ffn_tile_lists(const moe_shape& s, Tile* small_ws, Tile* big_ws, Tile*
     return l;
 }
 
-// one full round of the tiled kernel's units in the product with the fewer column tiles
+// row tiles of one full round of big units in the product with the fewer column tiles
 int tiled_join_tiles(const moe_shape& s) {
     const int narrow = s.d_model < s.d_ff ? s.d_model : s.d_ff;
     const int col_tiles = (narrow + 255) / 256;

@@ -24,8 +24,9 @@
 // are about equal, 17 and 14 us on a layer of 500 tokens, 8 experts, 768 x 3072, one expert per token (2.4 GFLOP and
 // 75 MB of weights per product); the rest is the start of the units (tile, row numbers, first lines: three dependent
 // trips to memory) and the last round.  Measured there: 47 + 46 us for the two products; a thread per column with
-// fused multiply-adds took 1353 + 2432 us.  Units of 32 columns need fewer row loads but leave room for two blocks per
-// CU only: 48 + 63 us.
+// fused multiply-adds took 1353 + 2432 us.  Units of 32 columns with operands through registers like these needed fewer row loads but
+// left room for two blocks per CU only: 48 + 63 us.  Copied straight into LDS (ffn_f32_wide_kernel) they take 39.0 us where there are several
+// for every CU, as in the first product; the second has too few of them (60.9 us) and stays with units of 16.
 #include <algorithm>
 #include <type_traits>
 

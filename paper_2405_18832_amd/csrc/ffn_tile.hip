@@ -6,9 +6,10 @@
 // throughput, not by reading the expert's parameters) run in LDS-tiled MFMA units, the others in weight-streaming units
 // (stream_unit.hpp), which the blocks turn to as they run out of tiled ones.  As two kernels one after the other the CUs without a unit
 // of a partly filled round waited for the last one twice per product, the sums of cut units were added up by the second kernel, and
-// where one kind does not occur its launch cost 2 to 3 us all the same.  Whole layers, two kernels -> one, us: 1501 tokens, 8 experts,
-// 768 x 3072, GeLU 63 -> 57; 5003 tokens, hot share of 32 experts, 2048 x 8192, k = 2 935 -> 860; 2586 tokens, hot share of 20
-// 574 -> 498; 16384 tokens, 41 experts 2180 -> 2140; 208 tokens, 128 experts 323 -> 299.
+// where one kind does not occur its launch cost 2 to 3 us all the same.  Whole layers, us, two kernels -> one, with what is said of its
+// units below and in stream_unit.hpp: 1501 tokens, 8 experts, 768 x 3072, GeLU 70.9 -> 64.9; 2048 tokens, 64 experts 137.1 -> 130.3; 5003
+// tokens, hot share of 32 experts, 2048 x 8192, k = 2 910 -> 853; 16384 tokens, 41 experts 2240 -> 2191; 4096 tokens, skewed, 1024 x 4096
+// 147.4 -> 145.3; hot share of 777 tokens, in four calls, 127.6 -> 117.0.
 // The four wavefronts that stream do so within the 256 registers that 8 wavefronts per CU leave each: their loads are issued step by
 // step (stream_unit.hpp) and their share of a sum is a quarter.  No register is spilled: a kernel that has scratch memory starts several us later.
 //
@@ -579,8 +580,11 @@ __device__ __forceinline__ void run_stream_units(const uint16_t* __restrict__ ac
     // The next unit is asked for when the current one's last loads are out, so that its number is there when they are consumed and no
     // block holds a unit that an idle one could run; its tile is looked up while the current one's output is stored.  (Asked for at the
     // start of the current unit: 16 experts of the hot share of 777 tokens, 1024 x 4096: 117 -> 131 us for the four calls.)
-    // Without tiled units all blocks start together and units cost about the same: every block takes its share, nothing is counted
-    // (64 experts of about 32 rows, 768 x 3072: 136 us for the layer, 147 counted).
+    // Without tiled units all blocks start together and units cost about the same: every block takes its share, nothing is counted.
+    // Layers without a large expert, us, counted -> shares: 64 experts, 768 x 3072, 256, 700, 2048 and 2900 tokens 121.0, 125.0, 133.9, 139.0 ->
+    // 117.8, 121.3, 129.6, 133.1; 128 experts, 900 tokens 224.8 -> 218.9.  It is the other way with units for some of the XCDs only (8 experts,
+    // 160 and 400 tokens 34.0, 40.9 -> 39.8, 43.8), where a run for each XCD spreads them, and with long units in several rounds (2048 x 8192,
+    // k = 2, 208 tokens 1281 -> 1341; 1024 x 4096, 128 experts, 300 to 3000 tokens 328 to 386 -> 331 to 388).
     struct NextUnit {
         decltype(take)& take_;
         const Tile* tiles;

@@ -8,7 +8,7 @@ namespace moe {
 // ---------------------------------------------------------------------------
 // bf16 weight-streaming product.
 //
-//   out[row, n] = sum_k act[row, k] * W_e[n, k]          (FIRST: relu, rounded to bf16)
+//   out[row, n] = sum_k act[row, k] * W_e[n, k]          (FIRST: activation, rounded to bf16)
 //
 // MFMA 16x16x32: the A operand is a packed 16(n) x 32(k) weight fragment -- one contiguous
 // 1 KiB load per wavefront, 16 bytes per lane, straight from HBM into registers -- and the B
@@ -48,7 +48,7 @@ namespace moe {
 // s_waitcnt immediate that waits for vmcnt <= n only (n < 64: low four bits in [3:0], the rest in [15:14])
 constexpr int vmcnt_imm(int n) { return 0x0F70 | (n & 15) | ((n >> 4) << 14); }
 
-constexpr size_t kStreamRowLdsMax = 128 * 1024;   // largest row tile kept in LDS by the streaming kernel
+constexpr size_t kStreamRowLdsMax = 128 * 1024;   // largest row tile kept in LDS by streaming units
 constexpr size_t stream_row_lds(int rows, int K) { return static_cast<size_t>(rows) * ((K + 63) / 64) * 128; }     // whole pairs of k-steps
 
 template <int TFC> struct StreamPF;
@@ -312,11 +312,12 @@ __device__ __forceinline__ void stream_unit(const uint16_t* __restrict__ act,
 }
 
 // The same unit when all four wavefronts of the block share the tile's rows over the same k range
-// (KSPLIT = 1: the block covers four column groups): the rows are copied once per block into LDS, in
-// MFMA-fragment order, instead of being fetched by every wavefront at every k-step.  That takes the
+// (KSPLIT = 1: the block covers four column groups): the rows are copied once per block into LDS
+// instead of being fetched by every wavefront at every k-step.  That takes the
 // row operand out of the vector-memory queue that the weights stream through (one quarter of the
 // requests, issued once, asynchronously) and out of the registers that hold loads in flight.
-// `tok_lds` holds, for every row fragment, ceil(K / 64) pairs of k-steps of 2 KiB each.
+// `tok_lds` holds, for every row fragment, ceil(K / 64) pairs of k-steps of 2 KiB each: rows of the blocked layout as two MFMA
+// fragments of 1 KiB, plain rows as 16 lines of 128 bytes whose 16-byte pieces are permuted by the row's number.
 template <int TFC, int FIRST, bool FOLD, typename Hooks = NoHooks>
 __device__ __forceinline__ void stream_unit_lds(const uint16_t* __restrict__ act,
                                                 const int32_t* __restrict__ rowmap,

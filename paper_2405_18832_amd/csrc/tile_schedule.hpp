@@ -96,8 +96,8 @@ __host__ __device__ __forceinline__ TileSchedule schedule_of(UnitShape shape, in
 }
 
 // Left-over units are cut whatever the small experts leave to stream beside them: a long sum is further from the exact one than the sum
-// of its parts.  (Whole ones of a first product, where streaming fills the chip, gained nothing: a layer of 5003 tokens, k = 2, hot share
-// of 32 experts, 2048 x 8192, 875 us, cut 874.)
+// of its parts (ffn_tile.hip, narrow_sums), and a large expert's rows do not depend on the small ones.  Whole ones of a first product where
+// streaming fills the chip are 1 to 2 % faster: a layer of 5003 tokens, k = 2, hot share of 32 experts, 2048 x 8192, 847 us, cut 857 to 864.
 __host__ __device__ __forceinline__ TileSchedule product_schedule(int big_tiles, int half_tiles, int N, int kblk, int G, bool gelu) {
     const UnitShape shape = tiled_product_units(big_tiles, half_tiles, N, kblk, G, gelu);
     if (shape == UnitShape::kFine) return schedule_of<FineUnits>(shape, half_tiles, N, kblk, G);
@@ -182,9 +182,9 @@ __device__ __forceinline__ int lane_of_unit() {
 // names the activation, kFirstRelu or kFirstGelu): activation, bf16, into the blocked h of N columns; FIRST == 0 (second product): fp32 into row-major y of N columns.  `bias`: the expert's N bias values
 // (fp32) or NULL, added before the activation / the store.  STREAMED: the store carries the non-temporal
 // hint, so the rows go to memory while the kernel runs instead of staying behind as dirty L2 lines that the
-// next kernel's weight stream has to push out (the streaming kernel's stores; measured on the Switch-base
+// next kernel's weight stream has to push out (the streaming units' stores; measured on the Switch-base
 // preset: following product 65 -> 62 us; no effect on the fp32 rows of the second product, which are stored
-// plainly).  The tiled kernel's rows are re-read from L2 and are stored plainly.
+// plainly).  The tiled units' rows are re-read from L2 and are stored plainly.
 template <int FIRST, bool STREAMED = false>
 __device__ __forceinline__ void store_out(void* outp, int row, int n, int N, const float* bias,
                                           f32x4 v) {

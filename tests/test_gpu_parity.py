@@ -82,22 +82,22 @@ EXTRA = {
     # together)
     "tokens_8k": wl.MoEConfig("tokens_8k", T=8192 + 40, d_model=128, d_ff=256, E=96, k=2, dtype="bf16",
                               renormalize=True, seed=41, zipf_s=1.1, gate_std=0.3),
-    # several full scheduling rounds of the tiled kernel, compared in full: about 65 row tiles x 8 column tiles
+    # several full rounds of tiled units, compared in full: about 65 row tiles x 8 column tiles
     # (two rounds of 256 units and a cut left-over round) in the first product, 65 x 4 in the second
     "rounds_full": wl.MoEConfig("rounds_full", T=16640 + 77, d_model=1024, d_ff=2048, E=3, k=1, dtype="bf16",
                                 renormalize=False, seed=43, zipf_s=1.0),
     "tokens_12k_top1": wl.MoEConfig("tokens_12k_top1", T=12000, d_model=128, d_ff=256, E=40, k=1, dtype="bf16",
                                     renormalize=False, seed=42, zipf_s=1.2, gate_std=0.3),
-    # GeLU as the trailing activation (Section 3.4): fp32 kernel, streaming kernel (rows in LDS / split
-    # contraction), tiled kernel incl. its K-cut last round
+    # GeLU as the trailing activation (Section 3.4): fp32 kernel, streaming units (rows in LDS / split
+    # contraction), tiled units incl. the K-cut last round
     "gelu_f32": wl.MoEConfig("gelu_f32", T=64, d_model=64, d_ff=256, E=8, k=2, dtype="f32", renormalize=True,
                              seed=21, activation="gelu"),
     "gelu_ragged": wl.MoEConfig("gelu_ragged", T=333, d_model=96, d_ff=160, E=11, k=2, dtype="bf16",
                                 renormalize=False, seed=22, zipf_s=1.0, gate_std=0.3, activation="gelu"),
     "gelu_wide": wl.MoEConfig("gelu_wide", T=96, d_model=256, d_ff=3072, E=6, k=2, dtype="bf16",
                               renormalize=True, seed=23, gate_std=0.3, activation="gelu"),
-    # experts with biases: fp32 kernel, streaming kernel (rows in LDS / split contraction), tiled kernel
-    # incl. its K-cut last round, together with GeLU
+    # experts with biases: fp32 kernel, streaming units (rows in LDS / split contraction), tiled units
+    # incl. the K-cut last round, together with GeLU
     "bias_f32": wl.MoEConfig("bias_f32", T=64, d_model=64, d_ff=256, E=8, k=2, dtype="f32", renormalize=True,
                              seed=31, expert_bias=True),
     "bias_ragged": wl.MoEConfig("bias_ragged", T=333, d_model=96, d_ff=160, E=11, k=2, dtype="bf16",
@@ -454,7 +454,7 @@ def test_layer_forward(gpu_lib, name):
     assert np.array_equal(outs["hot mask given"], outs["top-H on device"])
     # the two shares add up to the whole layer (each is rounded to storage once)
     # Besides the final rounding of each share, an element may differ by summation order: which large-expert tiles
-    # fall into the tiled kernel's last scheduling round, and are summed in K-slices, depends on how many tiles the
+    # fall into the last round of tiled units, and are summed in K-slices, depends on how many tiles the
     # share has (see test_expert_ffn: the same bound, 4e-3 of the row's rms, through flipped roundings of h).
     s = outs["hot mask given"] + outs["cold share"]
     ulp = 2.0 ** -7 if cfg.dtype == "bf16" else 2.0 ** -22
