@@ -74,25 +74,36 @@ class HipEvents:
         self.hip.hipEventDestroy(ev)
 
 
-# HBM-side bytes per launch of the expert-FFN kernels, from rocprofv3 --pmc FETCH_SIZE / WRITE_SIZE runs
-# (summaries and commands: profiles/<workload>_full_layer.txt).  Valid only for the kernel sources they
-# were taken with: reported as null once one of the sources below has changed.
-TRAFFIC_SOURCES = {"ffn.hip": "4f15afd4b8392328", "ffn_tile.hip": "5021647b0f1d9f16",
-                   "tile_schedule.hpp": "36f55c1699316219", "common.hpp": "95950a7d8edbf8f0",
-                   "stream_unit.hpp": "9122e21b36072d9c"}
+# HBM-side bytes per launch of the expert-FFN kernels (launches for one kind of units each, as the roofline times them), from
+# rocprofv3 --pmc FETCH_SIZE / WRITE_SIZE runs (summaries and commands: profiles/<workload>_full_layer.txt).  Valid only for the
+# kernel code they were taken with: reported as null once one of the sources below has changed in more than comments.
+TRAFFIC_SOURCES = {"ffn.hip": "2abf9e88fdd81d20", "ffn_tile.hip": "2e4065f5f3b84877",
+                   "tile_schedule.hpp": "e58b4c1988a0127f", "common.hpp": "051528cd856edf56",
+                   "stream_unit.hpp": "a2f6529edc5c0be5"}
 TRAFFIC_BYTES = {
-    ("nllb_decode", "stream_w1"): 1643741396, ("nllb_decode", "stream_w2"): 1645692016,
+    ("switch_base", "stream_w1"): 317094111, ("switch_base", "stream_w2"): 320165821,
+    ("switch_large_skew", "stream_w1"): 68439310, ("switch_large_skew", "stream_w2"): 68492121,
+    ("switch_large_skew", "tile_w1"): 90965320, ("switch_large_skew", "tile_w2"): 119279042,
+    ("nllb_decode", "stream_w1"): 1644021523, ("nllb_decode", "stream_w2"): 1645975040,
+    ("nllb_prefill_skew", "stream_w1"): 914076053, ("nllb_prefill_skew", "stream_w2"): 914083266,
+    ("nllb_prefill_skew", "tile_w1"): 2576302179, ("nllb_prefill_skew", "tile_w2"): 2484573723,
 }
 
 
-def recorded_traffic(workload: str, share: str, tag: str):
+def code_hash(text: str) -> str:
+    """Of a source file without its // comments and white space."""
     import hashlib
+    import re
+    return hashlib.sha256("".join(re.sub(r"//[^\n]*", "", text).split()).encode()).hexdigest()[:16]
+
+
+def recorded_traffic(workload: str, share: str, tag: str):
     if share != "full":
         return None
     for fn, want in TRAFFIC_SOURCES.items():
         path = os.path.join(ROOT, "paper_2405_18832_amd", "csrc", fn)
         try:
-            if hashlib.sha256(open(path, "rb").read()).hexdigest()[:16] != want:
+            if code_hash(open(path).read()) != want:
                 return None
         except OSError:
             return None
