@@ -80,7 +80,7 @@ __global__ __launch_bounds__(256, 2) void few_first_kernel(const FewRoute p, con
     __shared__ int32_t experts[kFewAssignments];
     __shared__ float weights[kFewAssignments];
     __shared__ FewLists lists;
-    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
+    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
     const int T = p.T, E = p.E, k = p.k, A = T * k, Ep = E + 1;
     hist[threadIdx.x] = 0;
     // four logits per thread and pass, their partial sums loaded before any is added
